@@ -1,14 +1,16 @@
 """Benchmark: likelihood evaluations per second on one MI355X.
 
 A step is one batch of parameter points (100 by default, a row of a
-likelihood scan), each put through the whole plain single-point path
-(device E-integral, weights, HBM-streaming fold of the 16384 x 4096 FP32
-response, Poisson -2lnL), with every input resident in HBM.  The K timed
-steps are one HIP-graph replay of K x 100 evaluations; the value is
-evaluations per second.
+likelihood scan), each put through the whole plain path (weights from the
+energy integral, dense FP64 fold of the 16384 x 4096 FP32 response, Poisson
+-2lnL), with every input resident in HBM.  The K timed steps are one call on
+K x 100 points, which share the stream over the response in blocks; the value
+is evaluations per second.
 
-Prints one JSON line: the plain rate as `value`, the roofline of the step
-kernel, the batched and gradient forms and the CPU oracle timed beside it.
+Prints one JSON line: the plain rate as `value`, the roofline of the fold
+kernel, the single-point launch (one point per stream over the response)
+against the HBM peak, the batched and gradient forms and the CPU oracle timed
+beside it.
 """
 import argparse
 import json
@@ -24,6 +26,7 @@ import numpy as np  # noqa: E402
 METRIC = ("likelihood evals/s at |Δ(−2lnL)|≤1e-3 vs FP64: "
           "plain vs batched/grad/surrogate")
 HBM_PEAK_GBS = 8000.0
+FP64_PEAK_TFLOPS = 78.6
 
 
 def algorithmic_bytes(n_t, n_reco):
@@ -129,10 +132,9 @@ def time_batched(ctxs, ths, reps=3, grad=False):
 
 
 def plain_config0_form(n_pts=4096, reps=5):
-    """The plain single-point path at the parity configuration (512 recoil x
-    256 reco bins, N_E = 256, 1e6 MC events): the response is 512 KiB and
-    stays in L2, so the chain of step launches is latency-bound.  One graph
-    replay of n_pts evaluations at prior points, timed with events."""
+    """The plain path at the parity configuration (512 recoil x 256 reco bins,
+    N_E = 256, 1e6 MC events), the 512 KiB response in L2: calls of n_pts
+    evaluations at prior points, timed with events."""
     import torch
     import synth
     p = build_plain(0)
@@ -155,9 +157,9 @@ def plain_config0_form(n_pts=4096, reps=5):
     ctx.close()
     return dict(evals_per_s=round(n_pts / (ms * 1e-3), 1), points=n_pts,
                 us_per_eval=round(ms * 1e3 / n_pts, 3),
-                what="plain single-point path at 512 x 256 (N_E = 256): the "
-                     "512 KiB response stays in L2; one graph replay of "
-                     f"{n_pts} evaluations ({n_pts + 4} step launches)")
+                what="plain path at 512 x 256 (N_E = 256): the 512 KiB "
+                     f"response stays in L2; calls of {n_pts} evaluations, "
+                     "four launches each")
 
 
 def templates_form(ctx, seed, n_pts=65536, reps=5):
@@ -306,11 +308,10 @@ def banded_form(ctx, R, tt, dense_out, stream):
                 bitwise_equal_to_dense=bool(torch.equal(out, dense_out)),
                 band_fraction=round(band_bytes / (4.0 * R.size), 4),
                 band_bytes_per_eval=alg,
-                band_gbs=round(alg / (us * 1e-6) / 1e9, 1),
-                what="the headline scan with band skipping: each fold tile reads "
-                     "only the columns where its rows' responses are non-zero "
-                     "(exact zeros elsewhere); results bitwise those of the "
-                     "dense read")
+                what="the headline scan with band skipping: each 256-column "
+                     "tile of the fold reads only the rows whose responses "
+                     "there are non-zero (exact zeros elsewhere); results "
+                     "bitwise those of the dense read")
 
 
 def seeded_fit_study(ctx, sur, S=64, gtols=(1e-2, 1e-4)):
@@ -824,7 +825,7 @@ def main():
                           device=dev)
         out = torch.empty(20, dtype=torch.float64, device=dev)
         ctx.set_fold_tiling(0, 0)           # eager launches, one per kernel
-        ctx.eval_nll_dev(th, out)
+        ctx.time_stage(5, 20)
         torch.cuda.synchronize()
         a = torch.empty(1 << 26, dtype=torch.float32, device=dev)
         b = torch.empty_like(a)
@@ -843,7 +844,7 @@ def main():
                        dtype=torch.float64, device=dev)
     outw = torch.empty(max(W, 1) * PPS, dtype=torch.float64, device=dev)
     stream = torch.cuda.Stream(device=dev)
-    # warm-up: captures the timed and the warm-up graphs and runs them once
+    # warm-up: allocates the workspaces and runs both lists once
     ctx.eval_nll_dev(thw, outw, stream=stream)
     ctx.eval_nll_dev(tt, out, stream=stream)
     stream.synchronize()
@@ -857,8 +858,7 @@ def main():
     stream.synchronize()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
-    # device time of the timed region on the stream the step kernels run
-    # on: NE + 4 launches, NE - 4 of them the steady-state k_step
+    # device time of the timed region on its stream
     dev_ms = ev0.elapsed_time(ev1)
     ms_step = dt * 1e3 / K
     evals_s = NE / dt
@@ -872,14 +872,13 @@ def main():
         lat.append(time.perf_counter() - t1)
     lat = np.array(lat[1:]) * 1e3
 
-    # roofline of the dominant kernel, the step kernel as the pipeline runs
-    # it: device time of the timed region (HIP events on its stream) per
-    # evaluation, which charges the 8 shorter fill/drain launches to the
-    # NE - 4 steady-state ones (a conservative average); the steady-state
-    # launch alone back to back, the fold role alone and the other stages
-    # for the breakdown
-    step_ms = dev_ms / NE
+    # roofline of the dominant kernel, the blocked fold: its multiply-adds
+    # over the device time of the whole timed region (HIP events on its
+    # stream), which charges the weights and the likelihood sums to it.  An
+    # isolated point streams R by itself: the single-point step launch alone
+    # back to back, its fold role alone and the other stages
     step_bb_ms = ctx.time_stage(5, 200)
+    step_ms = step_bb_ms
     # the same launch after 512 MiB of other data have been read through the
     # device's caches (the 256 MB Infinity Cache included): the cold-cache
     # figure (a read, so no dirty lines are left to write back)
@@ -899,17 +898,25 @@ def main():
     eint_ms = ctx.time_stage(1, 200)
     alg_bytes = algorithmic_bytes(c.n_t, c.n_reco)
     achieved = alg_bytes / (step_ms * 1e-3) / 1e9
-    roof = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
-                unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
-                traffic=measured_traffic(), kernel="k_step",
-                avg_kernel_us=round(step_ms * 1e3, 2),
-                algorithmic_bytes=alg_bytes,
-                note="effective rate: the algorithmic bytes of a launch over "
-                     "its time, whether HBM or the Infinity Cache served "
-                     "them (consecutive points walk R in opposite "
-                     "directions and reuse what the last one left cached); "
-                     "one launch after a 512 MiB cache flush: "
-                     "detail.step_after_cache_flush_us")
+    tflops = 2.0 * c.n_t * c.n_reco * NE / (dev_ms * 1e-3) / 1e12
+    roof = dict(bound="fp64 matrix cores", achieved=round(tflops, 2),
+                peak=FP64_PEAK_TFLOPS, unit="TFLOP/s",
+                frac=round(tflops / FP64_PEAK_TFLOPS, 4), kernel="k_blk_fold",
+                us_per_eval=round(dev_ms * 1e3 / NE, 3),
+                note="the points of a call share one stream over R per group of "
+                     "up to 64, so its matrix instructions and not its bytes "
+                     "bound the fold; the rate counts 2 N_T N_reco operations "
+                     "per evaluation over the device time of the whole call")
+    single = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
+                  unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
+                  traffic=measured_traffic(), kernel="k_step",
+                  avg_kernel_us=round(step_ms * 1e3, 2),
+                  algorithmic_bytes=alg_bytes,
+                  note="one point per stream over R, the steady-state launch of "
+                       "the single-point pipeline back to back; effective rate: "
+                       "the algorithmic bytes of a launch over its time, whether "
+                       "HBM or the Infinity Cache served them; one launch after "
+                       "a 512 MiB cache flush: detail.step_after_cache_flush_us")
     res = dict(metric=METRIC, value=round(evals_s, 1), unit="evals/s",
                n_gpus=1, steps=K, warmup=W, ms_per_step=round(ms_step, 5),
                points_per_step=PPS,
@@ -920,7 +927,7 @@ def main():
                            "(5 solar sources), dense FP32 response 256 MiB "
                            "from 1e8 seeded MC events",
                            n_t=c.n_t, n_reco=c.n_reco, n_e=c.n_e),
-               roofline=roof,
+               roofline=roof, single_point_roofline=single,
                detail=dict(sync_latency_ms_mean=round(float(lat.mean()), 4),
                            sync_latency_ms_std=round(float(lat.std()), 4),
                            eint_weights_us=round(eint_ms * 1e3, 2),
@@ -943,14 +950,14 @@ def main():
     # and the HBM read rate of a plain stream (2 GiB, far beyond the caches)
     rd = nr.nr_probe_hbm_read(0, 2 << 30, 10)
     res["detail"]["hbm_read_probe_gbs"] = round(rd, 1)
-    res["detail"]["step_frac_of_read_probe"] = round(roof["achieved"] / rd, 4)
+    res["detail"]["step_frac_of_read_probe"] = round(single["achieved"] / rd, 4)
     # the same stream over a buffer of R's size with ordinary loads and
     # passes alternating in direction, as consecutive fold passes read R:
     # HBM plus what L2 and the Infinity Cache keep between passes
     r_bytes = 4 * c.n_t * ((c.n_reco + 3) // 4 * 4)
     rc_ = nr.nr_probe_read(0, r_bytes, 40, nr.NR_PROBE_CACHED | nr.NR_PROBE_ALTERNATE)
     res["detail"]["cache_read_probe_gbs"] = round(rc_, 1)
-    res["detail"]["step_frac_of_cache_read_probe"] = round(roof["achieved"] / rc_, 4)
+    res["detail"]["step_frac_of_cache_read_probe"] = round(single["achieved"] / rc_, 4)
     log(f"[bench] probes: FP64 MFMA {probe:.1f} TFLOP/s, HBM read {rd:.0f} GB/s, "
         f"R-sized alternating cached read {rc_:.0f} GB/s")
     # gradient form: 1024 points at the same shapes, -2lnL + 7 derivatives

@@ -120,13 +120,15 @@ int nr_set_response(nr_ctx *ctx, const float *R, int n_t, int n_reco,
 int nr_set_data(nr_ctx *ctx, const double *n, const double *b, int n_reco,
                 const double *pull_mean, const double *pull_sigma);
 
-/* -2lnL for n_pts points (theta: [n_pts][7], host), one plain single-point
- * evaluation per point: device E-integral (Eq. (fT) summed per source over
- * the reachable nodes, as suffix sums of the per-node Laurent coefficients
- * in T), weights, HBM-streaming fold and likelihood reduction.  Successive
- * points overlap: one launch folds point p while it forms the weights of
- * p + 1, the node table of p + 2, reduces the fold of p - 1 and completes
- * the likelihood of p - 2.  nll: [n_pts] host.  Synchronous. */
+/* -2lnL for n_pts points (theta: [n_pts][7], host).  One or two points run
+ * the single-point launches: device E-integral (Eq. (fT) summed per source
+ * over the reachable nodes, as suffix sums of the per-node Laurent
+ * coefficients in T), weights, HBM-streaming fold and likelihood reduction;
+ * successive points overlap.  Three or more share the stream over R in
+ * blocks: their weights from the exact basis form of Eq. (fT), the fold as a
+ * product on the FP64 matrix cores, then the likelihood of every point.  A
+ * point's result does not depend on the block it falls in; the two routes
+ * agree to rounding.  nll: [n_pts] host.  Synchronous. */
 int nr_eval_nll(nr_ctx *ctx, const double *theta, int n_pts, double *nll);
 
 /* -2lnL and its gradient d(-2lnL)/d theta ([n_pts][7]) per point, through
@@ -140,8 +142,10 @@ int nr_eval_mu(nr_ctx *ctx, const double *theta, int n_pts, double *mu);
 /* Device-pointer variant of nr_eval_nll / nr_eval_nll_grad: d_theta
  * [n_pts][7] double, d_nll [n_pts] double, d_grad [n_pts][7] double or
  * NULL.  Enqueued on `stream` (hipStream_t, NULL = the default stream);
- * returns without waiting.  Replays a cached HIP graph for repeated
- * (pointer, n_pts) combinations. */
+ * returns without waiting.  With a gradient, replays a cached HIP graph for
+ * repeated (pointer, n_pts) combinations; a list of three or more points
+ * takes device memory for its block on first use (up to 128 MiB, more where
+ * one block of 16 points needs it), kept by the context. */
 int nr_eval_nll_dev(nr_ctx *ctx, const double *d_theta, int n_pts,
                     double *d_nll, double *d_grad, void *stream);
 
@@ -173,7 +177,8 @@ int nr_set_band_skipping(nr_ctx *ctx, int on);
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * computation, arguments and results of nr_eval_nll_dev, through the same
  * kernels, with nothing allocated.  The pipeline's node tables, fold vectors,
- * partial sums and adjoint buffers live in a static workspace of the library
+ * partial sums and adjoint buffers (and the blocks of a list of points, as
+ * many points at a time as fit) live in a static workspace of the library
  * (NR_NOALLOC_WORKSPACE_BYTES per device, held from the first nr_create on
  * that device until the process ends) instead of the context's buffers, and
  * the launches go directly onto `stream` with no graph of the library's own,

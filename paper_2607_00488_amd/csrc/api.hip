@@ -2,6 +2,7 @@
 // paragraph and Sec. III.B: the SM reference and the response are built once
 // and kept resident), stream-ordered launches, HIP-graph replay, errors.
 #include "batched.h"
+#include "block.h"
 #include "ess.h"
 #include "mlp.h"
 #include "../../include/nureweight.h"
@@ -181,9 +182,11 @@ struct nr_ctx {
     std::vector<int> src_off, src_n, src_group;
     std::vector<double> hE, hW, hPe, tc;
     std::vector<int> jmin;
-    std::vector<double> ssm, basis;
+    std::vector<double> ssm;
+    std::vector<double> sbasis;  // [n_src][n_t][kCompBasis] basis spectra (basis.h)
     double *d_E = nullptr /* 1/E per node */, *d_W = nullptr, *d_Pe = nullptr, *d_tc = nullptr;
-    double *d_ssm = nullptr, *d_basis = nullptr;
+    double* d_ssm = nullptr;
+    double* d_rf = nullptr;  // [n_rows][kRF or kRFComp] row factors (basis.h)
     int *d_group = nullptr, *d_jmin = nullptr, *d_srcoff = nullptr;
     double* d_table[2] = {nullptr, nullptr};  // [n_nodes + n_src] double4, by parity
     // node-scan work-groups: (source, 512-node chunk) pairs, and the chunk
@@ -200,6 +203,12 @@ struct nr_ctx {
     std::vector<int> rowband;
     int *d_rowband = nullptr, *d_tileband = nullptr;
     bool skip_zero = false;
+    // per column tile of the blocked fold the rows [lo, hi) holding its
+    // non-zero responses
+    int* d_blkband = nullptr;
+    // workspace of the blocked fold (lists of points), and its size
+    double* d_blk = nullptr;
+    size_t blk_bytes = 0;
     bool m_user = false;
     double n_sig = 0;
     std::vector<double> mrow;
@@ -313,27 +322,24 @@ inline bool reach(double me, double E, double T) {
     return T <= 2.0 * E * E / (me + 2.0 * E);
 }
 
-// The ten theta-independent pieces of source k's recoil spectrum at bin l:
-// per flavour the sums of nu P_a, nu P_a y^2 and nu P_a x over the reachable
-// nodes (the coefficients of g_L^2, g_R^2 and -g_L g_R in Eq.
-// (sm_cross_section)), and nu (1/T - 1/E) for the magnetic term (Eq.
-// (xs_mm)); S_theta(T_l) is sum_b c_b(theta) times these.
-void source_basis(const nr_ctx* c, int k, int l, double acc[10]) {
+// The seven theta-independent spectra of source k at bin l (basis.h): sums
+// over the reachable nodes.
+void source_basis(const nr_ctx* c, int k, int l, double acc[nr::kCompBasis]) {
     const int n_t = c->n_t;
     const double T = c->tc[l];
     const int hi = c->src_off[k] + c->src_n[k];
-    for (int q = 0; q < 10; ++q) acc[q] = 0.0;
+    for (int q = 0; q < nr::kCompBasis; ++q) acc[q] = 0.0;
     for (int j = c->jmin[(size_t)k * n_t + l]; j < hi; ++j) {
         const double E = c->hE[j], nu = c->hW[j], pe = c->hPe[j];
-        const double P[3] = {pe, (1 - pe) * (1 - c->ph.tau_frac),
-                             (1 - pe) * c->ph.tau_frac};
         const double y = 1.0 - T / E, x = c->ph.me * T / (E * E);
-        for (int a = 0; a < 3; ++a) {
-            acc[3 * a + 0] += nu * P[a];
-            acc[3 * a + 1] += nu * P[a] * y * y;
-            acc[3 * a + 2] += nu * P[a] * x;
-        }
-        acc[9] += nu * (P[0] + P[1] + P[2]) * (1.0 / T - 1.0 / E);
+        const double ve = nu * pe, vx = nu * (1.0 - pe);
+        acc[0] += ve;
+        acc[1] += vx;
+        acc[2] += ve * y * y;
+        acc[3] += vx * y * y;
+        acc[4] += ve * x;
+        acc[5] += vx * x;
+        acc[6] += nu * (1.0 / T - 1.0 / E);
     }
 }
 
@@ -346,10 +352,41 @@ void recompute_mrow(nr_ctx* c) {
         c->mrow[l] = tot > 0 ? c->n_sig * c->ssm[l] / tot : 0.0;
 }
 
+// Row factors (basis.h) of the rows [row0, row0 + n_t) from the summed
+// spectra of the sources src[0 .. n), a row's m and S_SM: with two groups
+// (fixed and scaled by f_8B) rows of kRF, with one rows of kRFComp.
+void row_factors(const nr_ctx* c, const int* src, int n, bool groups, const double* m,
+                 const double* ssm, double* F) {
+    constexpr int CB = nr::kCompBasis;
+    const int rl = groups ? nr::kRF : nr::kRFComp, ng = groups ? 2 : 1;
+    for (int l = 0; l < c->n_t; ++l) {
+        double* f = F + (size_t)l * rl;
+        for (int b = 0; b < rl; ++b) f[b] = 0.0;
+        if (!(ssm[l] > 0.0)) {
+            f[ng * CB] = m[l];  // weight 1
+            continue;
+        }
+        for (int q = 0; q < n; ++q) {
+            const double* I = &c->sbasis[((size_t)src[q] * c->n_t + l) * CB];
+            double* g = f + (groups && c->src_group[src[q]] ? CB : 0);
+            for (int b = 0; b < CB; ++b) g[b] += I[b];
+        }
+        for (int b = 0; b < ng * CB; ++b) f[b] *= m[l] / ssm[l];
+    }
+}
+
 int upload_mrow(nr_ctx* c) {
     if (!c->have_rsp || c->multi) return 0;
     HIPCHK(hipMemcpy(c->d_mrow, c->mrow.data(), sizeof(double) * c->n_t,
                      hipMemcpyHostToDevice));
+    if (!c->have_src) return 0;  // nr_set_sources comes back here
+    std::vector<int> src(c->n_src);
+    for (int k = 0; k < c->n_src; ++k) src[k] = k;
+    std::vector<double> F((size_t)c->n_t * nr::kRF);
+    row_factors(c, src.data(), c->n_src, true, c->mrow.data(), c->ssm.data(), F.data());
+    int rc;
+    if ((rc = dalloc(&c->d_rf, F.size()))) return rc;
+    HIPCHK(hipMemcpy(c->d_rf, F.data(), sizeof(double) * F.size(), hipMemcpyHostToDevice));
     return 0;
 }
 
@@ -400,6 +437,32 @@ int set_tile_bands(nr_ctx* c) {
     return 0;
 }
 
+// Rows [lo, hi) with non-zero responses of every column tile of the blocked
+// fold; lo on a multiple of four, the rows of one matrix instruction.
+int set_blk_bands(nr_ctx* c) {
+    const int n_ct = (c->ldr + nr::kBlkCols - 1) / nr::kBlkCols;
+    std::vector<int> bb((size_t)2 * n_ct, 0);
+    for (int t = 0; t < n_ct; ++t) {
+        const int c0 = t * nr::kBlkCols / 4, c1 = c0 + nr::kBlkCols / 4;
+        int lo = c->n_rows, hi = 0;
+        for (int l = 0; l < c->n_rows; ++l) {
+            const int a = c->rowband[2 * (size_t)l], b = c->rowband[2 * (size_t)l + 1];
+            if (a < b && a < c1 && b > c0) {
+                lo = std::min(lo, l);
+                hi = l + 1;
+            }
+        }
+        if (lo < hi) {
+            bb[2 * t] = lo & ~3;
+            bb[2 * t + 1] = hi;
+        }
+    }
+    int rc;
+    if ((rc = dalloc(&c->d_blkband, bb.size()))) return rc;
+    HIPCHK(hipMemcpy(c->d_blkband, bb.data(), sizeof(int) * bb.size(), hipMemcpyHostToDevice));
+    return 0;
+}
+
 int choose_tiling(nr_ctx* c, int rows_req) {
     c->n_fc = (c->ldr / 4 + 511) / 512;   // fold tiles are 2048 columns wide
     c->n_cc = (c->n_reco + 63) / 64;      // reduction groups of 64 columns
@@ -423,6 +486,7 @@ int choose_tiling(nr_ctx* c, int rows_req) {
     c->adj_grid = nr::adjoint_grid(c->n_t);
     if ((rc = dalloc(&c->d_jpart, (size_t)c->adj_grid * nr::kNBasis))) return rc;
     if ((rc = set_tile_bands(c))) return rc;
+    if ((rc = set_blk_bands(c))) return rc;
     clear_graphs(c);
     return 0;
 }
@@ -608,6 +672,23 @@ nr::FoldArgs fold_args(nr_ctx* c, const double* thp, const double* v,
     return fa;
 }
 
+nr::PtsWeightArgs weight_args(nr_ctx* c, const double* d_theta, int n_pts, int n_pad, int ldw,
+                              double* wt) {
+    nr::PtsWeightArgs a{};
+    a.rf = c->d_rf;
+    a.n_t = c->n_t;
+    a.n_comp = c->multi ? c->n_comp : 1;
+    a.theta = d_theta;
+    a.n_theta = c->n_theta;
+    a.rate_index = c->multi ? 5 : -1;
+    a.n_pts = n_pts;
+    a.n_pad = n_pad;
+    a.ldw = ldw;
+    a.ph = c->ph;
+    a.wt = wt;
+    return a;
+}
+
 int step(nr_ctx* c, const nr::FoldArgs* fold, const nr::RowArgs* rows,
          const nr::ScanArgs* scan, const nr::FoldArgs* fin, hipStream_t s,
          const nr::FoldArgs* fnl = nullptr) {
@@ -703,9 +784,7 @@ int enqueue_points(nr_ctx* c, const double* th, int n_pts, double* nll,
         aa.n_t = c->n_t;
         aa.n_reco = c->n_reco;
         aa.a = wk->a;
-        aa.ssm = c->d_ssm;
-        aa.mrow = c->d_mrow;
-        aa.basis = c->d_basis;
+        aa.rf = c->d_rf;
         aa.theta = thp(p);
         aa.gb = wk->gb;
         aa.jpart = wk->jpart;
@@ -721,6 +800,137 @@ int enqueue_points(nr_ctx* c, const double* th, int n_pts, double* nll,
     return 0;
 }
 
+// ---- lists of points through the blocked fold (block.hip).  Four launches
+// per block of points: weights, fold, likelihood sums, final.
+// The row splits depend on the response's shape only, never on the number of
+// points, so a point's result does not depend on the block it falls in.
+struct BlkWork {
+    double* wt;    // [n_rows][pts]
+    double* part;  // [n_split][pts][ldr]
+    double* dev;   // [pts][column tiles]
+};
+
+// Splits of the rows so that column tiles x splits fill the chip's 256
+// compute units once, each of at least 64 rows (two stages of the fold).
+// (At 16384 x 4096 that is 16 x 16: twice as many splits write and read back
+// 134 MB of partial sums for 64 points.)
+void blk_split(const nr_ctx* c, int* n_split, int* rows_per) {
+    const int n_ct = (c->ldr + nr::kBlkCols - 1) / nr::kBlkCols;
+    int s = std::max(1, std::min((256 + n_ct - 1) / n_ct, c->n_rows / 64));
+    const int step = nr::blk_fold_lds_rows();
+    *rows_per = ((c->n_rows + s - 1) / s + step - 1) / step * step;
+    *n_split = (c->n_rows + *rows_per - 1) / *rows_per;
+}
+
+size_t carve_blk(const nr_ctx* c, double* base, int pts, BlkWork* w) {
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        double* p = base ? base + off : nullptr;
+        off += (n + 31) / 32 * 32;
+        return p;
+    };
+    int ns, rp;
+    blk_split(c, &ns, &rp);
+    w->part = take((size_t)ns * pts * c->ldr);
+    w->wt = take((size_t)c->n_rows * pts);
+    w->dev = take((size_t)pts * ((c->n_reco + nr::kBlkFinCols - 1) / nr::kBlkFinCols));
+    return off * sizeof(double);
+}
+
+// Points per block in `limit` bytes of workspace: at most 4096, whole groups
+// of 64 (the fold's largest) where at least one fits, else whole blocks of
+// 16; 0 if not even one does.
+constexpr size_t kBlkBytes = (size_t)128 << 20;
+
+int blk_points(const nr_ctx* c, int n_pts, size_t limit) {
+    BlkWork w;
+    const size_t b16 = carve_blk(c, nullptr, 16, &w);
+    if (b16 > limit) return 0;
+    int pts = 16;
+    const int want = std::min((n_pts + 15) / 16 * 16, 4096);
+    while (pts + 16 <= want && carve_blk(c, nullptr, pts + 16, &w) <= limit) pts += 16;
+    return pts < want && pts > 64 ? pts / 64 * 64 : pts;
+}
+
+// Lists of three or more points share the stream over R (one or two run the
+// single-point launches, which need no workspace).  A context whose shapes
+// the allocation-free entry point accepts takes the same route in both entry
+// points, so that their results stay bitwise equal.
+constexpr int kBlkMinPts = 3;
+
+bool use_blocks(const nr_ctx* c, int n_pts) {
+    if (n_pts < kBlkMinPts) return false;
+    Work w;
+    if (carve_work(c, nullptr, &w) > (size_t)NR_NOALLOC_WORKSPACE_BYTES) return true;
+    return blk_points(c, 16, NR_NOALLOC_WORKSPACE_BYTES) > 0;
+}
+
+// The context's own workspace for a list of n_pts points.
+int ensure_blk(nr_ctx* c, int n_pts) {
+    BlkWork w;
+    const int pts = std::max(16, blk_points(c, n_pts, kBlkBytes));
+    const size_t need = carve_blk(c, nullptr, pts, &w);
+    if (need <= c->blk_bytes) return 0;
+    int rc;
+    c->blk_bytes = 0;
+    if ((rc = dalloc(&c->d_blk, need / sizeof(double)))) return rc;
+    c->blk_bytes = need;
+    return 0;
+}
+
+int enqueue_blocks(nr_ctx* c, const double* th, int n_pts, double* nll, double* mu,
+                   hipStream_t s, double* base, size_t limit) {
+    const int pts = std::max(16, blk_points(c, n_pts, limit));
+    BlkWork w;
+    carve_blk(c, base, pts, &w);
+    int ns, rp;
+    blk_split(c, &ns, &rp);
+    for (int p0 = 0; p0 < n_pts; p0 += pts) {
+        const int P = std::min(pts, n_pts - p0);
+        const double* thp = th + (size_t)p0 * c->n_theta;
+        HIPCHK(nr::launch_pts_weights(weight_args(c, thp, P, (P + 15) / 16 * 16, pts, w.wt), s));
+        nr::BlkFoldArgs fa{};
+        fa.wt = w.wt;
+        fa.ldw = pts;
+        fa.R = c->d_R;
+        fa.ldr = c->ldr;
+        fa.n_rows = c->n_rows;
+        fa.n_pts = P;
+        fa.n_ct = (c->ldr + nr::kBlkCols - 1) / nr::kBlkCols;
+        fa.n_split = ns;
+        fa.rows_per = rp;
+        fa.part = w.part;
+        fa.split_stride = (size_t)((P + 15) / 16 * 16) * c->ldr;
+        fa.band = c->skip_zero ? c->d_blkband : nullptr;
+        HIPCHK(nr::launch_blk_fold(fa, s));
+        nr::BlkFinishArgs ga{};
+        ga.part = w.part;
+        ga.split_stride = fa.split_stride;
+        ga.n_split = ns;
+        ga.ldr = c->ldr;
+        ga.n_reco = c->n_reco;
+        ga.n_pts = P;
+        ga.n_ct = (c->n_reco + nr::kBlkFinCols - 1) / nr::kBlkFinCols;
+        ga.theta = thp;
+        ga.n_theta = c->n_theta;
+        ga.bkg_index = c->multi ? 5 + c->n_comp : 6;
+        ga.n_bkg = c->multi ? c->n_bkg : 1;
+        ga.n = c->d_n;
+        ga.b = c->multi ? c->d_bkg : c->d_b;
+        ga.mask = c->multi ? c->d_mask : nullptr;
+        ga.dev = w.dev;
+        ga.out_mu = mu ? mu + (size_t)p0 * c->n_reco : nullptr;
+        ga.cdata = c->cdata;
+        for (int i = 0; i < c->n_theta; ++i) {
+            ga.pull_mean[i] = c->pull_mean[i];
+            ga.pull_sigma[i] = c->pull_sigma[i];
+        }
+        ga.nll = nll + p0;
+        HIPCHK(nr::launch_blk_finish(ga, s));
+    }
+    return 0;
+}
+
 // Replays a cached graph of the per-point launches when the same buffers and
 // point count come back (the common case in fits and scans).  One or two
 // points launch their five or six kernels directly: a graph replay starts
@@ -730,6 +940,10 @@ constexpr int kDirectMaxPts = 2;
 
 int run_points(nr_ctx* c, const double* th, int n_pts, double* nll,
                double* grad, double* mu, double* w, hipStream_t s) {
+    if (!grad && !w && use_blocks(c, n_pts)) {
+        int rc = ensure_blk(c, n_pts);
+        return rc ? rc : enqueue_blocks(c, th, n_pts, nll, mu, s, c->d_blk, kBlkBytes);
+    }
     if (!c->use_graph || n_pts > 4096 || w || n_pts <= kDirectMaxPts)
         return enqueue_points(c, th, n_pts, nll, grad, mu, w, s);
     GraphKey key{th, n_pts, nll, grad, mu, (void*)s};
@@ -831,20 +1045,6 @@ struct MultiCall {
     double* const* grad;         // device or null (array may be null)
     double* const* mu;           // device or null (array may be null)
 };
-
-nr::WgenArgs wgen_args(nr_ctx* c, const double* th, int P) {
-    nr::WgenArgs w{};
-    w.theta = th;
-    w.n_pts = P;
-    w.ldw = c->b_ldw;
-    w.n_t = c->n_t;
-    w.basis = c->d_basis;
-    w.ssm = c->d_ssm;
-    w.mrow = c->d_mrow;
-    w.ph = c->ph;
-    w.wt = c->d_wt;
-    return w;
-}
 
 // K range of a GEMM tile: the whole reduction, or with band skipping the
 // K-steps whose response entries for the tile are not all zero.  Forward
@@ -965,7 +1165,9 @@ int build_plan(const MultiCall& mc, bool grad, int cfg, BatchPlan* pl) {
 int enqueue_plan(const MultiCall& mc, bool grad, BatchPlan* pl, unsigned* ctr,
                  hipStream_t s) {
     for (int d = 0; d < mc.n; ++d)
-        HIPCHK(nr::launch_wgen(wgen_args(mc.ctx[d], mc.theta[d], mc.n_pts[d]), s));
+        HIPCHK(nr::launch_pts_weights(weight_args(mc.ctx[d], mc.theta[d], mc.n_pts[d],
+                                                  mc.ctx[d]->b_ldw, mc.ctx[d]->b_ldw,
+                                                  mc.ctx[d]->d_wt), s));
     HIPCHK(nr::launch_gemm(nr::kModeNll, pl->cfg, pl->d_probs_f, pl->d_tiles_f,
                            pl->n_tiles_f, ctr, pl->grid_f, s));
     for (int d = 0; d < mc.n; ++d) {
@@ -994,9 +1196,7 @@ int enqueue_plan(const MultiCall& mc, bool grad, BatchPlan* pl, unsigned* ctr,
             a.n_t = c->n_t;
             a.n_pts = mc.n_pts[d];
             a.n_nt = (c->n_reco + nr::gemm_tile_n(pl->cfg) - 1) / nr::gemm_tile_n(pl->cfg);
-            a.ssm = c->d_ssm;
-            a.mrow = c->d_mrow;
-            a.basis = c->d_basis;
+            a.rf = c->d_rf;
             a.theta = mc.theta[d];
             a.part_gb = c->d_bpgb;
             for (int i = 0; i < NR_NTHETA; ++i) {
@@ -1322,7 +1522,7 @@ void nr_destroy(nr_ctx* c) {
     (void)hipDeviceSynchronize();
     clear_graphs(c);
     dfree(&c->d_E); dfree(&c->d_W); dfree(&c->d_Pe); dfree(&c->d_tc);
-    dfree(&c->d_ssm); dfree(&c->d_basis); dfree(&c->d_tnll); dfree(&c->d_nev);
+    dfree(&c->d_ssm); dfree(&c->d_rf); dfree(&c->d_tnll); dfree(&c->d_nev);
     dfree(&c->d_compoff); dfree(&c->d_compsrc); dfree(&c->d_group0);
     dfree(&c->d_ssmc); dfree(&c->d_bkg); dfree(&c->d_mask);
     dfree(&c->d_group); dfree(&c->d_jmin); dfree(&c->d_srcoff);
@@ -1338,6 +1538,7 @@ void nr_destroy(nr_ctx* c) {
     dfree(&c->d_trec); dfree(&c->d_tdp); dfree(&c->d_thp); dfree(&c->d_tred);
     dfree(&c->d_v[0]); dfree(&c->d_v[1]);
     dfree(&c->d_rowband); dfree(&c->d_tileband);
+    dfree(&c->d_blkband); dfree(&c->d_blk);
     dfree(&c->d_scanblk); dfree(&c->d_ctot[0]); dfree(&c->d_ctot[1]);
     free_pinned(c);
     if (c->ev_in) (void)hipEventDestroy(c->ev_in);
@@ -1431,16 +1632,11 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
         }
     }
     c->n_blocks = (n_t + nr::kStepRows - 1) / nr::kStepRows;
-    // theta-independent basis spectra (FP64), used by the adjoint
-    c->basis.assign((size_t)nr::kNBasis * n_t, 0.0);
-    for (int l = 0; l < n_t; ++l)
-        for (int k = 0; k < n_src; ++k) {
-            double acc[10];
-            source_basis(c, k, l, acc);
-            const int g = c->src_group[k] ? 10 : 0;
-            for (int q = 0; q < 10; ++q)
-                c->basis[(size_t)(g + q) * n_t + l] += acc[q];
-        }
+    // theta-independent basis spectra (FP64) of every source
+    c->sbasis.assign((size_t)n_src * n_t * nr::kCompBasis, 0.0);
+    for (int k = 0; k < n_src; ++k)
+        for (int l = 0; l < n_t; ++l)
+            source_basis(c, k, l, &c->sbasis[((size_t)k * n_t + l) * nr::kCompBasis]);
     // upload
     if ((rc = dalloc(&c->d_E, c->n_nodes)) || (rc = dalloc(&c->d_W, c->n_nodes)) ||
         (rc = dalloc(&c->d_Pe, c->n_nodes)) || (rc = dalloc(&c->d_tc, n_t)) ||
@@ -1451,7 +1647,6 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
         (rc = dalloc(&c->d_group0, n_src)) ||
         (rc = dalloc(&c->d_table[0], (size_t)4 * (c->n_nodes + n_src))) ||
         (rc = dalloc(&c->d_table[1], (size_t)4 * (c->n_nodes + n_src))) ||
-        (rc = dalloc(&c->d_basis, (size_t)nr::kNBasis * n_t)) ||
         (rc = dalloc(&c->d_v[0], n_t)) || (rc = dalloc(&c->d_v[1], n_t)))
         return rc;
     {
@@ -1492,7 +1687,6 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
     HIPCHK(hipMemcpy(c->d_compoff, c->comp_off.data(), sizeof(int) * 2, hipMemcpyHostToDevice));
     HIPCHK(hipMemcpy(c->d_compsrc, c->comp_src.data(), sizeof(int) * n_src, hipMemcpyHostToDevice));
     HIPCHK(hipMemset(c->d_group0, 0, sizeof(int) * n_src));
-    HIPCHK(hipMemcpy(c->d_basis, c->basis.data(), sizeof(double) * c->basis.size(), hipMemcpyHostToDevice));
     // SM reference on the device with the same E-integral code the
     // evaluations use, so that w = S_theta / S_SM is exactly 1 at theta_SM.
     {
@@ -1651,9 +1845,12 @@ int nr_eval_nll_dev_noalloc(nr_ctx* c, const double* d_theta, int n_pts,
     // that a caller may capture them in its own graph
     Bridge br;
     if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
-    if ((rc = enqueue_points(c, d_theta, n_pts, d_nll, d_grad, nullptr, nullptr,
-                             br.work, &w)))
-        return rc;
+    if (!d_grad && use_blocks(c, n_pts))
+        rc = enqueue_blocks(c, d_theta, n_pts, d_nll, nullptr, br.work, base,
+                            NR_NOALLOC_WORKSPACE_BYTES);
+    else
+        rc = enqueue_points(c, d_theta, n_pts, d_nll, d_grad, nullptr, nullptr, br.work, &w);
+    if (rc) return rc;
     return bridge_end(br);
 }
 
@@ -1913,7 +2110,15 @@ int nr_set_components(nr_ctx* c, const nr_components* k, int n_reco) {
         if ((rc = step(c, nullptr, nullptr, &sa, nullptr, c->stream))) return rc;
         if ((rc = step(c, nullptr, &ra, nullptr, nullptr, c->stream))) return rc;
     }
+    std::vector<double> ssmc(n_rows), F(n_rows * nr::kRFComp);
+    HIPCHK(hipMemcpyAsync(ssmc.data(), c->d_ssmc, sizeof(double) * n_rows,
+                          hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    for (int q = 0; q < K; ++q)
+        row_factors(c, &src[off[q]], off[q + 1] - off[q], false, &mrow[(size_t)q * n_t],
+                    &ssmc[(size_t)q * n_t], &F[(size_t)q * n_t * nr::kRFComp]);
+    if ((rc = dalloc(&c->d_rf, F.size()))) return rc;
+    HIPCHK(hipMemcpy(c->d_rf, F.data(), sizeof(double) * F.size(), hipMemcpyHostToDevice));
     if ((rc = choose_tiling(c, 0))) return rc;
     return 0;
 }
@@ -1997,9 +2202,7 @@ int nr_time_stage(nr_ctx* c, int stage, int iters, double* avg_ms) {
         aa.n_t = c->n_t;
         aa.n_reco = c->n_reco;
         aa.a = c->d_a;
-        aa.ssm = c->d_ssm;
-        aa.mrow = c->d_mrow;
-        aa.basis = c->d_basis;
+        aa.rf = c->d_rf;
         aa.theta = th;
         aa.gb = c->d_gb;
         aa.jpart = c->d_jpart;
@@ -2591,12 +2794,10 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
 }
 
 // ------------------------------------------------------------ templates
-// Row factors F_bl = m_l I_b(T_l) / S_SM(T_l) (and m_l alone for the rows
-// with S_SM = 0, whose weight is 1) in FP64 on the host, one streaming pass
-// over R on the device, then the data of each bin beside its templates.
-// New data alone rewrite only the data slots.  In the multi-component form
-// each component's row block is folded with that component's basis and
-// SM spectrum.
+// One streaming FP64 pass over R with the row factors of every row (basis.h),
+// then the data of each bin beside its templates.  New data alone rewrite
+// only the data slots.  In the multi-component form each component's row
+// block is folded with its own factors.
 
 // Record length and gradient contractions per point of the context's form.
 static int tmpl_rl(const nr_ctx* c) {
@@ -2604,90 +2805,52 @@ static int tmpl_rl(const nr_ctx* c) {
                     : nr::kTmplRec;
 }
 static int tmpl_nacc(const nr_ctx* c) {
-    return c->multi ? 10 + c->n_comp + c->n_bkg : nr::kTmplCols;
+    return c->multi ? nr::kCompBasis + c->n_comp + c->n_bkg : nr::kTmplCols;
 }
 
-// Fold the row block [row0, row0 + n_t) of R with factors F [n_t][kTmplCols]
-// into the record columns dst (of records rl doubles long).
-static hipError_t fold_block(nr_ctx* c, const std::vector<double>& F, size_t row0,
-                             const int dst[nr::kTmplCols], int rl, double* d_F,
+// Fold the rows of block k (the whole response, or component k's rows) into
+// the record columns dst0 .. dst0 + n_dst - 1 (of records rl doubles long).
+static hipError_t fold_block(nr_ctx* c, int k, int frl, int dst0, int n_dst, int rl,
                              double* d_part, int n_slab) {
-    hipError_t e = hipMemcpy(d_F, F.data(), sizeof(double) * F.size(), hipMemcpyHostToDevice);
+    const size_t row0 = (size_t)k * c->n_t;
+    nr::TmplFoldArgs fa{c->d_R + row0 * c->ldr, c->ldr, c->n_t, c->n_reco,
+                        c->d_rf + row0 * frl, frl, d_part};
+    hipError_t e = nr::launch_tmpl_fold(fa, n_slab, c->stream);
     if (e != hipSuccess) return e;
-    nr::TmplFoldArgs fa{c->d_R + row0 * c->ldr, c->ldr, c->n_t, c->n_reco, d_F, d_part};
-    if ((e = nr::launch_tmpl_fold(fa, n_slab, c->stream)) != hipSuccess) return e;
     nr::TmplRecArgs ra{};
     ra.part = d_part;
     ra.n_slab = n_slab;
     ra.n_reco = c->n_reco;
+    ra.n_cols = frl;
+    ra.dst0 = dst0;
+    ra.n_dst = n_dst;
     ra.rec = c->d_trec;
     ra.rl = rl;
-    for (int b = 0; b < nr::kTmplCols; ++b) ra.dst[b] = dst[b];
-    if ((e = nr::launch_tmpl_records(ra, c->stream)) != hipSuccess) return e;
-    return hipStreamSynchronize(c->stream);  // F and part are reused
+    return nr::launch_tmpl_records(ra, c->stream);
 }
 
 static int build_templates(nr_ctx* c) {
     const int n_t = c->n_t, n_reco = c->n_reco, rl = tmpl_rl(c);
-    constexpr int NC = nr::kTmplCols;
     int rc;
     hipError_t e = hipSuccess;
     if (!c->tmpl_ok) {
         const int n_slab = (n_t + nr::kTmplSlabRows - 1) / nr::kTmplSlabRows;
-        double *d_F = nullptr, *d_part = nullptr;
+        const int frl = c->multi ? nr::kRFComp : nr::kRF;
+        double* d_part = nullptr;
         c->tmpl_data_ok = false;
-        if ((rc = dalloc(&d_F, (size_t)n_t * NC)) ||
-            (rc = dalloc(&d_part, (size_t)n_slab * NC * n_reco)) ||
+        if ((rc = dalloc(&d_part, (size_t)n_slab * frl * n_reco)) ||
             (rc = dalloc(&c->d_trec, (size_t)n_reco * rl))) {
-            dfree(&d_F);
             dfree(&d_part);
             return rc;
         }
-        std::vector<double> F((size_t)n_t * NC);
-        int dst[NC];
         if (!c->multi) {
-            for (int l = 0; l < n_t; ++l) {
-                const double ssm = c->ssm[l], m = c->mrow[l];
-                for (int b = 0; b < NC; ++b) F[(size_t)l * NC + b] = 0.0;
-                if (ssm > 0.0) {
-                    for (int b = 0; b < nr::kNBasis; ++b)
-                        F[(size_t)l * NC + b] = m * c->basis[(size_t)b * n_t + l] / ssm;
-                } else {
-                    F[(size_t)l * NC + nr::kNBasis] = m;
-                }
-            }
-            for (int b = 0; b < NC; ++b) dst[b] = b;
-            e = fold_block(c, F, 0, dst, rl, d_F, d_part, n_slab);
+            e = fold_block(c, 0, frl, 0, nr::kTmplCols, rl, d_part, n_slab);
         } else {
-            // per component: its sources' basis, its SM spectrum, its rows
-            const int K = c->n_comp;
-            std::vector<double> ssmc((size_t)K * n_t), mrow((size_t)K * n_t);
-            e = hipMemcpy(ssmc.data(), c->d_ssmc, sizeof(double) * ssmc.size(), hipMemcpyDeviceToHost);
-            if (e == hipSuccess)
-                e = hipMemcpy(mrow.data(), c->d_mrow, sizeof(double) * mrow.size(), hipMemcpyDeviceToHost);
-            for (int k = 0; k < K && e == hipSuccess; ++k) {
-                for (int l = 0; l < n_t; ++l) {
-                    double I[10] = {0}, acc[10];
-                    for (int q = c->comp_off[k]; q < c->comp_off[k + 1]; ++q) {
-                        source_basis(c, c->comp_src[q], l, acc);
-                        for (int b = 0; b < 10; ++b) I[b] += acc[b];
-                    }
-                    const size_t row = (size_t)k * n_t + l;
-                    double* f = &F[(size_t)l * NC];
-                    for (int b = 0; b < NC; ++b) f[b] = 0.0;
-                    if (ssmc[row] > 0.0) {
-                        for (int b = 0; b < 10; ++b) f[b] = mrow[row] * I[b] / ssmc[row];
-                    } else {
-                        f[nr::kNBasis] = mrow[row];
-                    }
-                }
-                for (int b = 0; b < NC; ++b) dst[b] = -1;
-                for (int b = 0; b < 10; ++b) dst[b] = nr::kTmplCompCols * k + b;
-                dst[nr::kNBasis] = nr::kTmplCompCols * k + 10;
-                e = fold_block(c, F, (size_t)k * n_t, dst, rl, d_F, d_part, n_slab);
-            }
+            for (int k = 0; k < c->n_comp && e == hipSuccess; ++k)
+                e = fold_block(c, k, frl, nr::kTmplCompCols * k, nr::kTmplCompCols, rl, d_part,
+                               n_slab);
         }
-        dfree(&d_F);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         dfree(&d_part);
         if (e != hipSuccess) return fail(NR_EHIP, "template fold: %s", hipGetErrorString(e));
         c->tmpl_ok = true;

@@ -1,21 +1,11 @@
 // Internal declarations of the batched (GEMM) path.
 #pragma once
-#include "common.h"
+#include "basis.h"
 
 namespace nr {
 
 constexpr int kModeNll = 0;  // forward: fused Poisson epilogue
 constexpr int kModeAdj = 1;  // adjoint: C = A R^T written as FP32
-
-struct WgenArgs {
-    const double* theta;  // [n_pts][7]
-    int n_pts, ldw, n_t;
-    const double* basis;  // [kNBasis][n_t]
-    const double* ssm;    // [n_t]
-    const double* mrow;   // [n_t]
-    Phys ph;
-    double* wt;           // [n_t][ldw]
-};
 
 // One GEMM problem of the grouped launch (one dataset / analysis).
 // Forward: C[M=n_pts][N=n_reco] = A[M][K=n_t] B[K][N] with A given as its
@@ -65,9 +55,7 @@ struct FinalArgs {
 struct ContractArgs {
     double* U;       // [n_pts][ldu]; its chunks' first columns take the partial sums
     int ldu, n_t, n_pts, n_nt;
-    const double* ssm;
-    const double* mrow;
-    const double* basis;
+    const double* rf;  // [n_t][kRF] row factors
     const double* theta;
     const double* part_gb;
     double pull_mean[kNTheta];
@@ -82,24 +70,25 @@ struct ContractArgs {
 //   mu_j = f_bkg b_j + G0_j + sum_b c_b(theta) G_bj,
 //   G_bj = sum_{l: S_SM(T_l) > 0} F_bl R_lj,  F_bl = m_l I_b(T_l) / S_SM(T_l),
 //   G0_j = sum_{l: S_SM(T_l) = 0} m_l R_lj   (rows with w := 1).
-constexpr int kTmplCols = kNBasis + 1;     // G_0..G_19, G0
-constexpr int kTmplRec = 24;               // per reco bin: G_0..G_19, G0, b, n, pad
+constexpr int kTmplCols = kNBasis + 1;     // G_0..G_13, G0
+constexpr int kTmplRec = 18;               // per reco bin: G_0..G_13, G0, b, n, pad
 constexpr int kTmplSlabRows = 256;         // response rows per template-fold work-group
 constexpr int kTmplWave = 64;              // points per evaluation work-group
 
 struct TmplFoldArgs {
     const float* R;
     int ldr, n_t, n_reco;
-    const double* F;   // [n_t][kTmplCols] row factors
-    double* part;      // [n_slab][kTmplCols][n_reco]
+    const double* rf;  // [n_t][rl] row factors, rl = kRF or kRFComp
+    int rl;
+    double* part;      // [n_slab][rl][n_reco]
 };
 
 struct TmplRecArgs {
     const double* part;
-    int n_slab, n_reco;
+    int n_slab, n_reco, n_cols;  // folded columns per slab
+    int dst0, n_dst;   // columns 0 .. n_dst - 1 go to the record's dst0 ..
     double* rec;       // [n_reco][rl]
     int rl;            // record length (doubles)
-    int dst[kTmplCols];  // record column of each folded column, -1: not kept
 };
 
 struct TmplDataArgs {
@@ -141,16 +130,16 @@ struct TmplFinalArgs {
 };
 
 // Multi-component template form (Eqs. (Rij), (fNp_reweight), (mu_total)):
-// component k's sources give 10 basis spectra (no group scaling: the rate
+// component k's sources give 7 basis spectra (no group scaling: the rate
 // parameter r_k scales the component), so per reco bin the record holds
-// G^(k)_0..9 and G0^(k) for each component, the background templates
+// G^(k)_0..6 and G0^(k) for each component, the background templates
 // MT Rate_q pdf_q(j), the common mask M_j and the data n_j:
 //   mu_j = M_j [ sum_k r_k (G0^(k)_j + sum_b c_b G^(k)_bj) + sum_q r_q B_qj ].
 constexpr int kTmplMaxComp = 8;
 constexpr int kTmplMaxBkg = 8;
 constexpr int kTmplSmallComp = 5;  // a smaller register class of the kernel
 constexpr int kTmplSmallBkg = 4;
-constexpr int kTmplCompCols = 11;
+constexpr int kTmplCompCols = kCompBasis + 1;
 
 struct TmplMultiDataArgs {
     const double* n;     // [n_reco]
@@ -166,12 +155,12 @@ struct TmplMultiEvalArgs {
     int rl, K, B, n_theta, n_reco, n_pts, cols_per;
     Phys ph;
     double* dpart;        // [n_split][n_pts]
-    double* hpart;        // [n_split][10 + K + B][n_pts] or null (gradient)
+    double* hpart;        // [n_split][kCompBasis + K + B][n_pts] or null (gradient)
     double* mu;           // [n_pts][n_reco] or null
 };
 
 struct TmplMultiFinalArgs {
-    const double* red;    // [1 + 10 + K + B][n_pts]
+    const double* red;    // [1 + kCompBasis + K + B][n_pts]
     const double* theta;
     int n_theta, K, B, n_pts;
     double cdata;
@@ -192,7 +181,6 @@ hipError_t launch_tmpl_eval(const TmplEvalArgs& a, int n_split, hipStream_t s);
 hipError_t launch_tmpl_reduce(const TmplReduceArgs& a, hipStream_t s);
 hipError_t launch_tmpl_final(const TmplFinalArgs& a, hipStream_t s);
 
-hipError_t launch_wgen(const WgenArgs& a, hipStream_t s);
 // Tile configurations of the GEMM: 0: 128x128, 1: 64x128, 2: 128x64,
 // 3: 64x64 (M x N per work-group).
 constexpr int kGemmConfigs = 4;

@@ -46,108 +46,6 @@ __device__ inline double wave_sum64(double v) {
     return v;
 }
 
-// Basis coefficients c_b(theta) of S_theta = sum_b c_b I_b (the flavour sum
-// of Eq. (sm_cross_section) with Eq. (xs_nsi) couplings and the magnetic
-// term of Eq. (xs_mm), split by source group and by the coupling products).
-__device__ inline void basis_coef(const double* th, const Phys& ph,
-                                  double c[kNBasis]) {
-    const double gle = ph.gLe + th[0], gre = ph.gR + th[1];
-    const double glm = ph.gLm, grm = ph.gR;
-    const double glt = ph.gLm + th[2], grt = ph.gR + th[3];
-    for (int g = 0; g < 2; ++g) {
-        const double f = g ? th[5] : 1.0;
-        const int o = g * 10;
-        c[o + 0] = f * gle * gle;
-        c[o + 1] = f * gre * gre;
-        c[o + 2] = -f * gle * gre;
-        c[o + 3] = f * glm * glm;
-        c[o + 4] = f * grm * grm;
-        c[o + 5] = -f * glm * grm;
-        c[o + 6] = f * glt * glt;
-        c[o + 7] = f * grt * grt;
-        c[o + 8] = -f * glt * grt;
-        c[o + 9] = f * ph.cmm * th[4];
-    }
-}
-
-__device__ inline void basis_dcoef(const double* th, const Phys& ph,
-                                   double dc[kNTheta][kNBasis]) {
-    for (int i = 0; i < kNTheta; ++i)
-        for (int b = 0; b < kNBasis; ++b) dc[i][b] = 0.0;
-    const double gle = ph.gLe + th[0], gre = ph.gR + th[1];
-    const double glm = ph.gLm, grm = ph.gR;
-    const double glt = ph.gLm + th[2], grt = ph.gR + th[3];
-    for (int g = 0; g < 2; ++g) {
-        const double f = g ? th[5] : 1.0;
-        const int o = g * 10;
-        dc[0][o + 0] = f * 2.0 * gle;
-        dc[0][o + 2] = -f * gre;
-        dc[1][o + 1] = f * 2.0 * gre;
-        dc[1][o + 2] = -f * gle;
-        dc[2][o + 6] = f * 2.0 * glt;
-        dc[2][o + 8] = -f * grt;
-        dc[3][o + 7] = f * 2.0 * grt;
-        dc[3][o + 8] = -f * glt;
-        dc[4][o + 9] = f * ph.cmm;
-    }
-    dc[5][10] = gle * gle;
-    dc[5][11] = gre * gre;
-    dc[5][12] = -gle * gre;
-    dc[5][13] = glm * glm;
-    dc[5][14] = grm * grm;
-    dc[5][15] = -glm * grm;
-    dc[5][16] = glt * glt;
-    dc[5][17] = grt * grt;
-    dc[5][18] = -glt * grt;
-    dc[5][19] = ph.cmm * th[4];
-}
-
-// ------------------------------------------------------------ weights
-// W^T[l][p] = m_l * w_l(theta_p) with w_l = S_theta(T_l) / S_SM(T_l) and
-// S_theta(T_l) = sum_b c_b(theta_p) I_b(T_l) (FP64), stored in the
-// K-major layout the GEMM streams.  One thread per point, a strip of rows
-// per work-group row; the basis row is wave-uniform.
-constexpr int kWgenRows = 32;
-constexpr int kWgenCols = kNBasis + 2;  // the basis, S_SM and m of a row
-
-__global__ __launch_bounds__(256) void k_wgen(WgenArgs a) {
-    // The work-group's strip of rows (basis values, S_SM, m) is staged in
-    // LDS once; every lane then reads the same entries (broadcast).  Read
-    // from memory inside the per-row loop they were a chain of dependent
-    // round trips per row.
-    __shared__ double strip[kWgenRows][kWgenCols];
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    const int l0 = blockIdx.y * kWgenRows;
-    const int nrow = min(kWgenRows, a.n_t - l0);
-    for (int q = threadIdx.x; q < kWgenRows * kWgenCols; q += 256) {
-        const int col = q / kWgenRows, r = q % kWgenRows, l = l0 + r;
-        double v = 0.0;
-        if (r < nrow)
-            v = col < kNBasis ? a.basis[(size_t)col * a.n_t + l]
-                              : (col == kNBasis ? a.ssm[l] : a.mrow[l]);
-        strip[r][col] = v;
-    }
-    __syncthreads();
-    if (p >= a.ldw) return;
-    double c[kNBasis];
-    const bool ok = p < a.n_pts;
-    if (ok) {
-        double th[kNTheta];
-        for (int i = 0; i < kNTheta; ++i) th[i] = a.theta[(size_t)p * kNTheta + i];
-        basis_coef(th, a.ph, c);
-    } else {
-        for (int b = 0; b < kNBasis; ++b) c[b] = 0.0;
-    }
-    for (int r = 0; r < nrow; ++r) {
-        double s = 0.0;
-#pragma unroll
-        for (int b = 0; b < kNBasis; ++b) s = fma(c[b], strip[r][b], s);
-        const double ssm = strip[r][kNBasis];
-        const double w = ssm > 0.0 ? s / ssm : 1.0;
-        a.wt[(size_t)(l0 + r) * a.ldw + p] = ok ? strip[r][kNBasis + 1] * w : 0.0;
-    }
-}
-
 // --------------------------------------------------------------- GEMM
 // Tiles of BM x BN outputs, K-steps of 16; four waves in 2 x 2, each
 // (BM/2) x (BN/2) = blocks of v_mfma_f64_16x16x4_f64.  The tile shape is a
@@ -532,14 +430,13 @@ __global__ void k_finalize(FinalArgs a) {
 // Gradient per point from the adjoint U[p][l] = sum_j a_pj R_lj:
 // grad_i = sum_l U_pl (m_l / S_SM(T_l)) sum_b dc_ib I_b(T_l) + [i = f_bkg]
 // sum_j a_pj b_j + pull term.
-// The contraction J[p][b] = sum_l U[p][l] v_l I_b(T_l), v_l = m_l / S_SM(T_l)
-// (0 where S_SM = 0), is itself a product of U (points x rows) with the
-// weighted basis (rows x 20): FP64 matrix instructions over blocks of 16
-// points and chunks of kCtrChunk rows, the four waves of a work-group on
-// quarters of its chunk.  With several chunks, each work-group leaves its
-// 16 x 20 partial sums in the first 20 columns of its own chunk of U (rows
-// only it reads, already consumed) and k_adj_final adds them per point in
-// chunk order; a single chunk finishes in place.
+// The contraction J[p][b] = sum_l U[p][l] F_lb is itself a product of U
+// (points x rows) with the row factors (rows x 14, padded to 16): FP64 matrix
+// instructions over blocks of 16 points and chunks of kCtrChunk rows, the
+// four waves of a work-group on quarters of its chunk.  With several chunks,
+// each work-group leaves its 16 x 14 partial sums in the first 14 columns of
+// its own chunk of U (rows only it reads, already consumed) and k_adj_final
+// adds them per point in chunk order; a single chunk finishes in place.
 constexpr int kCtrChunk = 1024;
 
 __host__ __device__ inline int ctr_chunks(int n_t) {
@@ -552,13 +449,11 @@ __host__ __device__ inline int ctr_chunks(int n_t) {
 __device__ inline void contract_finish(const ContractArgs& a, int p, const double J[kNBasis]) {
     double th[kNTheta];
     for (int i = 0; i < kNTheta; ++i) th[i] = a.theta[(size_t)p * kNTheta + i];
-    double dc[kNTheta][kNBasis];
-    basis_dcoef(th, a.ph, dc);
-    const double gb = row_sum(a.part_gb + (size_t)p * a.n_nt, a.n_nt);
+    double gr[kNTheta];
+    basis_grad(th, a.ph, J, gr);
+    gr[6] = row_sum(a.part_gb + (size_t)p * a.n_nt, a.n_nt);
     for (int i = 0; i < kNTheta; ++i) {
-        double g = 0.0;
-        for (int b = 0; b < kNBasis; ++b) g += dc[i][b] * J[b];
-        if (i == 6) g += gb;
+        double g = gr[i];
         if (a.pull_sigma[i] > 0.0)
             g += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
         a.grad[(size_t)p * kNTheta + i] = g;
@@ -577,40 +472,34 @@ __global__ __launch_bounds__(256) void k_adj_contract(ContractArgs a) {
     const int q0 = c0 + ((int)((long)len * wave / 4) & ~3);
     const int q1 = wave == 3 ? c1 : c0 + ((int)((long)len * (wave + 1) / 4) & ~3);
     const int p = pb * 16 + li;  // this lane's row of the point operand
-    v4d acc[2] = {(v4d){0.0, 0.0, 0.0, 0.0}, (v4d){0.0, 0.0, 0.0, 0.0}};
+    v4d acc = (v4d){0.0, 0.0, 0.0, 0.0};
     // MFMA sub-step e gives lane row l + 4 (lane / 16) + e of the 16-row
     // step; the next step's loads are issued before this step's arithmetic.
-    // A lane's four rows are consecutive: with even row strides they are
-    // read as 16-byte pairs (every row offset of a lane is even), else, and
-    // for a group that runs past the quarter, one by one.
-    const bool pairs = a.ldu % 2 == 0 && a.n_t % 2 == 0;
-    struct Step { double u[4], b0[4], b1[4], sm[4], m[4]; };
-    auto pair4 = [](const double* src, double out[4]) {
-        const double2 x = *reinterpret_cast<const double2*>(src);
-        const double2 y = *reinterpret_cast<const double2*>(src + 2);
-        out[0] = x.x; out[1] = x.y; out[2] = y.x; out[3] = y.y;
-    };
+    // A lane's four rows are consecutive: with an even row stride of U they
+    // are read as 16-byte pairs (every row offset of a lane is even), else,
+    // and for a group that runs past the quarter, one by one.
+    const bool pairs = a.ldu % 2 == 0;
+    struct Step { double u[4], f[4]; };
     auto load = [&](int l, Step& t) {
         const int r0 = l + 4 * lk;
+        const double* f = a.rf + (size_t)r0 * kRF + li;
         if (pairs && r0 + 3 < q1) {
-            pair4(a.ssm + r0, t.sm);
-            pair4(a.mrow + r0, t.m);
-            if (p < a.n_pts) pair4(a.U + (size_t)p * a.ldu + r0, t.u);
-            else t.u[0] = t.u[1] = t.u[2] = t.u[3] = 0.0;
-            pair4(a.basis + (size_t)li * a.n_t + r0, t.b0);
-            if (16 + li < kNBasis) pair4(a.basis + (size_t)(16 + li) * a.n_t + r0, t.b1);
-            else t.b1[0] = t.b1[1] = t.b1[2] = t.b1[3] = 0.0;
+            if (p < a.n_pts) {
+                const double2* u = reinterpret_cast<const double2*>(a.U + (size_t)p * a.ldu + r0);
+                const double2 x = u[0], y = u[1];
+                t.u[0] = x.x; t.u[1] = x.y; t.u[2] = y.x; t.u[3] = y.y;
+            } else {
+                t.u[0] = t.u[1] = t.u[2] = t.u[3] = 0.0;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t.f[e] = f[e * kRF];
             return;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int r = r0 + e;
-            const bool ok = r < q1;
-            t.sm[e] = ok ? a.ssm[r] : 0.0;
-            t.m[e] = ok ? a.mrow[r] : 0.0;
-            t.u[e] = ok && p < a.n_pts ? a.U[(size_t)p * a.ldu + r] : 0.0;
-            t.b0[e] = ok ? a.basis[(size_t)li * a.n_t + r] : 0.0;
-            t.b1[e] = ok && 16 + li < kNBasis ? a.basis[(size_t)(16 + li) * a.n_t + r] : 0.0;
+            const bool ok = r0 + e < q1;
+            t.u[e] = ok && p < a.n_pts ? a.U[(size_t)p * a.ldu + r0 + e] : 0.0;
+            t.f[e] = ok ? f[e * kRF] : 0.0;
         }
     };
     Step cur, nxt;
@@ -618,22 +507,15 @@ __global__ __launch_bounds__(256) void k_adj_contract(ContractArgs a) {
     for (int l = q0; l < q1; l += 16) {
         if (l + 16 < q1) load(l + 16, nxt);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const double v = cur.sm[e] > 0.0 ? cur.m[e] / cur.sm[e] : 0.0;
-            acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.u[e], cur.b0[e] * v, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.u[e], cur.b1[e] * v, acc[1], 0, 0, 0);
-        }
+        for (int e = 0; e < 4; ++e)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.u[e], cur.f[e], acc, 0, 0, 0);
         cur = nxt;
     }
     // output (i, j) of a block: lane j + 16 (i % 4), register i / 4; here
-    // i is the point and j the basis index within block y
+    // i is the point and j the basis index
+    if (li < kNBasis)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int b = 16 * y + li;
-            if (b < kNBasis) red[wave][4 * r + lk][b] = acc[y][r];
-        }
+        for (int r = 0; r < 4; ++r) red[wave][4 * r + lk][li] = acc[r];
     __syncthreads();
     // the four quarters in order; every wave has read its rows of U
     for (int q = tid; q < 16 * kNBasis; q += 256) {
@@ -648,7 +530,7 @@ __global__ __launch_bounds__(256) void k_adj_contract(ContractArgs a) {
 }
 
 // The chunk partials of each point, added in chunk order (one lane per
-// point and basis index, so that a point's 20 partials of a chunk are one
+// point and basis index, so that a point's 14 partials of a chunk are one
 // contiguous read), then the gradient.
 constexpr int kFinPts = 256 / kNBasis;  // points per work-group
 
@@ -667,36 +549,36 @@ __global__ __launch_bounds__(256) void k_adj_final(ContractArgs a, int nch) {
 }
 
 // ------------------------------------------------------------ templates
-// One thread per reco bin, one work-group row per slab of response rows:
-// kTmplCols FP64 sums of F_bl R_lj.  The row factors are wave-uniform.
+// One thread per reco bin, one work-group row per slab of response rows: the
+// FP64 sums of F_lb R_lj over the row's factors (wave-uniform).
+template <int RL>
 __global__ __launch_bounds__(256) void k_tmpl_fold(TmplFoldArgs a) {
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= a.n_reco) return;
     const int l0 = blockIdx.y * kTmplSlabRows;
     const int l1 = min(l0 + kTmplSlabRows, a.n_t);
-    double acc[kTmplCols];
+    double acc[RL];
 #pragma unroll
-    for (int b = 0; b < kTmplCols; ++b) acc[b] = 0.0;
+    for (int b = 0; b < RL; ++b) acc[b] = 0.0;
     for (int l = l0; l < l1; ++l) {
         const double r = a.R[(size_t)l * a.ldr + j];
-        const double* f = a.F + (size_t)l * kTmplCols;
+        const double* f = a.rf + (size_t)l * RL;
 #pragma unroll
-        for (int b = 0; b < kTmplCols; ++b) acc[b] = fma(f[b], r, acc[b]);
+        for (int b = 0; b < RL; ++b) acc[b] = fma(f[b], r, acc[b]);
     }
 #pragma unroll
-    for (int b = 0; b < kTmplCols; ++b)
-        a.part[((size_t)blockIdx.y * kTmplCols + b) * a.n_reco + j] = acc[b];
+    for (int b = 0; b < RL; ++b)
+        a.part[((size_t)blockIdx.y * RL + b) * a.n_reco + j] = acc[b];
 }
 
-// Slab sums in slab order, one (bin, template) per thread, into the record
-// column the caller maps each folded column to.
+// Slab sums in slab order, one (bin, template) per thread, into the record.
 __global__ __launch_bounds__(256) void k_tmpl_records(TmplRecArgs a) {
     const int j = blockIdx.x * 256 + threadIdx.x;
     const int b = blockIdx.y;
-    if (j >= a.n_reco || a.dst[b] < 0) return;
+    if (j >= a.n_reco) return;
     double s = 0.0;
-    for (int q = 0; q < a.n_slab; ++q) s += a.part[((size_t)q * kTmplCols + b) * a.n_reco + j];
-    a.rec[(size_t)j * a.rl + a.dst[b]] = s;
+    for (int q = 0; q < a.n_slab; ++q) s += a.part[((size_t)q * a.n_cols + b) * a.n_reco + j];
+    a.rec[(size_t)j * a.rl + a.dst0 + b] = s;
 }
 
 // The data of each bin beside its templates (rewritten alone by set_data).
@@ -707,7 +589,7 @@ __global__ __launch_bounds__(256) void k_tmpl_data(TmplDataArgs a) {
     const double nj = a.n[j];
     r[kTmplCols] = a.b[j];
     r[kTmplCols + 1] = nj;
-    r[kTmplCols + 2] = 0.0;  // pads the record to 24 doubles
+    r[kTmplCols + 2] = 0.0;  // pads the record to 18 doubles
 }
 
 // One thread per point, one work-group column per slice of reco bins.  The
@@ -801,12 +683,11 @@ __global__ __launch_bounds__(256) void k_tmpl_final(TmplFinalArgs a) {
     if (!a.grad) return;
     double h[kTmplCols];
     for (int b = 0; b < kTmplCols; ++b) h[b] = a.red[(size_t)(1 + b) * a.n_pts + p];
-    double dc[kNTheta][kNBasis];
-    basis_dcoef(th, a.ph, dc);
+    double gr[kNTheta];
+    basis_grad(th, a.ph, h, gr);
+    gr[6] = h[kNBasis];
     for (int i = 0; i < kNTheta; ++i) {
-        double g = 0.0;
-        for (int b = 0; b < kNBasis; ++b) g += dc[i][b] * h[b];
-        if (i == 6) g += h[kNBasis];
+        double g = gr[i];
         if (a.pull_sigma[i] > 0.0)
             g += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
         a.grad[(size_t)p * kNTheta + i] = g;
@@ -826,8 +707,8 @@ __global__ __launch_bounds__(256) void k_tmpl_mdata(TmplMultiDataArgs a) {
 }
 
 // As k_tmpl_eval, for the multi-component record: per (point, bin) the
-// component sums t_k = G0^(k) + sum_b c_b G^(k)_b (11 K products), mu from
-// the rates, and for the gradient the 10 + K + B contractions
+// component sums t_k = G0^(k) + sum_b c_b G^(k)_b (8 K products), mu from
+// the rates, and for the gradient the kCompBasis + K + B contractions
 //   H_b = sum_j a'_j sum_k r_k G^(k)_bj,  R_k = sum_j a'_j t_kj,
 //   Q_q = sum_j a'_j B_qj,  a'_j = M_j d(-2lnL)/d mu_j.
 // Loops run to compile-time maxima KM, BM with uniform predicates, so every
@@ -841,9 +722,8 @@ __global__ __launch_bounds__(kTmplWave) void k_tmpl_meval(TmplMultiEvalArgs a) {
     const bool ok = p < a.n_pts;
     const int pc = ok ? p : a.n_pts - 1;
     const double* th = a.theta + (size_t)pc * a.n_theta;
-    double t7[kNTheta] = {th[0], th[1], th[2], th[3], th[4], 1.0, 1.0};
-    double c[kNBasis];
-    basis_coef(t7, a.ph, c);  // c[0..9]: the coefficients without group scaling
+    double c[kCompBasis];
+    basis_coef7(th, a.ph, 1.0, c);
     double rk[KM], rb[BM];
 #pragma unroll
     for (int k = 0; k < KM; ++k) rk[k] = k < a.K ? th[5 + k] : 0.0;
@@ -853,29 +733,29 @@ __global__ __launch_bounds__(kTmplWave) void k_tmpl_meval(TmplMultiEvalArgs a) {
     const int j0 = sl * a.cols_per;
     const int j1 = min(j0 + a.cols_per, a.n_reco);
     double dsum = 0.0;
-    double H[10], Rk[KM], Qb[BM];
+    double H[kCompBasis], Rk[KM], Qb[BM];
 #pragma unroll
-    for (int b = 0; b < 10; ++b) H[b] = 0.0;
+    for (int b = 0; b < kCompBasis; ++b) H[b] = 0.0;
 #pragma unroll
     for (int k = 0; k < KM; ++k) Rk[k] = 0.0;
 #pragma unroll
     for (int q = 0; q < BM; ++q) Qb[q] = 0.0;
     for (int j = j0; j < j1; ++j) {
         const double* __restrict__ r = a.rec + (size_t)j * a.rl;
-        double s = 0.0, tk[KM], T[10];
+        double s = 0.0, tk[KM], T[kCompBasis];
 #pragma unroll
-        for (int b = 0; b < 10; ++b) T[b] = 0.0;
+        for (int b = 0; b < kCompBasis; ++b) T[b] = 0.0;
 #pragma unroll
         for (int k = 0; k < KM; ++k) {
             tk[k] = 0.0;
             if (k < a.K) {
                 const double* g = r + kTmplCompCols * k;
-                double t = g[10];
+                double t = g[kCompBasis];
 #pragma unroll
-                for (int b = 0; b < 10; ++b) t = fma(c[b], g[b], t);
+                for (int b = 0; b < kCompBasis; ++b) t = fma(c[b], g[b], t);
                 if (GRAD) {  // T_b = sum_k r_k G^(k)_bj, for H_b
 #pragma unroll
-                    for (int b = 0; b < 10; ++b) T[b] = fma(rk[k], g[b], T[b]);
+                    for (int b = 0; b < kCompBasis; ++b) T[b] = fma(rk[k], g[b], T[b]);
                 }
                 tk[k] = t;
                 s = fma(rk[k], t, s);
@@ -900,7 +780,7 @@ __global__ __launch_bounds__(kTmplWave) void k_tmpl_meval(TmplMultiEvalArgs a) {
             for (int k = 0; k < KM; ++k)
                 if (k < a.K) Rk[k] = fma(ap, tk[k], Rk[k]);
 #pragma unroll
-            for (int b = 0; b < 10; ++b) H[b] = fma(ap, T[b], H[b]);
+            for (int b = 0; b < kCompBasis; ++b) H[b] = fma(ap, T[b], H[b]);
 #pragma unroll
             for (int q = 0; q < BM; ++q)
                 if (q < a.B) Qb[q] = fma(ap, r[ob + q], Qb[q]);
@@ -909,16 +789,16 @@ __global__ __launch_bounds__(kTmplWave) void k_tmpl_meval(TmplMultiEvalArgs a) {
     if (!ok) return;
     a.dpart[(size_t)sl * a.n_pts + p] = dsum;
     if (GRAD) {
-        const int na = 10 + a.K + a.B;
+        const int na = kCompBasis + a.K + a.B;
         double* hp = a.hpart + (size_t)sl * na * a.n_pts + p;
 #pragma unroll
-        for (int b = 0; b < 10; ++b) hp[(size_t)b * a.n_pts] = H[b];
+        for (int b = 0; b < kCompBasis; ++b) hp[(size_t)b * a.n_pts] = H[b];
 #pragma unroll
         for (int k = 0; k < KM; ++k)
-            if (k < a.K) hp[(size_t)(10 + k) * a.n_pts] = Rk[k];
+            if (k < a.K) hp[(size_t)(kCompBasis + k) * a.n_pts] = Rk[k];
 #pragma unroll
         for (int q = 0; q < BM; ++q)
-            if (q < a.B) hp[(size_t)(10 + a.K + q) * a.n_pts] = Qb[q];
+            if (q < a.B) hp[(size_t)(kCompBasis + a.K + q) * a.n_pts] = Qb[q];
     }
 }
 
@@ -937,21 +817,14 @@ __global__ __launch_bounds__(256) void k_tmpl_mfinal(TmplMultiFinalArgs a) {
     a.nll[p] = 2.0 * a.red[p] + 2.0 * a.cdata + pulls;
     if (!a.grad) return;
     const double* h = a.red + a.n_pts + p;  // contraction v at h[v * n_pts]
-    double t7[kNTheta] = {th[0], th[1], th[2], th[3], th[4], 1.0, 1.0};
-    double dc[kNTheta][kNBasis];
-    basis_dcoef(t7, a.ph, dc);
     double* g = a.grad + (size_t)p * a.n_theta;
-    double hb[10];
+    double hb[kCompBasis], g5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int b = 0; b < 10; ++b) hb[b] = h[(size_t)b * a.n_pts];
+    for (int b = 0; b < kCompBasis; ++b) hb[b] = h[(size_t)b * a.n_pts];
+    basis_dcoef7(th, a.ph, 1.0, hb, g5);
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        double v = 0.0;
-#pragma unroll
-        for (int b = 0; b < 10; ++b) v += dc[i][b] * hb[b];
-        g[i] = v;
-    }
-    for (int i = 5; i < a.n_theta; ++i) g[i] = h[(size_t)(10 + i - 5) * a.n_pts];  // R_k, Q_q
+    for (int i = 0; i < 5; ++i) g[i] = g5[i];
+    for (int i = 5; i < a.n_theta; ++i) g[i] = h[(size_t)(kCompBasis + i - 5) * a.n_pts];  // R_k, Q_q
     for (int i = 0; i < a.n_theta; ++i)
         if (a.pull_sigma[i] > 0.0)
             g[i] += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
@@ -988,12 +861,18 @@ hipError_t launch_tmpl_mfinal(const TmplMultiFinalArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_tmpl_fold(const TmplFoldArgs& a, int n_slab, hipStream_t s) {
-    hipLaunchKernelGGL(k_tmpl_fold, dim3((a.n_reco + 255) / 256, n_slab), dim3(256), 0, s, a);
+    const dim3 grid((a.n_reco + 255) / 256, n_slab);
+    if (a.rl == kRF)
+        hipLaunchKernelGGL(k_tmpl_fold<kRF>, grid, dim3(256), 0, s, a);
+    else if (a.rl == kRFComp)
+        hipLaunchKernelGGL(k_tmpl_fold<kRFComp>, grid, dim3(256), 0, s, a);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
 hipError_t launch_tmpl_records(const TmplRecArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_tmpl_records, dim3((a.n_reco + 255) / 256, kTmplCols), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_tmpl_records, dim3((a.n_reco + 255) / 256, a.n_dst), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1022,12 +901,6 @@ hipError_t launch_tmpl_reduce(const TmplReduceArgs& a, hipStream_t s) {
 
 hipError_t launch_tmpl_final(const TmplFinalArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_tmpl_final, dim3((a.n_pts + 255) / 256), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_wgen(const WgenArgs& a, hipStream_t s) {
-    dim3 grid((a.ldw + 255) / 256, (a.n_t + kWgenRows - 1) / kWgenRows);
-    hipLaunchKernelGGL(k_wgen, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@ namespace nr {
 constexpr int kNTheta = 7;
 constexpr int kMaxTheta = 32;       // parameters of the multi-component form
 constexpr int kStepRows = 512;      // recoil rows per weights work-group
-constexpr int kNBasis = 20;         // theta-independent recoil basis spectra
+constexpr int kNBasis = 14;         // theta-independent recoil basis spectra
 
 // Physical constants in the units the device works in: the weak prefactor
 // 2 G_F^2 m_e / pi of Eq. (sm_cross_section) is set to one, so the
@@ -116,9 +116,7 @@ struct AdjArgs {
     const float* R;
     int ldr, n_t, n_reco;
     const double* a;      // [ldr]
-    const double* ssm;
-    const double* mrow;
-    const double* basis;  // [kNBasis][n_t]
+    const double* rf;     // [n_t][kRF] row factors (basis.h)
     const double* theta;
     const double* gb;     // [1]
     double* jpart;        // [grid][kNBasis]

@@ -1,6 +1,6 @@
 // Single-point path on gfx950: E-integral, weights, HBM-streaming fold,
 // Poisson likelihood reduction, and the adjoint of the fold.
-#include "common.h"
+#include "basis.h"
 
 #include <cmath>
 
@@ -439,49 +439,10 @@ __global__ __launch_bounds__(kStepThreads) void k_step_part(StepArgs a) {
 constexpr int kAdjThreads = 256;
 constexpr int kAdjMaxLd = 4096;
 
-// Coefficients of the 20 basis spectra and their theta-derivatives.  The
-// basis (per group g = non-8B / 8B, per flavour e, mu, tau) is
-// I_{g,a,LL} = sum nu P_a, I_{g,a,RR} = sum nu P_a y^2, I_{g,a,LR} =
-// sum nu P_a x, I_{g,D} = sum nu (sum_a P_a)(1/T - 1/E), so that
-// S_theta = sum_b c_b(theta) I_b  exactly (Eqs. (fT), (xs_total)).
-__device__ inline void basis_dcoef(const double* th, const Phys& ph,
-                                   double dc[kNTheta][kNBasis]) {
-    for (int i = 0; i < kNTheta; ++i)
-        for (int b = 0; b < kNBasis; ++b) dc[i][b] = 0.0;
-    const double gle = ph.gLe + th[0], gre = ph.gR + th[1];
-    const double glm = ph.gLm, grm = ph.gR;
-    const double glt = ph.gLm + th[2], grt = ph.gR + th[3];
-    for (int g = 0; g < 2; ++g) {
-        const double f = g ? th[5] : 1.0;
-        const int o = g * 10;
-        dc[0][o + 0] = f * 2.0 * gle;
-        dc[0][o + 2] = -f * gre;
-        dc[1][o + 1] = f * 2.0 * gre;
-        dc[1][o + 2] = -f * gle;
-        dc[2][o + 6] = f * 2.0 * glt;
-        dc[2][o + 8] = -f * grt;
-        dc[3][o + 7] = f * 2.0 * grt;
-        dc[3][o + 8] = -f * glt;
-        dc[4][o + 9] = f * ph.cmm;
-        if (g == 1) {
-            dc[5][o + 0] = gle * gle;
-            dc[5][o + 1] = gre * gre;
-            dc[5][o + 2] = -gle * gre;
-            dc[5][o + 3] = glm * glm;
-            dc[5][o + 4] = grm * grm;
-            dc[5][o + 5] = -glm * grm;
-            dc[5][o + 6] = glt * glt;
-            dc[5][o + 7] = grt * grt;
-            dc[5][o + 8] = -glt * grt;
-            dc[5][o + 9] = ph.cmm * th[4];
-        }
-    }
-}
-
 // Adjoint of the fold: u_l = sum_j R_lj a_j with a_j = d(-2lnL)/d mu_j
 // (one wave per row, 16-byte loads, wave-shuffle reduction), then the
 // contraction with the weight derivatives
-// d v_l / d theta_i = m_l / S_SM(T_l) * sum_b dc_ib I_b(T_l).
+// d v_l / d theta_i = sum_b dc_ib F_lb (the row factors of basis.h).
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint(AdjArgs a) {
     __shared__ double as[kAdjMaxLd];
     __shared__ double jsh[kAdjThreads / 64][kNBasis];
@@ -514,9 +475,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint(AdjArgs a) {
             s = fma((double)x.w, av[4 * c + 3], s);
         }
         const double u = wave_sum(s);
-        const double ssm = a.ssm[l];
-        if (ssm > 0.0 && lane < kNBasis)
-            J += u * (a.mrow[l] / ssm) * a.basis[(size_t)lane * a.n_t + l];
+        if (lane < kNBasis) J += u * a.rf[(size_t)l * kRF + lane];
     }
     if (lane < kNBasis) jsh[wave][lane] = J;
     __syncthreads();
@@ -552,12 +511,11 @@ __global__ __launch_bounds__(256) void k_adjoint_finish(AdjArgs a, int grid) {
     if (tid == 0) {
         double th[kNTheta];
         for (int i = 0; i < kNTheta; ++i) th[i] = a.theta[i];
-        double dc[kNTheta][kNBasis];
-        basis_dcoef(th, a.ph, dc);
+        double gr[kNTheta];
+        basis_grad(th, a.ph, jt, gr);
+        gr[6] = a.gb[0];
         for (int i = 0; i < kNTheta; ++i) {
-            double g = 0.0;
-            for (int b = 0; b < kNBasis; ++b) g += dc[i][b] * jt[b];
-            if (i == 6) g += a.gb[0];
+            double g = gr[i];
             if (a.pull_sigma[i] > 0.0)
                 g += 2.0 * (th[i] - a.pull_mean[i]) /
                      (a.pull_sigma[i] * a.pull_sigma[i]);
