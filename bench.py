@@ -1,16 +1,15 @@
 """Benchmark: likelihood evaluations per second on one MI355X.
 
 A step is one batch of parameter points (100 by default, a row of a
-likelihood scan), each put through the whole plain path (weights from the
-energy integral, dense FP64 fold of the 16384 x 4096 FP32 response, Poisson
--2lnL), with every input resident in HBM.  The K timed steps are one call on
-K x 100 points, which share the stream over the response in blocks; the value
-is evaluations per second.
+likelihood scan), put through the whole plain path in one call (recoil
+spectra, dense FP64 fold of the 16384 x 4096 FP32 response, Poisson -2lnL),
+with every input resident in HBM.  The points of a call share one pass over
+the response.  The K timed steps are K calls; the value is evaluations per
+second.
 
 Prints one JSON line: the plain rate as `value`, the roofline of the fold
-kernel, the single-point launch (one point per stream over the response)
-against the HBM peak, the batched and gradient forms and the CPU oracle timed
-beside it.
+kernel, the evaluation of an isolated point against the HBM peak, the batched
+and gradient forms and the CPU oracle timed beside it.
 """
 import argparse
 import json
@@ -26,7 +25,6 @@ import numpy as np  # noqa: E402
 METRIC = ("likelihood evals/s at |Δ(−2lnL)|≤1e-3 vs FP64: "
           "plain vs batched/grad/surrogate")
 HBM_PEAK_GBS = 8000.0
-FP64_PEAK_TFLOPS = 78.6
 
 
 def algorithmic_bytes(n_t, n_reco):
@@ -92,7 +90,7 @@ def build_batched(n_datasets=64):
     import synth
     import paper_2607_00488_amd as nr
     t0 = time.time()
-    ctxs, ths, flops = [], [], 0.0
+    ctxs, ths, r_bytes = [], [], 0
     src = synth.source_nodes(256)
     for sd in synth.batched_schedule(n_datasets):
         rsp = synth.response_mc(sd["n_t"], sd["n_reco"], sd["n_mc"],
@@ -106,9 +104,9 @@ def build_batched(n_datasets=64):
         ctx.set_data(synth.poisson_data(mu_sm, sd["seed_data"]), b)
         ctxs.append(ctx)
         ths.append(synth.theta_grid_scan(sd["n_pts"], sd["seed_theta"]))
-        flops += 2.0 * sd["n_pts"] * sd["n_t"] * sd["n_reco"]
+        r_bytes += 4 * sd["n_t"] * sd["n_reco"]
     log(f"[bench] batched inputs ({n_datasets} datasets) in {time.time() - t0:.1f}s")
-    return ctxs, ths, flops
+    return ctxs, ths, r_bytes
 
 
 def time_batched(ctxs, ths, reps=3, grad=False):
@@ -120,7 +118,7 @@ def time_batched(ctxs, ths, reps=3, grad=False):
     gr = ([torch.empty(len(t), 7, dtype=torch.float64, device=dev) for t in ths]
           if grad else None)
     s = torch.cuda.Stream(device=dev)
-    nr.eval_nll_multi_dev(ctxs, tt, nl, gr, stream=s)  # capture + run
+    nr.eval_nll_multi_dev(ctxs, tt, nl, gr, stream=s)  # tunes, allocates
     s.synchronize()
     t0 = time.perf_counter()
     for _ in range(reps):
@@ -205,8 +203,8 @@ def templates_form(ctx, seed, n_pts=65536, reps=5):
         max_abs_dnll_vs_plain=float(np.max(np.abs(got[:k] - plain))),
         bound="alu",
         what="exact template form: mu_j = f_bkg b_j + G0_j + sum_b c_b(theta) "
-             "G_bj with the 20 basis templates folded once through R; per "
-             "(point, bin) 21 FP64 products and one FP64 logarithm")
+             "G_bj with the 14 basis templates folded once through R; per "
+             "(point, bin) 16 FP64 products and one FP64 logarithm")
 
 
 def asimov_scan_form(p):
@@ -214,7 +212,7 @@ def asimov_scan_form(p):
     binning: Asimov data at eps_eL = 0.05, a 31-value scan of eps_eL over
     [-0.1, 0.2] with f_8B and f_bkg profiled (pulls 1 +- 0.1) by the batched
     L-BFGS driver, end to end (all fits, every likelihood and gradient call),
-    once with the batched GEMM form and once with the template form.  The
+    once with the batched form and once with the template form.  The
     context's data are restored afterwards."""
     import torch
     import synth
@@ -844,16 +842,20 @@ def main():
                        dtype=torch.float64, device=dev)
     outw = torch.empty(max(W, 1) * PPS, dtype=torch.float64, device=dev)
     stream = torch.cuda.Stream(device=dev)
-    # warm-up: allocates the workspaces and runs both lists once
-    ctx.eval_nll_dev(thw, outw, stream=stream)
-    ctx.eval_nll_dev(tt, out, stream=stream)
+    # warm-up: both lists once
+    def steps(th, res):
+        for k in range(0, len(th), PPS):
+            ctx.eval_nll_dev(th[k:k + PPS], res[k:k + PPS], stream=stream)
+
+    steps(thw, outw)
+    steps(tt, out)
     stream.synchronize()
     torch.cuda.synchronize()
     ev0 = torch.cuda.Event(enable_timing=True)
     ev1 = torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
     ev0.record(stream)
-    ctx.eval_nll_dev(tt, out, stream=stream)
+    steps(tt, out)
     ev1.record(stream)
     stream.synchronize()
     torch.cuda.synchronize()
@@ -872,11 +874,9 @@ def main():
         lat.append(time.perf_counter() - t1)
     lat = np.array(lat[1:]) * 1e3
 
-    # roofline of the dominant kernel, the blocked fold: its multiply-adds
-    # over the device time of the whole timed region (HIP events on its
-    # stream), which charges the weights and the likelihood sums to it.  An
-    # isolated point streams R by itself: the single-point step launch alone
-    # back to back, its fold role alone and the other stages
+    # roofline of the dominant kernel, the fold: the response's bytes over its
+    # own time (launches back to back); the same bytes over the device time of a
+    # step, and of the evaluation of an isolated point
     step_bb_ms = ctx.time_stage(5, 200)
     step_ms = step_bb_ms
     # the same launch after 512 MiB of other data have been read through the
@@ -898,25 +898,27 @@ def main():
     eint_ms = ctx.time_stage(1, 200)
     alg_bytes = algorithmic_bytes(c.n_t, c.n_reco)
     achieved = alg_bytes / (step_ms * 1e-3) / 1e9
-    tflops = 2.0 * c.n_t * c.n_reco * NE / (dev_ms * 1e-3) / 1e12
-    roof = dict(bound="fp64 matrix cores", achieved=round(tflops, 2),
-                peak=FP64_PEAK_TFLOPS, unit="TFLOP/s",
-                frac=round(tflops / FP64_PEAK_TFLOPS, 4), kernel="k_blk_fold",
+    rate = lambda ms: alg_bytes / (ms * 1e-3) / 1e9  # noqa: E731
+    roof = dict(bound="hbm", achieved=round(rate(fold_ms), 1), peak=HBM_PEAK_GBS,
+                unit="GB/s", frac=round(rate(fold_ms) / HBM_PEAK_GBS, 4),
+                kernel="k_sh_fold", avg_kernel_us=round(fold_ms * 1e3, 2),
+                algorithmic_bytes=alg_bytes,
+                step_device_us=round(dev_ms * 1e3 / K, 2),
+                step_gbs=round(rate(dev_ms / K), 1),
                 us_per_eval=round(dev_ms * 1e3 / NE, 3),
-                note="the points of a call share one stream over R per group of "
-                     "up to 64, so its matrix instructions and not its bytes "
-                     "bound the fold; the rate counts 2 N_T N_reco operations "
-                     "per evaluation over the device time of the whole call")
+                note="the points of a step share one pass over R: its 15 folded "
+                     "columns are formed once per call, on the FP64 matrix cores, "
+                     "and the points' spectra and likelihoods from them")
     single = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
                   unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
-                  traffic=measured_traffic(), kernel="k_step",
-                  avg_kernel_us=round(step_ms * 1e3, 2),
+                  traffic=measured_traffic(), launches=4,
+                  avg_us=round(step_ms * 1e3, 2),
                   algorithmic_bytes=alg_bytes,
-                  note="one point per stream over R, the steady-state launch of "
-                       "the single-point pipeline back to back; effective rate: "
-                       "the algorithmic bytes of a launch over its time, whether "
-                       "HBM or the Infinity Cache served them; one launch after "
-                       "a 512 MiB cache flush: detail.step_after_cache_flush_us")
+                  note="the whole evaluation of one point (fold, records, points, "
+                       "final), back to back; effective rate: the response's bytes "
+                       "over its time, whether HBM or the Infinity Cache served "
+                       "them; after a 512 MiB cache flush: "
+                       "detail.step_after_cache_flush_us")
     res = dict(metric=METRIC, value=round(evals_s, 1), unit="evals/s",
                n_gpus=1, steps=K, warmup=W, ms_per_step=round(ms_step, 5),
                points_per_step=PPS,
@@ -942,8 +944,8 @@ def main():
         log(f"[bench] plain with band skipping: "
             f"{forms['plain_banded']['evals_per_s']:.0f} evals/s, bitwise equal: "
             f"{forms['plain_banded']['bitwise_equal_to_dense']}")
-    # the FP64 matrix-core rate the chip sustains on register operands: the
-    # practical ceiling of the batched GEMM beside the data-sheet 78.6
+    # the FP64 matrix-core rate the chip sustains on register operands
+    # (data sheet: 78.6)
     import paper_2607_00488_amd as nr
     probe = nr.nr_probe_mfma_f64(0, 8192, 16)
     res["detail"]["fp64_mfma_probe_tflops"] = round(probe, 2)
@@ -961,28 +963,21 @@ def main():
     log(f"[bench] probes: FP64 MFMA {probe:.1f} TFLOP/s, HBM read {rd:.0f} GB/s, "
         f"R-sized alternating cached read {rc_:.0f} GB/s")
     # gradient form: 1024 points at the same shapes, -2lnL + 7 derivatives
-    # per point through the FP64-MFMA forward and adjoint products
     thg = synth.theta_prior(1024, p["seeds"]["theta"] + 5, f_range=(0.8, 1.2))
     dtg, _, _ = time_batched([ctx], [thg], reps=3, grad=True)
     forms["grad_batched"] = dict(
         evals_per_s=round(1024 / dtg, 1), points=1024, ms=round(dtg * 1e3, 3),
-        flop=2 * 2.0 * 1024 * c.n_t * c.n_reco,
-        tflops=round(2 * 2.0 * 1024 * c.n_t * c.n_reco / dtg / 1e12, 2),
-        peak_tflops=78.6,
-        frac_of_probe=round(2 * 2.0 * 1024 * c.n_t * c.n_reco / dtg / 1e12 / probe, 3),
-        what="nll + gradient, forward and adjoint GEMMs")
+        gbs=round(alg_bytes / dtg / 1e9, 1),
+        what="nll + gradient, one pass over R per call")
     dtb, _, _ = time_batched([ctx], [thg], reps=3, grad=False)
     forms["nll_batched_same_shapes"] = dict(
         evals_per_s=round(1024 / dtb, 1), points=1024, ms=round(dtb * 1e3, 3),
-        tflops=round(2.0 * 1024 * c.n_t * c.n_reco / dtb / 1e12, 2),
-        frac_of_probe=round(2.0 * 1024 * c.n_t * c.n_reco / dtb / 1e12 / probe, 3))
+        gbs=round(alg_bytes / dtb / 1e9, 1))
     log(f"[bench] grad batched: {1024 / dtg:.0f} evals/s; nll batched "
         f"{1024 / dtb:.0f} evals/s")
     if not args.no_banded:
-        # the same two with band skipping: every GEMM tile reduces only over the
-        # K-steps where its response entries are not all zero (results equal to
-        # rounding: the tuner may pick another tile shape, bitwise equality at a
-        # fixed shape is tested)
+        # the same two with band skipping (results equal to rounding: the tuner
+        # may pick another split, bitwise equality at a fixed one is tested)
         _, nl_d, g_d = time_batched([ctx], [thg], reps=1, grad=True)
         ctx.set_band_skipping(True)
         dtgb, nl_b, g_b = time_batched([ctx], [thg], reps=3, grad=True)
@@ -995,8 +990,8 @@ def main():
             max_rel_dgrad_vs_dense=float(np.max(np.abs(g_b[0] - g_d[0])) /
                                          np.max(np.abs(g_d[0]))),
             what="the batched likelihood and gradient with band skipping: each "
-                 "tile of the forward and adjoint GEMMs reduces only over the "
-                 "K-steps of 16 where its response entries are not all zero")
+                 "256-column tile of the fold reads only the rows whose responses "
+                 "there are non-zero")
         log(f"[bench] batched with band skipping: {1024 / dtbb:.0f} evals/s, "
             f"{1024 / dtgb:.0f} with gradient")
     forms["plain_config0"] = pc = plain_config0_form()
@@ -1017,7 +1012,7 @@ def main():
         f"{sc['templates']['seconds']:.3f} s / {sc['templates']['first_seconds']:.3f} s; "
         f"interval {sc['templates']['interval_90']}")
     if not args.no_batched:
-        ctxs, ths, flops = build_batched()
+        ctxs, ths, r_bytes_all = build_batched()
         dt2, nls, _ = time_batched(ctxs, ths, reps=2)
         npts = sum(len(t) for t in ths)
         # agreement with the single-point path: the first and last point of
@@ -1029,16 +1024,15 @@ def main():
             dscan = max(dscan, float(np.max(np.abs(pl - nls[d][k]))))
         forms["batched_scan_64_datasets"] = dict(
             evals_per_s=round(npts / dt2, 1), points=npts,
-            ms=round(dt2 * 1e3, 3), flop=flops,
-            tflops=round(flops / dt2 / 1e12, 2), peak_tflops=78.6,
-            frac_of_probe=round(flops / dt2 / 1e12 / probe, 3),
+            ms=round(dt2 * 1e3, 3), response_bytes=r_bytes_all,
+            gbs=round(r_bytes_all / dt2 / 1e9, 1),
             max_abs_dnll_vs_plain=dscan,
             checked="first and last point of each of the 16 shape classes "
                     "against the single-point path",
-            what="64 datasets, N_T 2048-16384, N_reco 512-4096, one grouped "
-                 "persistent FP64-MFMA launch per scan (graph replay)")
+            what="64 datasets, N_T 2048-16384, N_reco 512-4096, four launches "
+                 "per 16 of them")
         log(f"[bench] batched scan: {npts / dt2:.0f} evals/s, "
-            f"{flops / dt2 / 1e12:.1f} TFLOP/s, max |d| vs plain {dscan:.2e}")
+            f"{r_bytes_all / dt2 / 1e9:.0f} GB/s, max |d| vs plain {dscan:.2e}")
         for cx in ctxs:
             cx.close()
     if not args.no_surrogate:

@@ -120,19 +120,20 @@ int nr_set_response(nr_ctx *ctx, const float *R, int n_t, int n_reco,
 int nr_set_data(nr_ctx *ctx, const double *n, const double *b, int n_reco,
                 const double *pull_mean, const double *pull_sigma);
 
-/* -2lnL for n_pts points (theta: [n_pts][7], host).  One or two points run
- * the single-point launches: device E-integral (Eq. (fT) summed per source
- * over the reachable nodes, as suffix sums of the per-node Laurent
- * coefficients in T), weights, HBM-streaming fold and likelihood reduction;
- * successive points overlap.  Three or more share the stream over R in
- * blocks: their weights from the exact basis form of Eq. (fT), the fold as a
- * product on the FP64 matrix cores, then the likelihood of every point.  A
- * point's result does not depend on the block it falls in; the two routes
- * agree to rounding.  nll: [n_pts] host.  Synchronous. */
+/* -2lnL for n_pts points (theta: [n_pts][7], host).  The recoil spectrum of
+ * Eq. (fT) is exactly linear in 14 theta-independent spectra, so the fold of
+ * Eqs. (fNp_reweight), (mu_total) is taken once per call for all points: one
+ * pass over R forms 15 folded columns per bin (FP64 matrix cores), and every
+ * point's spectrum and Poisson sum follow from them.  A point's result does
+ * not depend on the list it is in.  Multi-component contexts: one or two
+ * points run the single-point launches (device E-integral as suffix sums of
+ * the per-node Laurent coefficients in T, weights, HBM-streaming fold,
+ * likelihood; successive points overlap), three or more share the stream over
+ * R in blocks of up to 64.  nll: [n_pts] host.  Synchronous. */
 int nr_eval_nll(nr_ctx *ctx, const double *theta, int n_pts, double *nll);
 
-/* -2lnL and its gradient d(-2lnL)/d theta ([n_pts][7]) per point, through
- * the adjoint of the fold (a second pass over R).  Synchronous. */
+/* -2lnL and its gradient d(-2lnL)/d theta ([n_pts][7]) per point, from the
+ * same pass over R.  Synchronous. */
 int nr_eval_nll_grad(nr_ctx *ctx, const double *theta, int n_pts,
                      double *nll, double *grad);
 
@@ -142,10 +143,10 @@ int nr_eval_mu(nr_ctx *ctx, const double *theta, int n_pts, double *mu);
 /* Device-pointer variant of nr_eval_nll / nr_eval_nll_grad: d_theta
  * [n_pts][7] double, d_nll [n_pts] double, d_grad [n_pts][7] double or
  * NULL.  Enqueued on `stream` (hipStream_t, NULL = the default stream);
- * returns without waiting.  With a gradient, replays a cached HIP graph for
- * repeated (pointer, n_pts) combinations; a list of three or more points
- * takes device memory for its block on first use (up to 128 MiB, more where
- * one block of 16 points needs it), kept by the context. */
+ * returns without waiting.  Allocates nothing, except on a multi-component
+ * context, where a list of three or more points takes device memory for its
+ * block on first use (up to 128 MiB, more where one block of 16 points needs
+ * it), kept by the context. */
 int nr_eval_nll_dev(nr_ctx *ctx, const double *d_theta, int n_pts,
                     double *d_nll, double *d_grad, void *stream);
 
@@ -154,15 +155,14 @@ int nr_eval_nll_dev(nr_ctx *ctx, const double *d_theta, int n_pts,
  * only within a few resolution widths of the light an electron of recoil
  * T_i makes, so every row of R, and every 128-row fold tile, has a column
  * band outside which all entries are exact zeros (nr_set_response and
- * nr_set_components record the bands).  With `on` non-zero the fold of
- * Eq. (matrix_reweight) and the adjoint pass of the gradient read only the
- * 16-byte column groups inside those bands and write zero partial sums for
- * the rest; in the batched forms every tile of the forward and adjoint
- * matrix products reduces only over the K-steps of 16 whose response
- * entries for it are not all zero.  The skipped terms are exact zeros and
- * no sum changes order, so every result is bitwise the one of the full
- * read (for the batched forms at the same tile shape; the tuner, which
- * times the banded and the dense products separately, may pick another).
+ * nr_set_components record the bands).  With `on` non-zero every 256-column
+ * tile of the fold of Eq. (matrix_reweight) reads only the rows that hold
+ * its non-zero responses (lists of one or two points of a multi-component
+ * context: every tile only the 16-byte column groups inside its rows'
+ * bands).  The skipped terms are exact zeros and no sum changes order, so
+ * every result is bitwise the one of the full read (for the batched forms
+ * at the same row split; the tuner, which times the banded and the dense
+ * fold separately, may pick another).
  * Off by default: the full dense read of R, as the method is written.
  * Applies to nr_eval_nll, nr_eval_nll_grad, nr_eval_mu, nr_eval_nll_dev,
  * nr_eval_nll_dev_noalloc and the batched and grouped entry points;
@@ -176,8 +176,7 @@ int nr_set_band_skipping(nr_ctx *ctx, int on);
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * computation, arguments and results of nr_eval_nll_dev, through the same
- * kernels, with nothing allocated.  The pipeline's node tables, fold vectors,
- * partial sums and adjoint buffers (and the blocks of a list of points, as
+ * kernels, with nothing allocated.  The partial sums of a list of points (as
  * many points at a time as fit) live in a static workspace of the library
  * (NR_NOALLOC_WORKSPACE_BYTES per device, held from the first nr_create on
  * that device until the process ends) instead of the context's buffers, and
@@ -194,19 +193,18 @@ int nr_set_band_skipping(nr_ctx *ctx, int on);
 int nr_eval_nll_dev_noalloc(nr_ctx *ctx, const double *d_theta, int n_pts,
                             double *d_nll, double *d_grad, void *stream);
 
-/* Batched form: n_pts points of one analysis at once.  The weights of all
- * points (from the theta-independent recoil basis, exact for Eq. (fT)) form
- * a matrix W[p][l] = m_l w_l(theta_p), and the fold of Eq. (mu_total)
- * becomes the dense product W R on the FP64 matrix cores (R widened from
- * FP32 as it is staged) with the Poisson reduction of Eq. (logL) fused into
- * its epilogue.  Synchronous; theta and nll are host arrays as in
- * nr_eval_nll. */
+/* Batched form: n_pts points of one analysis at once.  The points' row
+ * factors are a product of their coefficients with the theta-independent
+ * recoil basis (exact for Eq. (fT)), so the fold of Eq. (mu_total) is
+ * C (F^T R): R is read once per call on the FP64 matrix cores (widened from
+ * FP32) and the Poisson reduction of Eq. (logL) follows from the folded
+ * columns.  The number of row splits is tuned per shape class.  Synchronous;
+ * theta and nll are host arrays as in nr_eval_nll. */
 int nr_eval_nll_batched(nr_ctx *ctx, const double *theta, int n_pts,
                         double *nll);
 
-/* Batched likelihood and gradient: the adjoint a = d(-2lnL)/d mu is
- * propagated back through R as a second matrix product (U = A R^T) and
- * contracted with the weight derivatives.  grad: [n_pts][7] host. */
+/* Batched likelihood and gradient: a = d(-2lnL)/d mu contracted with the same
+ * folded columns.  grad: [n_pts][7] host. */
 int nr_eval_nll_grad_batched(nr_ctx *ctx, const double *theta, int n_pts,
                              double *nll, double *grad);
 
@@ -215,7 +213,7 @@ int nr_eval_mu_batched(nr_ctx *ctx, const double *theta, int n_pts,
                        double *mu);
 
 /* Several analyses (datasets with their own binning and response, all on
- * one device) in one grouped persistent launch: theta[d] ([n_pts[d]][7],
+ * one device) in four launches per 16 of them: theta[d] ([n_pts[d]][7],
  * host), nll[d] ([n_pts[d]], host).  The stream of ctx[0] is used. */
 int nr_eval_nll_multi(nr_ctx *const *ctx, int n_ctx,
                       const double *const *theta, const int *n_pts,
@@ -223,8 +221,7 @@ int nr_eval_nll_multi(nr_ctx *const *ctx, int n_ctx,
 
 /* Device-pointer variant of nr_eval_nll_multi (and of the batched gradient
  * when d_grad is not NULL: d_grad[d] is [n_pts[d]][7]).  Enqueued on
- * `stream` (NULL = the default stream); a cached HIP graph of the whole
- * grouped evaluation is replayed for repeated pointer sets. */
+ * `stream` (NULL = the default stream). */
 int nr_eval_nll_multi_dev(nr_ctx *const *ctx, int n_ctx,
                           const double *const *d_theta, const int *n_pts,
                           double *const *d_nll, double *const *d_grad,
@@ -302,15 +299,18 @@ int nr_get_reference(nr_ctx *ctx, double *s_sm, double *m);
  * work against it. */
 void *nr_stream(nr_ctx *ctx);
 
-/* Average device time in milliseconds of one stage of the single-point
- * path, launched `iters` times back to back on the context stream between
- * HIP events (stage 1: E-integral node table + weights, 2: fold +
- * likelihood, 3: adjoint, 4: the R-streaming fold alone, 5: the
- * steady-state launch of the point pipeline, all four roles at once).  The
- * launches run on the context's own inputs at the SM point (no stage's work
- * depends on theta) and write only library-internal buffers.  For roofline
- * measurements.  NR_ESTATE before set_sources, set_response and set_data
- * (stage 3: also for a multi-component context). */
+/* Average device time in milliseconds of one stage of the evaluation of an
+ * isolated point, launched `iters` times back to back on the context stream
+ * between HIP events: stage 1: E-integral node table + weights (the weights
+ * and diagnostic entry points), 2 and 5: the whole evaluation, 3: the same
+ * with the gradient, 4: the R-streaming fold alone.  Contexts on the
+ * point-by-point route (multi-component; responses of more than about 60000
+ * bins): 2: fold + likelihood, 3: adjoint, 4: fold alone, 5: the steady-state
+ * launch of the point pipeline.  The launches run on the context's own inputs
+ * at the SM point (no stage's work depends on theta) and write only
+ * library-internal buffers.  For roofline measurements.  NR_ESTATE before
+ * set_sources, set_response and set_data (stage 3: also for a multi-component
+ * context). */
 int nr_time_stage(nr_ctx *ctx, int stage, int iters, double *avg_ms);
 
 /* Tuning knobs for sweeps.  rows_per_wg > 0: recoil rows per fold tile (a

@@ -5,6 +5,7 @@
 #include "block.h"
 #include "ess.h"
 #include "mlp.h"
+#include "shared.h"
 #include "../../include/nureweight.h"
 
 #include <algorithm>
@@ -134,10 +135,6 @@ struct ApiLock {
     std::lock_guard<std::recursive_mutex> g{nr::api_mutex()};
 };
 
-// Incremented whenever a context's device buffers may have moved; cached
-// grouped-launch plans built under an older epoch are rebuilt.
-std::atomic<unsigned long> g_epoch{1};
-
 // Device address of the static workspace on each device, looked up once per
 // device by the first nr_create on it (under the API lock).
 std::vector<double*> g_scratch_dev;
@@ -153,19 +150,6 @@ int lookup_scratch(int device, int ndev) {
     g_scratch_dev[device] = static_cast<double*>(p);
     return 0;
 }
-
-// One grouped launch over several analyses: GEMM problem tables, tile lists
-// and the captured graph of the whole batched evaluation.
-struct BatchPlan {
-    nr::GemmProb* d_probs_f = nullptr;
-    nr::GemmTile* d_tiles_f = nullptr;
-    nr::GemmProb* d_probs_a = nullptr;
-    nr::GemmTile* d_tiles_a = nullptr;
-    int n_tiles_f = 0, n_tiles_a = 0, grid_f = 1, grid_a = 1;
-    int cfg = 0;  // GEMM tile configuration (see batched.h)
-    hipGraphExec_t graph = nullptr;
-    unsigned long epoch = 0;
-};
 
 }  // namespace
 
@@ -206,9 +190,17 @@ struct nr_ctx {
     // per column tile of the blocked fold the rows [lo, hi) holding its
     // non-zero responses
     int* d_blkband = nullptr;
-    // workspace of the blocked fold (lists of points), and its size
+    // workspace of the blocked fold (lists of points of the multi-component
+    // form), and its size
     double* d_blk = nullptr;
     size_t blk_bytes = 0;
+    // workspace of the basis form (shared.h), for lists of up to sh_pts points
+    // at a time: allocated with the response and kept, so that no evaluation
+    // allocates; and the one of the batched entry points, which grows
+    double* d_sh = nullptr;
+    int sh_pts = 0;
+    double* d_shb = nullptr;
+    size_t shb_bytes = 0;
     bool m_user = false;
     double n_sig = 0;
     std::vector<double> mrow;
@@ -248,21 +240,13 @@ struct nr_ctx {
     // graphs
     bool use_graph = true;
     std::map<GraphKey, hipGraphExec_t> graphs;
-    // batched (GEMM) path workspace
-    int b_cap = 0, b_ldw = 0, b_nnt = 0;
-    bool b_grad = false;
-    double* d_wt = nullptr;     // [n_t][ldw]   weights, K-major
-    double* d_bpart = nullptr;  // [cap][n_nt]  deviance partials
-    double* d_bpgb = nullptr;   // [cap][n_nt]  sum a b partials
-    double* d_bat = nullptr;    // [ldr][ldw]   d(-2lnL)/d mu, j-major
-    double* d_bu = nullptr;     // [cap][n_t]   adjoint rows
+    // staging of the batched entry points
+    int b_cap = 0;
     double *d_bth = nullptr, *d_bnll = nullptr, *d_bgrad = nullptr, *d_bmu = nullptr;
     size_t b_cap_mu = 0;
-    unsigned* d_gctr = nullptr;  // [4] tile counters (forward, adjoint)
-    std::map<std::vector<const void*>, BatchPlan*> plans;
     // template form: folded basis templates and the data, per reco bin
     bool tmpl_ok = false, tmpl_data_ok = false;
-    double* d_trec = nullptr;  // [n_reco][kTmplRec]
+    double* d_trec = nullptr;  // [n_reco][kShRec], or the multi-component records
     double *d_tdp = nullptr, *d_thp = nullptr;  // evaluation partials
     double* d_tred = nullptr;                   // [1 + kTmplCols][points] slice sums
     size_t t_cap_d = 0, t_cap_h = 0, t_cap_r = 0;
@@ -270,27 +254,12 @@ struct nr_ctx {
 
 namespace {
 
-// Graph executables and the tile tables their kernels read may still be in
-// flight (the _dev entry points return without waiting): wait for the device
-// before destroying or freeing them.
-void free_plan(BatchPlan* p) {
-    if (!p) return;
-    (void)hipDeviceSynchronize();
-    if (p->graph) (void)hipGraphExecDestroy(p->graph);
-    if (p->d_probs_f) (void)hipFree(p->d_probs_f);
-    if (p->d_tiles_f) (void)hipFree(p->d_tiles_f);
-    if (p->d_probs_a) (void)hipFree(p->d_probs_a);
-    if (p->d_tiles_a) (void)hipFree(p->d_tiles_a);
-    delete p;
-}
-
+// Graph executables may still be in flight (the _dev entry points return
+// without waiting): wait for the device before destroying them.
 void clear_graphs(nr_ctx* c) {
-    if (!c->graphs.empty() || !c->plans.empty()) (void)hipDeviceSynchronize();
+    if (!c->graphs.empty()) (void)hipDeviceSynchronize();
     for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     c->graphs.clear();
-    for (auto& kv : c->plans) free_plan(kv.second);
-    c->plans.clear();
-    ++g_epoch;
 }
 
 int set_device(nr_ctx* c) {
@@ -437,9 +406,10 @@ int set_tile_bands(nr_ctx* c) {
     return 0;
 }
 
-// Rows [lo, hi) with non-zero responses of every column tile of the blocked
-// fold; lo on a multiple of four, the rows of one matrix instruction.
+// Rows [lo, hi) with non-zero responses of every column tile of the basis and
+// blocked folds; lo on a multiple of four, the rows of one matrix instruction.
 int set_blk_bands(nr_ctx* c) {
+    static_assert(nr::kBlkCols == nr::kShTile, "one table of bands");
     const int n_ct = (c->ldr + nr::kBlkCols - 1) / nr::kBlkCols;
     std::vector<int> bb((size_t)2 * n_ct, 0);
     for (int t = 0; t < n_ct; ++t) {
@@ -462,6 +432,8 @@ int set_blk_bands(nr_ctx* c) {
     HIPCHK(hipMemcpy(c->d_blkband, bb.data(), sizeof(int) * bb.size(), hipMemcpyHostToDevice));
     return 0;
 }
+
+int ensure_shared(nr_ctx* c);
 
 int choose_tiling(nr_ctx* c, int rows_req) {
     c->n_fc = (c->ldr / 4 + 511) / 512;   // fold tiles are 2048 columns wide
@@ -487,6 +459,7 @@ int choose_tiling(nr_ctx* c, int rows_req) {
     if ((rc = dalloc(&c->d_jpart, (size_t)c->adj_grid * nr::kNBasis))) return rc;
     if ((rc = set_tile_bands(c))) return rc;
     if ((rc = set_blk_bands(c))) return rc;
+    if ((rc = ensure_shared(c))) return rc;
     clear_graphs(c);
     return 0;
 }
@@ -800,8 +773,172 @@ int enqueue_points(nr_ctx* c, const double* th, int n_pts, double* nll,
     return 0;
 }
 
-// ---- lists of points through the blocked fold (block.hip).  Four launches
-// per block of points: weights, fold, likelihood sums, final.
+// ---- the basis form (shared.hip): one pass over R per call, whatever the
+// number of points.
+
+// Row splits of the fold: column tiles x splits fill the chip's 256 compute
+// units `fill` times, a split of at least one stage.  They depend on the
+// response's shape only, so a point's result does not depend on its list.
+void sh_split(const nr_ctx* c, int fill_num, int fill_den, int* n_split, int* rows_per) {
+    const int n_ct = (c->ldr + nr::kShTile - 1) / nr::kShTile;
+    const int target = 256 * fill_num / fill_den;
+    const int s = std::max(1, std::min(target / n_ct, c->n_t / nr::kShStage));
+    *rows_per = ((c->n_t + s - 1) / s + nr::kShStage - 1) / nr::kShStage * nr::kShStage;
+    *n_split = (c->n_t + *rows_per - 1) / *rows_per;
+}
+
+// Configurations the autotuner picks from: work-groups per compute unit.
+// 0 (one) is what every call outside the batched entry points runs: at
+// 16384 x 4096 it reads R in 47 us, two in 53 us, four in 61 us (each doubling
+// writes and reads back twice the partial sums).
+constexpr int kShConfigs = 4;
+constexpr int kShFill[kShConfigs][2] = {{1, 1}, {2, 1}, {4, 1}, {1, 2}};
+
+struct ShWork {
+    double *part, *rec, *dpart, *hpart;
+};
+
+// Layout of the workspace for pts points at a time; the bytes it takes.
+size_t carve_sh(const nr_ctx* c, double* base, int pts, bool grad, int cfg, ShWork* w) {
+    size_t off = 0;
+    auto take = [&](size_t n) {
+        double* p = base ? base + off : nullptr;
+        off += (n + 31) / 32 * 32;
+        return p;
+    };
+    int ns, rp, tiles, slices;
+    sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &ns, &rp);
+    nr::sh_slices(pts, c->n_reco, &tiles, &slices);
+    w->part = take((size_t)ns * nr::kShCols * c->ldr);
+    w->rec = take((size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins * nr::kShRec);
+    w->dpart = take((size_t)slices * pts);
+    w->hpart = grad ? take((size_t)slices * nr::kShAcc * pts) : nullptr;
+    return off * sizeof(double);
+}
+
+// Points at a time in `limit` bytes: at most 4096 (beyond, the slices would
+// depend on the number of points), whole blocks of 16; 0 if not even one fits.
+constexpr size_t kShBytes = (size_t)64 << 20;
+
+int sh_points(const nr_ctx* c, size_t limit) {
+    ShWork w;
+    int lo = 0, hi = 256;  // blocks of 16 that fit / that are asked for
+    while (lo < hi) {
+        const int m = (lo + hi + 1) / 2;
+        if (carve_sh(c, nullptr, 16 * m, true, 0, &w) <= limit) lo = m;
+        else hi = m - 1;
+    }
+    return 16 * lo;
+}
+
+int ensure_shared(nr_ctx* c) {
+    if (c->multi) return 0;
+    ShWork w;
+    c->sh_pts = std::max(16, sh_points(c, kShBytes));
+    return dalloc(&c->d_sh, carve_sh(c, nullptr, c->sh_pts, true, 0, &w) / sizeof(double));
+}
+
+// Every single-component evaluation but the weights takes the basis form.  A
+// context whose shapes the allocation-free entry point accepts must take the
+// same route in both entry points (their results are bitwise equal): if the
+// basis form does not fit the static workspace there, both run the single-point
+// launches.
+bool use_shared(const nr_ctx* c) {
+    if (c->multi) return false;
+    Work w;
+    return carve_work(c, nullptr, &w) > (size_t)NR_NOALLOC_WORKSPACE_BYTES ||
+           sh_points(c, NR_NOALLOC_WORKSPACE_BYTES) > 0;
+}
+
+nr::ShFold sh_fold_args(const nr_ctx* c, int cfg, double* part) {
+    nr::ShFold f{};
+    f.R = c->d_R;
+    f.rf = c->d_rf;
+    f.part = part;
+    f.band = c->skip_zero ? c->d_blkband : nullptr;
+    f.ldr = c->ldr;
+    f.n_t = c->n_t;
+    f.n_ct = (c->ldr + nr::kShTile - 1) / nr::kShTile;
+    sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &f.n_split, &f.rows_per);
+    return f;
+}
+
+nr::ShRec sh_rec_args(const nr_ctx* c, const nr::ShFold& f, double* rec) {
+    nr::ShRec r{};
+    r.part = f.part;
+    r.n = c->d_n;
+    r.b = c->d_b;
+    r.rec = rec;
+    r.n_split = f.n_split;
+    r.ldr = c->ldr;
+    r.n_reco = c->n_reco;
+    return r;
+}
+
+nr::ShEval sh_eval_args(const nr_ctx* c, const double* rec, const double* th, int n_pts,
+                        double* dpart, double* hpart, double* mu) {
+    nr::ShEval e{};
+    e.rec = rec;
+    e.theta = th;
+    e.dpart = dpart;
+    e.hpart = hpart;
+    e.mu = mu;
+    e.ph = c->ph;
+    e.n_pts = n_pts;
+    e.n_reco = c->n_reco;
+    nr::sh_slices(n_pts, c->n_reco, &e.tiles, &e.n_slice);
+    return e;
+}
+
+nr::ShFinal sh_final_args(const nr_ctx* c, const nr::ShEval& e, double* nll, double* grad) {
+    nr::ShFinal f{};
+    f.dpart = e.dpart;
+    f.hpart = e.hpart;
+    f.theta = e.theta;
+    f.nll = nll;
+    f.grad = grad;
+    f.cdata = c->cdata;
+    for (int i = 0; i < NR_NTHETA; ++i) {
+        f.pull_mean[i] = c->pull_mean[i];
+        f.pull_sigma[i] = c->pull_sigma[i];
+    }
+    f.ph = c->ph;
+    f.n_pts = e.n_pts;
+    f.n_slice = e.n_slice;
+    return f;
+}
+
+// th: device memory, or with th_host pinned host memory whose copy there the
+// records launch makes.
+int enqueue_shared(nr_ctx* c, double* base, int pts, const double* th, const double* th_host,
+                   int n_pts, double* nll, double* grad, double* mu, hipStream_t s) {
+    ShWork w;
+    carve_sh(c, base, pts, true, 0, &w);
+    const nr::ShFold f = sh_fold_args(c, 0, w.part);
+    nr::ShRec r = sh_rec_args(c, f, w.rec);
+    if (th_host) {
+        r.th_src = th_host;
+        r.th_dst = const_cast<double*>(th);
+        r.n_th = n_pts * NR_NTHETA;
+    }
+    HIPCHK(nr::launch_sh_fold(&f, 1, s));
+    HIPCHK(nr::launch_sh_rec(&r, 1, s));
+    for (int p0 = 0; p0 < n_pts; p0 += pts) {
+        const nr::ShEval e = sh_eval_args(c, w.rec, th + (size_t)p0 * NR_NTHETA,
+                                          std::min(pts, n_pts - p0), w.dpart,
+                                          grad ? w.hpart : nullptr,
+                                          mu ? mu + (size_t)p0 * c->n_reco : nullptr);
+        const nr::ShFinal q = sh_final_args(c, e, nll + p0,
+                                            grad ? grad + (size_t)p0 * NR_NTHETA : nullptr);
+        HIPCHK(nr::launch_sh_eval(&e, 1, s));
+        HIPCHK(nr::launch_sh_final(&q, 1, s));
+    }
+    return 0;
+}
+
+// ---- lists of points of the multi-component form through the blocked fold
+// (block.hip).  Four launches per block of points: weights, fold, likelihood
+// sums, final.
 // The row splits depend on the response's shape only, never on the number of
 // points, so a point's result does not depend on the block it falls in.
 struct BlkWork {
@@ -859,7 +996,7 @@ int blk_points(const nr_ctx* c, int n_pts, size_t limit) {
 constexpr int kBlkMinPts = 3;
 
 bool use_blocks(const nr_ctx* c, int n_pts) {
-    if (n_pts < kBlkMinPts) return false;
+    if (!c->multi || n_pts < kBlkMinPts) return false;
     Work w;
     if (carve_work(c, nullptr, &w) > (size_t)NR_NOALLOC_WORKSPACE_BYTES) return true;
     return blk_points(c, 16, NR_NOALLOC_WORKSPACE_BYTES) > 0;
@@ -939,7 +1076,11 @@ int enqueue_blocks(nr_ctx* c, const double* th, int n_pts, double* nll, double* 
 constexpr int kDirectMaxPts = 2;
 
 int run_points(nr_ctx* c, const double* th, int n_pts, double* nll,
-               double* grad, double* mu, double* w, hipStream_t s) {
+               double* grad, double* mu, double* w, hipStream_t s,
+               const double* th_host = nullptr) {
+    if (!w && use_shared(c))
+        return enqueue_shared(c, c->d_sh, c->sh_pts, th, th_host, n_pts, nll, grad, mu, s);
+    if (th_host) th = th_host;
     if (!grad && !w && use_blocks(c, n_pts)) {
         int rc = ensure_blk(c, n_pts);
         return rc ? rc : enqueue_blocks(c, th, n_pts, nll, mu, s, c->d_blk, kBlkBytes);
@@ -999,40 +1140,31 @@ int check_single(nr_ctx* c) {
 namespace {
 
 // ------------------------------------------------------------ batched path
-int ensure_batch(nr_ctx* c, int n_pts, bool grad, size_t mu_elems) {
-    const int ldw = (n_pts + 3) / 4 * 4;
-    const int nnt = (c->n_reco + 63) / 64;  // column tiles of the narrowest config
+int ensure_batch(nr_ctx* c, int n_pts, size_t mu_elems) {
     int rc;
-    bool moved = false;
-    if (n_pts > c->b_cap || ldw > c->b_ldw || nnt != c->b_nnt) {
+    if (n_pts > c->b_cap) {
         const int cap = std::max(n_pts, 64);
-        const int ldc = (cap + 3) / 4 * 4;
-        if ((rc = dalloc(&c->d_wt, (size_t)c->n_t * ldc))) return rc;
-        HIPCHK(hipMemset(c->d_wt, 0, sizeof(double) * (size_t)c->n_t * ldc));
-        if ((rc = dalloc(&c->d_bpart, (size_t)cap * nnt))) return rc;
-        if ((rc = dalloc(&c->d_bpgb, (size_t)cap * nnt))) return rc;
         if ((rc = dalloc(&c->d_bth, (size_t)cap * NR_NTHETA))) return rc;
         if ((rc = dalloc(&c->d_bnll, (size_t)cap))) return rc;
         if ((rc = dalloc(&c->d_bgrad, (size_t)cap * NR_NTHETA))) return rc;
         c->b_cap = cap;
-        c->b_ldw = ldc;
-        c->b_nnt = nnt;
-        c->b_grad = false;
-        moved = true;
-    }
-    if (grad && !c->b_grad) {
-        if ((rc = dalloc(&c->d_bat, (size_t)c->ldr * c->b_ldw))) return rc;
-        HIPCHK(hipMemset(c->d_bat, 0, sizeof(double) * (size_t)c->ldr * c->b_ldw));
-        if ((rc = dalloc(&c->d_bu, (size_t)c->b_cap * c->n_t))) return rc;
-        c->b_grad = true;
-        moved = true;
     }
     if (mu_elems > c->b_cap_mu) {
         if ((rc = dalloc(&c->d_bmu, mu_elems))) return rc;
         c->b_cap_mu = mu_elems;
-        moved = true;
     }
-    if (moved) ++g_epoch;
+    return 0;
+}
+
+// The batched entry points' own workspace of one analysis.
+int ensure_shb(nr_ctx* c, int n_pts, bool grad, int cfg) {
+    ShWork w;
+    const size_t need = carve_sh(c, nullptr, n_pts, grad, cfg, &w);
+    if (need <= c->shb_bytes) return 0;
+    int rc;
+    c->shb_bytes = 0;
+    if ((rc = dalloc(&c->d_shb, need / sizeof(double)))) return rc;
+    c->shb_bytes = need;
     return 0;
 }
 
@@ -1046,174 +1178,40 @@ struct MultiCall {
     double* const* mu;           // device or null (array may be null)
 };
 
-// K range of a GEMM tile: the whole reduction, or with band skipping the
-// K-steps whose response entries for the tile are not all zero.  Forward
-// tiles cover response columns [c0, c1) and reduce over its rows; adjoint
-// tiles cover rows [c0, c1) and reduce over its columns.  An empty range
-// leaves the tile's sums at zero, as the skipped products are.
-void tile_k_range(const nr_ctx* c, bool adjoint, int c0, int c1, int K, int* k0, int* k1) {
-    constexpr int BK = nr::kGemmBK;
-    if (!c->skip_zero) {
-        *k0 = 0;
-        *k1 = K;
-        return;
-    }
-    int lo = K, hi = 0;
-    if (!adjoint) {
-        for (int l = 0; l < c->n_t; ++l) {
-            const int a = 4 * c->rowband[2 * (size_t)l], b = 4 * c->rowband[2 * (size_t)l + 1];
-            if (a < b && a < c1 && b > c0) {
-                lo = std::min(lo, l);
-                hi = std::max(hi, l + 1);
-            }
-        }
-    } else {
-        for (int l = c0; l < std::min(c1, c->n_t); ++l) {
-            const int a = 4 * c->rowband[2 * (size_t)l], b = 4 * c->rowband[2 * (size_t)l + 1];
-            if (a < b) {
-                lo = std::min(lo, a);
-                hi = std::max(hi, b);
-            }
-        }
-    }
-    if (lo >= hi) {
-        *k0 = *k1 = 0;
-        return;
-    }
-    *k0 = lo / BK * BK;
-    *k1 = std::min(K, (hi + BK - 1) / BK * BK);
-}
-
-int build_plan(const MultiCall& mc, bool grad, int cfg, BatchPlan* pl) {
-    const int TMt = nr::gemm_tile_m(cfg), TNt = nr::gemm_tile_n(cfg);
-    std::vector<nr::GemmProb> pf(mc.n), pa(mc.n);
-    std::vector<nr::GemmTile> tf, ta;
-    for (int d = 0; d < mc.n; ++d) {
-        nr_ctx* c = mc.ctx[d];
-        const int P = mc.n_pts[d];
-        nr::GemmProb f{};
-        f.At = c->d_wt;
-        f.lda = c->b_ldw;
-        f.B = c->d_R;
-        f.ldb = c->ldr;
-        f.M = P;
-        f.N = c->n_reco;
-        f.K = c->n_t;
-        f.n = c->d_n;
-        f.b = c->d_b;
-        f.theta = mc.theta[d];
-        f.part = c->d_bpart;
-        f.part_gb = c->d_bpgb;
-        f.n_nt = (c->n_reco + TNt - 1) / TNt;
-        f.aout = grad ? c->d_bat : nullptr;
-        f.lda_out = c->b_ldw;
-        f.mu = mc.mu ? mc.mu[d] : nullptr;
-        pf[d] = f;
-        const int mt = (P + TMt - 1) / TMt;
-        std::vector<int> kr(2 * (size_t)f.n_nt);
-        for (int j = 0; j < f.n_nt; ++j)
-            tile_k_range(c, false, j * TNt, (j + 1) * TNt, c->n_t, &kr[2 * j], &kr[2 * j + 1]);
-        for (int i = 0; i < mt; ++i)
-            for (int j = 0; j < f.n_nt; ++j)
-                tf.push_back({d, i, j, kr[2 * j + 1] - kr[2 * j], kr[2 * j], kr[2 * j + 1]});
-        if (grad) {
-            nr::GemmProb a{};
-            a.At = c->d_bat;
-            a.lda = c->b_ldw;
-            a.B = c->d_R;
-            a.ldb = c->ldr;
-            a.M = P;
-            a.N = c->n_t;
-            a.K = c->n_reco;
-            a.C = c->d_bu;
-            a.ldc = c->n_t;
-            pa[d] = a;
-            const int nt = (c->n_t + TNt - 1) / TNt;
-            std::vector<int> ka(2 * (size_t)nt);
-            for (int j = 0; j < nt; ++j)
-                tile_k_range(c, true, j * TNt, (j + 1) * TNt, c->n_reco, &ka[2 * j],
-                             &ka[2 * j + 1]);
-            for (int i = 0; i < mt; ++i)
-                for (int j = 0; j < nt; ++j)
-                    ta.push_back({d, i, j, ka[2 * j + 1] - ka[2 * j], ka[2 * j], ka[2 * j + 1]});
-        }
-    }
-    // longest tiles first: the persistent work-groups pull from this list
-    auto by_cost = [](const nr::GemmTile& x, const nr::GemmTile& y) { return x.cost > y.cost; };
-    std::stable_sort(tf.begin(), tf.end(), by_cost);
-    std::stable_sort(ta.begin(), ta.end(), by_cost);
+// All analyses of a call in four launches per kShGroup of them.
+int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
+    const bool grad = mc.grad != nullptr;
     int rc;
-    if ((rc = dalloc(&pl->d_probs_f, pf.size())) || (rc = dalloc(&pl->d_tiles_f, tf.size())))
-        return rc;
-    HIPCHK(hipMemcpy(pl->d_probs_f, pf.data(), sizeof(nr::GemmProb) * pf.size(), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(pl->d_tiles_f, tf.data(), sizeof(nr::GemmTile) * tf.size(), hipMemcpyHostToDevice));
-    pl->n_tiles_f = (int)tf.size();
-    pl->cfg = cfg;
-    pl->grid_f = nr::gemm_grid(nr::kModeNll, cfg, pl->n_tiles_f);
-    if (grad) {
-        if ((rc = dalloc(&pl->d_probs_a, pa.size())) || (rc = dalloc(&pl->d_tiles_a, ta.size())))
-            return rc;
-        HIPCHK(hipMemcpy(pl->d_probs_a, pa.data(), sizeof(nr::GemmProb) * pa.size(), hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(pl->d_tiles_a, ta.data(), sizeof(nr::GemmTile) * ta.size(), hipMemcpyHostToDevice));
-        pl->n_tiles_a = (int)ta.size();
-        pl->grid_a = nr::gemm_grid(nr::kModeAdj, cfg, pl->n_tiles_a);
-    }
-    pl->epoch = g_epoch.load();
-    return 0;
-}
-
-int enqueue_plan(const MultiCall& mc, bool grad, BatchPlan* pl, unsigned* ctr,
-                 hipStream_t s) {
     for (int d = 0; d < mc.n; ++d)
-        HIPCHK(nr::launch_pts_weights(weight_args(mc.ctx[d], mc.theta[d], mc.n_pts[d],
-                                                  mc.ctx[d]->b_ldw, mc.ctx[d]->b_ldw,
-                                                  mc.ctx[d]->d_wt), s));
-    HIPCHK(nr::launch_gemm(nr::kModeNll, pl->cfg, pl->d_probs_f, pl->d_tiles_f,
-                           pl->n_tiles_f, ctr, pl->grid_f, s));
-    for (int d = 0; d < mc.n; ++d) {
-        nr_ctx* c = mc.ctx[d];
-        nr::FinalArgs f{};
-        f.part = c->d_bpart;
-        f.theta = mc.theta[d];
-        f.n_pts = mc.n_pts[d];
-        f.n_nt = (c->n_reco + nr::gemm_tile_n(pl->cfg) - 1) / nr::gemm_tile_n(pl->cfg);
-        f.cdata = c->cdata;
-        for (int i = 0; i < NR_NTHETA; ++i) {
-            f.pull_mean[i] = c->pull_mean[i];
-            f.pull_sigma[i] = c->pull_sigma[i];
-        }
-        f.nll = mc.nll[d];
-        HIPCHK(nr::launch_finalize(f, s));
-    }
-    if (grad) {
-        HIPCHK(nr::launch_gemm(nr::kModeAdj, pl->cfg, pl->d_probs_a, pl->d_tiles_a,
-                               pl->n_tiles_a, ctr + 2, pl->grid_a, s));
-        for (int d = 0; d < mc.n; ++d) {
+        if ((rc = ensure_shb(mc.ctx[d], mc.n_pts[d], grad, cfg))) return rc;
+    for (int d0 = 0; d0 < mc.n; d0 += nr::kShGroup) {
+        const int n = std::min(nr::kShGroup, mc.n - d0);
+        nr::ShFold f[nr::kShGroup];
+        nr::ShRec r[nr::kShGroup];
+        nr::ShEval e[nr::kShGroup];
+        nr::ShFinal q[nr::kShGroup];
+        for (int i = 0; i < n; ++i) {
+            const int d = d0 + i;
             nr_ctx* c = mc.ctx[d];
-            nr::ContractArgs a{};
-            a.U = c->d_bu;
-            a.ldu = c->n_t;
-            a.n_t = c->n_t;
-            a.n_pts = mc.n_pts[d];
-            a.n_nt = (c->n_reco + nr::gemm_tile_n(pl->cfg) - 1) / nr::gemm_tile_n(pl->cfg);
-            a.rf = c->d_rf;
-            a.theta = mc.theta[d];
-            a.part_gb = c->d_bpgb;
-            for (int i = 0; i < NR_NTHETA; ++i) {
-                a.pull_mean[i] = c->pull_mean[i];
-                a.pull_sigma[i] = c->pull_sigma[i];
-            }
-            a.ph = c->ph;
-            a.grad = mc.grad[d];
-            HIPCHK(nr::launch_adj_contract(a, s));
+            ShWork w;
+            carve_sh(c, c->d_shb, mc.n_pts[d], grad, cfg, &w);
+            f[i] = sh_fold_args(c, cfg, w.part);
+            r[i] = sh_rec_args(c, f[i], w.rec);
+            e[i] = sh_eval_args(c, w.rec, mc.theta[d], mc.n_pts[d], w.dpart, w.hpart,
+                                mc.mu ? mc.mu[d] : nullptr);
+            q[i] = sh_final_args(c, e[i], mc.nll[d], grad ? mc.grad[d] : nullptr);
         }
+        HIPCHK(nr::launch_sh_fold(f, n, s));
+        HIPCHK(nr::launch_sh_rec(r, n, s));
+        HIPCHK(nr::launch_sh_eval(e, n, s));
+        HIPCHK(nr::launch_sh_final(q, n, s));
     }
     return 0;
 }
 
-// ---- project autotuner for the grouped GEMM.  A shape class is the sorted
+// ---- project autotuner for the grouped fold.  A shape class is the sorted
 // list of (points rounded up to 64, N_reco, N_T) of the call plus the mode;
-// the first call of a class times every tile configuration on the real
+// the first call of a class times every configuration on the real
 // problem (one warm-up and two timed runs each) and keeps the fastest, in
 // memory and in a small JSON file (NR_AUTOTUNE_CACHE, default
 // $HOME/.cache/nureweight/autotune.json).  NR_AUTOTUNE=0 skips tuning; a
@@ -1259,7 +1257,7 @@ void tune_load() {
         if (c == std::string::npos) break;
         char* end = nullptr;
         const long v = strtol(txt.c_str() + c + 1, &end, 10);
-        if (end != txt.c_str() + c + 1 && v >= 0 && v < nr::kGemmConfigs)
+        if (end != txt.c_str() + c + 1 && v >= 0 && v < kShConfigs)
             g_tune.best[key] = (int)v;
         i = (end && end > txt.c_str() + c) ? (size_t)(end - txt.c_str()) : j + 1;
     }
@@ -1305,7 +1303,7 @@ std::string shape_class(const MultiCall& mc, bool grad) {
 
 int tuned_config(const MultiCall& mc, bool grad, hipStream_t s, int* cfg_out) {
     const char* force = getenv("NR_GEMM_CONFIG");  // pins a configuration
-    if (force && force[0] >= '0' && force[0] < '0' + nr::kGemmConfigs && !force[1]) {
+    if (force && force[0] >= '0' && force[0] < '0' + kShConfigs && !force[1]) {
         *cfg_out = force[0] - '0';
         return 0;
     }
@@ -1318,43 +1316,28 @@ int tuned_config(const MultiCall& mc, bool grad, hipStream_t s, int* cfg_out) {
         auto it = g_tune.best.find(key);
         if (it != g_tune.best.end()) { *cfg_out = it->second; return 0; }
     }
-    nr_ctx* owner = mc.ctx[0];
-    // events and the trial plan's tables are released on every return
+    // events are released on every return
     struct Trial {
-        hipStream_t st;
         hipEvent_t e0 = nullptr, e1 = nullptr;
-        BatchPlan pl;
-        void drop_plan() {
-            if (pl.d_probs_f) (void)hipFree(pl.d_probs_f);
-            if (pl.d_tiles_f) (void)hipFree(pl.d_tiles_f);
-            if (pl.d_probs_a) (void)hipFree(pl.d_probs_a);
-            if (pl.d_tiles_a) (void)hipFree(pl.d_tiles_a);
-            pl = BatchPlan{};
-        }
         ~Trial() {
-            (void)hipStreamSynchronize(st);  // nothing in flight reads the tables
-            drop_plan();
             if (e0) (void)hipEventDestroy(e0);
             if (e1) (void)hipEventDestroy(e1);
         }
-    } t{s};
+    } t;
     HIPCHK(hipEventCreate(&t.e0));
     HIPCHK(hipEventCreate(&t.e1));
     float best_ms = 1e30f;
     int best = 0;
-    for (int cfg = 0; cfg < nr::kGemmConfigs; ++cfg) {
-        int rc = build_plan(mc, grad, cfg, &t.pl);
-        if (rc) return rc;
-        rc = enqueue_plan(mc, grad, &t.pl, owner->d_gctr, s);  // warm-up
+    for (int cfg = 0; cfg < kShConfigs; ++cfg) {
+        int rc = enqueue_multi(mc, cfg, s);  // warm-up
         if (rc) return rc;
         HIPCHK(hipEventRecord(t.e0, s));
-        for (int r = 0; r < 2 && !rc; ++r) rc = enqueue_plan(mc, grad, &t.pl, owner->d_gctr, s);
+        for (int r = 0; r < 2 && !rc; ++r) rc = enqueue_multi(mc, cfg, s);
         HIPCHK(hipEventRecord(t.e1, s));
         HIPCHK(hipEventSynchronize(t.e1));
         if (rc) return rc;
         float ms = 0;
         HIPCHK(hipEventElapsedTime(&ms, t.e0, t.e1));
-        t.drop_plan();
         if (ms < best_ms) { best_ms = ms; best = cfg; }
     }
     {
@@ -1368,65 +1351,9 @@ int tuned_config(const MultiCall& mc, bool grad, hipStream_t s, int* cfg_out) {
 }
 
 int run_multi(const MultiCall& mc, hipStream_t s) {
-    nr_ctx* owner = mc.ctx[0];
-    const bool grad = mc.grad != nullptr;
-    std::vector<const void*> key;
-    key.push_back((const void*)s);
-    key.push_back((const void*)(size_t)grad);
-    key.push_back((const void*)(size_t)(mc.mu != nullptr));
-    for (int d = 0; d < mc.n; ++d) {
-        key.push_back(mc.ctx[d]);
-        key.push_back(mc.theta[d]);
-        key.push_back((const void*)(size_t)mc.n_pts[d]);
-        key.push_back(mc.nll[d]);
-        if (grad) key.push_back(mc.grad[d]);
-        if (mc.mu) key.push_back(mc.mu[d]);
-    }
-    BatchPlan*& pl = owner->plans[key];
-    if (pl && pl->epoch != g_epoch) {
-        free_plan(pl);
-        pl = nullptr;
-    }
-    if (!pl) {
-        if (owner->plans.size() > 16) {
-            for (auto& kv : owner->plans)
-                if (kv.second && kv.first != key) free_plan(kv.second);
-            owner->plans.clear();
-        }
-        int cfg = 0;
-        int rc = tuned_config(mc, grad, s, &cfg);
-        if (rc) return rc;
-        BatchPlan*& np = owner->plans[key];
-        np = new BatchPlan();
-        rc = build_plan(mc, grad, cfg, np);
-        if (rc) { free_plan(np); owner->plans.erase(key); return rc; }
-        if (owner->use_graph) {
-            hipGraph_t g = nullptr;
-            hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
-            if (e == hipSuccess) {
-                rc = enqueue_plan(mc, grad, np, owner->d_gctr, s);
-                e = hipStreamEndCapture(s, &g);
-            }
-            if (!rc && e == hipSuccess) {
-                e = hipGraphInstantiate(&np->graph, g, nullptr, nullptr, 0);
-                if (e != hipSuccess) np->graph = nullptr;
-            }
-            if (g) (void)hipGraphDestroy(g);
-            if (rc || e != hipSuccess) {  // no half-built plan stays cached
-                free_plan(np);
-                owner->plans.erase(key);
-                return rc ? rc : fail(NR_EHIP, "graph capture: %s", hipGetErrorString(e));
-            }
-        }
-        np->epoch = g_epoch;
-        BatchPlan* use = np;
-        if (use->graph) HIPCHK(hipGraphLaunch(use->graph, s));
-        else return enqueue_plan(mc, grad, use, owner->d_gctr, s);
-        return 0;
-    }
-    if (pl->graph) HIPCHK(hipGraphLaunch(pl->graph, s));
-    else return enqueue_plan(mc, grad, pl, owner->d_gctr, s);
-    return 0;
+    int cfg = 0;
+    const int rc = tuned_config(mc, mc.grad != nullptr, s, &cfg);
+    return rc ? rc : enqueue_multi(mc, cfg, s);
 }
 
 int check_multi(nr_ctx* const* ctx, int n_ctx, const int* n_pts) {
@@ -1449,7 +1376,7 @@ int batched_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     if ((rc = check_single(c))) return rc;
     if ((rc = check_theta(theta, n_pts))) return rc;
     if ((rc = set_device(c))) return rc;
-    if ((rc = ensure_batch(c, n_pts, grad != nullptr, mu ? (size_t)n_pts * c->n_reco : 0)))
+    if ((rc = ensure_batch(c, n_pts, mu ? (size_t)n_pts * c->n_reco : 0)))
         return rc;
     HIPCHK(hipMemcpyAsync(c->d_bth, theta, sizeof(double) * n_pts * NR_NTHETA,
                           hipMemcpyHostToDevice, c->stream));
@@ -1502,11 +1429,10 @@ int nr_create(int device, nr_ctx** out) {
         return rc;
     }
     if (dalloc(&c->d_a, 1) || dalloc(&c->d_gb, 1) || dalloc(&c->d_thsm, nr::kMaxTheta) ||
-        dalloc(&c->d_gctr, 4) || dalloc(&c->d_tnll, 1 + NR_NTHETA)) {
+        dalloc(&c->d_tnll, 1 + NR_NTHETA)) {
         delete c;
         return NR_ENOMEM;
     }
-    (void)hipMemset(c->d_gctr, 0, 4 * sizeof(unsigned));
     // the SM point of either form: NSI and m2 zero, every rate one
     double sm[nr::kMaxTheta];
     for (int i = 0; i < nr::kMaxTheta; ++i) sm[i] = i < 5 ? 0.0 : 1.0;
@@ -1532,9 +1458,8 @@ void nr_destroy(nr_ctx* c) {
     dfree(&c->d_a); dfree(&c->d_gb); dfree(&c->d_jpart);
     dfree(&c->d_th); dfree(&c->d_out); dfree(&c->d_grad);
     dfree(&c->d_mu); dfree(&c->d_w); dfree(&c->d_thsm);
-    dfree(&c->d_wt); dfree(&c->d_bpart); dfree(&c->d_bpgb); dfree(&c->d_bat);
-    dfree(&c->d_bu); dfree(&c->d_bth); dfree(&c->d_bnll); dfree(&c->d_bgrad);
-    dfree(&c->d_bmu); dfree(&c->d_gctr);
+    dfree(&c->d_bth); dfree(&c->d_bnll); dfree(&c->d_bgrad); dfree(&c->d_bmu);
+    dfree(&c->d_sh); dfree(&c->d_shb);
     dfree(&c->d_trec); dfree(&c->d_tdp); dfree(&c->d_thp); dfree(&c->d_tred);
     dfree(&c->d_v[0]); dfree(&c->d_v[1]);
     dfree(&c->d_rowband); dfree(&c->d_tileband);
@@ -1845,7 +1770,10 @@ int nr_eval_nll_dev_noalloc(nr_ctx* c, const double* d_theta, int n_pts,
     // that a caller may capture them in its own graph
     Bridge br;
     if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
-    if (!d_grad && use_blocks(c, n_pts))
+    if (use_shared(c))
+        rc = enqueue_shared(c, base, std::min(c->sh_pts, sh_points(c, NR_NOALLOC_WORKSPACE_BYTES)),
+                            d_theta, nullptr, n_pts, d_nll, d_grad, nullptr, br.work);
+    else if (!d_grad && use_blocks(c, n_pts))
         rc = enqueue_blocks(c, d_theta, n_pts, d_nll, nullptr, br.work, base,
                             NR_NOALLOC_WORKSPACE_BYTES);
     else
@@ -1864,10 +1792,10 @@ static int eval_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     if (!mu && !w) {
         // likelihood (and gradient): theta in and -2lnL out through pinned
         // host memory the kernels read and write directly, no copies
-        if ((rc = ensure_pinned(c, n_pts))) return rc;
+        if ((rc = ensure_pinned(c, n_pts)) || (rc = ensure_stage(c, n_pts, 0, 0))) return rc;
         std::memcpy(c->h_th, theta, sizeof(double) * n_pts * c->n_theta);
-        rc = run_points(c, c->hd_th, n_pts, c->hd_out, grad ? c->hd_grad : nullptr,
-                        nullptr, nullptr, c->stream);
+        rc = run_points(c, c->d_th, n_pts, c->hd_out, grad ? c->hd_grad : nullptr,
+                        nullptr, nullptr, c->stream, c->hd_th);
         if (rc) return rc;
         HIPCHK(hipStreamSynchronize(c->stream));
         std::memcpy(nll, c->h_out, sizeof(double) * n_pts);
@@ -2209,11 +2137,29 @@ int nr_time_stage(nr_ctx* c, int stage, int iters, double* avg_ms) {
         aa.out_grad = c->d_tnll + 1;
         aa.ph = c->ph;
     }
+    // the basis form: its fold, or a whole evaluation of the SM point
+    const bool shared = use_shared(c);
+    ShWork sw{};
+    nr::ShFold sf{};
+    if (shared) {
+        carve_sh(c, c->d_sh, c->sh_pts, true, 0, &sw);
+        sf = sh_fold_args(c, 0, sw.part);
+    }
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     HIPCHK(hipEventRecord(e0, c->stream));
     for (int i = 0; i < iters; ++i) {
+        if (shared && stage != 1) {
+            if (stage == 4) {
+                HIPCHK(nr::launch_sh_fold(&sf, 1, c->stream));
+            } else if ((rc = enqueue_shared(c, c->d_sh, c->sh_pts, th, nullptr, 1, c->d_tnll,
+                                            stage == 3 ? c->d_tnll + 1 : nullptr, nullptr,
+                                            c->stream))) {
+                return rc;
+            }
+            continue;
+        }
         if (stage == 1) {
             rc = step(c, nullptr, nullptr, &sa, nullptr, c->stream);
             if (!rc) rc = step(c, nullptr, &ra, nullptr, nullptr, c->stream);
@@ -2270,8 +2216,6 @@ int nr_eval_nll_multi_dev(nr_ctx* const* ctx, int n_ctx,
             return fail(NR_EINVAL, "null device pointer for dataset %d", d);
     }
     if ((rc = set_device(ctx[0]))) return rc;
-    for (int d = 0; d < n_ctx; ++d)
-        if ((rc = ensure_batch(ctx[d], n_pts[d], d_grad != nullptr, 0))) return rc;
     Bridge br;
     if ((rc = bridge_begin(br, stream, ctx[0]->stream, ctx[0]->ev_in, ctx[0]->ev_out)))
         return rc;
@@ -2296,7 +2240,7 @@ int nr_eval_nll_multi(nr_ctx* const* ctx, int n_ctx, const double* const* theta,
     hipStream_t s = ctx[0]->stream;
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
-        if ((rc = ensure_batch(c, n_pts[d], false, 0))) return rc;
+        if ((rc = ensure_batch(c, n_pts[d], 0))) return rc;
     }
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
@@ -2781,7 +2725,7 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
     if ((rc = check_single(c))) return rc;
     if (!d_theta || !d_mu || n_pts <= 0) return fail(NR_EINVAL, "bad argument");
     if ((rc = set_device(c))) return rc;
-    if ((rc = ensure_batch(c, n_pts, false, 0))) return rc;
+    if ((rc = ensure_batch(c, n_pts, 0))) return rc;
     Bridge br;
     if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
     nr_ctx* cs[1] = {c};
@@ -2799,71 +2743,92 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
 // only the data slots.  In the multi-component form each component's row
 // block is folded with its own factors.
 
-// Record length and gradient contractions per point of the context's form.
+// Multi-component form: record length and gradient contractions per point.
 static int tmpl_rl(const nr_ctx* c) {
-    return c->multi ? (nr::kTmplCompCols * c->n_comp + c->n_bkg + 2 + 1) / 2 * 2
-                    : nr::kTmplRec;
+    return (nr::kTmplCompCols * c->n_comp + c->n_bkg + 2 + 1) / 2 * 2;
 }
-static int tmpl_nacc(const nr_ctx* c) {
-    return c->multi ? nr::kCompBasis + c->n_comp + c->n_bkg : nr::kTmplCols;
-}
+static int tmpl_nacc(const nr_ctx* c) { return nr::kCompBasis + c->n_comp + c->n_bkg; }
 
-// Fold the rows of block k (the whole response, or component k's rows) into
-// the record columns dst0 .. dst0 + n_dst - 1 (of records rl doubles long).
-static hipError_t fold_block(nr_ctx* c, int k, int frl, int dst0, int n_dst, int rl,
-                             double* d_part, int n_slab) {
+// Fold the rows of component k into the record columns dst0 ..
+static hipError_t fold_block(nr_ctx* c, int k, int dst0, int rl, double* d_part, int n_slab) {
     const size_t row0 = (size_t)k * c->n_t;
     nr::TmplFoldArgs fa{c->d_R + row0 * c->ldr, c->ldr, c->n_t, c->n_reco,
-                        c->d_rf + row0 * frl, frl, d_part};
+                        c->d_rf + row0 * nr::kRFComp, d_part};
     hipError_t e = nr::launch_tmpl_fold(fa, n_slab, c->stream);
     if (e != hipSuccess) return e;
     nr::TmplRecArgs ra{};
     ra.part = d_part;
     ra.n_slab = n_slab;
     ra.n_reco = c->n_reco;
-    ra.n_cols = frl;
+    ra.n_cols = nr::kRFComp;
     ra.dst0 = dst0;
-    ra.n_dst = n_dst;
+    ra.n_dst = nr::kTmplCompCols;
     ra.rec = c->d_trec;
     ra.rl = rl;
     return nr::launch_tmpl_records(ra, c->stream);
 }
 
+// Templates of the single-component form: the records of shared.h, folded once.
+static int build_records(nr_ctx* c) {
+    const size_t n_rec = (size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins;
+    double* d_part = nullptr;
+    nr::ShFold f = sh_fold_args(c, 0, nullptr);
+    f.band = nullptr;
+    int rc;
+    if ((rc = dalloc(&d_part, (size_t)f.n_split * nr::kShCols * c->ldr)) ||
+        (rc = dalloc(&c->d_trec, n_rec * nr::kShRec))) {
+        dfree(&d_part);
+        return rc;
+    }
+    f.part = d_part;
+    const nr::ShRec r = sh_rec_args(c, f, c->d_trec);
+    hipError_t e = nr::launch_sh_fold(&f, 1, c->stream);
+    if (e == hipSuccess) e = nr::launch_sh_rec(&r, 1, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    dfree(&d_part);
+    if (e != hipSuccess) return fail(NR_EHIP, "template fold: %s", hipGetErrorString(e));
+    c->tmpl_ok = c->tmpl_data_ok = true;
+    return 0;
+}
+
 static int build_templates(nr_ctx* c) {
-    const int n_t = c->n_t, n_reco = c->n_reco, rl = tmpl_rl(c);
     int rc;
     hipError_t e = hipSuccess;
+    if (!c->multi) {
+        if (!c->tmpl_ok) return build_records(c);
+        if (c->tmpl_data_ok) return 0;
+        nr::ShRec r{};
+        r.n = c->d_n;
+        r.b = c->d_b;
+        r.rec = c->d_trec;
+        r.n_reco = c->n_reco;
+        e = nr::launch_sh_data(r, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return fail(NR_EHIP, "template data: %s", hipGetErrorString(e));
+        c->tmpl_data_ok = true;
+        return 0;
+    }
+    const int n_t = c->n_t, n_reco = c->n_reco, rl = tmpl_rl(c);
     if (!c->tmpl_ok) {
         const int n_slab = (n_t + nr::kTmplSlabRows - 1) / nr::kTmplSlabRows;
-        const int frl = c->multi ? nr::kRFComp : nr::kRF;
         double* d_part = nullptr;
         c->tmpl_data_ok = false;
-        if ((rc = dalloc(&d_part, (size_t)n_slab * frl * n_reco)) ||
+        if ((rc = dalloc(&d_part, (size_t)n_slab * nr::kRFComp * n_reco)) ||
             (rc = dalloc(&c->d_trec, (size_t)n_reco * rl))) {
             dfree(&d_part);
             return rc;
         }
-        if (!c->multi) {
-            e = fold_block(c, 0, frl, 0, nr::kTmplCols, rl, d_part, n_slab);
-        } else {
-            for (int k = 0; k < c->n_comp && e == hipSuccess; ++k)
-                e = fold_block(c, k, frl, nr::kTmplCompCols * k, nr::kTmplCompCols, rl, d_part,
-                               n_slab);
-        }
+        for (int k = 0; k < c->n_comp && e == hipSuccess; ++k)
+            e = fold_block(c, k, nr::kTmplCompCols * k, rl, d_part, n_slab);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         dfree(&d_part);
         if (e != hipSuccess) return fail(NR_EHIP, "template fold: %s", hipGetErrorString(e));
         c->tmpl_ok = true;
     }
     if (!c->tmpl_data_ok) {
-        if (!c->multi) {
-            nr::TmplDataArgs da{c->d_n, c->d_b, n_reco, c->d_trec};
-            e = nr::launch_tmpl_data(da, c->stream);
-        } else {
-            nr::TmplMultiDataArgs da{c->d_n, c->d_bkg, c->d_mask, n_reco, c->n_comp,
-                                     c->n_bkg, rl, c->d_trec};
-            e = nr::launch_tmpl_mdata(da, c->stream);
-        }
+        nr::TmplMultiDataArgs da{c->d_n, c->d_bkg, c->d_mask, n_reco, c->n_comp,
+                                 c->n_bkg, rl, c->d_trec};
+        e = nr::launch_tmpl_mdata(da, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return fail(NR_EHIP, "template data: %s", hipGetErrorString(e));
         c->tmpl_data_ok = true;
@@ -2871,7 +2836,7 @@ static int build_templates(nr_ctx* c) {
     return 0;
 }
 
-// Reco bins per column slice: enough (point block x slice) work-groups for
+// Multi-component form: reco bins per column slice: enough (point block x slice) work-groups for
 // 16 waves per SIMD (8 with the gradient, whose partial sums are 22 times
 // larger), at least 16 bins and at most 64 slices.  Measured on MI355X at
 // 65536 points x 4096 bins: 4, 8, 16 waves per SIMD run 1.10, 1.02, 0.99 ms.
@@ -2897,9 +2862,10 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
     int rc;
     if ((rc = check_tmpl_form(c))) return rc;
     if ((!c->tmpl_ok || !c->tmpl_data_ok) && (rc = build_templates(c))) return rc;
-    int cp;
-    const size_t ns = (size_t)tmpl_split(c, n_pts, grad, &cp);
-    const size_t na = (size_t)tmpl_nacc(c);
+    int cp, slices = 0;
+    if (!c->multi) nr::sh_slices(n_pts, c->n_reco, &cp, &slices);
+    const size_t ns = (size_t)(c->multi ? tmpl_split(c, n_pts, grad, &cp) : slices);
+    const size_t na = (size_t)(c->multi ? tmpl_nacc(c) : nr::kShAcc);
     if (ns * n_pts > c->t_cap_d) {
         if ((rc = dalloc(&c->d_tdp, ns * n_pts))) return rc;
         c->t_cap_d = ns * n_pts;
@@ -2908,6 +2874,7 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
         if ((rc = dalloc(&c->d_thp, ns * na * n_pts))) return rc;
         c->t_cap_h = ns * na * n_pts;
     }
+    if (!c->multi) return 0;
     const size_t nred = (1 + na) * n_pts;
     if (nred > c->t_cap_r) {
         if ((rc = dalloc(&c->d_tred, nred))) return rc;
@@ -2918,22 +2885,17 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
 
 static int enqueue_tmpl(nr_ctx* c, const double* d_th, int n_pts, double* d_nll,
                         double* d_grad, double* d_mu, hipStream_t s) {
-    int cp;
-    const int ns = tmpl_split(c, n_pts, d_grad != nullptr, &cp);
     double* hpart = d_grad ? c->d_thp : nullptr;
     if (!c->multi) {
-        nr::TmplEvalArgs e{};
-        e.rec = c->d_trec;
-        e.theta = d_th;
-        e.n_reco = c->n_reco;
-        e.n_pts = n_pts;
-        e.cols_per = cp;
-        e.ph = c->ph;
-        e.dpart = c->d_tdp;
-        e.hpart = hpart;
-        e.mu = d_mu;
-        HIPCHK(nr::launch_tmpl_eval(e, ns, s));
-    } else {
+        const nr::ShEval e = sh_eval_args(c, c->d_trec, d_th, n_pts, c->d_tdp, hpart, d_mu);
+        const nr::ShFinal f = sh_final_args(c, e, d_nll, d_grad);
+        HIPCHK(nr::launch_sh_eval(&e, 1, s));
+        HIPCHK(nr::launch_sh_final(&f, 1, s));
+        return 0;
+    }
+    int cp;
+    const int ns = tmpl_split(c, n_pts, d_grad != nullptr, &cp);
+    {
         nr::TmplMultiEvalArgs e{};
         e.rec = c->d_trec;
         e.theta = d_th;
@@ -2952,21 +2914,7 @@ static int enqueue_tmpl(nr_ctx* c, const double* d_th, int n_pts, double* d_nll,
     }
     nr::TmplReduceArgs r{c->d_tdp, hpart, n_pts, ns, tmpl_nacc(c), c->d_tred};
     HIPCHK(nr::launch_tmpl_reduce(r, s));
-    if (!c->multi) {
-        nr::TmplFinalArgs f{};
-        f.red = c->d_tred;
-        f.theta = d_th;
-        f.n_pts = n_pts;
-        f.cdata = c->cdata;
-        for (int i = 0; i < NR_NTHETA; ++i) {
-            f.pull_mean[i] = c->pull_mean[i];
-            f.pull_sigma[i] = c->pull_sigma[i];
-        }
-        f.ph = c->ph;
-        f.nll = d_nll;
-        f.grad = d_grad;
-        HIPCHK(nr::launch_tmpl_final(f, s));
-    } else {
+    {
         nr::TmplMultiFinalArgs f{};
         f.red = c->d_tred;
         f.theta = d_th;
@@ -3018,11 +2966,15 @@ static int tmpl_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     if ((rc = check_theta(theta, n_pts, c->n_theta))) return rc;
     if ((rc = set_device(c))) return rc;
     if (!mu) {
-        // theta in and -2lnL out through pinned host memory, no copies
+        // -2lnL out through pinned host memory the kernels write to; theta,
+        // which every slice reads, copied in once
         if ((rc = ensure_pinned(c, n_pts))) return rc;
         if ((rc = ensure_tmpl(c, n_pts, grad != nullptr))) return rc;
+        if ((rc = ensure_stage(c, n_pts, 0, 0))) return rc;
         std::memcpy(c->h_th, theta, sizeof(double) * n_pts * c->n_theta);
-        if ((rc = enqueue_tmpl(c, c->hd_th, n_pts, c->hd_out, grad ? c->hd_grad : nullptr,
+        HIPCHK(hipMemcpyAsync(c->d_th, c->h_th, sizeof(double) * n_pts * c->n_theta,
+                              hipMemcpyHostToDevice, c->stream));
+        if ((rc = enqueue_tmpl(c, c->d_th, n_pts, c->hd_out, grad ? c->hd_grad : nullptr,
                                nullptr, c->stream)))
             return rc;
         HIPCHK(hipStreamSynchronize(c->stream));

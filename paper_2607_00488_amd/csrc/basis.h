@@ -26,17 +26,20 @@ constexpr int kRF = 16;
 constexpr int kRFComp = 8;
 
 // Coefficients of one group's seven spectra (f: the group's scale).
+// The multiply-adds are explicit, so that every kernel that inlines this rounds
+// alike.
 __device__ inline void basis_coef7(const double* th, const Phys& ph, double f, double c[7]) {
+#pragma clang fp contract(off)
     const double gle = ph.gLe + th[0], gre = ph.gR + th[1];
     const double glm = ph.gLm, grm = ph.gR;
     const double glt = ph.gLm + th[2], grt = ph.gR + th[3];
     const double t = ph.tau_frac, m = 1.0 - ph.tau_frac;
     c[0] = f * gle * gle;
-    c[1] = f * (m * glm * glm + t * glt * glt);
+    c[1] = f * fma(m * glm, glm, t * glt * glt);
     c[2] = f * gre * gre;
-    c[3] = f * (m * grm * grm + t * grt * grt);
+    c[3] = f * fma(m * grm, grm, t * grt * grt);
     c[4] = -f * gle * gre;
-    c[5] = -f * (m * glm * grm + t * glt * grt);
+    c[5] = -f * fma(m * glm, grm, t * glt * grt);
     c[6] = f * ph.cmm * th[4];
 }
 

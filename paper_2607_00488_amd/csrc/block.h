@@ -12,10 +12,10 @@ constexpr int kBlkFinCols = 128;  // columns per likelihood work-group
 // Weights of a list of points from the row factors (basis.h):
 // wt[r][p] = v_r(theta_p) for p < n_pts, 0 for n_pts <= p < n_pad.
 struct PtsWeightArgs {
-    const double* rf;     // [n_comp n_t][kRF], or [..][kRFComp] with rate_index >= 0
+    const double* rf;     // [n_comp n_t][kRFComp]
     int n_t, n_comp;
     const double* theta;  // [n_pts][n_theta]
-    int n_theta, rate_index;  // theta index of component 0's rate; -1: none
+    int n_theta, rate_index;  // theta index of component 0's rate
     int n_pts, n_pad, ldw;
     Phys ph;
     double* wt;           // [n_comp n_t][ldw]

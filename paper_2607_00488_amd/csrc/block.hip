@@ -21,16 +21,15 @@ constexpr int kStageRows = 4 * kStageQuads;  // 32 rows
 
 // --------------------------------------------------------------- weights
 // V^T[l][p] = sum_b F_lb c_b(theta_p), itself a product with a reduction of
-// 16 (or 8): four (two) FP64 matrix instructions per 16 rows x 16 points,
-// rows on the row operand, so that a lane's values of F are 32 contiguous
+// 8: two FP64 matrix instructions per 16 rows x 16 points, rows on the row operand, so that a lane's values of F are 32 contiguous
 // bytes and a row's 16 points leave as one 128-byte run.  Bound by writing
 // V^T: 1024 points x 16384 rows took 11 us per 64 points before, one thread
 // per point with the basis broadcast from LDS.
 constexpr int kWtPts = 64;   // points per work-group
 constexpr int kWtRows = 64;  // rows per work-group, 16 per wave
 
-template <int RL>  // row length of the factors
 __global__ __launch_bounds__(kThreads) void k_pts_weights(PtsWeightArgs a) {
+    constexpr int RL = kRFComp;  // row length of the factors
     __shared__ double cs[kWtPts][RL + 1];
     constexpr int KS = RL / 4;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -43,14 +42,9 @@ __global__ __launch_bounds__(kThreads) void k_pts_weights(PtsWeightArgs a) {
         for (int b = 0; b < RL; ++b) v[b] = 0.0;
         if (p < a.n_pts) {
             const double* th = a.theta + (size_t)p * a.n_theta;
-            if (RL == kRF) {
-                basis_coef(th, a.ph, v);
-                v[kNBasis] = 1.0;
-            } else {
-                const double r = th[a.rate_index + c];
-                basis_coef7(th, a.ph, r, v);
-                v[kCompBasis] = r;
-            }
+            const double r = th[a.rate_index + c];
+            basis_coef7(th, a.ph, r, v);
+            v[kCompBasis] = r;
         }
         for (int b = 0; b < RL; ++b) cs[tid][b] = v[b];
     }
@@ -322,10 +316,7 @@ hipError_t launch_pts_weights(const PtsWeightArgs& a, hipStream_t s) {
     if (a.n_pts <= 0 || a.n_pad < a.n_pts || a.n_pad > a.ldw || a.n_pad % 4)
         return hipErrorInvalidValue;
     const dim3 grid((a.n_t + kWtRows - 1) / kWtRows, (a.n_pad + kWtPts - 1) / kWtPts, a.n_comp);
-    if (a.rate_index < 0)
-        hipLaunchKernelGGL(k_pts_weights<kRF>, grid, dim3(kThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_pts_weights<kRFComp>, grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL(k_pts_weights, grid, dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,89 @@
+// Internal declarations of the basis form of the evaluation.
+//
+// A point's row factors are v_l = sum_b c_b(theta) F_lb (basis.h), so the fold
+// of any number of points is a product of three matrices,
+//   mu = C (F^T R) + f_bkg b,   C [points][15], F [rows][15], R [rows][bins],
+// and taking F^T R first costs one pass over R per call, whatever the number of
+// points: 15 multiply-adds per response entry instead of one (two with the
+// gradient) per entry and point.  The gradient needs nothing more of R:
+//   d(-2lnL)/d theta_i = sum_b dc_b/d theta_i h_b, h_b = sum_j a_j (F^T R)_bj.
+// Four launches: fold, records (split sums and data, one record per bin),
+// points (mu, deviance, h), final.
+#pragma once
+#include "basis.h"
+
+namespace nr {
+
+constexpr int kShCols = kNBasis + 1;  // folded columns: 14 spectra, constant rows
+constexpr int kShTile = 256;          // response columns per fold work-group
+constexpr int kShStage = 32;          // rows per stage of the fold
+constexpr int kShRec = 18;            // record: 15 columns, b_j, n_j, 1 / n_j
+constexpr int kShBins = 16;           // bins per tile of the points kernel
+constexpr int kShAcc = 16;            // contractions h per point (the last: b_j)
+constexpr int kShGroup = 16;          // analyses per grouped launch
+
+struct ShFold {
+    const float* R;    // [n_t][ldr]
+    const double* rf;  // [n_t][kRF]
+    double* part;      // [n_split][kShCols][ldr]
+    // per column tile the rows [lo, hi) that hold its non-zero responses (lo a
+    // multiple of four), or null (every row)
+    const int* band;
+    int ldr, n_t, n_ct, n_split, rows_per;
+};
+
+struct ShRec {
+    const double* part;
+    const double* n;  // [n_reco]
+    const double* b;  // [n_reco]
+    double* rec;      // [n_reco rounded up to kShBins][kShRec]
+    // points to copy to device memory beside the sums, or null
+    const double* th_src;
+    double* th_dst;
+    int n_th;         // values
+    int n_split, ldr, n_reco;
+};
+
+struct ShEval {
+    const double* rec;
+    const double* theta;  // [n_pts][7]
+    double* dpart;        // [n_slice][n_pts] deviance sums
+    double* hpart;        // [n_slice][kShAcc][n_pts], or null (no gradient)
+    double* mu;           // [n_pts][n_reco], or null
+    Phys ph;
+    int n_pts, n_reco, tiles, n_slice;  // tiles of kShBins bins per slice
+};
+
+struct ShFinal {
+    const double* dpart;
+    const double* hpart;
+    const double* theta;
+    double* nll;
+    double* grad;  // [n_pts][7] or null
+    double cdata;
+    double pull_mean[kNTheta];
+    double pull_sigma[kNTheta];
+    Phys ph;
+    int n_pts, n_slice;
+};
+
+// N analyses of one launch, by value: first[d] is the first work-group of d.
+template <class P, int N>
+struct ShGroup {
+    int n;
+    int first[N + 1];
+    P p[N];
+};
+
+// Each takes n <= kShGroup analyses (all with or all without gradient / mu).
+hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s);
+hipError_t launch_sh_rec(const ShRec* p, int n, hipStream_t s);
+hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s);
+hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s);
+// New data beside folded columns that stay.
+hipError_t launch_sh_data(const ShRec& p, hipStream_t s);
+
+// Column slices of an evaluation of n_pts points over n_reco bins.
+void sh_slices(int n_pts, int n_reco, int* tiles, int* n_slice);
+
+}  // namespace nr

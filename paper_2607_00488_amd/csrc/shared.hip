@@ -1,0 +1,544 @@
+// Basis form of the evaluation on gfx950 (shared.h): the recoil spectra of
+// Eq. (fT) as folded columns shared by every point of a call, the spectra of
+// Eqs. (fNp_reweight), (mu_total) and the Poisson -2lnL of Eq. (logL) with its
+// gradient from them, FP64 throughout.
+#include "shared.h"
+#include "lntab.h"
+
+#include <algorithm>
+#include <cmath>
+
+// Every multiply-add of this file is written out: the kernels' size classes
+// round alike, and a point's result does not depend on the class it falls in.
+#pragma clang fp contract(off)
+
+namespace nr {
+
+namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v2d __attribute__((ext_vector_type(2)));
+
+constexpr int kThreads = 256;
+
+// Pointers that come out of a struct array are global memory; said so, the
+// compiler emits global instead of flat accesses.
+template <class T>
+__device__ inline const __attribute__((address_space(1))) T* gm(const T* p) {
+    return (const __attribute__((address_space(1))) T*)p;
+}
+template <class T>
+__device__ inline __attribute__((address_space(1))) T* gm(T* p) {
+    return (__attribute__((address_space(1))) T*)p;
+}
+
+// The analysis a work-group belongs to, and its index within it.
+template <class P, int N>
+__device__ inline int sh_find(const ShGroup<P, N>& g, int* wg) {
+    int d = 0;
+    if constexpr (N > 1) {
+        int hi = g.n;
+        while (hi - d > 1) {
+            const int m = (d + hi) >> 1;
+            if ((int)blockIdx.x >= g.first[m]) d = m;
+            else hi = m;
+        }
+    }
+    *wg = (int)blockIdx.x - g.first[d];
+    return d;
+}
+
+// ------------------------------------------------------------------ fold
+// part[s][b][j] = sum over the rows l of split s of F_lb R_lj on the FP64
+// matrix cores, b the row operand (15 of 16 used), the response columns the
+// column operand.  Wave w owns 64 columns as four sets of 16 interleaved ones:
+// lane (li, lk) loads the float4 of columns 4 li .. 4 li + 3 of row 4 q + lk,
+// the column operand of four matrix instructions with k = lk, and F_{4q+lk, li}
+// the same way (a row of F is 128 contiguous bytes, shared by the four waves
+// through the cache), so nothing passes through LDS and no wave waits for
+// another.  The next stage of 32 rows (8 KB of R per wave) is loaded
+// unconditionally before the current one's arithmetic.
+//
+// Bound by the stream over R, with the matrix cores close behind (15 multiply-
+// adds per entry: 32 us of arithmetic at 16384 x 4096, measured with R in
+// cache).  16384 x 4096: 47 us, 5.7 TB/s, with one work-group per compute unit,
+// 53 us with 512 work-groups and 61 us with 1024 (more partial sums); stages of
+// 16 rows 56 us; masks on the prefetched factors, which made every stage wait
+// for the next one's loads, 64 us.
+template <int N>
+__global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
+    int t;
+    const ShFold& a = g.p[sh_find(g, &t)];
+    constexpr int ST = kShStage / 4;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int li = lane & 15, lk = lane >> 4;
+    const int ct = t % a.n_ct, sp = t / a.n_ct;
+    const int ldr = a.ldr, ld4 = ldr >> 2;
+    const int c4 = ct * (kShTile / 4) + wave * 16 + li;
+    int kb = sp * a.rows_per, ke = min(a.n_t, kb + a.rows_per);
+    if (a.band) {  // rows outside hold exact zeros in this tile's columns
+        kb = max(kb, gm(a.band)[2 * ct]);
+        ke = min(ke, gm(a.band)[2 * ct + 1]);
+    }
+    const auto* R = (const __attribute__((address_space(1))) char*)a.R;
+    const auto* F = (const __attribute__((address_space(1))) char*)a.rf;
+    // byte offsets of a lane within a stage (n_reco < 2^27 columns)
+    const unsigned roff = (unsigned)lk * ldr * 4u + 16u * min(c4, ld4 - 1);
+    const unsigned foff = (lk * 16 + li) * 8u;
+    const size_t rq = (size_t)ldr * 16;  // bytes of four rows
+    v4d acc[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = (v4d){0.0, 0.0, 0.0, 0.0};
+    struct Stage {
+        v4f x[ST];
+        double f[ST];
+    };
+    auto load = [&](int k, Stage& s) {
+        const auto* rb = R + (size_t)k * ldr * 4;
+        const auto* fb = F + (size_t)k * (kRF * 8);
+#pragma unroll
+        for (int q = 0; q < ST; ++q) {
+            s.f[q] = *(const __attribute__((address_space(1))) double*)(fb + q * (kRF * 32) + foff);
+            s.x[q] = *(const __attribute__((address_space(1))) v4f*)(rb + q * rq + roff);
+        }
+    };
+    auto quad = [&](double f, v4f x) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(f, (double)x[e], acc[e], 0, 0, 0);
+    };
+    auto compute = [&](const Stage& s) {
+#pragma unroll
+        for (int q = 0; q < ST; ++q) quad(s.f[q], s.x[q]);
+    };
+    const int nst = kb < ke ? (ke - kb) / kShStage : 0;  // whole stages
+    if (nst > 0) {
+        Stage s0, s1;
+        load(kb, s0);
+        int i = 0;
+        for (; i + 1 < nst; i += 2) {
+            load(kb + (i + 1) * kShStage, s1);
+            compute(s0);
+            load(kb + min(i + 2, nst - 1) * kShStage, s0);
+            compute(s1);
+        }
+        if (i < nst) compute(s0);
+    }
+    // the last rows, four at a time; past the end a zero factor on the last row
+    for (int k = kb + nst * kShStage; k < ke; k += 4) {
+        const int row = k + lk, rc = min(row, a.n_t - 1);
+        const double f = *(const __attribute__((address_space(1))) double*)(F + ((size_t)rc * kRF + li) * 8);
+        const v4f x = *(const __attribute__((address_space(1))) v4f*)(R + (size_t)rc * ldr * 4 + 16u * min(c4, ld4 - 1));
+        quad(row < ke ? f : 0.0, x);
+    }
+    if (c4 >= ld4) return;
+    auto* out = gm(a.part) + (size_t)sp * kShCols * ldr + 4 * (size_t)c4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int b = lk + 4 * r;  // output (i, j): lane j + 16 (i % 4), register i / 4
+        if (b >= kShCols) continue;
+        auto* o = (__attribute__((address_space(1))) v2d*)(out + (size_t)b * ldr);
+        o[0] = (v2d){acc[0][r], acc[1][r]};
+        o[1] = (v2d){acc[2][r], acc[3][r]};
+    }
+}
+
+// --------------------------------------------------------------- records
+// One work-group per 16 bins: the split sums in split order, one (column, bin)
+// per thread, and the bins' data; records leave as contiguous rows.  Bins past
+// the last one (the tail of the last tile) get mu = 1, n = 1: a zero term.
+template <int N>
+__global__ __launch_bounds__(kThreads) void k_sh_rec(ShGroup<ShRec, N> g) {
+    __shared__ double t[kShBins][kShRec];
+    int wg;
+    const int d = sh_find(g, &wg);
+    const ShRec& a = g.p[d];
+    const int tid = threadIdx.x, b = tid >> 4, jl = tid & 15;
+    const int j0 = wg * kShBins, j = j0 + jl;
+    if (a.th_src) {
+        const int step = (g.first[d + 1] - g.first[d]) * kThreads;
+        for (int i = wg * kThreads + tid; i < a.n_th; i += step) gm(a.th_dst)[i] = gm(a.th_src)[i];
+    }
+    const bool ok = j < a.n_reco;
+    if (b < kShCols) {
+        double s = 0.0;
+        if (ok) {
+            const auto* x = gm(a.part) + (size_t)b * a.ldr + j;
+            const size_t st = (size_t)kShCols * a.ldr;
+#pragma unroll 8
+            for (int q = 0; q < a.n_split; ++q) s += x[q * st];
+        } else if (b == kNBasis) {
+            s = 1.0;
+        }
+        t[jl][b] = s;
+    } else {
+        const double n = ok ? gm(a.n)[j] : 1.0;
+        t[jl][kShCols] = ok ? gm(a.b)[j] : 0.0;
+        t[jl][kShCols + 1] = n;
+        t[jl][kShCols + 2] = n > 0.0 ? 1.0 / n : 1.0;
+    }
+    __syncthreads();
+    auto* out = gm(a.rec) + (size_t)j0 * kShRec;
+    const double* src = &t[0][0];
+    for (int i = tid; i < kShBins * kShRec; i += kThreads) out[i] = src[i];
+}
+
+__global__ __launch_bounds__(kThreads) void k_sh_data(ShRec a) {
+    const int j = blockIdx.x * kThreads + threadIdx.x;
+    if (j >= a.n_reco) return;
+    double* r = a.rec + (size_t)j * kShRec;
+    const double n = a.n[j];
+    r[kShCols] = a.b[j];
+    r[kShCols + 1] = n;
+    r[kShCols + 2] = n > 0.0 ? 1.0 / n : 1.0;
+}
+
+// ---------------------------------------------------------------- points
+// One wave: NB blocks of 16 points over one slice of bins, 16 bins at a time.
+// mu is a product of the bins' records with the points' coefficients (16
+// columns: the 14 spectra, the constant rows, b_j with f_bkg) on the FP64
+// matrix cores, bins the row operand in an order that leaves a lane with the
+// four consecutive bins 4 lk .. 4 lk + 3 of one point.  In that layout a_j is
+// already the column operand of the gradient's contraction h = sum_j a_j G_j,
+// a second product with the same records.  The vector units are left with the
+// Poisson term: n ln(n / mu) as -n ln(mu (1 / n)), the logarithm of the ratio
+// (near a fit's minimum the two logarithms agree to many digits, and their
+// separate roundings would leave noise that stalls a line search).
+//
+// Bound by those vector instructions (about 25 per point and bin, 40 with the
+// gradient).
+__device__ __constant__ const LnTable g_ln = make_ln_table();
+
+// The terms that the fast path leaves out: an empty or underflowed spectrum, an
+// overflowed one, NaN.  An empty bin's term is mu_j, its derivative 2.
+__device__ __attribute__((noinline)) double2 sh_slow_term(double mu, double n) {
+    double d = mu, a = 2.0;
+    if (n > 0.0) {
+        d = mu > 0.0 ? (isinf(mu) ? mu : mu - n + n * log(n / mu)) : INFINITY;
+        a = 2.0 * (1.0 - n / mu);
+    }
+    return make_double2(d, a);
+}
+
+template <bool GRAD, bool MU, int NB, int N>
+__global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
+    __shared__ LnTable lt;
+    int wg;
+    const ShEval& a = g.p[sh_find(g, &wg)];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    static_assert(kThreads == kLnTab, "one table entry per thread");
+    lt.e[tid] = g_ln.e[tid];
+    __syncthreads();
+    const int n_pts = a.n_pts, n_grp = (n_pts + 16 * NB - 1) / (16 * NB);
+    const int w = wg * 4 + (tid >> 6), sl = w / n_grp, p0 = (w - sl * n_grp) * 16 * NB;
+    if (sl >= a.n_slice) return;
+    // this lane's four of each point's coefficients (k = 4 lk + s)
+    double c[NB][4];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        const int p = min(p0 + 16 * x + li, n_pts - 1);
+        double th[kNTheta], v[16];
+#pragma unroll
+        for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
+        basis_coef(th, a.ph, v);
+        v[kNBasis] = 1.0;
+        v[kNBasis + 1] = th[6];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            c[x][s] = lk == 0 ? v[s] : lk == 1 ? v[4 + s] : lk == 2 ? v[8 + s] : v[12 + s];
+    }
+    const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
+    const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
+    const auto* rec = gm(a.rec);
+    // row operand i holds bin 4 (i % 4) + i / 4: output register r of lane
+    // group lk is then bin 4 lk + r
+    const int fb = (4 * (li & 3) + (li >> 2)) * kShRec + 4 * lk;
+    struct Tile {
+        v2d f0, f1;   // record columns 4 lk .. 4 lk + 3 of this lane's row bin
+        v2d n[4];     // n, 1 / n of bins 4 lk + r
+        double gr[4]; // column li of bins 4 lk + r
+    };
+    auto load = [&](int t, Tile& q) {
+        const auto* r = rec + (size_t)t * (kShBins * kShRec);
+        const auto* f = (const __attribute__((address_space(1))) v2d*)(r + fb);
+        q.f0 = f[0];
+        q.f1 = f[1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const auto* b = r + (4 * lk + e) * kShRec;
+            q.n[e] = *(const __attribute__((address_space(1))) v2d*)(b + 16);
+            if (GRAD) q.gr[e] = b[li];
+        }
+    };
+    double dsum[NB];
+    v4d h[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        dsum[x] = 0.0;
+        h[x] = (v4d){0.0, 0.0, 0.0, 0.0};
+    }
+    const bool mu16 = MU && a.n_reco % 2 == 0 && ((size_t)a.mu & 15) == 0;
+    Tile cur, nxt;
+    load(t0, cur);
+    for (int t = t0; t < t1; ++t) {
+        load(min(t + 1, t1 - 1), nxt);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            v4d mu = (v4d){0.0, 0.0, 0.0, 0.0};
+            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f0.x, c[x][0], mu, 0, 0, 0);
+            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f0.y, c[x][1], mu, 0, 0, 0);
+            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f1.x, c[x][2], mu, 0, 0, 0);
+            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f1.y, c[x][3], mu, 0, 0, 0);
+            const int p = p0 + 16 * x + li, j = t * kShBins + 4 * lk;
+            if (MU && p < n_pts) {
+                auto* o = gm(a.mu) + (size_t)p * a.n_reco + j;
+                if (mu16 && j + 3 < a.n_reco) {
+                    ((__attribute__((address_space(1))) v2d*)o)[0] = (v2d){mu[0], mu[1]};
+                    ((__attribute__((address_space(1))) v2d*)o)[1] = (v2d){mu[2], mu[3]};
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (j + r < a.n_reco) o[r] = mu[r];
+                }
+            }
+            double dv[4], av[4];
+            bool fast = true;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double n = cur.n[r].x, q = mu[r] * cur.n[r].y;
+                // both positive and normal
+                fast = fast && __builtin_amdgcn_class(q, 0x100) && __builtin_amdgcn_class(mu[r], 0x100);
+                dv[r] = fma(-n, ln_tab(q, lt.e), mu[r] - n);
+                if (GRAD) {
+                    double y = __builtin_amdgcn_rcp(mu[r]);
+                    y = fma(y, fma(-mu[r], y, 1.0), y);
+                    y = fma(y, fma(-mu[r], y, 1.0), y);
+                    double u = n * y;
+                    u = fma(fma(-mu[r], u, n), y, u);
+                    av[r] = 2.0 * (1.0 - u);
+                }
+            }
+            if (!fast) {
+#pragma unroll 1
+                for (int r = 0; r < 4; ++r) {
+                    const double m = r == 0 ? mu[0] : r == 1 ? mu[1] : r == 2 ? mu[2] : mu[3];
+                    const double n = r == 0 ? cur.n[0].x : r == 1 ? cur.n[1].x : r == 2 ? cur.n[2].x : cur.n[3].x;
+                    double2 s = sh_slow_term(m, n);
+                    if (j + r >= a.n_reco) s = make_double2(0.0, 0.0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (e == r) {
+                            dv[e] = s.x;
+                            if (GRAD) av[e] = s.y;
+                        }
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                dsum[x] += dv[r];
+                if (GRAD) h[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.gr[r], av[r], h[x], 0, 0, 0);
+            }
+        }
+        cur = nxt;
+    }
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        const int p = p0 + 16 * x + li;
+        double s = dsum[x];
+        s += __shfl_xor(s, 16, 64);
+        s += __shfl_xor(s, 32, 64);
+        if (p >= n_pts) continue;
+        if (lk == 0) gm(a.dpart)[(size_t)sl * n_pts + p] = s;
+        if (GRAD)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                gm(a.hpart)[((size_t)sl * kShAcc + lk + 4 * r) * n_pts + p] = h[x][r];
+    }
+}
+
+// ----------------------------------------------------------------- final
+// -2lnL = 2 (sum of the slices' deviances + C_data) + pulls.
+__device__ inline double sh_nll(const ShFinal& a, double dev, const double th[kNTheta]) {
+    double pulls = 0.0;
+#pragma unroll
+    for (int i = 0; i < kNTheta; ++i)
+        if (a.pull_sigma[i] > 0.0) {
+            const double z = (th[i] - a.pull_mean[i]) / a.pull_sigma[i];
+            pulls += z * z;
+        }
+    return 2.0 * dev + 2.0 * a.cdata + pulls;
+}
+
+// One point per thread, the slices in order.
+template <int N>
+__global__ __launch_bounds__(64) void k_sh_final(ShGroup<ShFinal, N> g) {
+    int wg;
+    const ShFinal& a = g.p[sh_find(g, &wg)];
+    const int p = wg * 64 + threadIdx.x;
+    if (p >= a.n_pts) return;
+    double d = 0.0;
+#pragma unroll 8
+    for (int q = 0; q < a.n_slice; ++q) d += gm(a.dpart)[(size_t)q * a.n_pts + p];
+    double th[kNTheta];
+#pragma unroll
+    for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
+    gm(a.nll)[p] = sh_nll(a, d, th);
+}
+
+// 16 points per work-group, one (contraction, point) per thread; the constant
+// column's contraction is not needed, its threads sum the deviances.
+template <int N>
+__global__ __launch_bounds__(kThreads) void k_sh_final_grad(ShGroup<ShFinal, N> g) {
+    __shared__ double hs[16][kShAcc + 1];
+    int wg;
+    const ShFinal& a = g.p[sh_find(g, &wg)];
+    const int v = threadIdx.x >> 4, pl = threadIdx.x & 15, p = wg * 16 + pl;
+    double s = 0.0;
+    if (p < a.n_pts) {
+        const bool dev = v == kNBasis;
+        const auto* x = dev ? gm(a.dpart) + p : gm(a.hpart) + (size_t)v * a.n_pts + p;
+        const size_t st = (size_t)(dev ? 1 : kShAcc) * a.n_pts;
+#pragma unroll 8
+        for (int q = 0; q < a.n_slice; ++q) s += x[q * st];
+    }
+    hs[pl][v] = s;
+    __syncthreads();
+    if (v != 0 || p >= a.n_pts) return;
+    double th[kNTheta], gr[kNTheta], hh[kNBasis];
+#pragma unroll
+    for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
+#pragma unroll
+    for (int b = 0; b < kNBasis; ++b) hh[b] = hs[pl][b];
+    basis_grad(th, a.ph, hh, gr);
+    gr[6] = hs[pl][kNBasis + 1];
+    gm(a.nll)[p] = sh_nll(a, hs[pl][kNBasis], th);
+#pragma unroll
+    for (int i = 0; i < kNTheta; ++i) {
+        double q = gr[i];
+        if (a.pull_sigma[i] > 0.0)
+            q += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
+        gm(a.grad)[(size_t)p * kNTheta + i] = q;
+    }
+}
+
+// One analysis travels in a struct of its own size, several in one of
+// kShGroup (at most 4 KB of kernel arguments).
+template <class P, int N, class Wgs>
+ShGroup<P, N> make_group(const P* p, int n, Wgs wgs) {
+    static_assert(sizeof(ShGroup<P, N>) <= 4096, "kernel arguments");
+    ShGroup<P, N> g;
+    g.n = n;
+    g.first[0] = 0;
+    for (int d = 0; d < n; ++d) {
+        g.p[d] = p[d];
+        g.first[d + 1] = g.first[d] + wgs(p[d]);
+    }
+    return g;
+}
+
+#define SH_LAUNCH(KERNEL, P, THREADS, WGS)                                              \
+    do {                                                                                \
+        if (n == 1) {                                                                   \
+            const ShGroup<P, 1> g_ = make_group<P, 1>(p, 1, WGS);                       \
+            hipLaunchKernelGGL(KERNEL(1), dim3(g_.first[1]), dim3(THREADS), 0, s, g_);  \
+        } else {                                                                        \
+            const ShGroup<P, kShGroup> g_ = make_group<P, kShGroup>(p, n, WGS);         \
+            hipLaunchKernelGGL(KERNEL(kShGroup), dim3(g_.first[n]), dim3(THREADS), 0, s, g_); \
+        }                                                                               \
+    } while (0)
+
+template <bool GRAD, bool MU, int NB>
+void launch_eval(const ShEval* p, int n, hipStream_t s) {
+    const auto wgs = [](const ShEval& e) {
+        const int grp = (e.n_pts + 16 * NB - 1) / (16 * NB);
+        return (int)(((long)grp * e.n_slice + 3) / 4);
+    };
+#define SH_K(M) (k_sh_eval<GRAD, MU, NB, M>)
+    SH_LAUNCH(SH_K, ShEval, kThreads, wgs);
+#undef SH_K
+}
+
+template <bool GRAD, bool MU>
+void launch_eval_nb(const ShEval* p, int n, hipStream_t s) {
+    long waves = 0;  // of one block of 16 points each
+    for (int d = 0; d < n; ++d) waves += (long)((p[d].n_pts + 15) / 16) * p[d].n_slice;
+    // more blocks per wave share the record loads, but only once the chip's
+    // 1024 SIMDs stay full
+    if (waves >= 16384) launch_eval<GRAD, MU, 4>(p, n, s);
+    else if (waves >= 8192) launch_eval<GRAD, MU, 2>(p, n, s);
+    else launch_eval<GRAD, MU, 1>(p, n, s);
+}
+
+}  // namespace
+
+hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s) {
+    if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
+    for (int d = 0; d < n; ++d)
+        if (p[d].ldr % 4 || p[d].rows_per <= 0 || p[d].rows_per % kShStage || p[d].ldr >= (1 << 27) ||
+            p[d].n_ct != (p[d].ldr + kShTile - 1) / kShTile || p[d].n_split < 1 ||
+            (long)p[d].n_split * p[d].rows_per < p[d].n_t)
+            return hipErrorInvalidValue;
+#define SH_K(M) (k_sh_fold<M>)
+    SH_LAUNCH(SH_K, ShFold, kThreads, [](const ShFold& f) { return f.n_ct * f.n_split; });
+#undef SH_K
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_rec(const ShRec* p, int n, hipStream_t s) {
+    if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
+#define SH_K(M) (k_sh_rec<M>)
+    SH_LAUNCH(SH_K, ShRec, kThreads, [](const ShRec& r) { return (r.n_reco + kShBins - 1) / kShBins; });
+#undef SH_K
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_data(const ShRec& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_sh_data, dim3((p.n_reco + kThreads - 1) / kThreads), dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s) {
+    if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
+    for (int d = 0; d < n; ++d)
+        if (p[d].n_pts < 1 || !p[d].hpart != !p[0].hpart || !p[d].mu != !p[0].mu ||
+            (p[d].hpart && p[d].mu) ||
+            (long)p[d].tiles * p[d].n_slice * kShBins < p[d].n_reco)
+            return hipErrorInvalidValue;
+    if (p[0].hpart) launch_eval_nb<true, false>(p, n, s);
+    else if (p[0].mu) launch_eval_nb<false, true>(p, n, s);
+    else launch_eval_nb<false, false>(p, n, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s) {
+    if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
+    for (int d = 0; d < n; ++d)
+        if (!p[d].grad != !p[0].grad || (p[d].grad && !p[d].hpart)) return hipErrorInvalidValue;
+    if (p[0].grad) {
+#define SH_K(M) (k_sh_final_grad<M>)
+        SH_LAUNCH(SH_K, ShFinal, kThreads, [](const ShFinal& f) { return (f.n_pts + 15) / 16; });
+#undef SH_K
+    } else {
+#define SH_K(M) (k_sh_final<M>)
+        SH_LAUNCH(SH_K, ShFinal, 64, [](const ShFinal& f) { return (f.n_pts + 63) / 64; });
+#undef SH_K
+    }
+    return hipGetLastError();
+}
+
+// Slices of 64 bins up to 4096 points (fixed by the response's shape, so that
+// a point's result does not depend on its list); beyond, as few as leave about
+// 8192 waves of 64 points, since every slice writes its sums for every point.
+void sh_slices(int n_pts, int n_reco, int* tiles, int* n_slice) {
+    const int n_tile = (n_reco + kShBins - 1) / kShBins;
+    int t = 4;
+    if (n_pts > 4096) {
+        const int ns = std::max(1, (8192 + (n_pts + 63) / 64 - 1) / ((n_pts + 63) / 64));
+        t = std::max(t, (n_tile + ns - 1) / ns);
+    }
+    *tiles = t;
+    *n_slice = (n_tile + t - 1) / t;
+}
+
+}  // namespace nr
