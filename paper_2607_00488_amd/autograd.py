@@ -1,8 +1,7 @@
 """-2lnL as a differentiable torch function, and a batched L-BFGS fit.
 
 The forward and the backward both come from the library's kernels: one call
-computes -2lnL and its gradient (the adjoint of the fold); the gradient is
-kept for ``backward``.  Nothing here computes any part of the likelihood.
+computes -2lnL and its gradient; the gradient is kept for ``backward``.  Nothing here computes any part of the likelihood.
 """
 from __future__ import annotations
 
@@ -26,34 +25,22 @@ def _form(form) -> str:
     return form
 
 
-def _buffers(context: Context, P: int, dev, form: str):
-    """Fixed input/output buffers per (context, P, form): the library then
-    replays one cached graph for every call of a fit."""
-    cache = context.__dict__.setdefault("_autograd_bufs", {})
-    key = (P, str(dev), form)
-    b = cache.get(key)
-    if b is None:
-        D = context.n_theta
-        b = (torch.empty(P, D, dtype=torch.float64, device=dev),
-             torch.empty(P, dtype=torch.float64, device=dev),
-             torch.empty(P, D, dtype=torch.float64, device=dev))
-        cache[key] = b
-    return b
-
-
 class NllFunction(torch.autograd.Function):
     """nll[p] = -2lnL(theta[p]) for theta [P, n_theta] float64 on the
     context's device (n_theta = 7, or 5 + K + B for a multi-component
-    context, which only the template form takes).  ``form``: "batched" (the GEMM form, many points at once; also
-    True), "plain" (P single-point evaluations; also False) or "templates"
-    (the folded-template form)."""
+    context, which only the template form takes).  ``form``: "batched" (many
+    points at once, tuned; also True), "plain" (also False) or "templates" (the
+    columns folded beforehand)."""
 
     @staticmethod
     def forward(fctx, theta: torch.Tensor, context: Context, form="batched"):
         form = _form(form)
-        P = theta.shape[0]
-        th, nll, grad = _buffers(context, P, theta.device, form)
-        th.copy_(theta.detach())
+        # the library reads theta where it is; a copy only of other types,
+        # strides or broadcast rows
+        P, D = theta.shape[0], context.n_theta
+        th = theta.detach().to(torch.float64).expand(P, D).contiguous()
+        nll = torch.empty(P, dtype=torch.float64, device=th.device)
+        grad = torch.empty(P, D, dtype=torch.float64, device=th.device)
         stream = torch.cuda.current_stream(th.device)
         if form == "batched":
             eval_nll_multi_dev([context], [th], [nll], [grad], stream=stream)
@@ -61,9 +48,8 @@ class NllFunction(torch.autograd.Function):
             context.eval_nll_templates_dev(th, nll, grad, stream=stream)
         else:
             context.eval_nll_dev(th, nll, grad, stream=stream)
-        out, g = nll.clone(), grad.clone()
-        fctx.save_for_backward(g)
-        return out
+        fctx.save_for_backward(grad)
+        return nll
 
     @staticmethod
     def backward(fctx, g):
