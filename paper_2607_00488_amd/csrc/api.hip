@@ -1,7 +1,6 @@
 // C-ABI context: validation, theta-independent setup (Sec. III.A last
 // paragraph and Sec. III.B: the SM reference and the response are built once
 // and kept resident), stream-ordered launches, HIP-graph replay, errors.
-#include "batched.h"
 #include "block.h"
 #include "ess.h"
 #include "mlp.h"
@@ -246,10 +245,9 @@ struct nr_ctx {
     size_t b_cap_mu = 0;
     // template form: folded basis templates and the data, per reco bin
     bool tmpl_ok = false, tmpl_data_ok = false;
-    double* d_trec = nullptr;  // [n_reco][kShRec], or the multi-component records
+    double* d_trec = nullptr;  // records (shared.h)
     double *d_tdp = nullptr, *d_thp = nullptr;  // evaluation partials
-    double* d_tred = nullptr;                   // [1 + kTmplCols][points] slice sums
-    size_t t_cap_d = 0, t_cap_h = 0, t_cap_r = 0;
+    size_t t_cap_d = 0, t_cap_h = 0;
 };
 
 namespace {
@@ -808,7 +806,7 @@ size_t carve_sh(const nr_ctx* c, double* base, int pts, bool grad, int cfg, ShWo
     };
     int ns, rp, tiles, slices;
     sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &ns, &rp);
-    nr::sh_slices(pts, c->n_reco, &tiles, &slices);
+    nr::sh_slices(pts, c->n_reco, false, &tiles, &slices);
     w->part = take((size_t)ns * nr::kShCols * c->ldr);
     w->rec = take((size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins * nr::kShRec);
     w->dpart = take((size_t)slices * pts);
@@ -886,7 +884,12 @@ nr::ShEval sh_eval_args(const nr_ctx* c, const double* rec, const double* th, in
     e.ph = c->ph;
     e.n_pts = n_pts;
     e.n_reco = c->n_reco;
-    nr::sh_slices(n_pts, c->n_reco, &e.tiles, &e.n_slice);
+    if (c->multi) {
+        e.K = c->n_comp;
+        e.B = c->n_bkg;
+        e.n_theta = c->n_theta;
+    }
+    nr::sh_slices(n_pts, c->n_reco, c->multi, &e.tiles, &e.n_slice);
     return e;
 }
 
@@ -1460,7 +1463,7 @@ void nr_destroy(nr_ctx* c) {
     dfree(&c->d_mu); dfree(&c->d_w); dfree(&c->d_thsm);
     dfree(&c->d_bth); dfree(&c->d_bnll); dfree(&c->d_bgrad); dfree(&c->d_bmu);
     dfree(&c->d_sh); dfree(&c->d_shb);
-    dfree(&c->d_trec); dfree(&c->d_tdp); dfree(&c->d_thp); dfree(&c->d_tred);
+    dfree(&c->d_trec); dfree(&c->d_tdp); dfree(&c->d_thp);
     dfree(&c->d_v[0]); dfree(&c->d_v[1]);
     dfree(&c->d_rowband); dfree(&c->d_tileband);
     dfree(&c->d_blkband); dfree(&c->d_blk);
@@ -2743,31 +2746,6 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
 // only the data slots.  In the multi-component form each component's row
 // block is folded with its own factors.
 
-// Multi-component form: record length and gradient contractions per point.
-static int tmpl_rl(const nr_ctx* c) {
-    return (nr::kTmplCompCols * c->n_comp + c->n_bkg + 2 + 1) / 2 * 2;
-}
-static int tmpl_nacc(const nr_ctx* c) { return nr::kCompBasis + c->n_comp + c->n_bkg; }
-
-// Fold the rows of component k into the record columns dst0 ..
-static hipError_t fold_block(nr_ctx* c, int k, int dst0, int rl, double* d_part, int n_slab) {
-    const size_t row0 = (size_t)k * c->n_t;
-    nr::TmplFoldArgs fa{c->d_R + row0 * c->ldr, c->ldr, c->n_t, c->n_reco,
-                        c->d_rf + row0 * nr::kRFComp, d_part};
-    hipError_t e = nr::launch_tmpl_fold(fa, n_slab, c->stream);
-    if (e != hipSuccess) return e;
-    nr::TmplRecArgs ra{};
-    ra.part = d_part;
-    ra.n_slab = n_slab;
-    ra.n_reco = c->n_reco;
-    ra.n_cols = nr::kRFComp;
-    ra.dst0 = dst0;
-    ra.n_dst = nr::kTmplCompCols;
-    ra.rec = c->d_trec;
-    ra.rl = rl;
-    return nr::launch_tmpl_records(ra, c->stream);
-}
-
 // Templates of the single-component form: the records of shared.h, folded once.
 static int build_records(nr_ctx* c) {
     const size_t n_rec = (size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins;
@@ -2808,27 +2786,34 @@ static int build_templates(nr_ctx* c) {
         c->tmpl_data_ok = true;
         return 0;
     }
-    const int n_t = c->n_t, n_reco = c->n_reco, rl = tmpl_rl(c);
+    // every component's rows folded with their own factors
+    const int n_t = c->n_t, n_reco = c->n_reco, cols = nr::sh_cols(c->n_comp, c->n_bkg);
     if (!c->tmpl_ok) {
-        const int n_slab = (n_t + nr::kTmplSlabRows - 1) / nr::kTmplSlabRows;
+        const int n_slab = (n_t + nr::kShSlabRows - 1) / nr::kShSlabRows;
+        const size_t n_rec = (size_t)(n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins;
         double* d_part = nullptr;
         c->tmpl_data_ok = false;
         if ((rc = dalloc(&d_part, (size_t)n_slab * nr::kRFComp * n_reco)) ||
-            (rc = dalloc(&c->d_trec, (size_t)n_reco * rl))) {
+            (rc = dalloc(&c->d_trec, n_rec * (cols + 2)))) {
             dfree(&d_part);
             return rc;
         }
-        for (int k = 0; k < c->n_comp && e == hipSuccess; ++k)
-            e = fold_block(c, k, nr::kTmplCompCols * k, rl, d_part, n_slab);
+        for (int k = 0; k < c->n_comp && e == hipSuccess; ++k) {
+            const size_t row0 = (size_t)k * n_t;
+            e = nr::launch_sh_mfold({c->d_R + row0 * c->ldr, c->d_rf + row0 * nr::kRFComp, d_part,
+                                     c->ldr, n_t, n_reco}, c->stream);
+            if (e == hipSuccess)
+                e = nr::launch_sh_mrec({d_part, c->d_mask, c->d_trec, n_slab, n_reco, k, cols},
+                                       c->stream);
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         dfree(&d_part);
         if (e != hipSuccess) return fail(NR_EHIP, "template fold: %s", hipGetErrorString(e));
         c->tmpl_ok = true;
     }
     if (!c->tmpl_data_ok) {
-        nr::TmplMultiDataArgs da{c->d_n, c->d_bkg, c->d_mask, n_reco, c->n_comp,
-                                 c->n_bkg, rl, c->d_trec};
-        e = nr::launch_tmpl_mdata(da, c->stream);
+        e = nr::launch_sh_mdata({c->d_n, c->d_bkg, c->d_mask, c->d_trec, n_reco, c->n_comp,
+                                 c->n_bkg, cols}, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return fail(NR_EHIP, "template data: %s", hipGetErrorString(e));
         c->tmpl_data_ok = true;
@@ -2836,25 +2821,11 @@ static int build_templates(nr_ctx* c) {
     return 0;
 }
 
-// Multi-component form: reco bins per column slice: enough (point block x slice) work-groups for
-// 16 waves per SIMD (8 with the gradient, whose partial sums are 22 times
-// larger), at least 16 bins and at most 64 slices.  Measured on MI355X at
-// 65536 points x 4096 bins: 4, 8, 16 waves per SIMD run 1.10, 1.02, 0.99 ms.
-static int tmpl_split(const nr_ctx* c, int n_pts, bool grad, int* cols_per) {
-    const int n_pb = (n_pts + nr::kTmplWave - 1) / nr::kTmplWave;
-    const int target = grad ? 8192 : 16384;
-    int ns = (target + n_pb - 1) / n_pb;
-    ns = std::max(1, std::min(ns, std::min(64, (c->n_reco + 15) / 16)));
-    const int cp = (c->n_reco + ns - 1) / ns;
-    *cols_per = cp;
-    return (c->n_reco + cp - 1) / cp;
-}
-
 static int check_tmpl_form(const nr_ctx* c) {
-    if (c->multi && (c->n_comp > nr::kTmplMaxComp || c->n_bkg > nr::kTmplMaxBkg))
+    if (c->multi && (c->n_comp > nr::kShMaxComp || c->n_bkg > nr::kShMaxBkg))
         return fail(NR_EINVAL, "the template form takes up to %d components and %d "
-                    "background templates (have %d and %d)", nr::kTmplMaxComp,
-                    nr::kTmplMaxBkg, c->n_comp, c->n_bkg);
+                    "background templates (have %d and %d)", nr::kShMaxComp,
+                    nr::kShMaxBkg, c->n_comp, c->n_bkg);
     return 0;
 }
 
@@ -2862,10 +2833,10 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
     int rc;
     if ((rc = check_tmpl_form(c))) return rc;
     if ((!c->tmpl_ok || !c->tmpl_data_ok) && (rc = build_templates(c))) return rc;
-    int cp, slices = 0;
-    if (!c->multi) nr::sh_slices(n_pts, c->n_reco, &cp, &slices);
-    const size_t ns = (size_t)(c->multi ? tmpl_split(c, n_pts, grad, &cp) : slices);
-    const size_t na = (size_t)(c->multi ? tmpl_nacc(c) : nr::kShAcc);
+    int tiles, slices;
+    nr::sh_slices(n_pts, c->n_reco, c->multi, &tiles, &slices);
+    const size_t ns = (size_t)slices;
+    const size_t na = (size_t)(c->multi ? nr::sh_acc(c->n_comp, c->n_bkg) : nr::kShAcc);
     if (ns * n_pts > c->t_cap_d) {
         if ((rc = dalloc(&c->d_tdp, ns * n_pts))) return rc;
         c->t_cap_d = ns * n_pts;
@@ -2874,64 +2845,37 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
         if ((rc = dalloc(&c->d_thp, ns * na * n_pts))) return rc;
         c->t_cap_h = ns * na * n_pts;
     }
-    if (!c->multi) return 0;
-    const size_t nred = (1 + na) * n_pts;
-    if (nred > c->t_cap_r) {
-        if ((rc = dalloc(&c->d_tred, nred))) return rc;
-        c->t_cap_r = nred;
-    }
     return 0;
 }
 
 static int enqueue_tmpl(nr_ctx* c, const double* d_th, int n_pts, double* d_nll,
                         double* d_grad, double* d_mu, hipStream_t s) {
-    double* hpart = d_grad ? c->d_thp : nullptr;
+    const nr::ShEval e = sh_eval_args(c, c->d_trec, d_th, n_pts, c->d_tdp,
+                                      d_grad ? c->d_thp : nullptr, d_mu);
+    HIPCHK(nr::launch_sh_eval(&e, 1, s));
     if (!c->multi) {
-        const nr::ShEval e = sh_eval_args(c, c->d_trec, d_th, n_pts, c->d_tdp, hpart, d_mu);
         const nr::ShFinal f = sh_final_args(c, e, d_nll, d_grad);
-        HIPCHK(nr::launch_sh_eval(&e, 1, s));
         HIPCHK(nr::launch_sh_final(&f, 1, s));
         return 0;
     }
-    int cp;
-    const int ns = tmpl_split(c, n_pts, d_grad != nullptr, &cp);
-    {
-        nr::TmplMultiEvalArgs e{};
-        e.rec = c->d_trec;
-        e.theta = d_th;
-        e.rl = tmpl_rl(c);
-        e.K = c->n_comp;
-        e.B = c->n_bkg;
-        e.n_theta = c->n_theta;
-        e.n_reco = c->n_reco;
-        e.n_pts = n_pts;
-        e.cols_per = cp;
-        e.ph = c->ph;
-        e.dpart = c->d_tdp;
-        e.hpart = hpart;
-        e.mu = d_mu;
-        HIPCHK(nr::launch_tmpl_meval(e, ns, s));
+    nr::ShMultiFinal f{};
+    f.dpart = e.dpart;
+    f.hpart = e.hpart;
+    f.theta = d_th;
+    f.nll = d_nll;
+    f.grad = d_grad;
+    f.cdata = c->cdata;
+    for (int i = 0; i < nr::kMaxTheta; ++i) {
+        f.pull_mean[i] = c->pull_mean[i];
+        f.pull_sigma[i] = c->pull_sigma[i];
     }
-    nr::TmplReduceArgs r{c->d_tdp, hpart, n_pts, ns, tmpl_nacc(c), c->d_tred};
-    HIPCHK(nr::launch_tmpl_reduce(r, s));
-    {
-        nr::TmplMultiFinalArgs f{};
-        f.red = c->d_tred;
-        f.theta = d_th;
-        f.n_theta = c->n_theta;
-        f.K = c->n_comp;
-        f.B = c->n_bkg;
-        f.n_pts = n_pts;
-        f.cdata = c->cdata;
-        for (int i = 0; i < nr::kMaxTheta; ++i) {
-            f.pull_mean[i] = c->pull_mean[i];
-            f.pull_sigma[i] = c->pull_sigma[i];
-        }
-        f.ph = c->ph;
-        f.nll = d_nll;
-        f.grad = d_grad;
-        HIPCHK(nr::launch_tmpl_mfinal(f, s));
-    }
+    f.ph = c->ph;
+    f.n_pts = n_pts;
+    f.n_slice = e.n_slice;
+    f.K = c->n_comp;
+    f.B = c->n_bkg;
+    f.n_theta = c->n_theta;
+    HIPCHK(nr::launch_sh_mfinal(f, s));
     return 0;
 }
 

@@ -4,13 +4,13 @@
 // x = 2^k z with z in [0.6875, 1.375); the top eight bits of z's offset pick
 // one of 256 intervals with a reciprocal c of its centre, r = z c - 1 is formed
 // with one rounding (|r| <= 2^-8), and
-//   ln x = k ln 2 - ln c + (r - r^2/2 + r^3/3 - ... + r^7/7).
+//   ln x = k ln 2 - ln c + (r - r^2/2 + r^3/3 - ... - r^6/6).
 // The two intervals beside z = 1 have c = 1 exactly, so that near x = 1 the
 // result is accurate relative to its own small size (near a fit's minimum the
 // terms n ln(n / mu) are such numbers); elsewhere its absolute error stays
 // within a few 1e-16 times max(1, |ln x|).
 //
-// 17 instructions and one 16-byte LDS read, against 28 of the series in
+// 15 instructions and one 16-byte LDS read, against 28 of the series in
 // lnpos.h with its reciprocal of (m + 1).  The table is formed by the compiler
 // from the series of the inverse hyperbolic tangent.
 #pragma once
@@ -56,18 +56,16 @@ constexpr LnTable make_ln_table() {
 __host__ __device__
 #endif
 inline double ln_tab(double x, const LnEntry* tab) {
-    unsigned long long u;
-    memcpy(&u, &x, 8);
-    const unsigned hi = (unsigned)(u >> 32);
-    const int off = (int)(hi - kLnOff);
+    unsigned w[2];  // low, high
+    memcpy(w, &x, 8);
+    const int off = (int)(w[1] - kLnOff);
     const int k = off >> 20;
     const LnEntry t = tab[(off >> 12) & (kLnTab - 1)];
-    u = ((unsigned long long)(hi - ((unsigned)off & 0xfff00000u)) << 32) | (unsigned)u;
+    w[1] -= (unsigned)off & 0xfff00000u;
     double z;
-    memcpy(&z, &u, 8);
+    memcpy(&z, w, 8);
     const double r = fma(z, t.c, -1.0);
-    double p = fma(r, 1.0 / 7.0, -1.0 / 6.0);
-    p = fma(r, p, 1.0 / 5.0);
+    double p = fma(r, -1.0 / 6.0, 1.0 / 5.0);
     p = fma(r, p, -1.0 / 4.0);
     p = fma(r, p, 1.0 / 3.0);
     p = fma(r, p, -0.5);

@@ -98,6 +98,18 @@ struct MlpHidden {
     int k[3];
 };
 
+// -2lnL per point from the bin groups' sums, the data constant and the pulls.
+struct FinalArgs {
+    const double* part;   // [n_pts][n_nt]
+    const double* theta;  // [n_pts][7]
+    int n_pts, n_nt;
+    double cdata;
+    double pull_mean[kNTheta];
+    double pull_sigma[kNTheta];
+    double* nll;
+};
+
+hipError_t launch_finalize(const FinalArgs& a, hipStream_t s);
 hipError_t launch_mlp_gemm(int mode, const MlpGemm& g, hipStream_t s);
 // The whole network and the likelihood partials in one launch (kMlpNll's
 // output with the hidden layers formed in LDS); g as for kMlpNll except

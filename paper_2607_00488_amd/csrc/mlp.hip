@@ -405,6 +405,43 @@ __global__ __launch_bounds__(kMlpThreads, 2) void k_mlp_nll(MlpGemm g, MlpHidden
             red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
 }
 
+// -2lnL per point: sum of the column-tile deviance partials, data constant,
+// pulls (Eq. (logL)).
+// x[0] + x[1] + ... + x[n - 1] in index order; with n even (so that every
+// row of a [P][n] array starts 16-byte aligned) eight values at a time as
+// 16-byte pairs, all in flight before the additions.
+__device__ inline double row_sum(const double* x, int n) {
+    double s = 0.0;
+    int q = 0;
+    if ((n & 1) == 0) {
+        for (; q + 8 <= n; q += 8) {
+            double2 v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = reinterpret_cast<const double2*>(x + q)[i];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s += v[i].x;
+                s += v[i].y;
+            }
+        }
+    }
+    for (; q < n; ++q) s += x[q];
+    return s;
+}
+
+__global__ void k_finalize(FinalArgs a) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= a.n_pts) return;
+    const double d = row_sum(a.part + (size_t)p * a.n_nt, a.n_nt);
+    double pulls = 0.0;
+    for (int i = 0; i < kNTheta; ++i)
+        if (a.pull_sigma[i] > 0.0) {
+            const double z = (a.theta[(size_t)p * kNTheta + i] - a.pull_mean[i]) / a.pull_sigma[i];
+            pulls += z * z;
+        }
+    a.nll[p] = 2.0 * d + 2.0 * a.cdata + pulls;
+}
+
 __global__ void k_mlp_input(MlpInput a) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.B) return;
@@ -476,6 +513,11 @@ __global__ __launch_bounds__(256) void k_mlp_ksum(KSumArgs a) {
 }
 
 }  // namespace
+
+hipError_t launch_finalize(const FinalArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_finalize, dim3((a.n_pts + 255) / 256), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_mlp_ksum(const KSumArgs& a, hipStream_t s) {
     const long n = (long)a.M * a.N;

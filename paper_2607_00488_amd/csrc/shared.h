@@ -44,15 +44,34 @@ struct ShRec {
     int n_split, ldr, n_reco;
 };
 
+// The multi-component likelihood is the same product with a record of 8 columns
+// per component (seven spectra and the constant rows, coefficients r_k c_b and
+// r_k) and one per background (coefficient r_q), all times the common mask M_j:
+//   mu_j = M_j [sum_k r_k (G0^(k)_j + sum_b c_b G^(k)_bj) + sum_q r_q B_qj].
+// Its columns are padded with zeros to a multiple of four: two size classes, the
+// smaller for five components and four backgrounds (the solar species).
+constexpr int kShMaxComp = 8;
+constexpr int kShMaxBkg = 8;
+constexpr int kShCompCols = kCompBasis + 1;
+constexpr int kShSmall = 44, kShLarge = 72;  // columns of the classes
+
 struct ShEval {
     const double* rec;
-    const double* theta;  // [n_pts][7]
+    const double* theta;  // [n_pts][n_theta]
     double* dpart;        // [n_slice][n_pts] deviance sums
-    double* hpart;        // [n_slice][kShAcc][n_pts], or null (no gradient)
+    double* hpart;        // [n_slice][n_acc][n_pts], or null (no gradient)
     double* mu;           // [n_pts][n_reco], or null
     Phys ph;
     int n_pts, n_reco, tiles, n_slice;  // tiles of kShBins bins per slice
+    // multi-component form: components, backgrounds (K = 0: single-component)
+    int K, B, n_theta;
 };
+
+// Columns of a record and contractions of the gradient (whole blocks of 16).
+inline int sh_cols(int K, int B) {
+    return K == 0 ? kShAcc : kShCompCols * K + B <= kShSmall ? kShSmall : kShLarge;
+}
+inline int sh_acc(int K, int B) { return (sh_cols(K, B) + 15) / 16 * 16; }
 
 struct ShFinal {
     const double* dpart;
@@ -65,6 +84,42 @@ struct ShFinal {
     double pull_sigma[kNTheta];
     Phys ph;
     int n_pts, n_slice;
+};
+
+// Multi-component likelihood and gradient.
+struct ShMultiFinal {
+    const double* dpart;
+    const double* hpart;
+    const double* theta;
+    double* nll;
+    double* grad;  // [n_pts][n_theta] or null
+    double cdata;
+    double pull_mean[kMaxTheta];
+    double pull_sigma[kMaxTheta];
+    Phys ph;
+    int n_pts, n_slice, K, B, n_theta;
+};
+
+// Columns of one component folded (k_tmpl slabs, see launch_sh_mfold) and the
+// data of a multi-component record.
+struct ShMultiFold {
+    const float* R;    // this component's rows
+    const double* rf;  // [n_t][kRFComp]
+    double* part;      // [n_slab][kRFComp][n_reco]
+    int ldr, n_t, n_reco;
+};
+struct ShMultiRec {
+    const double* part;
+    const double* mask;  // [n_reco] or null
+    double* rec;         // [..][cols + 2]
+    int n_slab, n_reco, comp, cols;
+};
+struct ShMultiData {
+    const double* n;
+    const double* bkg;   // [B][n_reco]
+    const double* mask;  // [n_reco] or null
+    double* rec;
+    int n_reco, K, B, cols;
 };
 
 // N analyses of one launch, by value: first[d] is the first work-group of d.
@@ -80,10 +135,15 @@ hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s);
 hipError_t launch_sh_rec(const ShRec* p, int n, hipStream_t s);
 hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s);
 hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s);
+hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s);
+constexpr int kShSlabRows = 64;  // response rows per multi-component fold work-group
+hipError_t launch_sh_mfold(const ShMultiFold& p, hipStream_t s);
+hipError_t launch_sh_mrec(const ShMultiRec& p, hipStream_t s);
+hipError_t launch_sh_mdata(const ShMultiData& p, hipStream_t s);
 // New data beside folded columns that stay.
 hipError_t launch_sh_data(const ShRec& p, hipStream_t s);
 
 // Column slices of an evaluation of n_pts points over n_reco bins.
-void sh_slices(int n_pts, int n_reco, int* tiles, int* n_slice);
+void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice);
 
 }  // namespace nr

@@ -3,6 +3,7 @@
 // Eqs. (fNp_reweight), (mu_total) and the Poisson -2lnL of Eq. (logL) with its
 // gradient from them, FP64 throughout.
 #include "shared.h"
+#include "lnpos.h"
 #include "lntab.h"
 
 #include <algorithm>
@@ -207,7 +208,9 @@ __global__ __launch_bounds__(kThreads) void k_sh_data(ShRec a) {
 // separate roundings would leave noise that stalls a line search).
 //
 // Bound by those vector instructions (about 25 per point and bin, 40 with the
-// gradient).
+// gradient) and the matrix instructions, which share the FP64 rate with them
+// (64 cycles of about 150 per 64 elements).  65536 points x 4096 bins: 291 us,
+// against 510 with one point per lane and the series logarithm.
 __device__ __constant__ const LnTable g_ln = make_ln_table();
 
 // The terms that the fast path leaves out: an empty or underflowed spectrum, an
@@ -215,15 +218,19 @@ __device__ __constant__ const LnTable g_ln = make_ln_table();
 __device__ __attribute__((noinline)) double2 sh_slow_term(double mu, double n) {
     double d = mu, a = 2.0;
     if (n > 0.0) {
-        d = mu > 0.0 ? (isinf(mu) ? mu : mu - n + n * log(n / mu)) : INFINITY;
+        d = mu > 0.0 ? (isinf(mu) ? mu : mu - n + n * ln_pos(n / mu)) : INFINITY;
         a = 2.0 * (1.0 - n / mu);
     }
     return make_double2(d, a);
 }
 
-template <bool GRAD, bool MU, int NB, int N>
+template <bool GRAD, bool MU, int NB, int KS, int N>
 __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
+    constexpr bool MULTI = KS != kShAcc / 4;
+    constexpr int RL = 4 * KS + 2;          // record length
+    constexpr int HB = (4 * KS + 15) / 16;  // blocks of 16 contractions
     __shared__ LnTable lt;
+    __shared__ double cs[MULTI ? 4 : 1][MULTI ? 16 : 1][MULTI ? 4 * KS + 1 : 1];
     int wg;
     const ShEval& a = g.p[sh_find(g, &wg)];
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
@@ -233,50 +240,90 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
     const int n_pts = a.n_pts, n_grp = (n_pts + 16 * NB - 1) / (16 * NB);
     const int w = wg * 4 + (tid >> 6), sl = w / n_grp, p0 = (w - sl * n_grp) * 16 * NB;
     if (sl >= a.n_slice) return;
-    // this lane's four of each point's coefficients (k = 4 lk + s)
-    double c[NB][4];
+    // this lane's KS of each point's 4 KS coefficients (k = KS lk + s)
+    double c[NB][KS];
+    if constexpr (MULTI) {
+        static_assert(NB == 1, "one block of points");
+        const int p = min(p0 + li, n_pts - 1);
+        const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
+        auto& row = cs[tid >> 6][li];
+        double t5[5], v[kCompBasis];
 #pragma unroll
-    for (int x = 0; x < NB; ++x) {
-        const int p = min(p0 + 16 * x + li, n_pts - 1);
-        double th[kNTheta], v[16];
+        for (int i = 0; i < 5; ++i) t5[i] = th[i];
+        basis_coef7(t5, a.ph, 1.0, v);
+        for (int k = lk; k < a.K; k += 4) {
+            const double r = th[5 + k];
 #pragma unroll
-        for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
-        basis_coef(th, a.ph, v);
-        v[kNBasis] = 1.0;
-        v[kNBasis + 1] = th[6];
+            for (int b = 0; b < kCompBasis; ++b) row[kShCompCols * k + b] = r * v[b];
+            row[kShCompCols * k + kCompBasis] = r;
+        }
+        for (int q = kShCompCols * a.K + lk; q < 4 * KS; q += 4) {
+            const int b = q - kShCompCols * a.K;
+            row[q] = b < a.B ? th[5 + a.K + b] : 0.0;
+        }
+        // written and read by this wave alone
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            c[x][s] = lk == 0 ? v[s] : lk == 1 ? v[4 + s] : lk == 2 ? v[8 + s] : v[12 + s];
+        for (int s = 0; s < KS; ++s) c[0][s] = row[KS * lk + s];
+    } else {
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            const int p = min(p0 + 16 * x + li, n_pts - 1);
+            double th[kNTheta], v[16];
+#pragma unroll
+            for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
+            basis_coef(th, a.ph, v);
+            v[kNBasis] = 1.0;
+            v[kNBasis + 1] = th[6];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                c[x][s] = lk == 0 ? v[s] : lk == 1 ? v[4 + s] : lk == 2 ? v[8 + s] : v[12 + s];
+        }
     }
     const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
     const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
     const auto* rec = gm(a.rec);
     // row operand i holds bin 4 (i % 4) + i / 4: output register r of lane
     // group lk is then bin 4 lk + r
-    const int fb = (4 * (li & 3) + (li >> 2)) * kShRec + 4 * lk;
+    const int fb = (4 * (li & 3) + (li >> 2)) * RL + KS * lk;
     struct Tile {
-        v2d f0, f1;   // record columns 4 lk .. 4 lk + 3 of this lane's row bin
-        v2d n[4];     // n, 1 / n of bins 4 lk + r
-        double gr[4]; // column li of bins 4 lk + r
+        double f[KS];      // record columns KS lk .. of this lane's row bin
+        v2d n[4];          // n, 1 / n of bins 4 lk + r
+        double gr[HB][4];  // columns 16 y + li of bins 4 lk + r
     };
     auto load = [&](int t, Tile& q) {
-        const auto* r = rec + (size_t)t * (kShBins * kShRec);
-        const auto* f = (const __attribute__((address_space(1))) v2d*)(r + fb);
-        q.f0 = f[0];
-        q.f1 = f[1];
+        const auto* r = rec + (size_t)t * (kShBins * RL);
+        if constexpr (KS % 2 == 0) {
+            const auto* f = (const __attribute__((address_space(1))) v2d*)(r + fb);
+#pragma unroll
+            for (int s = 0; s < KS / 2; ++s) {
+                const v2d v = f[s];
+                q.f[2 * s] = v.x;
+                q.f[2 * s + 1] = v.y;
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < KS; ++s) q.f[s] = r[fb + s];
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const auto* b = r + (4 * lk + e) * kShRec;
-            q.n[e] = *(const __attribute__((address_space(1))) v2d*)(b + 16);
-            if (GRAD) q.gr[e] = b[li];
+            const auto* b = r + (4 * lk + e) * RL;
+            q.n[e] = *(const __attribute__((address_space(1))) v2d*)(b + 4 * KS);
+            if (GRAD)
+#pragma unroll
+                for (int y = 0; y < HB; ++y)  // the last block may end past the columns
+                    q.gr[y][e] = (4 * KS) % 16 == 0 || 16 * y + li < 4 * KS ? b[16 * y + li] : 0.0;
         }
     };
     double dsum[NB];
-    v4d h[NB];
+    v4d h[NB][HB];
 #pragma unroll
     for (int x = 0; x < NB; ++x) {
         dsum[x] = 0.0;
-        h[x] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int y = 0; y < HB; ++y) h[x][y] = (v4d){0.0, 0.0, 0.0, 0.0};
     }
     const bool mu16 = MU && a.n_reco % 2 == 0 && ((size_t)a.mu & 15) == 0;
     Tile cur, nxt;
@@ -286,10 +333,9 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
 #pragma unroll
         for (int x = 0; x < NB; ++x) {
             v4d mu = (v4d){0.0, 0.0, 0.0, 0.0};
-            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f0.x, c[x][0], mu, 0, 0, 0);
-            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f0.y, c[x][1], mu, 0, 0, 0);
-            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f1.x, c[x][2], mu, 0, 0, 0);
-            mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f1.y, c[x][3], mu, 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                mu = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.f[s], c[x][s], mu, 0, 0, 0);
             const int p = p0 + 16 * x + li, j = t * kShBins + 4 * lk;
             if (MU && p < n_pts) {
                 auto* o = gm(a.mu) + (size_t)p * a.n_reco + j;
@@ -307,8 +353,9 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const double n = cur.n[r].x, q = mu[r] * cur.n[r].y;
-                // both positive and normal
-                fast = fast && __builtin_amdgcn_class(q, 0x100) && __builtin_amdgcn_class(mu[r], 0x100);
+                // positive and normal
+                fast = fast && __builtin_amdgcn_class(q, 0x100);
+                if (GRAD) fast = fast && __builtin_amdgcn_class(mu[r], 0x100);
                 dv[r] = fma(-n, ln_tab(q, lt.e), mu[r] - n);
                 if (GRAD) {
                     double y = __builtin_amdgcn_rcp(mu[r]);
@@ -337,7 +384,11 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 dsum[x] += dv[r];
-                if (GRAD) h[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.gr[r], av[r], h[x], 0, 0, 0);
+                if (GRAD)
+#pragma unroll
+                    for (int y = 0; y < HB; ++y)
+                        h[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur.gr[y][r], av[r], h[x][y],
+                                                                       0, 0, 0);
             }
         }
         cur = nxt;
@@ -352,8 +403,10 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
         if (lk == 0) gm(a.dpart)[(size_t)sl * n_pts + p] = s;
         if (GRAD)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                gm(a.hpart)[((size_t)sl * kShAcc + lk + 4 * r) * n_pts + p] = h[x][r];
+            for (int y = 0; y < HB; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    gm(a.hpart)[((size_t)sl * (16 * HB) + 16 * y + lk + 4 * r) * n_pts + p] = h[x][y][r];
     }
 }
 
@@ -422,6 +475,131 @@ __global__ __launch_bounds__(kThreads) void k_sh_final_grad(ShGroup<ShFinal, N> 
     }
 }
 
+// ------------------------------------------------- multi-component form
+// One thread per reco bin, one work-group row per slab of one component's
+// response rows: the FP64 sums of F_lb R_lj (the row's factors wave-uniform).
+__global__ __launch_bounds__(kThreads) void k_sh_mfold(ShMultiFold a) {
+    const int j = blockIdx.x * kThreads + threadIdx.x;
+    if (j >= a.n_reco) return;
+    const int l0 = blockIdx.y * kShSlabRows, l1 = min(l0 + kShSlabRows, a.n_t);
+    double acc[kRFComp];
+#pragma unroll
+    for (int b = 0; b < kRFComp; ++b) acc[b] = 0.0;
+    for (int l = l0; l < l1; ++l) {
+        const double r = a.R[(size_t)l * a.ldr + j];
+        const double* f = a.rf + (size_t)l * kRFComp;
+#pragma unroll
+        for (int b = 0; b < kRFComp; ++b) acc[b] = fma(f[b], r, acc[b]);
+    }
+#pragma unroll
+    for (int b = 0; b < kRFComp; ++b)
+        a.part[((size_t)blockIdx.y * kRFComp + b) * a.n_reco + j] = acc[b];
+}
+
+// Slab sums in slab order, times the mask, into the component's columns.
+__global__ __launch_bounds__(kThreads) void k_sh_mrec(ShMultiRec a) {
+    const int j = blockIdx.x * kThreads + threadIdx.x, b = blockIdx.y;
+    if (j >= a.n_reco) return;
+    double s = 0.0;
+    for (int q = 0; q < a.n_slab; ++q) s += a.part[((size_t)q * kRFComp + b) * a.n_reco + j];
+    a.rec[(size_t)j * (a.cols + 2) + kShCompCols * a.comp + b] = a.mask ? s * a.mask[j] : s;
+}
+
+// Backgrounds, zero columns and data.  Bins past the last one hold zeros: their
+// mu = 0 takes the points kernel's slow term, which leaves them out.
+__global__ __launch_bounds__(kThreads) void k_sh_mdata(ShMultiData a) {
+    const int j = blockIdx.x * kThreads + threadIdx.x;
+    const int n_pad = (a.n_reco + kShBins - 1) / kShBins * kShBins;
+    if (j >= n_pad) return;
+    double* r = a.rec + (size_t)j * (a.cols + 2);
+    const bool ok = j < a.n_reco;
+    const double m = ok && a.mask ? a.mask[j] : 1.0;
+    if (!ok)
+        for (int q = 0; q < kShCompCols * a.K; ++q) r[q] = 0.0;
+    for (int q = kShCompCols * a.K; q < a.cols; ++q) {
+        const int b = q - kShCompCols * a.K;
+        r[q] = ok && b < a.B ? a.bkg[(size_t)b * a.n_reco + j] * m : 0.0;
+    }
+    const double n = ok ? a.n[j] : 0.0;
+    r[a.cols] = n;
+    r[a.cols + 1] = n > 0.0 ? 1.0 / n : 1.0;
+}
+
+__device__ inline double sh_mnll(const ShMultiFinal& a, int p, double dev) {
+    const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
+    double pulls = 0.0;
+    for (int i = 0; i < a.n_theta; ++i)
+        if (a.pull_sigma[i] > 0.0) {
+            const double z = (th[i] - a.pull_mean[i]) / a.pull_sigma[i];
+            pulls += z * z;
+        }
+    return 2.0 * dev + 2.0 * a.cdata + pulls;
+}
+
+__global__ __launch_bounds__(64) void k_sh_mfinal(ShMultiFinal a) {
+    const int p = blockIdx.x * 64 + threadIdx.x;
+    if (p >= a.n_pts) return;
+    double d = 0.0;
+#pragma unroll 8
+    for (int q = 0; q < a.n_slice; ++q) d += gm(a.dpart)[(size_t)q * a.n_pts + p];
+    gm(a.nll)[p] = sh_mnll(a, p, d);
+}
+
+// 16 points per work-group: the slices of every contraction, then
+//   d/d theta_i (i < 5) = sum_k r_k sum_b dc_ib h_kb,
+//   d/d r_k = sum_b c_b h_kb + h_k,const,  d/d r_q = h_q,
+// written as whole rows.
+template <int COLS>
+__global__ __launch_bounds__(kThreads) void k_sh_mfinal_grad(ShMultiFinal a) {
+    constexpr int ACC = (COLS + 15) / 16 * 16;
+    __shared__ double hs[16][COLS + 1];
+    __shared__ double dv[16];
+    __shared__ double gs[16][kMaxTheta + 1];
+    const int v0 = threadIdx.x >> 4, pl = threadIdx.x & 15, p0 = blockIdx.x * 16, p = p0 + pl;
+    const int n_col = kShCompCols * a.K + a.B;
+    if (p < a.n_pts) {
+        for (int v = v0; v <= n_col; v += 16) {  // v = n_col: the deviance
+            const bool dev = v == n_col;
+            const auto* x = dev ? gm(a.dpart) + p : gm(a.hpart) + (size_t)v * a.n_pts + p;
+            const size_t st = (size_t)(dev ? 1 : ACC) * a.n_pts;
+            double s = 0.0;
+#pragma unroll 8
+            for (int q = 0; q < a.n_slice; ++q) s += x[q * st];
+            if (dev) dv[pl] = s;
+            else hs[pl][v] = s;
+        }
+    }
+    __syncthreads();
+    if (v0 == 0 && p < a.n_pts) {
+        const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
+        double t5[5], c[kCompBasis], H[kCompBasis], g5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int i = 0; i < 5; ++i) t5[i] = th[i];
+        basis_coef7(t5, a.ph, 1.0, c);
+        for (int b = 0; b < kCompBasis; ++b) H[b] = 0.0;
+        for (int k = 0; k < a.K; ++k) {
+            const double* h = &hs[pl][kShCompCols * k];
+            const double r = th[5 + k];
+            double R = h[kCompBasis];
+            for (int b = 0; b < kCompBasis; ++b) {
+                H[b] = fma(r, h[b], H[b]);
+                R = fma(c[b], h[b], R);
+            }
+            gs[pl][5 + k] = R;
+        }
+        basis_dcoef7(t5, a.ph, 1.0, H, g5);
+        for (int i = 0; i < 5; ++i) gs[pl][i] = g5[i];
+        for (int q = 0; q < a.B; ++q) gs[pl][5 + a.K + q] = hs[pl][kShCompCols * a.K + q];
+        for (int i = 0; i < a.n_theta; ++i)
+            if (a.pull_sigma[i] > 0.0)
+                gs[pl][i] += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
+        gm(a.nll)[p] = sh_mnll(a, p, dv[pl]);
+    }
+    __syncthreads();
+    const int n = min(16, a.n_pts - p0) * a.n_theta;
+    for (int i = threadIdx.x; i < n; i += kThreads)
+        gm(a.grad)[(size_t)p0 * a.n_theta + i] = gs[i / a.n_theta][i % a.n_theta];
+}
+
 // One analysis travels in a struct of its own size, several in one of
 // kShGroup (at most 4 KB of kernel arguments).
 template <class P, int N, class Wgs>
@@ -448,19 +626,29 @@ ShGroup<P, N> make_group(const P* p, int n, Wgs wgs) {
         }                                                                               \
     } while (0)
 
-template <bool GRAD, bool MU, int NB>
+template <bool GRAD, bool MU, int NB, int KS = kShAcc / 4>
 void launch_eval(const ShEval* p, int n, hipStream_t s) {
     const auto wgs = [](const ShEval& e) {
         const int grp = (e.n_pts + 16 * NB - 1) / (16 * NB);
         return (int)(((long)grp * e.n_slice + 3) / 4);
     };
-#define SH_K(M) (k_sh_eval<GRAD, MU, NB, M>)
-    SH_LAUNCH(SH_K, ShEval, kThreads, wgs);
+    if constexpr (KS == kShAcc / 4) {
+#define SH_K(M) (k_sh_eval<GRAD, MU, NB, KS, M>)
+        SH_LAUNCH(SH_K, ShEval, kThreads, wgs);
 #undef SH_K
+    } else {
+        const ShGroup<ShEval, 1> g = make_group<ShEval, 1>(p, 1, wgs);
+        hipLaunchKernelGGL((k_sh_eval<GRAD, MU, NB, KS, 1>), dim3(g.first[1]), dim3(kThreads), 0, s, g);
+    }
 }
 
 template <bool GRAD, bool MU>
 void launch_eval_nb(const ShEval* p, int n, hipStream_t s) {
+    if (p[0].K) {
+        if (sh_cols(p[0].K, p[0].B) == kShSmall) launch_eval<GRAD, MU, 1, kShSmall / 4>(p, n, s);
+        else launch_eval<GRAD, MU, 1, kShLarge / 4>(p, n, s);
+        return;
+    }
     long waves = 0;  // of one block of 16 points each
     for (int d = 0; d < n; ++d) waves += (long)((p[d].n_pts + 15) / 16) * p[d].n_slice;
     // more blocks per wave share the record loads, but only once the chip's
@@ -502,7 +690,8 @@ hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s) {
     if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
     for (int d = 0; d < n; ++d)
         if (p[d].n_pts < 1 || !p[d].hpart != !p[0].hpart || !p[d].mu != !p[0].mu ||
-            (p[d].hpart && p[d].mu) ||
+            (p[d].hpart && p[d].mu) || (p[d].K && (n > 1 || p[d].K > kShMaxComp || p[d].B > kShMaxBkg ||
+                                                   p[d].n_theta != 5 + p[d].K + p[d].B)) ||
             (long)p[d].tiles * p[d].n_slice * kShBins < p[d].n_reco)
             return hipErrorInvalidValue;
     if (p[0].hpart) launch_eval_nb<true, false>(p, n, s);
@@ -527,14 +716,48 @@ hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_sh_mfold(const ShMultiFold& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_sh_mfold, dim3((p.n_reco + kThreads - 1) / kThreads,
+                                        (p.n_t + kShSlabRows - 1) / kShSlabRows),
+                       dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_mrec(const ShMultiRec& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_sh_mrec, dim3((p.n_reco + kThreads - 1) / kThreads, kRFComp),
+                       dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_mdata(const ShMultiData& p, hipStream_t s) {
+    hipLaunchKernelGGL(k_sh_mdata, dim3((p.n_reco + kShBins + kThreads - 1) / kThreads),
+                       dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s) {
+    if (p.K < 1 || p.K > kShMaxComp || p.B > kShMaxBkg || (p.grad && !p.hpart))
+        return hipErrorInvalidValue;
+    if (!p.grad)
+        hipLaunchKernelGGL(k_sh_mfinal, dim3((p.n_pts + 63) / 64), dim3(64), 0, s, p);
+    else if (sh_cols(p.K, p.B) == kShSmall)
+        hipLaunchKernelGGL(k_sh_mfinal_grad<kShSmall>, dim3((p.n_pts + 15) / 16), dim3(kThreads), 0, s, p);
+    else
+        hipLaunchKernelGGL(k_sh_mfinal_grad<kShLarge>, dim3((p.n_pts + 15) / 16), dim3(kThreads), 0, s, p);
+    return hipGetLastError();
+}
+
 // Slices of 64 bins up to 4096 points (fixed by the response's shape, so that
 // a point's result does not depend on its list); beyond, as few as leave about
 // 8192 waves of 64 points, since every slice writes its sums for every point.
-void sh_slices(int n_pts, int n_reco, int* tiles, int* n_slice) {
+// The multi-component form writes three to five times as many: about 2048 waves
+// of 16 points.
+void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice) {
     const int n_tile = (n_reco + kShBins - 1) / kShBins;
     int t = 4;
-    if (n_pts > 4096) {
-        const int ns = std::max(1, (8192 + (n_pts + 63) / 64 - 1) / ((n_pts + 63) / 64));
+    const int grp = multi ? (n_pts + 15) / 16 : (n_pts + 63) / 64, waves = multi ? 2048 : 8192;
+    if (multi || n_pts > 4096) {
+        const int ns = std::max(1, (waves + grp - 1) / grp);
         t = std::max(t, (n_tile + ns - 1) / ns);
     }
     *tiles = t;

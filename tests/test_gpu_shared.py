@@ -92,3 +92,47 @@ def test_more_analyses_than_one_launch_takes(monkeypatch):
     for c, th, out in zip(ctxs, ths, outs):
         assert np.array_equal(out, c.eval_nll(th))
         c.close()
+
+
+@pytest.mark.parametrize("K,B", [(1, 0), (5, 4), (4, 8), (5, 5), (8, 8)])
+def test_multi_component_columns(K, B):
+    """Both column classes, their last columns and the padded bins, against the
+    streaming path (other kernels): spectra and likelihoods directly, the
+    gradient from its spectra, which are quadratic in the couplings and linear
+    in m2 and the rates, so that a central difference over a unit step is exact."""
+    import paper_2607_00488_amd as nr
+    n_t, n_reco, P = 67, 33, 21
+    src = (synth.source_nodes(N_E) * 2)[:max(K, 5)]
+    g = synth.rng(8400 + 10 * K + B)
+    shapes = [(16.0, 2.0 + k) for k in range(K)]
+    d = synth.component_inputs(n_t, n_reco, 30_000, 8401, shapes=shapes)
+    ctx = nr.Context(0)
+    ctx.set_sources(src, n_t)
+    ctx.set_components(np.arange(len(src), dtype=np.int32) % K, d["hist"],
+                       g.uniform(0.8, 1.2, K), g.uniform(50.0, 500.0, K),
+                       bkg_pdf=g.uniform(0.5, 1.5, (B, n_reco)) / n_reco if B else None,
+                       bkg_rate=g.uniform(50.0, 500.0, B) if B else None,
+                       comp_mask=d["comp_mask"], mask=d["mask"], exposure=1.5)
+    th = g.uniform(0.8, 1.2, (P, 5 + K + B))
+    th[:, :5] = synth.theta_prior(P, 8402)[:, :5]
+    ctx.set_data(np.ones(n_reco), None)
+    n = g.poisson(ctx.eval_mu(th[:1])[0]).astype(np.float64)
+    ctx.set_data(n, None)
+    rel = (n_t + 3 * N_E + 2 + 128) * EPS
+    mu, nll = ctx.eval_mu(th), ctx.eval_nll(th)
+    assert np.all(np.abs(ctx.eval_mu_templates(th) - mu) <= rel * np.abs(mu))
+    v, grad = ctx.eval_nll_templates(th, grad=True)
+    tol = 2 * np.abs(mu - n).sum(1) * rel + 2 * (mu + n).sum(1) * 64 * EPS
+    assert np.all(np.abs(v - nll) <= tol)
+    assert np.array_equal(ctx.eval_nll_templates(th), v)
+    q = np.divide(n, mu, out=np.zeros_like(mu), where=n > 0)  # an empty bin's a is 2
+    a, w = 2 * (1 - q), np.abs(2 * (1 - q)) + 2 * q
+    for k in range(5 + K + B):
+        up, dn = th.copy(), th.copy()
+        up[:, k] += 1.0
+        dn[:, k] -= 1.0
+        hi, lo = ctx.eval_mu(up) - mu, ctx.eval_mu(dn) - mu
+        ref = (a * (hi - lo) / 2).sum(1)
+        bound = 8 * rel * (w * (np.abs(hi) + np.abs(lo) + 2 * mu)).sum(1)
+        assert np.all(np.abs(grad[:, k] - ref) <= bound), k
+    ctx.close()

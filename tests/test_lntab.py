@@ -5,7 +5,7 @@ take.
 
 Bounds: r carries one rounding of 2^-53 |r| and the table two of its entry (the
 reciprocal cancels: its logarithm is the entry's), the series truncates below
-2^-59 and the last two sums round once each: 4e-16 max(1, |ln x|) absolute, and
+2^-58 (2^-56 relative beside x = 1) and the last two sums round once each: 4e-16 max(1, |ln x|) absolute, and
 beside x = 1, where the entry is zero, 4e-16 relative."""
 import ctypes as C
 import os
