@@ -74,9 +74,13 @@ void dfree(T** p) {
 }
 
 // A NULL stream argument of the _dev entry points means the HIP default
-// stream.  Work cannot be captured on it, so it runs on an internal stream
-// ordered after everything already on the default stream, and the default
-// stream waits for its end.
+// stream.  Their kernels are launched on it directly, except where a call may
+// capture a graph (work cannot be captured on the default stream) or the caller
+// holds the context's stream and may order work against it: then they run on
+// the internal stream, ordered after everything already on the default stream,
+// and the default stream waits for their end.  That detour's four event calls
+// and two waits cost a batched call of 64 points 
+// 30 us of host time of 45 (121 against 109 us a call at 16384 x 4096).
 struct Bridge {
     hipStream_t work = nullptr;
     hipEvent_t out = nullptr;
@@ -156,6 +160,8 @@ struct nr_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     hipEvent_t ev_in = nullptr, ev_out = nullptr;  // default-stream bridge
+    bool stream_given = false;  // the caller holds `stream`
+    bool null_pending = false;  // work of this context may be on the default stream
     double* d_v[2] = {nullptr, nullptr};  // [n_t] fold vectors, by parity
     nr::Phys ph{};
     // sources and grid
@@ -262,6 +268,25 @@ void clear_graphs(nr_ctx* c) {
 
 int set_device(nr_ctx* c) {
     HIPCHK(hipSetDevice(c->device));
+    return 0;
+}
+
+// Stream of a _dev call (see Bridge).
+int dev_begin(Bridge& b, nr_ctx* c, void* user, bool captures) {
+    if (captures || c->stream_given)
+        return bridge_begin(b, user, c->stream, c->ev_in, c->ev_out);
+    b.work = (hipStream_t)user;
+    if (!user) c->null_pending = true;
+    return 0;
+}
+
+// Before the context's own stream is used: it waits for what _dev calls have
+// left on the default stream (they share the context's buffers).
+int own_stream(nr_ctx* c) {
+    if (!c->null_pending) return 0;
+    c->null_pending = false;
+    HIPCHK(hipEventRecord(c->ev_in, nullptr));
+    HIPCHK(hipStreamWaitEvent(c->stream, c->ev_in, 0));
     return 0;
 }
 
@@ -1378,7 +1403,7 @@ int batched_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     if ((rc = check_ready(c))) return rc;
     if ((rc = check_single(c))) return rc;
     if ((rc = check_theta(theta, n_pts))) return rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     if ((rc = ensure_batch(c, n_pts, mu ? (size_t)n_pts * c->n_reco : 0)))
         return rc;
     HIPCHK(hipMemcpyAsync(c->d_bth, theta, sizeof(double) * n_pts * NR_NTHETA,
@@ -1475,7 +1500,13 @@ void nr_destroy(nr_ctx* c) {
     delete c;
 }
 
-void* nr_stream(nr_ctx* c) { return c ? (void*)c->stream : nullptr; }
+void* nr_stream(nr_ctx* c) {
+    const ApiLock api_lock;
+    if (!c) return nullptr;
+    c->stream_given = true;
+    if (hipSetDevice(c->device) == hipSuccess) (void)own_stream(c);
+    return (void*)c->stream;
+}
 
 int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
                    double t_lo, double t_hi, const nr_physics* phys) {
@@ -1490,7 +1521,7 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
                   phys->tau_frac >= 0 && phys->tau_frac <= 1))
         return fail(NR_EINVAL, "invalid physical constants");
     int rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     c->ph = make_phys(phys);
     // copy, validate and sort the node tables (summation order is free)
     c->src_off.assign(n_src + 1, 0);
@@ -1745,7 +1776,7 @@ int nr_eval_nll_dev(nr_ctx* c, const double* d_theta, int n_pts, double* d_nll,
     if (d_grad && (rc = check_single(c))) return rc;
     if ((rc = set_device(c))) return rc;
     Bridge br;
-    if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
+    if ((rc = dev_begin(br, c, stream, !use_shared(c)))) return rc;
     if ((rc = run_points(c, d_theta, n_pts, d_nll, d_grad, nullptr, nullptr, br.work)))
         return rc;
     return bridge_end(br);
@@ -1772,7 +1803,7 @@ int nr_eval_nll_dev_noalloc(nr_ctx* c, const double* d_theta, int n_pts,
     // launched directly on the caller's stream (no graph of our own), so
     // that a caller may capture them in its own graph
     Bridge br;
-    if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
+    if ((rc = dev_begin(br, c, stream, false))) return rc;
     if (use_shared(c))
         rc = enqueue_shared(c, base, std::min(c->sh_pts, sh_points(c, NR_NOALLOC_WORKSPACE_BYTES)),
                             d_theta, nullptr, n_pts, d_nll, d_grad, nullptr, br.work);
@@ -1791,7 +1822,7 @@ static int eval_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     if ((rc = check_ready(c))) return rc;
     if ((grad || w) && (rc = check_single(c))) return rc;
     if ((rc = check_theta(theta, n_pts, c->n_theta))) return rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     if (!mu && !w) {
         // likelihood (and gradient): theta in and -2lnL out through pinned
         // host memory the kernels read and write directly, no copies
@@ -1882,7 +1913,7 @@ int nr_eval_ess(nr_ctx* c, const double* theta, int n_pts, double* ess) {
     if ((rc = check_single(c))) return rc;
     if (!c->have_nev) return fail(NR_ESTATE, "nr_eval_ess needs nr_set_mc_events first");
     if ((rc = check_theta(theta, n_pts))) return rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     if ((rc = ensure_stage(c, n_pts, (size_t)n_pts * c->n_reco, c->n_t))) return rc;
     HIPCHK(hipMemcpyAsync(c->d_th, theta, sizeof(double) * n_pts * NR_NTHETA,
                           hipMemcpyHostToDevice, c->stream));
@@ -2001,7 +2032,7 @@ int nr_set_components(nr_ctx* c, const nr_components* k, int n_reco) {
             bkg[(size_t)b * n_reco + j] =
                 k->exposure * k->bkg_rate[b] * k->bkg_pdf[(size_t)b * n_reco + j];
     int rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     clear_graphs(c);
     if ((rc = dalloc(&c->d_R, n_rows * ldr)) || (rc = dalloc(&c->d_mrow, n_rows)) ||
         (rc = dalloc(&c->d_bkg, bkg.size())) || (rc = dalloc(&c->d_ssmc, n_rows)) ||
@@ -2110,7 +2141,7 @@ int nr_time_stage(nr_ctx* c, int stage, int iters, double* avg_ms) {
     int rc;
     if ((rc = check_ready(c))) return rc;
     if (stage == 3 && (rc = check_single(c))) return rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     // Timing launches read the context's own inputs at the SM point (the
     // work of every stage does not depend on theta) and write only internal
     // buffers: the fold reads fold vector 0 and writes partial sums 0, the
@@ -2220,8 +2251,9 @@ int nr_eval_nll_multi_dev(nr_ctx* const* ctx, int n_ctx,
     }
     if ((rc = set_device(ctx[0]))) return rc;
     Bridge br;
-    if ((rc = bridge_begin(br, stream, ctx[0]->stream, ctx[0]->ev_in, ctx[0]->ev_out)))
-        return rc;
+    if ((rc = dev_begin(br, ctx[0], stream, false))) return rc;
+    if (!stream)
+        for (int d = 1; d < n_ctx; ++d) ctx[d]->null_pending = true;
     MultiCall mc{ctx, n_ctx, d_theta, n_pts, d_nll, d_grad, nullptr};
     if ((rc = run_multi(mc, br.work))) return rc;
     return bridge_end(br);
@@ -2244,7 +2276,9 @@ int nr_eval_nll_multi(nr_ctx* const* ctx, int n_ctx, const double* const* theta,
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
         if ((rc = ensure_batch(c, n_pts[d], 0))) return rc;
+        if (c->null_pending) ctx[0]->null_pending = true;  // all run on ctx[0]'s stream
     }
+    if ((rc = own_stream(ctx[0]))) return rc;
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
         HIPCHK(hipMemcpyAsync(c->d_bth, theta[d], sizeof(double) * n_pts[d] * NR_NTHETA,
@@ -2290,7 +2324,6 @@ struct nr_mlp {
     long step = 0;
     int train_cap = 0;
     hipStream_t stream = nullptr;
-    hipEvent_t ev_in = nullptr, ev_out = nullptr;
 };
 
 namespace {
@@ -2305,6 +2338,7 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
             if ((rc = dalloc(&q->z[l], (size_t)cap * q->H))) return rc;
             HIPCHK(nr::launch_fill_ones_col(q->h[l], cap, q->H + 8, q->H, q->stream));
         }
+        HIPCHK(hipStreamSynchronize(q->stream));  // the callers use other streams
         const int nnt = (q->n_out + 127) / 128;
         if ((rc = dalloc(&q->part, (size_t)cap * nnt))) return rc;
         if ((rc = dalloc(&q->outside, (size_t)cap))) return rc;
@@ -2447,8 +2481,6 @@ int nr_mlp_create(int device, int hidden, int n_out, nr_mlp** out) {
     q->n_params = q->off[4];
     hipError_t e = hipSetDevice(device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&q->stream, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&q->ev_in, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&q->ev_out, hipEventDisableTiming);
     if (e != hipSuccess) {
         delete q;
         return fail(NR_EHIP, "mlp stream: %s", hipGetErrorString(e));
@@ -2475,15 +2507,13 @@ void nr_mlp_destroy(nr_mlp* q) {
     const ApiLock api_lock;
     if (!q) return;
     (void)hipSetDevice(q->device);
-    (void)hipStreamSynchronize(q->stream);
+    (void)hipDeviceSynchronize();
     dfree(&q->w); dfree(&q->g); dfree(&q->m); dfree(&q->v); dfree(&q->w16);
     dfree(&q->w16t);
     dfree(&q->x); dfree(&q->dy); dfree(&q->dz[0]); dfree(&q->dz[1]);
     for (int l = 0; l < 3; ++l) { dfree(&q->h[l]); dfree(&q->z[l]); }
     dfree(&q->tile_loss); dfree(&q->part); dfree(&q->outside);
     dfree(&q->mean); dfree(&q->stdv); dfree(&q->gpart);
-    if (q->ev_in) (void)hipEventDestroy(q->ev_in);
-    if (q->ev_out) (void)hipEventDestroy(q->ev_out);
     (void)hipStreamDestroy(q->stream);
     delete q;
 }
@@ -2555,12 +2585,9 @@ int nr_mlp_targets_dev(nr_mlp* q, const double* d_mu, int P, float* d_t, void* s
     const ApiLock api_lock;
     if (!q || !d_mu || !d_t || P <= 0) return fail(NR_EINVAL, "bad argument");
     HIPCHK(hipSetDevice(q->device));
-    nr::TargetArgs a{d_mu, P, q->n_out, q->mean, q->stdv, d_t};
-    Bridge br;
-    int rc;
-    if ((rc = bridge_begin(br, stream, q->stream, q->ev_in, q->ev_out))) return rc;
-    HIPCHK(nr::launch_targets(a, br.work));
-    return bridge_end(br);
+    const nr::TargetArgs a{d_mu, P, q->n_out, q->mean, q->stdv, d_t};
+    HIPCHK(nr::launch_targets(a, (hipStream_t)stream));
+    return 0;
 }
 
 int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
@@ -2571,9 +2598,7 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
     HIPCHK(hipSetDevice(q->device));
     int rc;
     if ((rc = mlp_alloc_batch(q, B, true))) return rc;
-    Bridge br;
-    if ((rc = bridge_begin(br, stream, q->stream, q->ev_in, q->ev_out))) return rc;
-    hipStream_t s = br.work;
+    hipStream_t s = (hipStream_t)stream;
     const int H = q->H, ldh = H + 8, N = q->n_out;
     if ((rc = mlp_input(q, d_theta, B, s))) return rc;
     if ((rc = mlp_hidden_forward(q, B, s))) return rc;
@@ -2629,7 +2654,6 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
     ad.bc2 = 1.0f - powf(0.999f, (float)q->step);
     HIPCHK(nr::launch_adam(ad, s));
     if ((rc = mlp_transpose(q, s))) return rc;
-    if ((rc = bridge_end(br))) return rc;
     if (loss) {
         const int tiles = ((B + 127) / 128) * ((N + 127) / 128);
         std::vector<double> tl(tiles);
@@ -2651,9 +2675,7 @@ int nr_mlp_logmu_dev(nr_mlp* q, const double* d_theta, int B, float* d_logmu,
     HIPCHK(hipSetDevice(q->device));
     int rc;
     if ((rc = mlp_alloc_batch(q, B, false))) return rc;
-    Bridge br;
-    if ((rc = bridge_begin(br, stream, q->stream, q->ev_in, q->ev_out))) return rc;
-    hipStream_t s = br.work;
+    hipStream_t s = (hipStream_t)stream;
     const int ldh = q->H + 8;
     if ((rc = mlp_input(q, d_theta, B, s))) return rc;
     if ((rc = mlp_hidden_forward(q, B, s))) return rc;
@@ -2663,7 +2685,7 @@ int nr_mlp_logmu_dev(nr_mlp* q, const double* d_theta, int B, float* d_logmu,
     go.C32 = d_logmu;
     go.ldc = q->n_out;
     HIPCHK(nr::launch_mlp_gemm(nr::kMlpLogMu, go, s));
-    return bridge_end(br);
+    return 0;
 }
 
 int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
@@ -2677,9 +2699,7 @@ int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
     if (c->n_reco != q->n_out) return fail(NR_EINVAL, "surrogate outputs %d bins, data has %d", q->n_out, c->n_reco);
     HIPCHK(hipSetDevice(q->device));
     if ((rc = mlp_alloc_batch(q, B, false))) return rc;
-    Bridge br;
-    if ((rc = bridge_begin(br, stream, q->stream, q->ev_in, q->ev_out))) return rc;
-    hipStream_t s = br.work;
+    hipStream_t s = (hipStream_t)stream;
     const int ldh = q->H + 8;
     // bin groups per point tile: about two work-groups per compute unit
     const int n_pt = (B + 127) / 128;
@@ -2717,7 +2737,7 @@ int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
     }
     f.nll = d_nll;
     HIPCHK(nr::launch_finalize(f, s));
-    return bridge_end(br);
+    return 0;
 }
 
 int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
@@ -2730,7 +2750,7 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
     if ((rc = set_device(c))) return rc;
     if ((rc = ensure_batch(c, n_pts, 0))) return rc;
     Bridge br;
-    if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
+    if ((rc = dev_begin(br, c, stream, false))) return rc;
     nr_ctx* cs[1] = {c};
     const double* ths[1] = {d_theta};
     double* nls[1] = {c->d_bnll};
@@ -2771,6 +2791,7 @@ static int build_records(nr_ctx* c) {
 
 static int build_templates(nr_ctx* c) {
     int rc;
+    if ((rc = own_stream(c))) return rc;
     hipError_t e = hipSuccess;
     if (!c->multi) {
         if (!c->tmpl_ok) return build_records(c);
@@ -2898,7 +2919,7 @@ int nr_eval_nll_templates_dev(nr_ctx* c, const double* d_theta, int n_pts,
     if ((rc = set_device(c))) return rc;
     if ((rc = ensure_tmpl(c, n_pts, d_grad != nullptr))) return rc;
     Bridge br;
-    if ((rc = bridge_begin(br, stream, c->stream, c->ev_in, c->ev_out))) return rc;
+    if ((rc = dev_begin(br, c, stream, false))) return rc;
     if ((rc = enqueue_tmpl(c, d_theta, n_pts, d_nll, d_grad, nullptr, br.work))) return rc;
     return bridge_end(br);
 }
@@ -2908,7 +2929,7 @@ static int tmpl_sync(nr_ctx* c, const double* theta, int n_pts, double* nll,
     int rc;
     if ((rc = check_ready(c))) return rc;
     if ((rc = check_theta(theta, n_pts, c->n_theta))) return rc;
-    if ((rc = set_device(c))) return rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     if (!mu) {
         // -2lnL out through pinned host memory the kernels write to; theta,
         // which every slice reads, copied in once
