@@ -5,6 +5,7 @@
 #include "ess.h"
 #include "mlp.h"
 #include "shared.h"
+#include "train.h"
 #include "../../include/nureweight.h"
 
 #include <algorithm>
@@ -2313,6 +2314,10 @@ struct nr_mlp {
     nr::bf16 *x = nullptr, *h[3] = {nullptr, nullptr, nullptr};
     float* z[3] = {nullptr, nullptr, nullptr};
     nr::bf16 *dy = nullptr, *dz[2] = {nullptr, nullptr};
+    // operands of the fused step's weight gradients, rows of cap values: input,
+    // activations, output and hidden gradients, transposed
+    nr::bf16 *xt = nullptr, *ht[3] = {nullptr, nullptr, nullptr}, *dyt = nullptr;
+    nr::bf16* dzt[3] = {nullptr, nullptr, nullptr};
     double* tile_loss = nullptr;
     double* part = nullptr;
     float* gpart = nullptr;     // K-split weight-gradient slabs
@@ -2352,6 +2357,18 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
         if ((rc = dalloc(&q->dz[1], (size_t)cap * q->H))) return rc;
         const int tiles = (cap / 128) * ((q->n_out + 127) / 128);
         if ((rc = dalloc(&q->tile_loss, (size_t)tiles))) return rc;
+        if (q->H == nr::kFusedHidden) {
+            if ((rc = dalloc(&q->xt, (size_t)cap * 32)) ||
+                (rc = dalloc(&q->dyt, (size_t)cap * q->n_out)))
+                return rc;
+            for (int l = 0; l < 3; ++l) {
+                if ((rc = dalloc(&q->ht[l], (size_t)cap * (q->H + 8))) ||
+                    (rc = dalloc(&q->dzt[l], (size_t)cap * q->H)))
+                    return rc;
+                HIPCHK(nr::launch_train_ones(q->ht[l], q->H, cap, q->stream));
+            }
+            HIPCHK(hipStreamSynchronize(q->stream));
+        }
         q->train_cap = cap;
     }
     return 0;
@@ -2374,6 +2391,16 @@ nr::MlpGemm mg(const nr::bf16* A, long sam, long sak, const nr::bf16* B,
     return g;
 }
 
+// Chunks a product's reduction is summed in: enough 128 x 128 tiles x chunks to
+// fill the chip about twice, chunks of at least 64.
+nr::TrainSplit mlp_split(int M, int N, int K) {
+    constexpr int kTK = 32, kTile = 128, kMinChunk = 64;
+    const int tiles = ((M + kTile - 1) / kTile) * ((N + kTile - 1) / kTile);
+    const int n = std::max(1, std::min((512 + tiles - 1) / tiles, K / kMinChunk));
+    const int chunk = ((K + n - 1) / n + kTK - 1) / kTK * kTK;
+    return {chunk, (K + chunk - 1) / chunk};
+}
+
 // A GEMM with a long reduction and few output tiles — the weight gradients
 // G^T = dZ^T H (K = batch; 256 x 264 for a hidden layer: 6 tiles) and the
 // first backward product dY W (K = the 4096 outputs) — is split along K
@@ -2383,17 +2410,14 @@ nr::MlpGemm mg(const nr::bf16* A, long sam, long sak, const nr::bf16* B,
 // C32, or SiLU' into g.C16).  No float atomics: a training step stays
 // bitwise reproducible.
 int mlp_split_gemm(nr_mlp* q, nr::MlpGemm g, int mode, float* C32, long ldc, hipStream_t s) {
-    constexpr int kTK = 32, kTile = 128, kMinChunk = 64;
-    const int tiles = ((g.M + kTile - 1) / kTile) * ((g.N + kTile - 1) / kTile);
-    int n_split = std::max(1, std::min((512 + tiles - 1) / tiles, g.K / kMinChunk));
+    const nr::TrainSplit sp = mlp_split(g.M, g.N, g.K);
+    const int n_split = sp.n_split, chunk = sp.chunk;
     if (n_split <= 1) {
         g.C32 = C32;
         g.ldc = ldc;
         HIPCHK(nr::launch_mlp_gemm(mode, g, s));
         return 0;
     }
-    const int chunk = ((g.K + n_split - 1) / n_split + kTK - 1) / kTK * kTK;
-    n_split = (g.K + chunk - 1) / chunk;
     const long ldp = g.N;                 // slab rows
     const long slab = (long)g.M * ldp;
     const size_t need = (size_t)n_split * slab;
@@ -2440,6 +2464,68 @@ int mlp_hidden_forward(nr_mlp* q, int B, hipStream_t s) {
         g.ldc16 = ldh;
         HIPCHK(nr::launch_mlp_gemm(nr::kMlpSilu, g, s));
     }
+    return 0;
+}
+
+// One training step of a network of kFusedHidden units, but for the step count:
+// the sums and roundings of the layer-by-layer step in five launches.
+int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamArgs& ad, int B,
+                    hipStream_t s) {
+    const int H = q->H, N = q->n_out;
+    nr::TrainBufs b{};
+    b.xt = q->xt;
+    for (int l = 0; l < 3; ++l) {
+        b.ht[l] = q->ht[l];
+        b.z[l] = q->z[l];
+        b.dzt[l] = q->dzt[l];
+    }
+    b.h2 = q->h[2];
+    b.dy = q->dy;
+    b.dyt = q->dyt;
+    b.dz2 = q->dz[0];
+    b.ldt = q->cap;
+    nr::TrainFwd f{};
+    f.theta = th;
+    for (int i = 0; i < NR_NTHETA; ++i) {
+        f.lo[i] = q->lo[i];
+        f.hi[i] = q->hi[i];
+    }
+    for (int l = 0; l < 3; ++l) {
+        f.w[l] = q->w16 + q->off[l];
+        f.k[l] = q->kp[l];
+    }
+    f.B = B;
+    f.b = b;
+    HIPCHK(nr::launch_train_fwd(f, s));
+    HIPCHK(nr::launch_train_mse({q->w16 + q->off[3], t, B, N, 1.0f / ((float)B * (float)N),
+                                 q->tile_loss, b}, s));
+    HIPCHK(nr::launch_train_dh({q->w16t + q->off[3], B, N, mlp_split(B, H, N), b}, s));
+    HIPCHK(nr::launch_train_hidden({{q->w16t + q->off[2], q->w16t + q->off[1]}, B,
+                                    mlp_split(B, H, H), b}, s));
+    nr::TrainW w{};
+    for (int l = 0; l < 4; ++l) {
+        nr::TrainLayer& L = w.l[l];
+        L.A = l == 3 ? q->dyt : q->dzt[l];
+        L.Bm = l == 0 ? q->xt : q->ht[l - 1];
+        L.M = q->nn[l];
+        L.N = q->kp[l];
+        L.sp = mlp_split(L.M, L.N, B);
+        L.w = q->w + q->off[l];
+        L.g = q->g + q->off[l];
+        L.m = q->m + q->off[l];
+        L.v = q->v + q->off[l];
+        L.w16 = q->w16 + q->off[l];
+        L.w16t = l ? q->w16t + q->off[l] : nullptr;
+    }
+    w.B = B;
+    w.ldt = q->cap;
+    w.lr = ad.lr;
+    w.b1 = ad.b1;
+    w.b2 = ad.b2;
+    w.eps = ad.eps;
+    w.bc1 = ad.bc1;
+    w.bc2 = ad.bc2;
+    HIPCHK(nr::launch_train_w(w, s));
     return 0;
 }
 
@@ -2512,6 +2598,8 @@ void nr_mlp_destroy(nr_mlp* q) {
     dfree(&q->w16t);
     dfree(&q->x); dfree(&q->dy); dfree(&q->dz[0]); dfree(&q->dz[1]);
     for (int l = 0; l < 3; ++l) { dfree(&q->h[l]); dfree(&q->z[l]); }
+    for (int l = 0; l < 3; ++l) { dfree(&q->ht[l]); dfree(&q->dzt[l]); }
+    dfree(&q->xt); dfree(&q->dyt);
     dfree(&q->tile_loss); dfree(&q->part); dfree(&q->outside);
     dfree(&q->mean); dfree(&q->stdv); dfree(&q->gpart);
     (void)hipStreamDestroy(q->stream);
@@ -2600,45 +2688,7 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
     if ((rc = mlp_alloc_batch(q, B, true))) return rc;
     hipStream_t s = (hipStream_t)stream;
     const int H = q->H, ldh = H + 8, N = q->n_out;
-    if ((rc = mlp_input(q, d_theta, B, s))) return rc;
-    if ((rc = mlp_hidden_forward(q, B, s))) return rc;
-    // output layer with the MSE gradient in the epilogue
-    nr::MlpGemm go = mg(q->h[2], ldh, 1, q->w16 + q->off[3], 1, ldh, B, N, ldh);
-    go.aux = d_t;
-    go.ldaux = N;
-    go.C16 = q->dy;
-    go.ldc16 = N;
-    go.scale = 1.0f / ((float)B * (float)N);
-    go.tile_loss = q->tile_loss;
-    HIPCHK(nr::launch_mlp_gemm(nr::kMlpMse, go, s));
-    // output layer weight gradient: G3^T = dY^T H2
-    if ((rc = mlp_split_gemm(q, mg(q->dy, 1, N, q->h[2], ldh, 1, N, ldh, B),
-                             nr::kMlpStore32, q->g + q->off[3], ldh, s)))
-        return rc;
-    // back through the hidden layers
-    const nr::bf16* up = q->dy;   // gradient w.r.t. the next layer's output
-    int upw = N;                  // its width
-    for (int l = 2; l >= 0; --l) {
-        nr::bf16* dzl = q->dz[l & 1];
-        // dZ_l = (up W_{l+1}) * SiLU'(Z_l): W_{l+1}(k, n) from the transposed
-        // copy [kp][nn], contiguous along the reduction index k
-        nr::MlpGemm gd = mg(up, upw, 1, q->w16t + q->off[l + 1], 1, q->nn[l + 1],
-                            B, H, upw);
-        gd.aux = q->z[l];
-        gd.ldaux = H;
-        gd.C16 = dzl;
-        gd.ldc16 = H;
-        if ((rc = mlp_split_gemm(q, gd, nr::kMlpDSilu, nullptr, 0, s))) return rc;
-        // G_l^T = dZ_l^T H_{l-1}  (H_{-1} = x)
-        const nr::bf16* in = l == 0 ? q->x : q->h[l - 1];
-        const int kin = l == 0 ? 32 : ldh;
-        if ((rc = mlp_split_gemm(q, mg(dzl, 1, H, in, kin, 1, H, q->kp[l], B),
-                                 nr::kMlpStore32, q->g + q->off[l], q->kp[l], s)))
-            return rc;
-        up = dzl;
-        upw = H;
-    }
-    q->step += 1;
+    const float step = (float)(q->step + 1);
     nr::AdamArgs ad{};
     ad.w = q->w;
     ad.w16 = q->w16;
@@ -2650,10 +2700,53 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
     ad.b1 = 0.9f;
     ad.b2 = 0.999f;
     ad.eps = 1e-8f;
-    ad.bc1 = 1.0f - powf(0.9f, (float)q->step);
-    ad.bc2 = 1.0f - powf(0.999f, (float)q->step);
-    HIPCHK(nr::launch_adam(ad, s));
-    if ((rc = mlp_transpose(q, s))) return rc;
+    ad.bc1 = 1.0f - powf(0.9f, step);
+    ad.bc2 = 1.0f - powf(0.999f, step);
+    if (H == nr::kFusedHidden) {
+        if ((rc = mlp_train_fused(q, d_theta, d_t, ad, B, s))) return rc;
+    } else {
+        if ((rc = mlp_input(q, d_theta, B, s))) return rc;
+        if ((rc = mlp_hidden_forward(q, B, s))) return rc;
+        // output layer with the MSE gradient in the epilogue
+        nr::MlpGemm go = mg(q->h[2], ldh, 1, q->w16 + q->off[3], 1, ldh, B, N, ldh);
+        go.aux = d_t;
+        go.ldaux = N;
+        go.C16 = q->dy;
+        go.ldc16 = N;
+        go.scale = 1.0f / ((float)B * (float)N);
+        go.tile_loss = q->tile_loss;
+        HIPCHK(nr::launch_mlp_gemm(nr::kMlpMse, go, s));
+        // output layer weight gradient: G3^T = dY^T H2
+        if ((rc = mlp_split_gemm(q, mg(q->dy, 1, N, q->h[2], ldh, 1, N, ldh, B),
+                                 nr::kMlpStore32, q->g + q->off[3], ldh, s)))
+            return rc;
+        // back through the hidden layers
+        const nr::bf16* up = q->dy;   // gradient w.r.t. the next layer's output
+        int upw = N;                  // its width
+        for (int l = 2; l >= 0; --l) {
+            nr::bf16* dzl = q->dz[l & 1];
+            // dZ_l = (up W_{l+1}) * SiLU'(Z_l): W_{l+1}(k, n) from the transposed
+            // copy [kp][nn], contiguous along the reduction index k
+            nr::MlpGemm gd = mg(up, upw, 1, q->w16t + q->off[l + 1], 1, q->nn[l + 1],
+                                B, H, upw);
+            gd.aux = q->z[l];
+            gd.ldaux = H;
+            gd.C16 = dzl;
+            gd.ldc16 = H;
+            if ((rc = mlp_split_gemm(q, gd, nr::kMlpDSilu, nullptr, 0, s))) return rc;
+            // G_l^T = dZ_l^T H_{l-1}  (H_{-1} = x)
+            const nr::bf16* in = l == 0 ? q->x : q->h[l - 1];
+            const int kin = l == 0 ? 32 : ldh;
+            if ((rc = mlp_split_gemm(q, mg(dzl, 1, H, in, kin, 1, H, q->kp[l], B),
+                                     nr::kMlpStore32, q->g + q->off[l], q->kp[l], s)))
+                return rc;
+            up = dzl;
+            upw = H;
+        }
+        HIPCHK(nr::launch_adam(ad, s));
+        if ((rc = mlp_transpose(q, s))) return rc;
+    }
+    q->step += 1;
     if (loss) {
         const int tiles = ((B + 127) / 128) * ((N + 127) / 128);
         std::vector<double> tl(tiles);

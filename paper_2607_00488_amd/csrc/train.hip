@@ -1,0 +1,534 @@
+// Training step of the surrogate network on gfx950 (train.h), for hidden layers
+// of 256 outputs.  The products, the order of their sums and every rounding are
+// those of the layer-by-layer GEMMs with K-split slabs that networks of other
+// widths run; what is fused is the passes between them.
+//
+// Matrix operands come straight from memory (L2) into the registers of
+// v_mfma_f32_32x32x16_bf16: a fragment is 32 rows x 16 reduction indices, lane
+// (li, lh) holding indices 8 lh .. 8 lh + 7 of row li, one 16-byte load.
+#include "train.h"
+
+#include <cmath>
+
+namespace nr {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int H = kFusedHidden;
+constexpr int kKp = H + 8;         // padded input width of layers 1 to 3
+constexpr int kRows = 32;          // points per work-group of the chained layers
+constexpr int kLda = H + 24;       // LDS row (bf16): 16-byte aligned, zeros to 272
+constexpr int kThreads = 256;
+
+__device__ inline bf16x8 frag(const bf16* p) {
+    const uint4 v = *reinterpret_cast<const uint4*>(p);
+    return *reinterpret_cast<const bf16x8*>(&v);
+}
+__device__ inline bf16x8 zero8() {
+    const uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    return *reinterpret_cast<const bf16x8*>(&v);
+}
+__device__ inline f32x16 zero16() {
+    f32x16 v;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[r] = 0.f;
+    return v;
+}
+// row of register r in a 32 x 32 block
+__device__ inline int blk_row(int r, int lh) { return (r >> 2) * 8 + lh * 4 + (r & 3); }
+
+// d rounded once to BF16: through the float with an odd last bit where d lies
+// between two floats (the conversion the stand-alone input kernel compiles to).
+__device__ inline bf16 bf16_of(double d) {
+    const float f = (float)d;
+    const double b = (double)f;
+    unsigned u = __float_as_uint(f);
+    if (b != d && !(u & 1u)) u += fabs(d) > fabs(b) ? 1u : ~0u;
+    return (bf16)__uint_as_float(u);
+}
+
+__device__ inline float silu(float z) {
+    return z * __builtin_amdgcn_rcpf(1.f + __expf(-z));
+}
+__device__ inline float dsilu(float v, float z) {
+    const float sg = 1.f / (1.f + __expf(-z));
+    return v * sg * (1.f + z * (1.f - sg));
+}
+
+// Columns [0, n_col) of the points in LDS, as rows of a transposed buffer:
+// eight points per 16-byte store.
+__device__ inline void store_t(const bf16 (*As)[kLda], int n_col, bf16* dst, int ldt, int m0, int B) {
+    for (int c = threadIdx.x; c < n_col * (kRows / 8); c += kThreads) {
+        const int col = c / (kRows / 8), p = c % (kRows / 8) * 8;
+        if (m0 + p >= B) continue;
+        bf16 v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = As[p + e][col];
+        *reinterpret_cast<uint4*>(dst + (size_t)col * ldt + m0 + p) = *reinterpret_cast<const uint4*>(v);
+    }
+}
+
+// --------------------------------------------------------------- forward
+// Input map and the three hidden layers of 32 points per work-group, the
+// activations in LDS: wave w forms outputs 64 w .. 64 w + 63 (points as the row
+// operand; the weights six K-steps ahead).  Bound by the latency of the weights (286 KB from L2 per
+// work-group).
+template <int NKS>
+__device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ W, int K,
+                                          float* z, int m0, int B) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    constexpr int D = NKS < 6 ? NKS : 6;
+    bf16x8 ring[D][2];
+    // k clamped into the row: columns past K meet the tile's zero columns
+    auto wload = [&](int ks, bf16x8 out[2]) {
+        const int k = min(ks * 16 + lh * 8, K - 8);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) out[y] = frag(W + (size_t)(wave * 64 + y * 32 + li) * K + k);
+    };
+#pragma unroll
+    for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
+    f32x16 acc[2] = {zero16(), zero16()};
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        const bf16x8 b0 = ring[ks % D][0], b1 = ring[ks % D][1];
+        if (ks + D < NKS) wload(ks + D, ring[ks % D]);
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&As[li][ks * 16 + lh * 8]);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, acc[1], 0, 0, 0);
+    }
+    __syncthreads();  // every wave has read this layer's input
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int p = blk_row(r, lh), o = wave * 64 + y * 32 + li;
+            As[p][o] = (bf16)silu(acc[y][r]);
+            if (m0 + p < B) z[(size_t)(m0 + p) * H + o] = acc[y][r];
+        }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kThreads) void k_train_fwd(TrainFwd a) {
+    __shared__ __attribute__((aligned(16))) bf16 As[kRows][kLda];
+    const int tid = threadIdx.x, m0 = blockIdx.x * kRows;
+    for (int q = tid; q < kRows * (kLda / 8); q += kThreads)
+        *reinterpret_cast<uint4*>(&As[q / (kLda / 8)][q % (kLda / 8) * 8]) = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    if (tid < kRows) {
+        const double* th = a.theta + (size_t)min(m0 + tid, a.B - 1) * kNTheta;
+        for (int i = 0; i < kNTheta; ++i)
+            As[tid][i] = bf16_of(2.0 * (th[i] - a.lo[i]) / (a.hi[i] - a.lo[i]) - 1.0);
+        As[tid][kNTheta] = (bf16)1.f;
+        As[tid][H] = (bf16)1.f;  // the bias input of the later layers
+    }
+    __syncthreads();
+    store_t(As, 32, a.b.xt, a.b.ldt, m0, a.B);
+    fwd_layer<2>(As, a.w[0], a.k[0], a.b.z[0], m0, a.B);
+    store_t(As, H, a.b.ht[0], a.b.ldt, m0, a.B);
+    fwd_layer<17>(As, a.w[1], a.k[1], a.b.z[1], m0, a.B);
+    store_t(As, H, a.b.ht[1], a.b.ldt, m0, a.B);
+    fwd_layer<17>(As, a.w[2], a.k[2], a.b.z[2], m0, a.B);
+    store_t(As, H, a.b.ht[2], a.b.ldt, m0, a.B);
+    for (int c = tid; c < kRows * (H / 8); c += kThreads) {
+        const int r = c / (H / 8), k = c % (H / 8) * 8;
+        if (m0 + r < a.B)
+            *reinterpret_cast<uint4*>(a.b.h2 + (size_t)(m0 + r) * kKp + k) =
+                *reinterpret_cast<const uint4*>(&As[r][k]);
+    }
+}
+
+// ---------------------------------------------------- output layer, loss
+// 128 points x 128 outputs per work-group, waves 2 x 2; the targets of a wave's
+// block are loaded before its products.  d(loss)/dY leaves twice, as rows of
+// points and as rows of outputs, each through LDS in whole 256-byte runs.  Bound
+// by those streams (targets 4 B, dY 2 x 2 B per output).
+constexpr int kTS = 128 + 8;  // LDS row of a staged tile
+
+__global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
+    __shared__ __attribute__((aligned(16))) bf16 T1[128][kTS];  // [point][output]
+    __shared__ __attribute__((aligned(16))) bf16 T2[128][kTS];  // [output][point]
+    __shared__ double red[4];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
+    const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
+    const int n_last = a.N - 1, m_last = a.B - 1 - m0;  // last valid row of the tile
+    float t[2][2][16];
+    const float* tb = a.t + (size_t)m0 * a.N;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const unsigned row = (unsigned)min(wm * 64 + x * 32 + blk_row(r, lh), m_last) * (unsigned)a.N;
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                t[x][y][r] = tb[row + (unsigned)min(n0 + wn * 64 + y * 32 + li, n_last)];
+        }
+    const bf16 *ap[2], *bp[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        ap[x] = a.b.h2 + (size_t)(m0 + min(wm * 64 + x * 32 + li, m_last)) * kKp;
+        bp[x] = a.w + (size_t)min(n0 + wn * 64 + x * 32 + li, n_last) * kKp;
+    }
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = zero16();
+    constexpr int NKS = (kKp + 15) / 16, D = 3;
+    bf16x8 fa[D][2], fb[D][2];
+    auto load = [&](int ks, bf16x8 u[2], bf16x8 v[2]) {
+        const int k = min(ks * 16 + lh * 8, kKp - 8);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            u[x] = frag(ap[x] + k);
+            v[x] = frag(bp[x] + k);
+        }
+    };
+#pragma unroll
+    for (int ks = 0; ks < D; ++ks) load(ks, fa[ks], fb[ks]);
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        bf16x8 u[2], v[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            // the second half of the last step lies past the columns
+            u[x] = ks == NKS - 1 && lh ? zero8() : fa[ks % D][x];
+            v[x] = fb[ks % D][x];
+        }
+        if (ks + D < NKS) load(ks + D, fa[ks % D], fb[ks % D]);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(u[x], v[y], acc[x][y], 0, 0, 0);
+    }
+    double lsum = 0.0;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            const int nl = wn * 64 + y * 32 + li;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                bf16 d[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 4 * q + e, ml = wm * 64 + x * 32 + blk_row(r, lh);
+                    const float rr = acc[x][y][r] - t[x][y][r];
+                    d[e] = (bf16)(a.scale * 2.f * rr);
+                    if (ml <= m_last && n0 + nl <= n_last) lsum += (double)rr * rr;
+                    T1[ml][nl] = d[e];
+                }
+                *reinterpret_cast<uint2*>(&T2[nl][wm * 64 + x * 32 + 8 * q + 4 * lh]) =
+                    *reinterpret_cast<const uint2*>(d);
+            }
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o, 64);
+    if (lane == 0) red[wave] = lsum;
+    __syncthreads();
+    if (tid == 0)
+        a.tile_loss[blockIdx.y * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = tid + i * kThreads, row = c >> 4, k = (c & 15) * 8;
+        if (row <= m_last && n0 + k < a.N)
+            *reinterpret_cast<uint4*>(a.b.dy + (size_t)(m0 + row) * a.N + n0 + k) =
+                *reinterpret_cast<const uint4*>(&T1[row][k]);
+        if (n0 + row < a.N && k <= m_last)
+            *reinterpret_cast<uint4*>(a.b.dyt + (size_t)(n0 + row) * a.b.ldt + m0 + k) =
+                *reinterpret_cast<const uint4*>(&T2[row][k]);
+    }
+}
+
+// ------------------------------------------------------- split products
+// One tile of C[m][n] = sum_k A[m][k] B[n][k], both rows contiguous along k, the
+// sum taken in chunks: round by round every wave forms one chunk of the whole
+// tile, then the threads add the round's chunks in order to their elements
+// (element tid + i T of the tile, rows of 32 BN).  No partial sums leave the
+// work-group, where the K-split GEMM wrote and read back a slab per chunk.
+template <int BM, int BN, int NW>
+struct SplitTile {
+    static constexpr int T = NW * 64, TM = 32 * BM, TN = 32 * BN, EPT = TM * TN / T;
+    static_assert(TM * TN % T == 0, "whole elements per thread");
+
+    static __device__ __forceinline__ void run(const bf16* __restrict__ A, size_t lda,
+                                               const bf16* __restrict__ B, size_t ldb, int M, int N,
+                                               int K, TrainSplit sp, int m0, int n0,
+                                               float (*part)[TM][TN], float v[EPT]) {
+        const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+        const bf16 *ap[BM], *bp[BN];
+#pragma unroll
+        for (int x = 0; x < BM; ++x) ap[x] = A + (size_t)min(m0 + 32 * x + li, M - 1) * lda + lh * 8;
+#pragma unroll
+        for (int y = 0; y < BN; ++y) bp[y] = B + (size_t)min(n0 + 32 * y + li, N - 1) * ldb + lh * 8;
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) v[i] = 0.f;
+        for (int q0 = 0; q0 < sp.n_split; q0 += NW) {
+            const int q = q0 + wave;
+            if (q < sp.n_split) {
+                const int kb = q * sp.chunk, ke = min(K, kb + sp.chunk);
+                f32x16 acc[BM][BN];
+#pragma unroll
+                for (int x = 0; x < BM; ++x)
+#pragma unroll
+                    for (int y = 0; y < BN; ++y) acc[x][y] = zero16();
+                struct Stage {  // 32 reduction indices
+                    bf16x8 a[2][BM], b[2][BN];
+                };
+                auto load = [&](int k, Stage& s) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                        for (int x = 0; x < BM; ++x) s.a[h][x] = frag(ap[x] + k + 16 * h);
+#pragma unroll
+                        for (int y = 0; y < BN; ++y) s.b[h][y] = frag(bp[y] + k + 16 * h);
+                    }
+                };
+                auto compute = [&](const Stage& s) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int x = 0; x < BM; ++x)
+#pragma unroll
+                            for (int y = 0; y < BN; ++y)
+                                acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    s.a[h][x], s.b[h][y], acc[x][y], 0, 0, 0);
+                };
+                const int nst = (ke - kb) / 32;
+                if (nst > 0) {
+                    Stage s0, s1;
+                    load(kb, s0);
+                    int i = 0;
+                    for (; i + 1 < nst; i += 2) {
+                        load(kb + (i + 1) * 32, s1);
+                        compute(s0);
+                        load(kb + min(i + 2, nst - 1) * 32, s0);
+                        compute(s1);
+                    }
+                    if (i < nst) compute(s0);
+                }
+                // the last indices, a multiple of eight: 16 at a time, fragments
+                // past the end zero (their address clamped)
+                for (int k = kb + nst * 32; k < ke; k += 16) {
+                    const bool ok = k + lh * 8 < ke;
+                    const int kc = min(k, ke - 8 - lh * 8);
+#pragma unroll
+                    for (int x = 0; x < BM; ++x) {
+                        const bf16x8 f = frag(ap[x] + kc), u = ok ? f : zero8();
+#pragma unroll
+                        for (int y = 0; y < BN; ++y) {
+                            const bf16x8 w = frag(bp[y] + kc);
+                            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                u, ok ? w : zero8(), acc[x][y], 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int x = 0; x < BM; ++x)
+#pragma unroll
+                    for (int y = 0; y < BN; ++y)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            part[wave][32 * x + blk_row(r, lh)][32 * y + li] = acc[x][y][r];
+            }
+            __syncthreads();
+            const int nq = min(NW, sp.n_split - q0);
+            for (int w = 0; w < nq; ++w) {
+                const float* p = &part[w][0][0];
+#pragma unroll
+                for (int i = 0; i < EPT; ++i) v[i] += p[tid + i * T];
+            }
+            __syncthreads();
+        }
+    }
+};
+
+// dZ_2 = (dY W_3) SiLU'(Z_2): 64 points x 64 units per work-group, eight waves.
+// Work-groups of the same points run on one XCD (eight apart), whose L2 then
+// serves dY to all four of them.
+typedef SplitTile<2, 2, 8> DhTile;
+
+__global__ __launch_bounds__(512) void k_train_dh(TrainDh a) {
+    __shared__ float part[8][DhTile::TM][DhTile::TN];
+    float v[DhTile::EPT];
+    const int u = blockIdx.x >> 3, n0 = (u & 3) * 64, m0 = ((u >> 2) * 8 + (blockIdx.x & 7)) * 64;
+    if (m0 >= a.B) return;
+    DhTile::run(a.b.dy, a.N, a.wt, a.N, a.B, H, a.N, a.sp, m0, n0, part, v);
+#pragma unroll
+    for (int i = 0; i < DhTile::EPT; ++i) {
+        const int e = threadIdx.x + i * DhTile::T, m = m0 + e / DhTile::TN, n = n0 + e % DhTile::TN;
+        if (m >= a.B) continue;
+        a.b.dz2[(size_t)m * H + n] = (bf16)dsilu(v[i], a.b.z[2][(size_t)m * H + n]);
+    }
+}
+
+// dZ_1 and dZ_0 of 32 points per work-group, as the forward chain; the chunks of
+// a layer's reduction are summed one after the other in registers.
+__device__ __forceinline__ void bwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ Wt, TrainSplit sp,
+                                          const float* z, int m0, int B) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    constexpr int NKS = H / 16, D = 6;
+    bf16x8 ring[D][2];
+    auto wload = [&](int ks, bf16x8 out[2]) {
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+            out[y] = frag(Wt + (size_t)(wave * 64 + y * 32 + li) * H + ks * 16 + lh * 8);
+    };
+#pragma unroll
+    for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
+    f32x16 zv[2];
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            zv[y][r] = z[(size_t)min(m0 + blk_row(r, lh), B - 1) * H + wave * 64 + y * 32 + li];
+    f32x16 acc[2] = {zero16(), zero16()}, v[2] = {zero16(), zero16()};
+    const int cks = sp.chunk / 16;
+    int left = cks;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) {
+        const bf16x8 b0 = ring[ks % D][0], b1 = ring[ks % D][1];
+        if (ks + D < NKS) wload(ks + D, ring[ks % D]);
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&As[li][ks * 16 + lh * 8]);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, acc[1], 0, 0, 0);
+        if (--left == 0 || ks == NKS - 1) {
+            left = cks;
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                v[y] += acc[y];
+                acc[y] = zero16();
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            As[blk_row(r, lh)][wave * 64 + y * 32 + li] = (bf16)dsilu(v[y][r], zv[y][r]);
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kThreads) void k_train_hidden(TrainHidden a) {
+    __shared__ __attribute__((aligned(16))) bf16 As[kRows][kLda];
+    const int tid = threadIdx.x, m0 = blockIdx.x * kRows;
+    for (int c = tid; c < kRows * (H / 8); c += kThreads) {
+        const int r = c / (H / 8), k = c % (H / 8) * 8;
+        *reinterpret_cast<uint4*>(&As[r][k]) =
+            *reinterpret_cast<const uint4*>(a.b.dz2 + (size_t)min(m0 + r, a.B - 1) * H + k);
+    }
+    __syncthreads();
+    store_t(As, H, a.b.dzt[2], a.b.ldt, m0, a.B);
+    bwd_layer(As, a.wt[0], a.sp, a.b.z[1], m0, a.B);
+    store_t(As, H, a.b.dzt[1], a.b.ldt, m0, a.B);
+    bwd_layer(As, a.wt[1], a.sp, a.b.z[0], m0, a.B);
+    store_t(As, H, a.b.dzt[0], a.b.ldt, m0, a.B);
+}
+
+// Every layer's weight gradient with its Adam step: 64 x 96 tiles of G, four
+// waves; the thread that ends up with an element of G updates its parameter, its
+// moments and its BF16 copies (the transposed one through LDS, in runs of 64).
+typedef SplitTile<2, 3, 4> WTile;
+
+__global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
+    __shared__ __attribute__((aligned(16))) union {
+        float part[4][WTile::TM][WTile::TN];
+        bf16 t[WTile::TN][WTile::TM + 8];
+    } sh;
+    int li = 3;
+    while (li > 0 && (int)blockIdx.x < a.l[li].first) --li;
+    const TrainLayer& L = a.l[li];
+    const int nt = (L.N + WTile::TN - 1) / WTile::TN, t = (int)blockIdx.x - L.first;
+    const int m0 = t / nt * WTile::TM, n0 = t % nt * WTile::TN;
+    float v[WTile::EPT];
+    WTile::run(L.A, a.ldt, L.Bm, a.ldt, L.M, L.N, a.B, L.sp, m0, n0, sh.part, v);
+#pragma unroll
+    for (int i = 0; i < WTile::EPT; ++i) {
+        const int e = threadIdx.x + i * WTile::T, ml = e / WTile::TN, nl = e % WTile::TN;
+        if (m0 + ml >= L.M || n0 + nl >= L.N) continue;
+        const size_t o = (size_t)(m0 + ml) * L.N + n0 + nl;
+        const float g = v[i];
+        // fused as the layer-by-layer step's Adam kernel is
+        const float m = fmaf(1.f - a.b1, g, a.b1 * L.m[o]);
+        const float s = fmaf(g, (1.f - a.b2) * g, a.b2 * L.v[o]);
+        const float w = L.w[o] - a.lr * (m / a.bc1) / (sqrtf(s / a.bc2) + a.eps);
+        L.g[o] = g;
+        L.m[o] = m;
+        L.v[o] = s;
+        L.w[o] = w;
+        L.w16[o] = (bf16)w;
+        sh.t[nl][ml] = (bf16)w;
+    }
+    if (!L.w16t) return;
+    __syncthreads();
+    for (int c = threadIdx.x; c < WTile::TN * (WTile::TM / 8); c += WTile::T) {
+        const int nl = c / (WTile::TM / 8), ml = c % (WTile::TM / 8) * 8;
+        if (n0 + nl < L.N && m0 + ml < L.M)
+            *reinterpret_cast<uint4*>(L.w16t + (size_t)(n0 + nl) * L.M + m0 + ml) =
+                *reinterpret_cast<const uint4*>(&sh.t[nl][ml]);
+    }
+}
+
+__global__ void k_train_ones(bf16* ht, int row0, int ldt) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= ldt) return;
+    for (int r = 0; r < 8; ++r) ht[(size_t)(row0 + r) * ldt + p] = (bf16)(r == 0 ? 1.f : 0.f);
+}
+
+bool split_ok(const TrainSplit& s, int K) {
+    return s.chunk > 0 && s.chunk % 32 == 0 && s.n_split > 0 && (long)s.chunk * s.n_split >= K &&
+           (long)s.chunk * (s.n_split - 1) < K;
+}
+
+}  // namespace
+
+hipError_t launch_train_fwd(const TrainFwd& a, hipStream_t s) {
+    if (a.B <= 0 || a.B % 8 || a.b.ldt < a.B || a.b.ldt % 8 || a.k[0] != 32 || a.k[1] != kKp ||
+        a.k[2] != kKp)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_train_fwd, dim3((a.B + kRows - 1) / kRows), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_mse(const TrainMse& a, hipStream_t s) {
+    if (a.N <= 0 || a.N % 8 || a.B % 8 || a.b.ldt < a.B || a.N >= (1 << 24))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_train_mse, dim3((a.N + 127) / 128, (a.B + 127) / 128), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_dh(const TrainDh& a, hipStream_t s) {
+    if (a.N % 8 || !split_ok(a.sp, a.N)) return hipErrorInvalidValue;
+    const int n_mt = (a.B + 63) / 64;
+    hipLaunchKernelGGL(k_train_dh, dim3((n_mt + 7) / 8 * 8 * 4), dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_hidden(const TrainHidden& a, hipStream_t s) {
+    if (!split_ok(a.sp, H)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_train_hidden, dim3((a.B + kRows - 1) / kRows), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_w(TrainW a, hipStream_t s) {
+    int n = 0;
+    for (int l = 0; l < 4; ++l) {
+        if (a.l[l].M % 8 || a.l[l].N % 8 || !split_ok(a.l[l].sp, a.B)) return hipErrorInvalidValue;
+        a.l[l].first = n;
+        n += ((a.l[l].M + WTile::TM - 1) / WTile::TM) * ((a.l[l].N + WTile::TN - 1) / WTile::TN);
+    }
+    hipLaunchKernelGGL(k_train_w, dim3(n), dim3(WTile::T), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_ones(bf16* ht, int row0, int ldt, hipStream_t s) {
+    hipLaunchKernelGGL(k_train_ones, dim3((ldt + 255) / 256), dim3(256), 0, s, ht, row0, ldt);
+    return hipGetLastError();
+}
+
+}  // namespace nr
