@@ -2314,10 +2314,13 @@ struct nr_mlp {
     nr::bf16 *x = nullptr, *h[3] = {nullptr, nullptr, nullptr};
     float* z[3] = {nullptr, nullptr, nullptr};
     nr::bf16 *dy = nullptr, *dz[2] = {nullptr, nullptr};
-    // operands of the fused step's weight gradients, rows of cap values: input,
-    // activations, output and hidden gradients, transposed
+    // matrices of the fused step (train.h): input, activations, output and hidden
+    // gradients, weights by outputs and by inputs (packed: they are up to date)
     nr::bf16 *xt = nullptr, *ht[3] = {nullptr, nullptr, nullptr}, *dyt = nullptr;
-    nr::bf16* dzt[3] = {nullptr, nullptr, nullptr};
+    nr::bf16 *h2f = nullptr, *dyf = nullptr, *dz2f = nullptr;
+    nr::bf16 *dzt[3] = {nullptr, nullptr, nullptr};
+    nr::bf16 *wf[4] = {}, *wt[4] = {};
+    bool packed = false;
     double* tile_loss = nullptr;
     double* part = nullptr;
     float* gpart = nullptr;     // K-split weight-gradient slabs
@@ -2352,22 +2355,31 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
     }
     if (train && B > q->train_cap) {
         const int cap = q->cap;
-        if ((rc = dalloc(&q->dy, (size_t)cap * q->n_out))) return rc;
-        if ((rc = dalloc(&q->dz[0], (size_t)cap * q->H))) return rc;
-        if ((rc = dalloc(&q->dz[1], (size_t)cap * q->H))) return rc;
         const int tiles = (cap / 128) * ((q->n_out + 127) / 128);
         if ((rc = dalloc(&q->tile_loss, (size_t)tiles))) return rc;
-        if (q->H == nr::kFusedHidden) {
-            if ((rc = dalloc(&q->xt, (size_t)cap * 32)) ||
-                (rc = dalloc(&q->dyt, (size_t)cap * q->n_out)))
+        const int H = q->H, N = q->n_out;
+        if (H == nr::kFusedHidden) {
+            if ((rc = dalloc(&q->xt, nr::frag_size(32, cap))) ||
+                (rc = dalloc(&q->dyt, nr::frag_size(N, cap))) ||
+                (rc = dalloc(&q->dyf, nr::frag_size(cap, N))) ||
+                (rc = dalloc(&q->h2f, nr::frag_size(cap, H + 8))) ||
+                (rc = dalloc(&q->dz2f, nr::frag_size(cap, H))))
                 return rc;
             for (int l = 0; l < 3; ++l) {
-                if ((rc = dalloc(&q->ht[l], (size_t)cap * (q->H + 8))) ||
-                    (rc = dalloc(&q->dzt[l], (size_t)cap * q->H)))
+                if ((rc = dalloc(&q->ht[l], nr::frag_size(H + 8, cap))) ||
+                    (rc = dalloc(&q->dzt[l], nr::frag_size(H, cap))))
                     return rc;
-                HIPCHK(nr::launch_train_ones(q->ht[l], q->H, cap, q->stream));
+                HIPCHK(nr::launch_train_ones(q->ht[l], nr::frag_steps(cap), q->stream));
             }
+            for (int l = 0; l < 4 && !q->wf[l]; ++l)
+                if ((rc = dalloc(&q->wf[l], nr::frag_size(q->nn[l], q->kp[l]))) ||
+                    (rc = dalloc(&q->wt[l], nr::frag_size(q->kp[l], q->nn[l]))))
+                    return rc;
             HIPCHK(hipStreamSynchronize(q->stream));
+        } else {
+            if ((rc = dalloc(&q->dy, (size_t)cap * N)) || (rc = dalloc(&q->dz[0], (size_t)cap * H)) ||
+                (rc = dalloc(&q->dz[1], (size_t)cap * H)))
+                return rc;
         }
         q->train_cap = cap;
     }
@@ -2472,6 +2484,11 @@ int mlp_hidden_forward(nr_mlp* q, int B, hipStream_t s) {
 int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamArgs& ad, int B,
                     hipStream_t s) {
     const int H = q->H, N = q->n_out;
+    if (!q->packed) {
+        for (int l = 0; l < 4; ++l)
+            HIPCHK(nr::launch_train_pack({q->w16 + q->off[l], q->wf[l], q->wt[l], q->nn[l], q->kp[l]}, s));
+        q->packed = true;
+    }
     nr::TrainBufs b{};
     b.xt = q->xt;
     for (int l = 0; l < 3; ++l) {
@@ -2479,28 +2496,25 @@ int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamA
         b.z[l] = q->z[l];
         b.dzt[l] = q->dzt[l];
     }
-    b.h2 = q->h[2];
-    b.dy = q->dy;
+    b.h2 = q->h2f;
+    b.dy = q->dyf;
     b.dyt = q->dyt;
-    b.dz2 = q->dz[0];
-    b.ldt = q->cap;
+    b.dz2 = q->dz2f;
+    b.steps = nr::frag_steps(q->cap);
     nr::TrainFwd f{};
     f.theta = th;
     for (int i = 0; i < NR_NTHETA; ++i) {
         f.lo[i] = q->lo[i];
         f.hi[i] = q->hi[i];
     }
-    for (int l = 0; l < 3; ++l) {
-        f.w[l] = q->w16 + q->off[l];
-        f.k[l] = q->kp[l];
-    }
+    for (int l = 0; l < 3; ++l) f.wf[l] = q->wf[l];
     f.B = B;
     f.b = b;
     HIPCHK(nr::launch_train_fwd(f, s));
-    HIPCHK(nr::launch_train_mse({q->w16 + q->off[3], t, B, N, 1.0f / ((float)B * (float)N),
+    HIPCHK(nr::launch_train_mse({q->wf[3], t, B, N, 1.0f / ((float)B * (float)N),
                                  q->tile_loss, b}, s));
-    HIPCHK(nr::launch_train_dh({q->w16t + q->off[3], B, N, mlp_split(B, H, N), b}, s));
-    HIPCHK(nr::launch_train_hidden({{q->w16t + q->off[2], q->w16t + q->off[1]}, B,
+    HIPCHK(nr::launch_train_dh({q->wt[3], B, N, mlp_split(B, H, N), b}, s));
+    HIPCHK(nr::launch_train_hidden({{q->wt[2], q->wt[1]}, B,
                                     mlp_split(B, H, H), b}, s));
     nr::TrainW w{};
     for (int l = 0; l < 4; ++l) {
@@ -2515,10 +2529,11 @@ int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamA
         L.m = q->m + q->off[l];
         L.v = q->v + q->off[l];
         L.w16 = q->w16 + q->off[l];
-        L.w16t = l ? q->w16t + q->off[l] : nullptr;
+        L.wf = q->wf[l];
+        L.wt = q->wt[l];
     }
     w.B = B;
-    w.ldt = q->cap;
+    w.steps = b.steps;
     w.lr = ad.lr;
     w.b1 = ad.b1;
     w.b2 = ad.b2;
@@ -2599,7 +2614,8 @@ void nr_mlp_destroy(nr_mlp* q) {
     dfree(&q->x); dfree(&q->dy); dfree(&q->dz[0]); dfree(&q->dz[1]);
     for (int l = 0; l < 3; ++l) { dfree(&q->h[l]); dfree(&q->z[l]); }
     for (int l = 0; l < 3; ++l) { dfree(&q->ht[l]); dfree(&q->dzt[l]); }
-    dfree(&q->xt); dfree(&q->dyt);
+    for (int l = 0; l < 4; ++l) { dfree(&q->wf[l]); dfree(&q->wt[l]); }
+    dfree(&q->xt); dfree(&q->dyt); dfree(&q->dyf); dfree(&q->h2f); dfree(&q->dz2f);
     dfree(&q->tile_loss); dfree(&q->part); dfree(&q->outside);
     dfree(&q->mean); dfree(&q->stdv); dfree(&q->gpart);
     (void)hipStreamDestroy(q->stream);
@@ -2623,6 +2639,7 @@ int nr_mlp_set_params(nr_mlp* q, const float* params, long n) {
     HIPCHK(hipStreamSynchronize(q->stream));
     HIPCHK(hipMemset(q->m, 0, sizeof(float) * n));
     HIPCHK(hipMemset(q->v, 0, sizeof(float) * n));
+    q->packed = false;
     q->step = 0;
     return 0;
 }

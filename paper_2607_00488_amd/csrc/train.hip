@@ -5,7 +5,8 @@
 //
 // Matrix operands come straight from memory (L2) into the registers of
 // v_mfma_f32_32x32x16_bf16: a fragment is 32 rows x 16 reduction indices, lane
-// (li, lh) holding indices 8 lh .. 8 lh + 7 of row li, one 16-byte load.
+// (li, lh) holding indices 8 lh .. 8 lh + 7 of row li, and every producer writes
+// its matrices in that order (train.h), so that a fragment is one 1 KB run.
 #include "train.h"
 
 #include <cmath>
@@ -58,16 +59,21 @@ __device__ inline float dsilu(float v, float z) {
     return v * sg * (1.f + z * (1.f - sg));
 }
 
-// Columns [0, n_col) of the points in LDS, as rows of a transposed buffer:
-// eight points per 16-byte store.
-__device__ inline void store_t(const bf16 (*As)[kLda], int n_col, bf16* dst, int ldt, int m0, int B) {
+// Fragment `step` of row block `rb` of a matrix in fragment order.
+__device__ inline bf16x8 frag_of(const bf16* x, int rb, int step, int steps) {
+    return frag(x + ((size_t)rb * steps + step) * 512 + (threadIdx.x & 63) * 8);
+}
+
+// Columns [0, n_col) of the points in LDS as rows of a matrix whose reduction
+// runs over the points: eight of them per 16-byte store.
+__device__ inline void store_t(const bf16 (*As)[kLda], int n_col, bf16* dst, int steps, int m0, int B) {
     for (int c = threadIdx.x; c < n_col * (kRows / 8); c += kThreads) {
-        const int col = c / (kRows / 8), p = c % (kRows / 8) * 8;
+        const int col = c % n_col, p = c / n_col * 8;
         if (m0 + p >= B) continue;
         bf16 v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = As[p + e][col];
-        *reinterpret_cast<uint4*>(dst + (size_t)col * ldt + m0 + p) = *reinterpret_cast<const uint4*>(v);
+        *reinterpret_cast<uint4*>(dst + frag_at(col, m0 + p, steps)) = *reinterpret_cast<const uint4*>(v);
     }
 }
 
@@ -77,16 +83,14 @@ __device__ inline void store_t(const bf16 (*As)[kLda], int n_col, bf16* dst, int
 // operand; the weights six K-steps ahead).  Bound by the latency of the weights (286 KB from L2 per
 // work-group).
 template <int NKS>
-__device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ W, int K,
-                                          float* z, int m0, int B) {
+__device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ W, float* z,
+                                          int m0, int B) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     constexpr int D = NKS < 6 ? NKS : 6;
     bf16x8 ring[D][2];
-    // k clamped into the row: columns past K meet the tile's zero columns
     auto wload = [&](int ks, bf16x8 out[2]) {
-        const int k = min(ks * 16 + lh * 8, K - 8);
 #pragma unroll
-        for (int y = 0; y < 2; ++y) out[y] = frag(W + (size_t)(wave * 64 + y * 32 + li) * K + k);
+        for (int y = 0; y < 2; ++y) out[y] = frag_of(W, wave * 2 + y, ks, NKS);
     };
 #pragma unroll
     for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
@@ -125,18 +129,19 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(TrainFwd a) {
         As[tid][H] = (bf16)1.f;  // the bias input of the later layers
     }
     __syncthreads();
-    store_t(As, 32, a.b.xt, a.b.ldt, m0, a.B);
-    fwd_layer<2>(As, a.w[0], a.k[0], a.b.z[0], m0, a.B);
-    store_t(As, H, a.b.ht[0], a.b.ldt, m0, a.B);
-    fwd_layer<17>(As, a.w[1], a.k[1], a.b.z[1], m0, a.B);
-    store_t(As, H, a.b.ht[1], a.b.ldt, m0, a.B);
-    fwd_layer<17>(As, a.w[2], a.k[2], a.b.z[2], m0, a.B);
-    store_t(As, H, a.b.ht[2], a.b.ldt, m0, a.B);
-    for (int c = tid; c < kRows * (H / 8); c += kThreads) {
-        const int r = c / (H / 8), k = c % (H / 8) * 8;
-        if (m0 + r < a.B)
-            *reinterpret_cast<uint4*>(a.b.h2 + (size_t)(m0 + r) * kKp + k) =
-                *reinterpret_cast<const uint4*>(&As[r][k]);
+    store_t(As, 32, a.b.xt, a.b.steps, m0, a.B);
+    fwd_layer<2>(As, a.wf[0], a.b.z[0], m0, a.B);
+    store_t(As, H, a.b.ht[0], a.b.steps, m0, a.B);
+    fwd_layer<17>(As, a.wf[1], a.b.z[1], m0, a.B);
+    store_t(As, H, a.b.ht[1], a.b.steps, m0, a.B);
+    fwd_layer<17>(As, a.wf[2], a.b.z[2], m0, a.B);
+    store_t(As, H, a.b.ht[2], a.b.steps, m0, a.B);
+    // 272 columns: the bias column and the zeros after it are in the tile
+    constexpr int KS = (kKp + 15) / 16;
+    for (int c = tid; c < kRows * KS * 2; c += kThreads) {
+        const int r = c % kRows, k = c / kRows * 8;
+        *reinterpret_cast<uint4*>(a.b.h2 + frag_at(m0 + r, k, KS)) =
+            *reinterpret_cast<const uint4*>(&As[r][k]);
     }
 }
 
@@ -166,12 +171,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
             for (int y = 0; y < 2; ++y)
                 t[x][y][r] = tb[row + (unsigned)min(n0 + wn * 64 + y * 32 + li, n_last)];
         }
-    const bf16 *ap[2], *bp[2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        ap[x] = a.b.h2 + (size_t)(m0 + min(wm * 64 + x * 32 + li, m_last)) * kKp;
-        bp[x] = a.w + (size_t)min(n0 + wn * 64 + x * 32 + li, n_last) * kKp;
-    }
     f32x16 acc[2][2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
@@ -179,12 +178,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
         for (int y = 0; y < 2; ++y) acc[x][y] = zero16();
     constexpr int NKS = (kKp + 15) / 16, D = 3;
     bf16x8 fa[D][2], fb[D][2];
+    // row blocks past the last point or output: any of them, never stored
+    const int rb_a = m0 / 32 + wm * 2, rb_b = n0 / 32 + wn * 2;
+    const int last_a = (a.B - 1) / 32, last_b = n_last / 32;
     auto load = [&](int ks, bf16x8 u[2], bf16x8 v[2]) {
-        const int k = min(ks * 16 + lh * 8, kKp - 8);
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
-            u[x] = frag(ap[x] + k);
-            v[x] = frag(bp[x] + k);
+            u[x] = frag_of(a.b.h2, min(rb_a + x, last_a), ks, NKS);
+            v[x] = frag_of(a.wf, min(rb_b + x, last_b), ks, NKS);
         }
     };
 #pragma unroll
@@ -194,8 +195,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
         bf16x8 u[2], v[2];
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
-            // the second half of the last step lies past the columns
-            u[x] = ks == NKS - 1 && lh ? zero8() : fa[ks % D][x];
+            u[x] = fa[ks % D][x];  // zeros past the columns in both
             v[x] = fb[ks % D][x];
         }
         if (ks + D < NKS) load(ks + D, fa[ks % D], fb[ks % D]);
@@ -232,21 +232,22 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
     __syncthreads();
     if (tid == 0)
         a.tile_loss[blockIdx.y * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+    const int n_steps = frag_steps(a.N);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int c = tid + i * kThreads, row = c >> 4, k = (c & 15) * 8;
+        const int c = tid + i * kThreads, row = c & 127, k = (c >> 7) * 8;
         if (row <= m_last && n0 + k < a.N)
-            *reinterpret_cast<uint4*>(a.b.dy + (size_t)(m0 + row) * a.N + n0 + k) =
+            *reinterpret_cast<uint4*>(a.b.dy + frag_at(m0 + row, n0 + k, n_steps)) =
                 *reinterpret_cast<const uint4*>(&T1[row][k]);
         if (n0 + row < a.N && k <= m_last)
-            *reinterpret_cast<uint4*>(a.b.dyt + (size_t)(n0 + row) * a.b.ldt + m0 + k) =
+            *reinterpret_cast<uint4*>(a.b.dyt + frag_at(n0 + row, m0 + k, a.b.steps)) =
                 *reinterpret_cast<const uint4*>(&T2[row][k]);
     }
 }
 
 // ------------------------------------------------------- split products
-// One tile of C[m][n] = sum_k A[m][k] B[n][k], both rows contiguous along k, the
-// sum taken in chunks: round by round every wave forms one chunk of the whole
+// One tile of C[m][n] = sum_k A[m][k] B[n][k], both in fragment order, the sum
+// taken in chunks: round by round every wave forms one chunk of the whole
 // tile, then the threads add the round's chunks in order to their elements
 // (element tid + i T of the tile, rows of 32 BN).  No partial sums leave the
 // work-group, where the K-split GEMM wrote and read back a slab per chunk.
@@ -255,16 +256,17 @@ struct SplitTile {
     static constexpr int T = NW * 64, TM = 32 * BM, TN = 32 * BN, EPT = TM * TN / T;
     static_assert(TM * TN % T == 0, "whole elements per thread");
 
-    static __device__ __forceinline__ void run(const bf16* __restrict__ A, size_t lda,
-                                               const bf16* __restrict__ B, size_t ldb, int M, int N,
-                                               int K, TrainSplit sp, int m0, int n0,
-                                               float (*part)[TM][TN], float v[EPT]) {
+    static __device__ __forceinline__ void run(const bf16* __restrict__ A, const bf16* __restrict__ B,
+                                               int M, int N, int K, int steps, TrainSplit sp, int m0,
+                                               int n0, float (*part)[TM][TN], float v[EPT]) {
         const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-        const bf16 *ap[BM], *bp[BN];
+        const bf16 *ap[BM], *bp[BN];  // row blocks past the last: any, never stored
 #pragma unroll
-        for (int x = 0; x < BM; ++x) ap[x] = A + (size_t)min(m0 + 32 * x + li, M - 1) * lda + lh * 8;
+        for (int x = 0; x < BM; ++x)
+            ap[x] = A + (size_t)min(m0 / 32 + x, (M - 1) / 32) * steps * 512 + lane * 8;
 #pragma unroll
-        for (int y = 0; y < BN; ++y) bp[y] = B + (size_t)min(n0 + 32 * y + li, N - 1) * ldb + lh * 8;
+        for (int y = 0; y < BN; ++y)
+            bp[y] = B + (size_t)min(n0 / 32 + y, (N - 1) / 32) * steps * 512 + lane * 8;
 #pragma unroll
         for (int i = 0; i < EPT; ++i) v[i] = 0.f;
         for (int q0 = 0; q0 < sp.n_split; q0 += NW) {
@@ -283,9 +285,9 @@ struct SplitTile {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-                        for (int x = 0; x < BM; ++x) s.a[h][x] = frag(ap[x] + k + 16 * h);
+                        for (int x = 0; x < BM; ++x) s.a[h][x] = frag(ap[x] + (k + 16 * h) * 32);
 #pragma unroll
-                        for (int y = 0; y < BN; ++y) s.b[h][y] = frag(bp[y] + k + 16 * h);
+                        for (int y = 0; y < BN; ++y) s.b[h][y] = frag(bp[y] + (k + 16 * h) * 32);
                     }
                 };
                 auto compute = [&](const Stage& s) {
@@ -311,17 +313,16 @@ struct SplitTile {
                     }
                     if (i < nst) compute(s0);
                 }
-                // the last indices, a multiple of eight: 16 at a time, fragments
-                // past the end zero (their address clamped)
+                // the last indices, a multiple of eight: 16 at a time, zeros past
+                // the end
                 for (int k = kb + nst * 32; k < ke; k += 16) {
                     const bool ok = k + lh * 8 < ke;
-                    const int kc = min(k, ke - 8 - lh * 8);
 #pragma unroll
                     for (int x = 0; x < BM; ++x) {
-                        const bf16x8 f = frag(ap[x] + kc), u = ok ? f : zero8();
+                        const bf16x8 f = frag(ap[x] + k * 32), u = ok ? f : zero8();
 #pragma unroll
                         for (int y = 0; y < BN; ++y) {
-                            const bf16x8 w = frag(bp[y] + kc);
+                            const bf16x8 w = frag(bp[y] + k * 32);
                             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                                 u, ok ? w : zero8(), acc[x][y], 0, 0, 0);
                         }
@@ -357,12 +358,12 @@ __global__ __launch_bounds__(512) void k_train_dh(TrainDh a) {
     float v[DhTile::EPT];
     const int u = blockIdx.x >> 3, n0 = (u & 3) * 64, m0 = ((u >> 2) * 8 + (blockIdx.x & 7)) * 64;
     if (m0 >= a.B) return;
-    DhTile::run(a.b.dy, a.N, a.wt, a.N, a.B, H, a.N, a.sp, m0, n0, part, v);
+    DhTile::run(a.b.dy, a.wt, a.B, H, a.N, frag_steps(a.N), a.sp, m0, n0, part, v);
 #pragma unroll
     for (int i = 0; i < DhTile::EPT; ++i) {
         const int e = threadIdx.x + i * DhTile::T, m = m0 + e / DhTile::TN, n = n0 + e % DhTile::TN;
         if (m >= a.B) continue;
-        a.b.dz2[(size_t)m * H + n] = (bf16)dsilu(v[i], a.b.z[2][(size_t)m * H + n]);
+        a.b.dz2[frag_at(m, n, H / 16)] = (bf16)dsilu(v[i], a.b.z[2][(size_t)m * H + n]);
     }
 }
 
@@ -376,7 +377,7 @@ __device__ __forceinline__ void bwd_layer(bf16 (*As)[kLda], const bf16* __restri
     auto wload = [&](int ks, bf16x8 out[2]) {
 #pragma unroll
         for (int y = 0; y < 2; ++y)
-            out[y] = frag(Wt + (size_t)(wave * 64 + y * 32 + li) * H + ks * 16 + lh * 8);
+            out[y] = frag_of(Wt, wave * 2 + y, ks, NKS);
     };
 #pragma unroll
     for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
@@ -418,27 +419,29 @@ __global__ __launch_bounds__(kThreads) void k_train_hidden(TrainHidden a) {
     __shared__ __attribute__((aligned(16))) bf16 As[kRows][kLda];
     const int tid = threadIdx.x, m0 = blockIdx.x * kRows;
     for (int c = tid; c < kRows * (H / 8); c += kThreads) {
-        const int r = c / (H / 8), k = c % (H / 8) * 8;
+        const int r = c % kRows, k = c / kRows * 8;  // rows past the last point: never stored
         *reinterpret_cast<uint4*>(&As[r][k]) =
-            *reinterpret_cast<const uint4*>(a.b.dz2 + (size_t)min(m0 + r, a.B - 1) * H + k);
+            *reinterpret_cast<const uint4*>(a.b.dz2 + frag_at(m0 + r, k, H / 16));
     }
     __syncthreads();
-    store_t(As, H, a.b.dzt[2], a.b.ldt, m0, a.B);
+    store_t(As, H, a.b.dzt[2], a.b.steps, m0, a.B);
     bwd_layer(As, a.wt[0], a.sp, a.b.z[1], m0, a.B);
-    store_t(As, H, a.b.dzt[1], a.b.ldt, m0, a.B);
+    store_t(As, H, a.b.dzt[1], a.b.steps, m0, a.B);
     bwd_layer(As, a.wt[1], a.sp, a.b.z[0], m0, a.B);
-    store_t(As, H, a.b.dzt[0], a.b.ldt, m0, a.B);
+    store_t(As, H, a.b.dzt[0], a.b.steps, m0, a.B);
 }
 
 // Every layer's weight gradient with its Adam step: 64 x 96 tiles of G, four
 // waves; the thread that ends up with an element of G updates its parameter, its
-// moments and its BF16 copies (the transposed one through LDS, in runs of 64).
+// moments and its BF16 copies (those in fragment order through LDS).
 typedef SplitTile<2, 3, 4> WTile;
 
 __global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
     __shared__ __attribute__((aligned(16))) union {
         float part[4][WTile::TM][WTile::TN];
-        bf16 t[WTile::TN][WTile::TM + 8];
+        struct {
+            bf16 f[WTile::TM][WTile::TN + 8], t[WTile::TN][WTile::TM + 8];
+        } w;
     } sh;
     int li = 3;
     while (li > 0 && (int)blockIdx.x < a.l[li].first) --li;
@@ -446,7 +449,7 @@ __global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
     const int nt = (L.N + WTile::TN - 1) / WTile::TN, t = (int)blockIdx.x - L.first;
     const int m0 = t / nt * WTile::TM, n0 = t % nt * WTile::TN;
     float v[WTile::EPT];
-    WTile::run(L.A, a.ldt, L.Bm, a.ldt, L.M, L.N, a.B, L.sp, m0, n0, sh.part, v);
+    WTile::run(L.A, L.Bm, L.M, L.N, a.B, a.steps, L.sp, m0, n0, sh.part, v);
 #pragma unroll
     for (int i = 0; i < WTile::EPT; ++i) {
         const int e = threadIdx.x + i * WTile::T, ml = e / WTile::TN, nl = e % WTile::TN;
@@ -462,22 +465,41 @@ __global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
         L.v[o] = s;
         L.w[o] = w;
         L.w16[o] = (bf16)w;
-        sh.t[nl][ml] = (bf16)w;
+        sh.w.f[ml][nl] = sh.w.t[nl][ml] = (bf16)w;
     }
-    if (!L.w16t) return;
     __syncthreads();
+    const int sm = frag_steps(L.M), sn = frag_steps(L.N);
+    // M and N are multiples of eight: whole 16-byte pieces
     for (int c = threadIdx.x; c < WTile::TN * (WTile::TM / 8); c += WTile::T) {
-        const int nl = c / (WTile::TM / 8), ml = c % (WTile::TM / 8) * 8;
+        const int nl = c % WTile::TN, ml = c / WTile::TN * 8;
         if (n0 + nl < L.N && m0 + ml < L.M)
-            *reinterpret_cast<uint4*>(L.w16t + (size_t)(n0 + nl) * L.M + m0 + ml) =
-                *reinterpret_cast<const uint4*>(&sh.t[nl][ml]);
+            *reinterpret_cast<uint4*>(L.wt + frag_at(n0 + nl, m0 + ml, sm)) =
+                *reinterpret_cast<const uint4*>(&sh.w.t[nl][ml]);
+    }
+    for (int c = threadIdx.x; c < WTile::TM * (WTile::TN / 8); c += WTile::T) {
+        const int ml = c % WTile::TM, nl = c / WTile::TM * 8;
+        if (n0 + nl < L.N && m0 + ml < L.M)
+            *reinterpret_cast<uint4*>(L.wf + frag_at(m0 + ml, n0 + nl, sn)) =
+                *reinterpret_cast<const uint4*>(&sh.w.f[ml][nl]);
     }
 }
 
-__global__ void k_train_ones(bf16* ht, int row0, int ldt) {
+__global__ void k_train_ones(bf16* ht, int steps) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= ldt) return;
-    for (int r = 0; r < 8; ++r) ht[(size_t)(row0 + r) * ldt + p] = (bf16)(r == 0 ? 1.f : 0.f);
+    if (p >= steps * 16) return;
+    for (int r = 0; r < 8; ++r) ht[frag_at(H + r, p, steps)] = (bf16)(r == 0 ? 1.f : 0.f);
+}
+
+// One element of the padded matrix per thread.
+__global__ void k_train_pack(TrainPack a) {
+    const int pm = (a.M + 31) / 32 * 32, pn = (a.N + 31) / 32 * 32;
+    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (long)pm * pn) return;
+    const int m = (int)(e / pn), n = (int)(e % pn);
+    const bf16 w = m < a.M && n < a.N ? a.w[(size_t)m * a.N + n] : (bf16)0.f;
+    const int sm = frag_steps(a.M), sn = frag_steps(a.N);
+    if (n < sn * 16) a.wf[frag_at(m, n, sn)] = w;
+    if (m < sm * 16) a.wt[frag_at(n, m, sm)] = w;
 }
 
 bool split_ok(const TrainSplit& s, int K) {
@@ -488,15 +510,13 @@ bool split_ok(const TrainSplit& s, int K) {
 }  // namespace
 
 hipError_t launch_train_fwd(const TrainFwd& a, hipStream_t s) {
-    if (a.B <= 0 || a.B % 8 || a.b.ldt < a.B || a.b.ldt % 8 || a.k[0] != 32 || a.k[1] != kKp ||
-        a.k[2] != kKp)
-        return hipErrorInvalidValue;
+    if (a.B <= 0 || a.B % 8 || a.b.steps * 16 < (a.B + 31) / 32 * 32) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_train_fwd, dim3((a.B + kRows - 1) / kRows), dim3(kThreads), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_train_mse(const TrainMse& a, hipStream_t s) {
-    if (a.N <= 0 || a.N % 8 || a.B % 8 || a.b.ldt < a.B || a.N >= (1 << 24))
+    if (a.N <= 0 || a.N % 8 || a.B % 8 || a.b.steps * 16 < a.B || a.N >= (1 << 24))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_train_mse, dim3((a.N + 127) / 128, (a.B + 127) / 128), dim3(kThreads), 0, s, a);
     return hipGetLastError();
@@ -526,8 +546,14 @@ hipError_t launch_train_w(TrainW a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_train_ones(bf16* ht, int row0, int ldt, hipStream_t s) {
-    hipLaunchKernelGGL(k_train_ones, dim3((ldt + 255) / 256), dim3(256), 0, s, ht, row0, ldt);
+hipError_t launch_train_ones(bf16* ht, int steps, hipStream_t s) {
+    hipLaunchKernelGGL(k_train_ones, dim3((steps * 16 + 255) / 256), dim3(256), 0, s, ht, steps);
+    return hipGetLastError();
+}
+
+hipError_t launch_train_pack(const TrainPack& a, hipStream_t s) {
+    const long n = (long)((a.M + 31) / 32 * 32) * ((a.N + 31) / 32 * 32);
+    hipLaunchKernelGGL(k_train_pack, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
