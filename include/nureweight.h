@@ -352,6 +352,15 @@ int nr_mlp_targets_dev(nr_mlp *mlp, const double *d_mu, int P, float *d_t,
 int nr_mlp_train_step_dev(nr_mlp *mlp, const double *d_theta, const float *d_t,
                           int B, float lr, double *loss, void *stream);
 
+/* n_steps such steps on gathered rows: step i takes rows d_idx[i B ..
+ * (i + 1) B) of d_theta and d_t (64-bit indices on the device, inside both
+ * arrays) with the learning rate lr[i] (host); bitwise the steps on tensors
+ * gathered before.  Enqueued on `stream`, returns without waiting.  Hidden
+ * layers of 256 only (NR_EINVAL). */
+int nr_mlp_train_epoch_dev(nr_mlp *mlp, const double *d_theta, const float *d_t,
+                           const long long *d_idx, int n_steps, int B,
+                           const float *lr, void *stream);
+
 /* Predicted log mu [B][n_out] (device FP32). */
 int nr_mlp_logmu_dev(nr_mlp *mlp, const double *d_theta, int B,
                      float *d_logmu, void *stream);

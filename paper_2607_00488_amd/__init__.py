@@ -33,6 +33,7 @@ EXPORTS = (
     "nr_mlp_create", "nr_mlp_destroy", "nr_mlp_num_params", "nr_mlp_set_params",
     "nr_mlp_get_params", "nr_mlp_get_grads", "nr_mlp_set_box",
     "nr_mlp_set_output_norm", "nr_mlp_targets_dev", "nr_mlp_train_step_dev",
+    "nr_mlp_train_epoch_dev",
     "nr_mlp_logmu_dev", "nr_mlp_nll_dev", "nr_eval_mu_batched_dev",
     "nr_build_templates", "nr_eval_nll_templates", "nr_eval_mu_templates",
     "nr_eval_nll_templates_dev", "nr_probe_mfma_f64", "nr_probe_hbm_read",
@@ -139,6 +140,7 @@ def load():
     L.nr_mlp_set_output_norm.argtypes = [P, pF, pF]
     L.nr_mlp_targets_dev.argtypes = [P, P, I, P, P]
     L.nr_mlp_train_step_dev.argtypes = [P, P, P, I, C.c_float, pD, P]
+    L.nr_mlp_train_epoch_dev.argtypes = [P, P, P, P, I, I, C.POINTER(C.c_float), P]
     L.nr_mlp_logmu_dev.argtypes = [P, P, I, P, P]
     L.nr_mlp_nll_dev.argtypes = [P, P, P, I, P, P, P]
     L.nr_eval_mu_batched_dev.argtypes = [P, P, I, P, P]
@@ -521,6 +523,12 @@ def nr_mlp_train_step_dev(h, d_theta, d_t, B, lr, want_loss=False,
         h, C.c_void_p(d_theta), C.c_void_p(d_t), int(B), float(lr),
         C.byref(loss) if want_loss else None, C.c_void_p(stream or 0)))
     return loss.value
+
+
+def nr_mlp_train_epoch_dev(h, d_theta, d_t, d_idx, n_steps, B, lr, stream=None):
+    _check(load().nr_mlp_train_epoch_dev(
+        h, C.c_void_p(d_theta), C.c_void_p(d_t), C.c_void_p(d_idx),
+        int(n_steps), int(B), (C.c_float * n_steps)(*lr), C.c_void_p(stream or 0)))
 
 
 def nr_mlp_logmu_dev(h, d_theta, B, d_logmu, stream=None):

@@ -2481,8 +2481,8 @@ int mlp_hidden_forward(nr_mlp* q, int B, hipStream_t s) {
 
 // One training step of a network of kFusedHidden units, but for the step count:
 // the sums and roundings of the layer-by-layer step in five launches.
-int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamArgs& ad, int B,
-                    hipStream_t s) {
+int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const long long* idx,
+                    const nr::AdamArgs& ad, int B, hipStream_t s) {
     const int H = q->H, N = q->n_out;
     if (!q->packed) {
         for (int l = 0; l < 4; ++l)
@@ -2503,6 +2503,7 @@ int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamA
     b.steps = nr::frag_steps(q->cap);
     nr::TrainFwd f{};
     f.theta = th;
+    f.idx = idx;
     for (int i = 0; i < NR_NTHETA; ++i) {
         f.lo[i] = q->lo[i];
         f.hi[i] = q->hi[i];
@@ -2511,7 +2512,7 @@ int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const nr::AdamA
     f.B = B;
     f.b = b;
     HIPCHK(nr::launch_train_fwd(f, s));
-    HIPCHK(nr::launch_train_mse({q->wf[3], t, B, N, 1.0f / ((float)B * (float)N),
+    HIPCHK(nr::launch_train_mse({q->wf[3], t, idx, B, N, 1.0f / ((float)B * (float)N),
                                  q->tile_loss, b}, s));
     HIPCHK(nr::launch_train_dh({q->wt[3], B, N, mlp_split(B, H, N), b}, s));
     HIPCHK(nr::launch_train_hidden({{q->wt[2], q->wt[1]}, B,
@@ -2695,15 +2696,10 @@ int nr_mlp_targets_dev(nr_mlp* q, const double* d_mu, int P, float* d_t, void* s
     return 0;
 }
 
-int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
-                          int B, float lr, double* loss, void* stream) {
-    const ApiLock api_lock;
-    if (!q || !d_theta || !d_t || B <= 0 || B % 8)
-        return fail(NR_EINVAL, "batch must be a positive multiple of 8");
-    HIPCHK(hipSetDevice(q->device));
+// One step on rows idx[0 .. B) (null: the first B) of theta and the targets.
+static int mlp_train_step(nr_mlp* q, const double* d_theta, const float* d_t, const long long* idx,
+                          int B, float lr, hipStream_t s) {
     int rc;
-    if ((rc = mlp_alloc_batch(q, B, true))) return rc;
-    hipStream_t s = (hipStream_t)stream;
     const int H = q->H, ldh = H + 8, N = q->n_out;
     const float step = (float)(q->step + 1);
     nr::AdamArgs ad{};
@@ -2720,7 +2716,7 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
     ad.bc1 = 1.0f - powf(0.9f, step);
     ad.bc2 = 1.0f - powf(0.999f, step);
     if (H == nr::kFusedHidden) {
-        if ((rc = mlp_train_fused(q, d_theta, d_t, ad, B, s))) return rc;
+        if ((rc = mlp_train_fused(q, d_theta, d_t, idx, ad, B, s))) return rc;
     } else {
         if ((rc = mlp_input(q, d_theta, B, s))) return rc;
         if ((rc = mlp_hidden_forward(q, B, s))) return rc;
@@ -2764,6 +2760,38 @@ int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
         if ((rc = mlp_transpose(q, s))) return rc;
     }
     q->step += 1;
+    return 0;
+}
+
+int nr_mlp_train_epoch_dev(nr_mlp* q, const double* d_theta, const float* d_t,
+                           const long long* d_idx, int n_steps, int B, const float* lr,
+                           void* stream) {
+    const ApiLock api_lock;
+    if (!q || !d_theta || !d_t || !d_idx || !lr || n_steps <= 0 || B <= 0 || B % 8)
+        return fail(NR_EINVAL, "null argument, no steps, or a batch that is no positive multiple of 8");
+    if (q->H != nr::kFusedHidden)
+        return fail(NR_EINVAL, "needs hidden layers of %d", nr::kFusedHidden);
+    HIPCHK(hipSetDevice(q->device));
+    int rc;
+    if ((rc = mlp_alloc_batch(q, B, true))) return rc;
+    for (int i = 0; i < n_steps; ++i)
+        if ((rc = mlp_train_step(q, d_theta, d_t, d_idx + (size_t)i * B, B, lr[i],
+                                 (hipStream_t)stream)))
+            return rc;
+    return 0;
+}
+
+int nr_mlp_train_step_dev(nr_mlp* q, const double* d_theta, const float* d_t,
+                          int B, float lr, double* loss, void* stream) {
+    const ApiLock api_lock;
+    if (!q || !d_theta || !d_t || B <= 0 || B % 8)
+        return fail(NR_EINVAL, "batch must be a positive multiple of 8");
+    HIPCHK(hipSetDevice(q->device));
+    int rc;
+    if ((rc = mlp_alloc_batch(q, B, true))) return rc;
+    hipStream_t s = (hipStream_t)stream;
+    if ((rc = mlp_train_step(q, d_theta, d_t, nullptr, B, lr, s))) return rc;
+    const int N = q->n_out;
     if (loss) {
         const int tiles = ((B + 127) / 128) * ((N + 127) / 128);
         std::vector<double> tl(tiles);

@@ -46,7 +46,8 @@ struct TrainPack {
 };
 
 struct TrainFwd {
-    const double* theta;  // [B][7]
+    const double* theta;  // [..][7]
+    const long long* idx; // [B] rows of theta, or null (0 .. B - 1)
     double lo[kNTheta], hi[kNTheta];
     const bf16* wf[3];
     int B;
@@ -55,7 +56,8 @@ struct TrainFwd {
 
 struct TrainMse {
     const bf16* wf;    // output weights
-    const float* t;    // [B][N] targets, rows
+    const float* t;    // [..][N] targets, rows
+    const long long* idx;  // [B] rows of t, or null
     int B, N;
     float scale;
     double* tile_loss; // [ceil(B / 128)][ceil(N / 128)]

@@ -80,28 +80,28 @@ __device__ inline void store_t(const bf16 (*As)[kLda], int n_col, bf16* dst, int
 // --------------------------------------------------------------- forward
 // Input map and the three hidden layers of 32 points per work-group, the
 // activations in LDS: wave w forms outputs 64 w .. 64 w + 63 (points as the row
-// operand; the weights six K-steps ahead).  Bound by the latency of the weights (286 KB from L2 per
-// work-group).
+// operand).  Every layer's weights are in flight before the first layer starts
+// (one wave per SIMD holds them all): the chain was bound by their latency, layer
+// by layer.
 template <int NKS>
-__device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ W, float* z,
-                                          int m0, int B) {
+__device__ __forceinline__ void load_weights(const bf16* __restrict__ W, bf16x8 w[NKS][2]) {
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) w[ks][y] = frag_of(W, wave * 2 + y, ks, NKS);
+}
+
+template <int NKS>
+__device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16x8 w[NKS][2], float* z, int m0,
+                                          int B) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
-    constexpr int D = NKS < 6 ? NKS : 6;
-    bf16x8 ring[D][2];
-    auto wload = [&](int ks, bf16x8 out[2]) {
-#pragma unroll
-        for (int y = 0; y < 2; ++y) out[y] = frag_of(W, wave * 2 + y, ks, NKS);
-    };
-#pragma unroll
-    for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
     f32x16 acc[2] = {zero16(), zero16()};
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-        const bf16x8 b0 = ring[ks % D][0], b1 = ring[ks % D][1];
-        if (ks + D < NKS) wload(ks + D, ring[ks % D]);
         const bf16x8 a = *reinterpret_cast<const bf16x8*>(&As[li][ks * 16 + lh * 8]);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w[ks][0], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w[ks][1], acc[1], 0, 0, 0);
     }
     __syncthreads();  // every wave has read this layer's input
 #pragma unroll
@@ -115,14 +115,20 @@ __device__ __forceinline__ void fwd_layer(bf16 (*As)[kLda], const bf16* __restri
     __syncthreads();
 }
 
-__global__ __launch_bounds__(kThreads) void k_train_fwd(TrainFwd a) {
+__global__ __launch_bounds__(kThreads, 1) void k_train_fwd(TrainFwd a) {
     __shared__ __attribute__((aligned(16))) bf16 As[kRows][kLda];
     const int tid = threadIdx.x, m0 = blockIdx.x * kRows;
+    bf16x8 w0[2][2], w1[17][2], w2[17][2];
+    load_weights<2>(a.wf[0], w0);
+    load_weights<17>(a.wf[1], w1);
+    load_weights<17>(a.wf[2], w2);
+    __builtin_amdgcn_sched_barrier(0);
     for (int q = tid; q < kRows * (kLda / 8); q += kThreads)
         *reinterpret_cast<uint4*>(&As[q / (kLda / 8)][q % (kLda / 8) * 8]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     if (tid < kRows) {
-        const double* th = a.theta + (size_t)min(m0 + tid, a.B - 1) * kNTheta;
+        const int p = min(m0 + tid, a.B - 1);
+        const double* th = a.theta + (a.idx ? a.idx[p] : (long long)p) * kNTheta;
         for (int i = 0; i < kNTheta; ++i)
             As[tid][i] = bf16_of(2.0 * (th[i] - a.lo[i]) / (a.hi[i] - a.lo[i]) - 1.0);
         As[tid][kNTheta] = (bf16)1.f;
@@ -130,11 +136,11 @@ __global__ __launch_bounds__(kThreads) void k_train_fwd(TrainFwd a) {
     }
     __syncthreads();
     store_t(As, 32, a.b.xt, a.b.steps, m0, a.B);
-    fwd_layer<2>(As, a.wf[0], a.b.z[0], m0, a.B);
+    fwd_layer<2>(As, w0, a.b.z[0], m0, a.B);
     store_t(As, H, a.b.ht[0], a.b.steps, m0, a.B);
-    fwd_layer<17>(As, a.wf[1], a.b.z[1], m0, a.B);
+    fwd_layer<17>(As, w1, a.b.z[1], m0, a.B);
     store_t(As, H, a.b.ht[1], a.b.steps, m0, a.B);
-    fwd_layer<17>(As, a.wf[2], a.b.z[2], m0, a.B);
+    fwd_layer<17>(As, w2, a.b.z[2], m0, a.B);
     store_t(As, H, a.b.ht[2], a.b.steps, m0, a.B);
     // 272 columns: the bias column and the zeros after it are in the tile
     constexpr int KS = (kKp + 15) / 16;
@@ -160,16 +166,21 @@ __global__ __launch_bounds__(kThreads, 2) void k_train_mse(TrainMse a) {
     const int wm = wave >> 1, wn = wave & 1, li = lane & 31, lh = lane >> 5;
     const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
     const int n_last = a.N - 1, m_last = a.B - 1 - m0;  // last valid row of the tile
+    __shared__ long long rows[128];  // first target of every point
+    if (tid < 128) {
+        const int p = m0 + min(tid, m_last);
+        rows[tid] = (a.idx ? a.idx[p] : (long long)p) * a.N;
+    }
+    __syncthreads();
     float t[2][2][16];
-    const float* tb = a.t + (size_t)m0 * a.N;
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const unsigned row = (unsigned)min(wm * 64 + x * 32 + blk_row(r, lh), m_last) * (unsigned)a.N;
+            const float* tb = a.t + rows[wm * 64 + x * 32 + blk_row(r, lh)];
 #pragma unroll
             for (int y = 0; y < 2; ++y)
-                t[x][y][r] = tb[row + (unsigned)min(n0 + wn * 64 + y * 32 + li, n_last)];
+                t[x][y][r] = tb[min(n0 + wn * 64 + y * 32 + li, n_last)];
         }
     f32x16 acc[2][2];
 #pragma unroll
@@ -301,17 +312,22 @@ struct SplitTile {
                                     s.a[h][x], s.b[h][y], acc[x][y], 0, 0, 0);
                 };
                 const int nst = (ke - kb) / 32;
-                if (nst > 0) {
-                    Stage s0, s1;
-                    load(kb, s0);
+                if (nst > 0) {  // two stages ahead; the loads past the end repeat the last
+                    Stage s0, s1, s2;
+                    auto at = [&](int i) { return kb + min(i, nst - 1) * 32; };
+                    load(at(0), s0);
+                    load(at(1), s1);
                     int i = 0;
-                    for (; i + 1 < nst; i += 2) {
-                        load(kb + (i + 1) * 32, s1);
+                    for (; i + 2 < nst; i += 3) {
+                        load(at(i + 2), s2);
                         compute(s0);
-                        load(kb + min(i + 2, nst - 1) * 32, s0);
+                        load(at(i + 3), s0);
                         compute(s1);
+                        load(at(i + 4), s1);
+                        compute(s2);
                     }
                     if (i < nst) compute(s0);
+                    if (i + 1 < nst) compute(s1);
                 }
                 // the last indices, a multiple of eight: 16 at a time, zeros past
                 // the end
@@ -369,34 +385,27 @@ __global__ __launch_bounds__(512) void k_train_dh(TrainDh a) {
 
 // dZ_1 and dZ_0 of 32 points per work-group, as the forward chain; the chunks of
 // a layer's reduction are summed one after the other in registers.
-__device__ __forceinline__ void bwd_layer(bf16 (*As)[kLda], const bf16* __restrict__ Wt, TrainSplit sp,
-                                          const float* z, int m0, int B) {
+__device__ __forceinline__ void load_z(const float* z, int m0, int B, f32x16 zv[2]) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
-    constexpr int NKS = H / 16, D = 6;
-    bf16x8 ring[D][2];
-    auto wload = [&](int ks, bf16x8 out[2]) {
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-            out[y] = frag_of(Wt, wave * 2 + y, ks, NKS);
-    };
-#pragma unroll
-    for (int ks = 0; ks < D; ++ks) wload(ks, ring[ks]);
-    f32x16 zv[2];
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
             zv[y][r] = z[(size_t)min(m0 + blk_row(r, lh), B - 1) * H + wave * 64 + y * 32 + li];
+}
+
+__device__ __forceinline__ void bwd_layer(bf16 (*As)[kLda], const bf16x8 w[H / 16][2], TrainSplit sp,
+                                          const f32x16 zv[2]) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    constexpr int NKS = H / 16;
     f32x16 acc[2] = {zero16(), zero16()}, v[2] = {zero16(), zero16()};
     const int cks = sp.chunk / 16;
     int left = cks;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-        const bf16x8 b0 = ring[ks % D][0], b1 = ring[ks % D][1];
-        if (ks + D < NKS) wload(ks + D, ring[ks % D]);
         const bf16x8 a = *reinterpret_cast<const bf16x8*>(&As[li][ks * 16 + lh * 8]);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w[ks][0], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w[ks][1], acc[1], 0, 0, 0);
         if (--left == 0 || ks == NKS - 1) {
             left = cks;
 #pragma unroll
@@ -415,9 +424,16 @@ __device__ __forceinline__ void bwd_layer(bf16 (*As)[kLda], const bf16* __restri
     __syncthreads();
 }
 
-__global__ __launch_bounds__(kThreads) void k_train_hidden(TrainHidden a) {
+__global__ __launch_bounds__(kThreads, 1) void k_train_hidden(TrainHidden a) {
     __shared__ __attribute__((aligned(16))) bf16 As[kRows][kLda];
     const int tid = threadIdx.x, m0 = blockIdx.x * kRows;
+    bf16x8 w1[H / 16][2], w0[H / 16][2];
+    f32x16 z1[2], z0[2];
+    load_weights<H / 16>(a.wt[0], w1);
+    load_z(a.b.z[1], m0, a.B, z1);
+    load_weights<H / 16>(a.wt[1], w0);
+    load_z(a.b.z[0], m0, a.B, z0);
+    __builtin_amdgcn_sched_barrier(0);
     for (int c = tid; c < kRows * (H / 8); c += kThreads) {
         const int r = c % kRows, k = c / kRows * 8;  // rows past the last point: never stored
         *reinterpret_cast<uint4*>(&As[r][k]) =
@@ -425,20 +441,20 @@ __global__ __launch_bounds__(kThreads) void k_train_hidden(TrainHidden a) {
     }
     __syncthreads();
     store_t(As, H, a.b.dzt[2], a.b.steps, m0, a.B);
-    bwd_layer(As, a.wt[0], a.sp, a.b.z[1], m0, a.B);
+    bwd_layer(As, w1, a.sp, z1);
     store_t(As, H, a.b.dzt[1], a.b.steps, m0, a.B);
-    bwd_layer(As, a.wt[1], a.sp, a.b.z[0], m0, a.B);
+    bwd_layer(As, w0, a.sp, z0);
     store_t(As, H, a.b.dzt[0], a.b.steps, m0, a.B);
 }
 
 // Every layer's weight gradient with its Adam step: 64 x 96 tiles of G, four
 // waves; the thread that ends up with an element of G updates its parameter, its
 // moments and its BF16 copies (those in fragment order through LDS).
-typedef SplitTile<2, 3, 4> WTile;
+typedef SplitTile<2, 3, 6> WTile;
 
 __global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
     __shared__ __attribute__((aligned(16))) union {
-        float part[4][WTile::TM][WTile::TN];
+        float part[6][WTile::TM][WTile::TN];
         struct {
             bf16 f[WTile::TM][WTile::TN + 8], t[WTile::TN][WTile::TM + 8];
         } w;

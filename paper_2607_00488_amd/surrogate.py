@@ -23,7 +23,8 @@ from . import (Context, eval_nll_multi_dev, nr_eval_mu_batched_dev,
                nr_mlp_create, nr_mlp_destroy, nr_mlp_get_grads,
                nr_mlp_get_params, nr_mlp_nll_dev, nr_mlp_num_params,
                nr_mlp_set_box, nr_mlp_set_output_norm, nr_mlp_set_params,
-               nr_mlp_targets_dev, nr_mlp_train_step_dev, nr_mlp_logmu_dev)
+               nr_mlp_targets_dev, nr_mlp_train_epoch_dev,
+               nr_mlp_train_step_dev, nr_mlp_logmu_dev)
 
 
 def layer_shapes(hidden: int, n_out: int):
@@ -115,14 +116,32 @@ class Surrogate:
         losses = []
         t0 = time.time()
         step = 0
+
+        def rate(step):
+            return lr_min + 0.5 * (lr_max - lr_min) * (
+                1 + math.cos(math.pi * step / max(1, total)))
+
+        # whole epochs in one call, the batches gathered by the kernels, where
+        # no loss is asked for and the tensors are laid out as they read them
+        whole = (self.hidden == 256 and not log_every and steps_per_epoch > 0 and
+                 theta.dtype == torch.float64 and theta.is_contiguous() and
+                 targets.dtype == torch.float32 and targets.is_contiguous() and
+                 theta.shape[1:] == (7,) and targets.shape == (P, self.n_out) and
+                 theta.device == targets.device == self.dev)
         for ep in range(epochs):
             perm = torch.randperm(P, device=self.dev, generator=gen)
-            for b in range(steps_per_epoch):
+            if whole:
+                nr_mlp_train_epoch_dev(
+                    self.h, theta.data_ptr(), targets.data_ptr(), perm.data_ptr(),
+                    steps_per_epoch, batch,
+                    [rate(step + b) for b in range(steps_per_epoch)],
+                    stream.cuda_stream)
+                step += steps_per_epoch
+            for b in range(0 if whole else steps_per_epoch):
                 idx = perm[b * batch:(b + 1) * batch]
                 th = theta.index_select(0, idx)
                 tg = targets.index_select(0, idx)
-                lr = lr_min + 0.5 * (lr_max - lr_min) * (
-                    1 + math.cos(math.pi * step / max(1, total)))
+                lr = rate(step)
                 want = log_every and (step % log_every == 0)
                 v = nr_mlp_train_step_dev(self.h, th.data_ptr(), tg.data_ptr(),
                                           batch, lr, bool(want),

@@ -68,3 +68,24 @@ def test_ragged_steps(B, N):
         assert np.all(np.abs(new - want) <= tol), (step, np.max(np.abs(new - want) / tol))
         params = new
     s.close()
+
+
+@pytest.mark.parametrize("P,batch,N", [(1000, 136, 72), (4096, 2048, 264), (50, 64, 8)])
+def test_gathered_epochs_match_stepwise_training(P, batch, N):
+    """Whole epochs whose kernels gather the batches, against the same epochs step
+    by step on tensors gathered before (asking for losses selects that): bitwise,
+    a batch larger than the sample (no step at all) included."""
+    import torch
+    from paper_2607_00488_amd.surrogate import Surrogate
+    lo, hi = synth.theta_box()
+    g = synth.rng(31)
+    th = torch.tensor(g.uniform(lo, hi, (P, 7)), device="cuda:0")
+    tg = torch.tensor(g.standard_normal((P, N)).astype(np.float32), device="cuda:0")
+    out = []
+    for log_every in (0, 1):
+        s = Surrogate(N, lo, hi, hidden=H, seed=32)
+        r = s.train(th, tg, epochs=3, batch=batch, log_every=log_every)
+        assert r["steps"] == 3 * (P // batch)
+        out.append(s.params())
+        s.close()
+    assert np.array_equal(*out)
