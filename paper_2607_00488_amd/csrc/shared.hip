@@ -50,6 +50,21 @@ __device__ inline int sh_find(const ShGroup<P, N>& g, int* wg) {
     return d;
 }
 
+// x[0] + x[st] + ... + x[(n - 1) st] in order, U of them in flight at a time.
+template <int U>
+__device__ inline double sum_strided(const __attribute__((address_space(1))) double* x, size_t st, int n) {
+    double s = 0.0;
+    for (int q = 0; q < n; q += U) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[min(q + u, n - 1) * st];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q + u < n) s += v[u];
+    }
+    return s;
+}
+
 // ------------------------------------------------------------------ fold
 // part[s][b][j] = sum over the rows l of split s of F_lb R_lj on the FP64
 // matrix cores, b the row operand (15 of 16 used), the response columns the
@@ -165,10 +180,7 @@ __global__ __launch_bounds__(kThreads) void k_sh_rec(ShGroup<ShRec, N> g) {
     if (b < kShCols) {
         double s = 0.0;
         if (ok) {
-            const auto* x = gm(a.part) + (size_t)b * a.ldr + j;
-            const size_t st = (size_t)kShCols * a.ldr;
-#pragma unroll 8
-            for (int q = 0; q < a.n_split; ++q) s += x[q * st];
+            s = sum_strided<16>(gm(a.part) + (size_t)b * a.ldr + j, (size_t)kShCols * a.ldr, a.n_split);
         } else if (b == kNBasis) {
             s = 1.0;
         }
@@ -423,49 +435,50 @@ __device__ inline double sh_nll(const ShFinal& a, double dev, const double th[kN
     return 2.0 * dev + 2.0 * a.cdata + pulls;
 }
 
-// One point per thread, the slices in order.
+// The slices of one quantity: the two halves, each in order, by two threads.
+template <class T>
+__device__ inline double sh_half(const T* x, size_t st, int n, int half) {
+    const int h = (n + 1) / 2, q0 = half ? h : 0, q1 = half ? n : h;
+    return q0 < q1 ? sum_strided<16>(gm(x) + q0 * st, st, q1 - q0) : 0.0;
+}
+
+// 32 points per work-group.
 template <int N>
 __global__ __launch_bounds__(64) void k_sh_final(ShGroup<ShFinal, N> g) {
     int wg;
     const ShFinal& a = g.p[sh_find(g, &wg)];
-    const int p = wg * 64 + threadIdx.x;
-    if (p >= a.n_pts) return;
-    double d = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < a.n_slice; ++q) d += gm(a.dpart)[(size_t)q * a.n_pts + p];
+    const int pl = threadIdx.x & 31, p = wg * 32 + pl, pc = min(p, a.n_pts - 1);
     double th[kNTheta];
 #pragma unroll
-    for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
-    gm(a.nll)[p] = sh_nll(a, d, th);
+    for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)pc * kNTheta + i];
+    double d = sh_half(a.dpart + pc, a.n_pts, a.n_slice, threadIdx.x >> 5);
+    d += __shfl_xor(d, 32, 64);
+    if (threadIdx.x < 32 && p < a.n_pts) gm(a.nll)[p] = sh_nll(a, d, th);
 }
 
-// 16 points per work-group, one (contraction, point) per thread; the constant
-// column's contraction is not needed, its threads sum the deviances.
+// 8 points per work-group, one half of one (contraction, point) per thread; the
+// constant column's contraction is not needed, its threads sum the deviances.
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_sh_final_grad(ShGroup<ShFinal, N> g) {
-    __shared__ double hs[16][kShAcc + 1];
+    __shared__ double hs[2][8][kShAcc + 1], ths[8][kNTheta];
     int wg;
     const ShFinal& a = g.p[sh_find(g, &wg)];
-    const int v = threadIdx.x >> 4, pl = threadIdx.x & 15, p = wg * 16 + pl;
-    double s = 0.0;
-    if (p < a.n_pts) {
-        const bool dev = v == kNBasis;
-        const auto* x = dev ? gm(a.dpart) + p : gm(a.hpart) + (size_t)v * a.n_pts + p;
-        const size_t st = (size_t)(dev ? 1 : kShAcc) * a.n_pts;
-#pragma unroll 8
-        for (int q = 0; q < a.n_slice; ++q) s += x[q * st];
-    }
-    hs[pl][v] = s;
+    const int half = threadIdx.x >> 7, v = (threadIdx.x >> 3) & 15, pl = threadIdx.x & 7;
+    const int p = wg * 8 + pl, pc = min(p, a.n_pts - 1);
+    if (half == 0 && v < kNTheta) ths[pl][v] = gm(a.theta)[(size_t)pc * kNTheta + v];
+    hs[half][pl][v] = v == kNBasis ? sh_half(a.dpart + pc, a.n_pts, a.n_slice, half)
+                                   : sh_half(a.hpart + (size_t)v * a.n_pts + pc,
+                                             (size_t)kShAcc * a.n_pts, a.n_slice, half);
     __syncthreads();
-    if (v != 0 || p >= a.n_pts) return;
+    if (threadIdx.x >= 8 || p >= a.n_pts) return;
     double th[kNTheta], gr[kNTheta], hh[kNBasis];
 #pragma unroll
-    for (int i = 0; i < kNTheta; ++i) th[i] = gm(a.theta)[(size_t)p * kNTheta + i];
+    for (int i = 0; i < kNTheta; ++i) th[i] = ths[pl][i];
 #pragma unroll
-    for (int b = 0; b < kNBasis; ++b) hh[b] = hs[pl][b];
+    for (int b = 0; b < kNBasis; ++b) hh[b] = hs[0][pl][b] + hs[1][pl][b];
     basis_grad(th, a.ph, hh, gr);
-    gr[6] = hs[pl][kNBasis + 1];
-    gm(a.nll)[p] = sh_nll(a, hs[pl][kNBasis], th);
+    gr[6] = hs[0][pl][kNBasis + 1] + hs[1][pl][kNBasis + 1];
+    gm(a.nll)[p] = sh_nll(a, hs[0][pl][kNBasis] + hs[1][pl][kNBasis], th);
 #pragma unroll
     for (int i = 0; i < kNTheta; ++i) {
         double q = gr[i];
@@ -525,8 +538,8 @@ __global__ __launch_bounds__(kThreads) void k_sh_mdata(ShMultiData a) {
     r[a.cols + 1] = n > 0.0 ? 1.0 / n : 1.0;
 }
 
-__device__ inline double sh_mnll(const ShMultiFinal& a, int p, double dev) {
-    const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
+template <class T>
+__device__ inline double sh_mnll(const ShMultiFinal& a, const T* th, double dev) {
     double pulls = 0.0;
     for (int i = 0; i < a.n_theta; ++i)
         if (a.pull_sigma[i] > 0.0) {
@@ -539,10 +552,9 @@ __device__ inline double sh_mnll(const ShMultiFinal& a, int p, double dev) {
 __global__ __launch_bounds__(64) void k_sh_mfinal(ShMultiFinal a) {
     const int p = blockIdx.x * 64 + threadIdx.x;
     if (p >= a.n_pts) return;
-    double d = 0.0;
-#pragma unroll 8
-    for (int q = 0; q < a.n_slice; ++q) d += gm(a.dpart)[(size_t)q * a.n_pts + p];
-    gm(a.nll)[p] = sh_mnll(a, p, d);
+    const double d = sh_half(a.dpart + p, a.n_pts, a.n_slice, 0) +
+                     sh_half(a.dpart + p, a.n_pts, a.n_slice, 1);
+    gm(a.nll)[p] = sh_mnll(a, gm(a.theta) + (size_t)p * a.n_theta, d);
 }
 
 // 16 points per work-group: the slices of every contraction, then
@@ -554,24 +566,25 @@ __global__ __launch_bounds__(kThreads) void k_sh_mfinal_grad(ShMultiFinal a) {
     constexpr int ACC = (COLS + 15) / 16 * 16;
     __shared__ double hs[16][COLS + 1];
     __shared__ double dv[16];
-    __shared__ double gs[16][kMaxTheta + 1];
+    __shared__ double gs[16][kMaxTheta + 1], ths[16][kMaxTheta + 1];
     const int v0 = threadIdx.x >> 4, pl = threadIdx.x & 15, p0 = blockIdx.x * 16, p = p0 + pl;
     const int n_col = kShCompCols * a.K + a.B;
+    const int n_row = min(16, a.n_pts - p0);
+    for (int i = threadIdx.x; i < n_row * a.n_theta; i += kThreads)
+        ths[i / a.n_theta][i % a.n_theta] = gm(a.theta)[(size_t)p0 * a.n_theta + i];
     if (p < a.n_pts) {
         for (int v = v0; v <= n_col; v += 16) {  // v = n_col: the deviance
             const bool dev = v == n_col;
-            const auto* x = dev ? gm(a.dpart) + p : gm(a.hpart) + (size_t)v * a.n_pts + p;
+            const double* x = dev ? a.dpart + p : a.hpart + (size_t)v * a.n_pts + p;
             const size_t st = (size_t)(dev ? 1 : ACC) * a.n_pts;
-            double s = 0.0;
-#pragma unroll 8
-            for (int q = 0; q < a.n_slice; ++q) s += x[q * st];
+            const double s = sh_half(x, st, a.n_slice, 0) + sh_half(x, st, a.n_slice, 1);
             if (dev) dv[pl] = s;
             else hs[pl][v] = s;
         }
     }
     __syncthreads();
     if (v0 == 0 && p < a.n_pts) {
-        const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
+        const double* th = ths[pl];
         double t5[5], c[kCompBasis], H[kCompBasis], g5[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
         for (int i = 0; i < 5; ++i) t5[i] = th[i];
         basis_coef7(t5, a.ph, 1.0, c);
@@ -592,11 +605,10 @@ __global__ __launch_bounds__(kThreads) void k_sh_mfinal_grad(ShMultiFinal a) {
         for (int i = 0; i < a.n_theta; ++i)
             if (a.pull_sigma[i] > 0.0)
                 gs[pl][i] += 2.0 * (th[i] - a.pull_mean[i]) / (a.pull_sigma[i] * a.pull_sigma[i]);
-        gm(a.nll)[p] = sh_mnll(a, p, dv[pl]);
+        gm(a.nll)[p] = sh_mnll(a, th, dv[pl]);
     }
     __syncthreads();
-    const int n = min(16, a.n_pts - p0) * a.n_theta;
-    for (int i = threadIdx.x; i < n; i += kThreads)
+    for (int i = threadIdx.x; i < n_row * a.n_theta; i += kThreads)
         gm(a.grad)[(size_t)p0 * a.n_theta + i] = gs[i / a.n_theta][i % a.n_theta];
 }
 
@@ -706,11 +718,11 @@ hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s) {
         if (!p[d].grad != !p[0].grad || (p[d].grad && !p[d].hpart)) return hipErrorInvalidValue;
     if (p[0].grad) {
 #define SH_K(M) (k_sh_final_grad<M>)
-        SH_LAUNCH(SH_K, ShFinal, kThreads, [](const ShFinal& f) { return (f.n_pts + 15) / 16; });
+        SH_LAUNCH(SH_K, ShFinal, kThreads, [](const ShFinal& f) { return (f.n_pts + 7) / 8; });
 #undef SH_K
     } else {
 #define SH_K(M) (k_sh_final<M>)
-        SH_LAUNCH(SH_K, ShFinal, 64, [](const ShFinal& f) { return (f.n_pts + 63) / 64; });
+        SH_LAUNCH(SH_K, ShFinal, 64, [](const ShFinal& f) { return (f.n_pts + 31) / 32; });
 #undef SH_K
     }
     return hipGetLastError();
@@ -747,17 +759,19 @@ hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Slices of 64 bins up to 4096 points (fixed by the response's shape, so that
-// a point's result does not depend on its list); beyond, as few as leave about
-// 8192 waves of 64 points, since every slice writes its sums for every point.
-// The multi-component form writes three to five times as many: about 2048 waves
-// of 16 points.
+// Slices of 64 bins up to 4096 points (fixed by the response's shape, so that a
+// point's result does not depend on its list); beyond, as few as fill whole rounds
+// of resident waves of 64 points, since every slice writes its sums for every
+// point: 6144 are two rounds of the likelihood kernel's three waves per SIMD and
+// three of the gradient's two (65536 x 4096: 8192 waves, 2.7 rounds, took 291 us).
+// The multi-component form writes three to five times as many: one round of its
+// gradient's two waves of 16 points per SIMD.
 void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice) {
     const int n_tile = (n_reco + kShBins - 1) / kShBins;
     int t = 4;
-    const int grp = multi ? (n_pts + 15) / 16 : (n_pts + 63) / 64, waves = multi ? 2048 : 8192;
+    const int grp = multi ? (n_pts + 15) / 16 : (n_pts + 63) / 64, waves = multi ? 2048 : 6144;
     if (multi || n_pts > 4096) {
-        const int ns = std::max(1, (waves + grp - 1) / grp);
+        const int ns = std::max(1, waves / grp);
         t = std::max(t, (n_tile + ns - 1) / ns);
     }
     *tiles = t;

@@ -64,7 +64,7 @@ def test_many_points_per_wave(n_pts):
     """Two and four blocks of points per wave: bitwise the lists' results,
     whose slices of 64 bins are the same."""
     import torch
-    p = inputs(64, 512, N_E, 100_000, 8311, 8312)
+    p = inputs(64, 256, N_E, 100_000, 8311, 8312)
     ctx = gpu_context(p)
     th = synth.theta_prior(n_pts, 8313, f_range=(0.8, 1.2))
     tt = torch.tensor(th, device="cuda:0")
