@@ -937,21 +937,38 @@ nr::ShFinal sh_final_args(const nr_ctx* c, const nr::ShEval& e, double* nll, dou
     return f;
 }
 
-// th: device memory, or with th_host pinned host memory whose copy there the
-// records launch makes.
+// Work-groups per slice of the launch that makes records and points together, for
+// n_pts points on folded columns of n_split splits; 0: a launch for either.  One
+// block of 16 points per wave, or two, as long as adding the splits up again in
+// every work-group reads no more than 32 MB.  At 16384 x 4096: 1 point 74 -> 68 us,
+// 100 points 60 -> 54; at 512 x 256, where the launches are short whatever they do,
+// 1057 points take 13.7 us with a launch for either and 13.9 together: up to 512.
+int sh_tail_wgs(const nr_ctx* c, int n_pts, int n_split) {
+    if (n_pts > 512) return 0;
+    const size_t bytes = sizeof(double) * n_split * nr::kShCols * c->ldr;
+    for (int per : {64, 128}) {
+        const int ny = (n_pts + per - 1) / per;
+        if (ny * bytes <= (size_t)32 << 20) return ny;
+    }
+    return 0;
+}
+
+// th: device memory, or with th_host pinned host memory whose copy there the fold
+// launch makes.
 int enqueue_shared(nr_ctx* c, double* base, int pts, const double* th, const double* th_host,
                    int n_pts, double* nll, double* grad, double* mu, hipStream_t s) {
     ShWork w;
     carve_sh(c, base, pts, true, 0, &w);
-    const nr::ShFold f = sh_fold_args(c, 0, w.part);
-    nr::ShRec r = sh_rec_args(c, f, w.rec);
+    nr::ShFold f = sh_fold_args(c, 0, w.part);
     if (th_host) {
-        r.th_src = th_host;
-        r.th_dst = const_cast<double*>(th);
-        r.n_th = n_pts * NR_NTHETA;
+        f.th_src = th_host;
+        f.th_dst = const_cast<double*>(th);
+        f.n_th = n_pts * NR_NTHETA;
     }
+    const nr::ShRec r = sh_rec_args(c, f, w.rec);
     HIPCHK(nr::launch_sh_fold(&f, 1, s));
-    HIPCHK(nr::launch_sh_rec(&r, 1, s));
+    const int ny = n_pts <= pts ? sh_tail_wgs(c, n_pts, f.n_split) : 0;
+    if (!ny) HIPCHK(nr::launch_sh_rec(&r, 1, s));
     for (int p0 = 0; p0 < n_pts; p0 += pts) {
         const nr::ShEval e = sh_eval_args(c, w.rec, th + (size_t)p0 * NR_NTHETA,
                                           std::min(pts, n_pts - p0), w.dpart,
@@ -959,7 +976,9 @@ int enqueue_shared(nr_ctx* c, double* base, int pts, const double* th, const dou
                                           mu ? mu + (size_t)p0 * c->n_reco : nullptr);
         const nr::ShFinal q = sh_final_args(c, e, nll + p0,
                                             grad ? grad + (size_t)p0 * NR_NTHETA : nullptr);
-        HIPCHK(nr::launch_sh_eval(&e, 1, s));
+        const nr::ShTail t{r, e, ny};
+        if (ny) HIPCHK(nr::launch_sh_tail(&t, 1, s));
+        else HIPCHK(nr::launch_sh_eval(&e, 1, s));
         HIPCHK(nr::launch_sh_final(&q, 1, s));
     }
     return 0;
@@ -1219,6 +1238,8 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
         nr::ShRec r[nr::kShGroup];
         nr::ShEval e[nr::kShGroup];
         nr::ShFinal q[nr::kShGroup];
+        nr::ShTail t[nr::kShGroup];
+        bool tail = true;
         for (int i = 0; i < n; ++i) {
             const int d = d0 + i;
             nr_ctx* c = mc.ctx[d];
@@ -1229,10 +1250,16 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
             e[i] = sh_eval_args(c, w.rec, mc.theta[d], mc.n_pts[d], w.dpart, w.hpart,
                                 mc.mu ? mc.mu[d] : nullptr);
             q[i] = sh_final_args(c, e[i], mc.nll[d], grad ? mc.grad[d] : nullptr);
+            t[i] = {r[i], e[i], sh_tail_wgs(c, mc.n_pts[d], f[i].n_split)};
+            tail = tail && t[i].ny;
         }
         HIPCHK(nr::launch_sh_fold(f, n, s));
-        HIPCHK(nr::launch_sh_rec(r, n, s));
-        HIPCHK(nr::launch_sh_eval(e, n, s));
+        if (tail) {
+            HIPCHK(nr::launch_sh_tail(t, n, s));
+        } else {
+            HIPCHK(nr::launch_sh_rec(r, n, s));
+            HIPCHK(nr::launch_sh_eval(e, n, s));
+        }
         HIPCHK(nr::launch_sh_final(q, n, s));
     }
     return 0;

@@ -7,8 +7,8 @@
 // points: 15 multiply-adds per response entry instead of one (two with the
 // gradient) per entry and point.  The gradient needs nothing more of R:
 //   d(-2lnL)/d theta_i = sum_b dc_b/d theta_i h_b, h_b = sum_j a_j (F^T R)_bj.
-// Four launches: fold, records (split sums and data, one record per bin),
-// points (mu, deviance, h), final.
+// Launches: fold; records (split sums and data, one record per bin) and points
+// (mu, deviance, h), together for short lists; final.
 #pragma once
 #include "basis.h"
 
@@ -29,6 +29,10 @@ struct ShFold {
     // per column tile the rows [lo, hi) that hold its non-zero responses (lo a
     // multiple of four), or null (every row)
     const int* band;
+    // points to copy to device memory beside the fold, or null
+    const double* th_src;
+    double* th_dst;
+    int n_th;  // values
     int ldr, n_t, n_ct, n_split, rows_per;
 };
 
@@ -37,10 +41,6 @@ struct ShRec {
     const double* n;  // [n_reco]
     const double* b;  // [n_reco]
     double* rec;      // [n_reco rounded up to kShBins][kShRec]
-    // points to copy to device memory beside the sums, or null
-    const double* th_src;
-    double* th_dst;
-    int n_th;         // values
     int n_split, ldr, n_reco;
 };
 
@@ -72,6 +72,15 @@ inline int sh_cols(int K, int B) {
     return K == 0 ? kShAcc : kShCompCols * K + B <= kShSmall ? kShSmall : kShLarge;
 }
 inline int sh_acc(int K, int B) { return (sh_cols(K, B) + 15) / 16 * 16; }
+
+// Records and points of a short list in one launch; slices of kShTailBins bins,
+// their points dealt to ny work-groups each.
+constexpr int kShTailBins = 64;
+struct ShTail {
+    ShRec r;
+    ShEval e;
+    int ny;
+};
 
 struct ShFinal {
     const double* dpart;
@@ -134,6 +143,7 @@ struct ShGroup {
 hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s);
 hipError_t launch_sh_rec(const ShRec* p, int n, hipStream_t s);
 hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s);
+hipError_t launch_sh_tail(const ShTail* p, int n, hipStream_t s);
 hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s);
 hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s);
 constexpr int kShSlabRows = 64;  // response rows per multi-component fold work-group

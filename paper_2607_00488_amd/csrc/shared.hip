@@ -92,6 +92,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     const int ct = t % a.n_ct, sp = t / a.n_ct;
     const int ldr = a.ldr, ld4 = ldr >> 2;
     const int c4 = ct * (kShTile / 4) + wave * 16 + li;
+    // the points of the call on their way to device memory: loaded here, stored
+    // at the end
+    const int gi = t * kThreads + tid, gn = a.n_ct * a.n_split * kThreads;
+    double th = 0.0;
+    if (a.th_src) {
+        if (gi < a.n_th) th = gm(a.th_src)[gi];
+        for (int i = gi + gn; i < a.n_th; i += gn) gm(a.th_dst)[i] = gm(a.th_src)[i];
+    }
     int kb = sp * a.rows_per, ke = min(a.n_t, kb + a.rows_per);
     if (a.band) {  // rows outside hold exact zeros in this tile's columns
         kb = max(kb, gm(a.band)[2 * ct]);
@@ -148,6 +156,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
         const v4f x = *(const __attribute__((address_space(1))) v4f*)(R + (size_t)rc * ldr * 4 + 16u * min(c4, ld4 - 1));
         quad(row < ke ? f : 0.0, x);
     }
+    if (a.th_src && gi < a.n_th) gm(a.th_dst)[gi] = th;
     if (c4 >= ld4) return;
     auto* out = gm(a.part) + (size_t)sp * kShCols * ldr + 4 * (size_t)c4;
 #pragma unroll
@@ -168,14 +177,9 @@ template <int N>
 __global__ __launch_bounds__(kThreads) void k_sh_rec(ShGroup<ShRec, N> g) {
     __shared__ double t[kShBins][kShRec];
     int wg;
-    const int d = sh_find(g, &wg);
-    const ShRec& a = g.p[d];
+    const ShRec& a = g.p[sh_find(g, &wg)];
     const int tid = threadIdx.x, b = tid >> 4, jl = tid & 15;
     const int j0 = wg * kShBins, j = j0 + jl;
-    if (a.th_src) {
-        const int step = (g.first[d + 1] - g.first[d]) * kThreads;
-        for (int i = wg * kThreads + tid; i < a.n_th; i += step) gm(a.th_dst)[i] = gm(a.th_src)[i];
-    }
     const bool ok = j < a.n_reco;
     if (b < kShCols) {
         double s = 0.0;
@@ -236,29 +240,34 @@ __device__ __attribute__((noinline)) double2 sh_slow_term(double mu, double n) {
     return make_double2(d, a);
 }
 
-template <bool GRAD, bool MU, int NB, int KS, int N>
-__global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
-    constexpr bool MULTI = KS != kShAcc / 4;
+__device__ inline const __attribute__((address_space(1))) v2d* as_pair(
+    const __attribute__((address_space(1))) double* p) {
+    return (const __attribute__((address_space(1))) v2d*)p;
+}
+__device__ inline const v2d* as_pair(const double* p) { return reinterpret_cast<const v2d*>(p); }
+
+template <int KS>
+struct ShCoefs {  // the multi-component form's coefficients, a wave's 16 points
+    static constexpr bool kMulti = KS != kShAcc / 4;
+    double v[kMulti ? 16 : 1][kMulti ? 4 * KS + 1 : 1];
+};
+
+// One wave: the points from p0 over tiles [t0, t1) of slice sl; rec: the record of
+// the first bin of tile t_rec.
+template <bool GRAD, bool MU, int NB, int KS, class Rec>
+__device__ __forceinline__ void sh_points(const ShEval& a, Rec rec, int t_rec, const LnTable& lt,
+                                          ShCoefs<KS>& cs, int p0, int sl, int t0, int t1) {
+    constexpr bool MULTI = ShCoefs<KS>::kMulti;
     constexpr int RL = 4 * KS + 2;          // record length
     constexpr int HB = (4 * KS + 15) / 16;  // blocks of 16 contractions
-    __shared__ LnTable lt;
-    __shared__ double cs[MULTI ? 4 : 1][MULTI ? 16 : 1][MULTI ? 4 * KS + 1 : 1];
-    int wg;
-    const ShEval& a = g.p[sh_find(g, &wg)];
-    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
-    static_assert(kThreads == kLnTab, "one table entry per thread");
-    lt.e[tid] = g_ln.e[tid];
-    __syncthreads();
-    const int n_pts = a.n_pts, n_grp = (n_pts + 16 * NB - 1) / (16 * NB);
-    const int w = wg * 4 + (tid >> 6), sl = w / n_grp, p0 = (w - sl * n_grp) * 16 * NB;
-    if (sl >= a.n_slice) return;
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4, n_pts = a.n_pts;
     // this lane's KS of each point's 4 KS coefficients (k = KS lk + s)
     double c[NB][KS];
     if constexpr (MULTI) {
         static_assert(NB == 1, "one block of points");
         const int p = min(p0 + li, n_pts - 1);
         const auto* th = gm(a.theta) + (size_t)p * a.n_theta;
-        auto& row = cs[tid >> 6][li];
+        auto& row = cs.v[li];
         double t5[5], v[kCompBasis];
 #pragma unroll
         for (int i = 0; i < 5; ++i) t5[i] = th[i];
@@ -294,9 +303,6 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
                 c[x][s] = lk == 0 ? v[s] : lk == 1 ? v[4 + s] : lk == 2 ? v[8 + s] : v[12 + s];
         }
     }
-    const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
-    const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
-    const auto* rec = gm(a.rec);
     // row operand i holds bin 4 (i % 4) + i / 4: output register r of lane
     // group lk is then bin 4 lk + r
     const int fb = (4 * (li & 3) + (li >> 2)) * RL + KS * lk;
@@ -306,9 +312,9 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
         double gr[HB][4];  // columns 16 y + li of bins 4 lk + r
     };
     auto load = [&](int t, Tile& q) {
-        const auto* r = rec + (size_t)t * (kShBins * RL);
+        const auto* r = rec + (t - t_rec) * (kShBins * RL);
         if constexpr (KS % 2 == 0) {
-            const auto* f = (const __attribute__((address_space(1))) v2d*)(r + fb);
+            const auto* f = as_pair(r + fb);
 #pragma unroll
             for (int s = 0; s < KS / 2; ++s) {
                 const v2d v = f[s];
@@ -322,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const auto* b = r + (4 * lk + e) * RL;
-            q.n[e] = *(const __attribute__((address_space(1))) v2d*)(b + 4 * KS);
+            q.n[e] = *as_pair(b + 4 * KS);
             if (GRAD)
 #pragma unroll
                 for (int y = 0; y < HB; ++y)  // the last block may end past the columns
@@ -420,6 +426,82 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
                 for (int r = 0; r < 4; ++r)
                     gm(a.hpart)[((size_t)sl * (16 * HB) + 16 * y + lk + 4 * r) * n_pts + p] = h[x][y][r];
     }
+}
+
+
+template <bool GRAD, bool MU, int NB, int KS, int N>
+__global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
+    __shared__ LnTable lt;
+    __shared__ ShCoefs<KS> cs[4];
+    int wg;
+    const ShEval& a = g.p[sh_find(g, &wg)];
+    const int tid = threadIdx.x;
+    static_assert(kThreads == kLnTab, "one table entry per thread");
+    lt.e[tid] = g_ln.e[tid];
+    __syncthreads();
+    const int n_grp = (a.n_pts + 16 * NB - 1) / (16 * NB);
+    const int w = wg * 4 + (tid >> 6), sl = w / n_grp, p0 = (w - sl * n_grp) * 16 * NB;
+    if (sl >= a.n_slice) return;
+    const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
+    const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
+    sh_points<GRAD, MU, NB, KS>(a, gm(a.rec), 0, lt, cs[tid >> 6], p0, sl, t0, t1);
+}
+
+// Short lists: one launch makes the records of one slice of bins, in LDS, and
+// takes every point over them, instead of a launch for either with the records in
+// memory between (each costs about 4 us whatever it does).  With many points
+// several work-groups share a slice, each adding up its splits again.
+template <bool GRAD, bool MU, int N>
+__global__ __launch_bounds__(kThreads) void k_sh_tail(ShGroup<ShTail, N> g) {
+    __shared__ LnTable lt;
+    __shared__ ShCoefs<kShAcc / 4> cs;  // unused by this form
+    __shared__ __attribute__((aligned(16))) double rec[kShTailBins][kShRec];
+    int wg;
+    const ShTail& q = g.p[sh_find(g, &wg)];
+    const ShRec& r = q.r;
+    const ShEval& a = q.e;
+    const int tid = threadIdx.x, sl = wg % a.n_slice, y = wg / a.n_slice;
+    lt.e[tid] = g_ln.e[tid];
+    const int j0 = sl * kShTailBins;
+    // one bin per lane, four columns per wave; eight splits of all four in flight
+    {
+        const int jl = tid & 63, j = j0 + jl, b0 = (tid >> 6) * 4;
+        const bool ok = j < r.n_reco;
+        const int jc = min(j, r.n_reco - 1);
+        const size_t st = (size_t)kShCols * r.ldr;
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int p = 0; p < r.n_split; p += 8) {
+            double v[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[u][e] = gm(r.part)[min(p + u, r.n_split - 1) * st +
+                                         (size_t)min(b0 + e, kShCols - 1) * r.ldr + jc];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p + u < r.n_split)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] += v[u][e];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int b = b0 + e;
+            if (b < kShCols) rec[jl][b] = ok ? s[e] : b == kNBasis ? 1.0 : 0.0;
+        }
+        if (b0 == 12) {
+            const double n = ok ? gm(r.n)[jc] : 1.0;
+            rec[jl][kShCols] = ok ? gm(r.b)[jc] : 0.0;
+            rec[jl][kShCols + 1] = n;
+            rec[jl][kShCols + 2] = n > 0.0 ? 1.0 / n : 1.0;
+        }
+    }
+    __syncthreads();
+    const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
+    const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
+    const int n_blk = (a.n_pts + 15) / 16;
+    for (int b = y * 4 + (tid >> 6); b < n_blk; b += q.ny * 4)
+        sh_points<GRAD, MU, 1, kShAcc / 4>(a, &rec[0][0], t0, lt, cs, 16 * b, sl, t0, t1);
 }
 
 // ----------------------------------------------------------------- final
@@ -712,6 +794,31 @@ hipError_t launch_sh_eval(const ShEval* p, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_sh_tail(const ShTail* p, int n, hipStream_t s) {
+    if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
+    for (int d = 0; d < n; ++d)
+        if (p[d].ny < 1 || p[d].e.tiles * kShBins != kShTailBins || p[d].e.K ||
+            !p[d].e.hpart != !p[0].e.hpart || !p[d].e.mu != !p[0].e.mu ||
+            (p[d].e.hpart && p[d].e.mu) || p[d].r.n_reco != p[d].e.n_reco ||
+            (long)kShTailBins * p[d].e.n_slice < p[d].e.n_reco)
+            return hipErrorInvalidValue;
+    const auto wgs = [](const ShTail& t) { return t.e.n_slice * t.ny; };
+    if (p[0].e.hpart) {
+#define SH_K(M) (k_sh_tail<true, false, M>)
+        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+#undef SH_K
+    } else if (p[0].e.mu) {
+#define SH_K(M) (k_sh_tail<false, true, M>)
+        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+#undef SH_K
+    } else {
+#define SH_K(M) (k_sh_tail<false, false, M>)
+        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+#undef SH_K
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_sh_final(const ShFinal* p, int n, hipStream_t s) {
     if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
     for (int d = 0; d < n; ++d)
@@ -763,7 +870,7 @@ hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s) {
 // point's result does not depend on its list); beyond, as few as fill whole rounds
 // of resident waves of 64 points, since every slice writes its sums for every
 // point: 6144 are two rounds of the likelihood kernel's three waves per SIMD and
-// three of the gradient's two (65536 x 4096: 8192 waves, 2.7 rounds, took 291 us).
+// three of the gradient's two (65536 x 4096: 3072 to 16384 waves within 5 %).
 // The multi-component form writes three to five times as many: one round of its
 // gradient's two waves of 16 points per SIMD.
 void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice) {
