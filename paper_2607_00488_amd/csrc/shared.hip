@@ -447,12 +447,16 @@ __global__ __launch_bounds__(kThreads) void k_sh_eval(ShGroup<ShEval, N> g) {
     sh_points<GRAD, MU, NB, KS>(a, gm(a.rec), 0, lt, cs[tid >> 6], p0, sl, t0, t1);
 }
 
+constexpr int kTailThreads = 64 * (kShCols + 1);
+
 // Short lists: one launch makes the records of one slice of bins, in LDS, and
 // takes every point over them, instead of a launch for either with the records in
 // memory between (each costs about 4 us whatever it does).  With many points
-// several work-groups share a slice, each adding up its splits again.
+// several work-groups share a slice, each adding up its splits again: sixteen
+// splits of every column in flight at once (a wave per column; four waves of four
+// columns waited twice as often: one point at 16384 x 4096 67.6 -> 66.4 us).
 template <bool GRAD, bool MU, int N>
-__global__ __launch_bounds__(kThreads) void k_sh_tail(ShGroup<ShTail, N> g) {
+__global__ __launch_bounds__(kTailThreads) void k_sh_tail(ShGroup<ShTail, N> g) {
     __shared__ LnTable lt;
     __shared__ ShCoefs<kShAcc / 4> cs;  // unused by this form
     __shared__ __attribute__((aligned(16))) double rec[kShTailBins][kShRec];
@@ -460,47 +464,29 @@ __global__ __launch_bounds__(kThreads) void k_sh_tail(ShGroup<ShTail, N> g) {
     const ShTail& q = g.p[sh_find(g, &wg)];
     const ShRec& r = q.r;
     const ShEval& a = q.e;
-    const int tid = threadIdx.x, sl = wg % a.n_slice, y = wg / a.n_slice;
-    lt.e[tid] = g_ln.e[tid];
+    const int tid = threadIdx.x, wave = tid >> 6, sl = wg % a.n_slice, y = wg / a.n_slice;
     const int j0 = sl * kShTailBins;
-    // one bin per lane, four columns per wave; eight splits of all four in flight
+    // one bin per lane, one column per wave (the last wave: the bin's data)
     {
-        const int jl = tid & 63, j = j0 + jl, b0 = (tid >> 6) * 4;
+        const int jl = tid & 63, j = j0 + jl, jc = min(j, r.n_reco - 1);
         const bool ok = j < r.n_reco;
-        const int jc = min(j, r.n_reco - 1);
-        const size_t st = (size_t)kShCols * r.ldr;
-        double s[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int p = 0; p < r.n_split; p += 8) {
-            double v[8][4];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    v[u][e] = gm(r.part)[min(p + u, r.n_split - 1) * st +
-                                         (size_t)min(b0 + e, kShCols - 1) * r.ldr + jc];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (p + u < r.n_split)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s[e] += v[u][e];
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int b = b0 + e;
-            if (b < kShCols) rec[jl][b] = ok ? s[e] : b == kNBasis ? 1.0 : 0.0;
-        }
-        if (b0 == 12) {
+        if (wave < kShCols) {
+            const double s = sum_strided<16>(gm(r.part) + (size_t)wave * r.ldr + jc,
+                                             (size_t)kShCols * r.ldr, r.n_split);
+            rec[jl][wave] = ok ? s : wave == kNBasis ? 1.0 : 0.0;
+        } else {
             const double n = ok ? gm(r.n)[jc] : 1.0;
             rec[jl][kShCols] = ok ? gm(r.b)[jc] : 0.0;
             rec[jl][kShCols + 1] = n;
             rec[jl][kShCols + 2] = n > 0.0 ? 1.0 / n : 1.0;
         }
+        if (tid < kThreads) lt.e[tid] = g_ln.e[tid];
     }
     __syncthreads();
     const int n_tile = (a.n_reco + kShBins - 1) / kShBins;
     const int t0 = sl * a.tiles, t1 = min(n_tile, t0 + a.tiles);
     const int n_blk = (a.n_pts + 15) / 16;
-    for (int b = y * 4 + (tid >> 6); b < n_blk; b += q.ny * 4)
+    for (int b = wave * q.ny + y; b < n_blk; b += q.ny * (kTailThreads / 64))
         sh_points<GRAD, MU, 1, kShAcc / 4>(a, &rec[0][0], t0, lt, cs, 16 * b, sl, t0, t1);
 }
 
@@ -805,15 +791,15 @@ hipError_t launch_sh_tail(const ShTail* p, int n, hipStream_t s) {
     const auto wgs = [](const ShTail& t) { return t.e.n_slice * t.ny; };
     if (p[0].e.hpart) {
 #define SH_K(M) (k_sh_tail<true, false, M>)
-        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+        SH_LAUNCH(SH_K, ShTail, kTailThreads, wgs);
 #undef SH_K
     } else if (p[0].e.mu) {
 #define SH_K(M) (k_sh_tail<false, true, M>)
-        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+        SH_LAUNCH(SH_K, ShTail, kTailThreads, wgs);
 #undef SH_K
     } else {
 #define SH_K(M) (k_sh_tail<false, false, M>)
-        SH_LAUNCH(SH_K, ShTail, kThreads, wgs);
+        SH_LAUNCH(SH_K, ShTail, kTailThreads, wgs);
 #undef SH_K
     }
     return hipGetLastError();
