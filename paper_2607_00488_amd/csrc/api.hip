@@ -2572,8 +2572,7 @@ int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const long long
     return 0;
 }
 
-int mlp_input(nr_mlp* q, const double* th, int B, hipStream_t s,
-              int* outside = nullptr) {
+nr::MlpInput mlp_input_args(const nr_mlp* q, const double* th, int B, int* outside) {
     nr::MlpInput in{};
     in.theta = th;
     in.B = B;
@@ -2583,7 +2582,11 @@ int mlp_input(nr_mlp* q, const double* th, int B, hipStream_t s,
     }
     in.x = q->x;
     in.outside = outside ? outside : q->outside;
-    HIPCHK(nr::launch_mlp_input(in, s));
+    return in;
+}
+
+int mlp_input(nr_mlp* q, const double* th, int B, hipStream_t s, int* outside = nullptr) {
+    HIPCHK(nr::launch_mlp_input(mlp_input_args(q, th, B, outside), s));
     return 0;
 }
 
@@ -2869,26 +2872,12 @@ int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
     // bin groups per point tile: about two work-groups per compute unit
     const int n_pt = (B + 127) / 128;
     const int nnt = std::max(1, std::min((q->n_out + 127) / 128, (512 + n_pt - 1) / n_pt));
-    if ((rc = mlp_input(q, d_theta, B, s, d_outside))) return rc;
     nr::MlpGemm go = mg(q->h[2], ldh, 1, q->w16 + q->off[3], 1, ldh, B, q->n_out, ldh);
     go.mean = q->mean;
     go.stdv = q->stdv;
     go.nobs = c->d_n;
     go.part = q->part;
     go.n_nt = nnt;
-    if (q->H == nr::kFusedHidden) {
-        // the whole network in one launch, activations kept in LDS
-        nr::MlpHidden hd{};
-        hd.x = q->x;
-        for (int l = 0; l < 3; ++l) {
-            hd.w[l] = q->w16 + q->off[l];
-            hd.k[l] = q->kp[l];
-        }
-        HIPCHK(nr::launch_mlp_nll_fused(go, hd, s));
-    } else {
-        if ((rc = mlp_hidden_forward(q, B, s))) return rc;
-        HIPCHK(nr::launch_mlp_gemm(nr::kMlpNll, go, s));
-    }
     nr::FinalArgs f{};
     f.part = q->part;
     f.theta = d_theta;
@@ -2901,6 +2890,24 @@ int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
         f.pull_sigma[i] = c->pull_sigma[i];
     }
     f.nll = d_nll;
+    if (q->H == nr::kFusedHidden) {
+        // the whole network in one launch, activations kept in LDS, theta in and,
+        // with one bin group, -2lnL out (launches for the input and the end took
+        // 7.6 and 4.9 us of 205 at 65536 points)
+        nr::MlpHidden hd{};
+        hd.in = mlp_input_args(q, d_theta, B, d_outside);
+        for (int l = 0; l < 3; ++l) {
+            hd.w[l] = q->w16 + q->off[l];
+            hd.k[l] = q->kp[l];
+        }
+        hd.fin = f;
+        HIPCHK(nr::launch_mlp_nll_fused(go, hd, s));
+        if (nnt == 1) return 0;
+    } else {
+        if ((rc = mlp_input(q, d_theta, B, s, d_outside))) return rc;
+        if ((rc = mlp_hidden_forward(q, B, s))) return rc;
+        HIPCHK(nr::launch_mlp_gemm(nr::kMlpNll, go, s));
+    }
     HIPCHK(nr::launch_finalize(f, s));
     return 0;
 }

@@ -61,6 +61,16 @@ struct KSumArgs {
     long ldc16;
 };
 
+// d rounded once to BF16: through the float with an odd last bit where d lies
+// between two floats.
+__device__ inline bf16 bf16_of(double d) {
+    const float f = (float)d;
+    const double b = (double)f;
+    unsigned u = __float_as_uint(f);
+    if (b != d && !(u & 1u)) u += fabs(d) > fabs(b) ? 1u : ~0u;
+    return (bf16)__uint_as_float(u);
+}
+
 struct MlpInput {
     const double* theta;  // [B][7]
     int B;
@@ -87,17 +97,6 @@ struct TargetArgs {
     float* t;             // [P][N] standardised log mu
 };
 
-// The hidden layers for the fused inference kernel: input x [M][32]
-// (normalised theta, 1, zeros) and three layers of kFusedHidden outputs
-// with weights W_l [kFusedHidden][k_l], k_0 = 32 and k_1 = k_2 =
-// kFusedHidden + 8 (the inputs, the bias column, zeros).
-constexpr int kFusedHidden = 256;
-struct MlpHidden {
-    const bf16* x;
-    const bf16* w[3];
-    int k[3];
-};
-
 // -2lnL per point from the bin groups' sums, the data constant and the pulls.
 struct FinalArgs {
     const double* part;   // [n_pts][n_nt]
@@ -109,11 +108,23 @@ struct FinalArgs {
     double* nll;
 };
 
+// The whole network's kernel: theta in (in.x is not read or written), three layers
+// of kFusedHidden outputs with weights W_l [kFusedHidden][k_l], k_0 = 32 and
+// k_1 = k_2 = kFusedHidden + 8 (the inputs, the bias column, zeros).  With one bin
+// group (n_nt = 1) the kernel ends with `fin` itself.
+constexpr int kFusedHidden = 256;
+struct MlpHidden {
+    MlpInput in;
+    const bf16* w[3];
+    int k[3];
+    FinalArgs fin;
+};
+
 hipError_t launch_finalize(const FinalArgs& a, hipStream_t s);
 hipError_t launch_mlp_gemm(int mode, const MlpGemm& g, hipStream_t s);
 // The whole network and the likelihood partials in one launch (kMlpNll's
 // output with the hidden layers formed in LDS); g as for kMlpNll except
-// that g.A is not read.
+// that g.A is not read.  One bin group: -2lnL instead of the partials.
 hipError_t launch_mlp_nll_fused(const MlpGemm& g, const MlpHidden& h, hipStream_t s);
 hipError_t launch_mlp_ksum(const KSumArgs& a, hipStream_t s);
 hipError_t launch_mlp_input(const MlpInput& a, hipStream_t s);

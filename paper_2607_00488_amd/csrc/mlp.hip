@@ -249,6 +249,30 @@ __device__ __forceinline__ void hidden_layer(bf16 (*As)[kNllLda], const bf16* __
     __syncthreads();
 }
 
+// Normalised theta and the bias input (1) of point p; whether theta lies outside
+// the box.
+__device__ inline bool mlp_input_row(const MlpInput& a, int p, bf16* x) {
+    bool out = false;
+    for (int i = 0; i < kNTheta; ++i) {
+        const double t = a.theta[(long)p * kNTheta + i];
+        out = out || !(t >= a.lo[i] && t <= a.hi[i]);
+        x[i] = bf16_of(2.0 * (t - a.lo[i]) / (a.hi[i] - a.lo[i]) - 1.0);
+    }
+    x[kNTheta] = (bf16)1.f;
+    return out;
+}
+
+// -2lnL of point p with deviance sum d: the data constant and the pulls.
+__device__ inline double finish_point(const FinalArgs& a, int p, double d) {
+    double pulls = 0.0;
+    for (int i = 0; i < kNTheta; ++i)
+        if (a.pull_sigma[i] > 0.0) {
+            const double z = (a.theta[(size_t)p * kNTheta + i] - a.pull_mean[i]) / a.pull_sigma[i];
+            pulls += z * z;
+        }
+    return 2.0 * d + 2.0 * a.cdata + pulls;
+}
+
 // FUSED: the kernel first forms the points' activations itself from the
 // network input through the three hidden layers (the whole network in one
 // launch, nothing but theta's encoding read and the partial sums written);
@@ -264,16 +288,20 @@ __global__ __launch_bounds__(kMlpThreads, 2) void k_mlp_nll(MlpGemm g, MlpHidden
     const int m0 = blockIdx.x * TM;
     constexpr int CH = kNllKS * 2;          // 16-byte chunks per row
     if constexpr (FUSED) {
-        // the tile: inputs in columns 0..31, the bias input (1) at column
-        // kFusedHidden, zeros elsewhere
+        // the tile: normalised theta and 1 in columns 0..7, the bias input (1) at
+        // column kFusedHidden, zeros elsewhere
         for (int q = tid; q < TM * (kNllLda / 8); q += kMlpThreads) {
-            const int row = q / (kNllLda / 8), k = (q % (kNllLda / 8)) * 8, m = m0 + row;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (k < 32 && m < g.M) v = *reinterpret_cast<const uint4*>(hd.x + (long)m * 32 + k);
-            *reinterpret_cast<uint4*>(&As[row][k]) = v;
+            const int row = q / (kNllLda / 8), k = (q % (kNllLda / 8)) * 8;
+            *reinterpret_cast<uint4*>(&As[row][k]) = make_uint4(0u, 0u, 0u, 0u);
         }
         __syncthreads();
-        if (tid < TM) As[tid][kFusedHidden] = (bf16)1.f;
+        if (tid < TM) {
+            As[tid][kFusedHidden] = (bf16)1.f;
+            if (m0 + tid < g.M) {
+                const bool out = mlp_input_row(hd.in, m0 + tid, &As[tid][0]);
+                if (hd.in.outside && blockIdx.y == 0) hd.in.outside[m0 + tid] = out ? 1 : 0;
+            }
+        }
         __syncthreads();
         hidden_layer<2>(As, hd.w[0], hd.k[0], wave, li, lh);
         hidden_layer<kNllKS>(As, hd.w[1], hd.k[1], wave, li, lh);
@@ -400,9 +428,11 @@ __global__ __launch_bounds__(kMlpThreads, 2) void k_mlp_nll(MlpGemm g, MlpHidden
         if (lh == 0) red[wave][y * 32 + li] = pp[y];
     }
     __syncthreads();
-    if (tid < TM && m0 + tid < g.M)
-        g.part[(long)(m0 + tid) * g.n_nt + blockIdx.y] =
-            red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+    if (tid < TM && m0 + tid < g.M) {
+        const double d = red[0][tid] + red[1][tid] + red[2][tid] + red[3][tid];
+        if (FUSED && gridDim.y == 1) hd.fin.nll[m0 + tid] = finish_point(hd.fin, m0 + tid, d);
+        else g.part[(long)(m0 + tid) * g.n_nt + blockIdx.y] = d;
+    }
 }
 
 // -2lnL per point: sum of the column-tile deviance partials, data constant,
@@ -432,27 +462,14 @@ __device__ inline double row_sum(const double* x, int n) {
 __global__ void k_finalize(FinalArgs a) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_pts) return;
-    const double d = row_sum(a.part + (size_t)p * a.n_nt, a.n_nt);
-    double pulls = 0.0;
-    for (int i = 0; i < kNTheta; ++i)
-        if (a.pull_sigma[i] > 0.0) {
-            const double z = (a.theta[(size_t)p * kNTheta + i] - a.pull_mean[i]) / a.pull_sigma[i];
-            pulls += z * z;
-        }
-    a.nll[p] = 2.0 * d + 2.0 * a.cdata + pulls;
+    a.nll[p] = finish_point(a, p, row_sum(a.part + (size_t)p * a.n_nt, a.n_nt));
 }
 
 __global__ void k_mlp_input(MlpInput a) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.B) return;
-    bool out = false;
     bf16* x = a.x + (long)p * 32;
-    for (int i = 0; i < kNTheta; ++i) {
-        const double t = a.theta[(long)p * kNTheta + i];
-        out = out || !(t >= a.lo[i] && t <= a.hi[i]);
-        x[i] = (bf16)(float)(2.0 * (t - a.lo[i]) / (a.hi[i] - a.lo[i]) - 1.0);
-    }
-    x[kNTheta] = (bf16)1.f;
+    const bool out = mlp_input_row(a, p, x);
     for (int i = kNTheta + 1; i < 32; ++i) x[i] = (bf16)0.f;
     if (a.outside) a.outside[p] = out ? 1 : 0;
 }
@@ -556,7 +573,7 @@ hipError_t launch_mlp_gemm(int mode, const MlpGemm& g, hipStream_t s) {
 hipError_t launch_mlp_nll_fused(const MlpGemm& g, const MlpHidden& h, hipStream_t s) {
     if (g.K > kNllKS * 16 || g.sak != 1 || g.sbk != 1 || g.n_nt < 1 || g.N % 8 ||
         g.n_nt > (g.N + TN - 1) / TN || g.M % 8 || h.k[0] != 32 ||
-        h.k[1] != kFusedHidden + 8 || h.k[2] != kFusedHidden + 8 || g.K != kFusedHidden + 8)
+        h.k[1] != kFusedHidden + 8 || h.k[2] != kFusedHidden + 8 || g.K != kFusedHidden + 8 || h.in.B != g.M)
         return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_mlp_nll<true>, dim3((g.M + TM - 1) / TM, g.n_nt), dim3(kMlpThreads),
                        0, s, g, h);

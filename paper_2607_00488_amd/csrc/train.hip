@@ -41,16 +41,6 @@ __device__ inline f32x16 zero16() {
 // row of register r in a 32 x 32 block
 __device__ inline int blk_row(int r, int lh) { return (r >> 2) * 8 + lh * 4 + (r & 3); }
 
-// d rounded once to BF16: through the float with an odd last bit where d lies
-// between two floats (the conversion the stand-alone input kernel compiles to).
-__device__ inline bf16 bf16_of(double d) {
-    const float f = (float)d;
-    const double b = (double)f;
-    unsigned u = __float_as_uint(f);
-    if (b != d && !(u & 1u)) u += fabs(d) > fabs(b) ? 1u : ~0u;
-    return (bf16)__uint_as_float(u);
-}
-
 __device__ inline float silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.f + __expf(-z));
 }
