@@ -2341,13 +2341,13 @@ struct nr_mlp {
     nr::bf16 *x = nullptr, *h[3] = {nullptr, nullptr, nullptr};
     float* z[3] = {nullptr, nullptr, nullptr};
     nr::bf16 *dy = nullptr, *dz[2] = {nullptr, nullptr};
-    // matrices of the fused step (train.h): input, activations, output and hidden
-    // gradients, weights by outputs and by inputs (packed: they are up to date)
+    // a network of kFusedHidden units: its weights in fragment order (train.h), by
+    // outputs and by inputs, kept with w16; the fused step's input, activations,
+    // output and hidden gradients
+    nr::bf16 *wf[4] = {}, *wt[4] = {};
     nr::bf16 *xt = nullptr, *ht[3] = {nullptr, nullptr, nullptr}, *dyt = nullptr;
     nr::bf16 *h2f = nullptr, *dyf = nullptr, *dz2f = nullptr;
     nr::bf16 *dzt[3] = {nullptr, nullptr, nullptr};
-    nr::bf16 *wf[4] = {}, *wt[4] = {};
-    bool packed = false;
     double* tile_loss = nullptr;
     double* part = nullptr;
     float* gpart = nullptr;     // K-split weight-gradient slabs
@@ -2398,10 +2398,6 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
                     return rc;
                 HIPCHK(nr::launch_train_ones(q->ht[l], nr::frag_steps(cap), q->stream));
             }
-            for (int l = 0; l < 4 && !q->wf[l]; ++l)
-                if ((rc = dalloc(&q->wf[l], nr::frag_size(q->nn[l], q->kp[l]))) ||
-                    (rc = dalloc(&q->wt[l], nr::frag_size(q->kp[l], q->nn[l]))))
-                    return rc;
             HIPCHK(hipStreamSynchronize(q->stream));
         } else {
             if ((rc = dalloc(&q->dy, (size_t)cap * N)) || (rc = dalloc(&q->dz[0], (size_t)cap * H)) ||
@@ -2511,11 +2507,6 @@ int mlp_hidden_forward(nr_mlp* q, int B, hipStream_t s) {
 int mlp_train_fused(nr_mlp* q, const double* th, const float* t, const long long* idx,
                     const nr::AdamArgs& ad, int B, hipStream_t s) {
     const int H = q->H, N = q->n_out;
-    if (!q->packed) {
-        for (int l = 0; l < 4; ++l)
-            HIPCHK(nr::launch_train_pack({q->w16 + q->off[l], q->wf[l], q->wt[l], q->nn[l], q->kp[l]}, s));
-        q->packed = true;
-    }
     nr::TrainBufs b{};
     b.xt = q->xt;
     for (int l = 0; l < 3; ++l) {
@@ -2626,6 +2617,15 @@ int nr_mlp_create(int device, int hidden, int n_out, nr_mlp** out) {
         delete q;
         return rc;
     }
+    for (int l = 0; l < 4 && hidden == nr::kFusedHidden; ++l) {
+        const size_t nf = nr::frag_size(q->nn[l], q->kp[l]), nt = nr::frag_size(q->kp[l], q->nn[l]);
+        if ((rc = dalloc(&q->wf[l], nf)) || (rc = dalloc(&q->wt[l], nt))) {
+            nr_mlp_destroy(q);
+            return rc;
+        }
+        (void)hipMemset(q->wf[l], 0, sizeof(nr::bf16) * nf);
+        (void)hipMemset(q->wt[l], 0, sizeof(nr::bf16) * nt);
+    }
     (void)hipMemset(q->w, 0, sizeof(float) * q->n_params);
     (void)hipMemset(q->w16, 0, sizeof(nr::bf16) * q->n_params);
     (void)hipMemset(q->w16t, 0, sizeof(nr::bf16) * q->n_params);
@@ -2667,10 +2667,13 @@ int nr_mlp_set_params(nr_mlp* q, const float* params, long n) {
     HIPCHK(hipMemcpy(q->w16, h16.data(), sizeof(nr::bf16) * n, hipMemcpyHostToDevice));
     int rt;
     if ((rt = mlp_transpose(q, q->stream))) return rt;
+    if (q->H == nr::kFusedHidden)
+        for (int l = 0; l < 4; ++l)
+            HIPCHK(nr::launch_train_pack({q->w16 + q->off[l], q->wf[l], q->wt[l], q->nn[l], q->kp[l]},
+                                         q->stream));
     HIPCHK(hipStreamSynchronize(q->stream));
     HIPCHK(hipMemset(q->m, 0, sizeof(float) * n));
     HIPCHK(hipMemset(q->v, 0, sizeof(float) * n));
-    q->packed = false;
     q->step = 0;
     return 0;
 }
@@ -2896,10 +2899,7 @@ int nr_mlp_nll_dev(nr_mlp* q, nr_ctx* c, const double* d_theta, int B,
         // 7.6 and 4.9 us of 205 at 65536 points)
         nr::MlpHidden hd{};
         hd.in = mlp_input_args(q, d_theta, B, d_outside);
-        for (int l = 0; l < 3; ++l) {
-            hd.w[l] = q->w16 + q->off[l];
-            hd.k[l] = q->kp[l];
-        }
+        for (int l = 0; l < 4; ++l) hd.w[l] = q->wf[l];
         hd.fin = f;
         HIPCHK(nr::launch_mlp_nll_fused(go, hd, s));
         if (nnt == 1) return 0;

@@ -108,15 +108,14 @@ struct FinalArgs {
     double* nll;
 };
 
-// The whole network's kernel: theta in (in.x is not read or written), three layers
-// of kFusedHidden outputs with weights W_l [kFusedHidden][k_l], k_0 = 32 and
-// k_1 = k_2 = kFusedHidden + 8 (the inputs, the bias column, zeros).  With one bin
-// group (n_nt = 1) the kernel ends with `fin` itself.
+// The whole network's kernel: theta in (in.x is not read or written), the weights of
+// the three layers of kFusedHidden outputs and of the output layer in fragment order
+// by outputs (train.h; 2 and 17 steps of 16 inputs).  With one bin group (n_nt = 1)
+// the kernel ends with `fin` itself.
 constexpr int kFusedHidden = 256;
 struct MlpHidden {
     MlpInput in;
-    const bf16* w[3];
-    int k[3];
+    const bf16* w[4];
     FinalArgs fin;
 };
 
@@ -124,7 +123,7 @@ hipError_t launch_finalize(const FinalArgs& a, hipStream_t s);
 hipError_t launch_mlp_gemm(int mode, const MlpGemm& g, hipStream_t s);
 // The whole network and the likelihood partials in one launch (kMlpNll's
 // output with the hidden layers formed in LDS); g as for kMlpNll except
-// that g.A is not read.  One bin group: -2lnL instead of the partials.
+// that g.A and g.B are not read.  One bin group: -2lnL instead of the partials.
 hipError_t launch_mlp_nll_fused(const MlpGemm& g, const MlpHidden& h, hipStream_t s);
 hipError_t launch_mlp_ksum(const KSumArgs& a, hipStream_t s);
 hipError_t launch_mlp_input(const MlpInput& a, hipStream_t s);
