@@ -34,30 +34,6 @@ def algorithmic_bytes(n_t, n_reco):
     return 4 * n_t * n_reco + 16 * n_t + 16 * n_reco
 
 
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles",
-                               "k_step_plain_16384x4096_hbm_traffic.md")
-# the step kernel and the host code that picks its tiling
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2607_00488_amd", "csrc", f)
-                  for f in ("plain.hip", "common.h", "api.hip")]
-
-
-def measured_traffic():
-    """HBM bytes per k_step launch from the committed counter summary, or
-    None when the kernel sources changed since the counters were taken."""
-    import hashlib
-    try:
-        txt = open(TRAFFIC_PROFILE).read()
-        src = b"".join(open(f, "rb").read() for f in KERNEL_SOURCES)
-    except OSError:
-        return None
-    vals = dict(ln.split(": ", 1) for ln in txt.splitlines()
-                if ln.startswith(("traffic_bytes_per_launch:",
-                                  "kernel_source_sha256:")))
-    if vals.get("kernel_source_sha256") != hashlib.sha256(src).hexdigest():
-        return None
-    return int(vals["traffic_bytes_per_launch"])
-
-
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
@@ -497,8 +473,7 @@ def components_form(n_pts=400):
     """The multi-component form at the paper-scale binning: five signal
     components (one per solar source) with their own 16384 x 4096 responses
     stacked row-wise (1.25 GiB of FP32 read per evaluation), two background
-    templates, masks; single-point evaluations through the step-kernel
-    pipeline, timed as one graph replay."""
+    templates, masks; lists of points through the blocked fold."""
     import torch
     import synth
     import paper_2607_00488_amd as nr
@@ -574,15 +549,14 @@ def components_form(n_pts=400):
                 frac_hbm=round(alg / (step_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                 setup_seconds=round(t_setup, 1),
                 what="Eqs. (Rij), (fNp_reweight), (mu_total): 5 components x "
-                     "16384 x 4096 FP32 responses stacked, one R stream per "
-                     "evaluation through the step kernel")
+                     "16384 x 4096 FP32 responses stacked, lists of points "
+                     "through the blocked fold")
 
 
 def gemm_counter_pass():
-    """The batched likelihood GEMM alone, for hardware counters: 1024 points
-    on a 4096 x 4096 dataset (one of the 64-dataset scan's shapes; 256
-    tiles of 128 x 128, one per compute unit), eight calls after the tuner
-    has picked its tile."""
+    """The batched likelihood alone, for hardware counters: 1024 points on a
+    4096 x 4096 dataset (one of the 64-dataset scan's shapes), eight calls
+    after the tuner has picked the fold's row split."""
     import torch
     import synth
     import paper_2607_00488_amd as nr
@@ -603,16 +577,15 @@ def gemm_counter_pass():
         nr.eval_nll_multi_dev([ctx], [tt], [nl])
     torch.cuda.synchronize()
     ctx.close()
-    log("[bench] GEMM counter pass done: 8 calls of 2 x 1024 x 4096 x 4096 flop")
+    log("[bench] batched counter pass done: 8 calls of 1024 points at 4096 x 4096")
 
 
 def grad_counter_pass():
     """The batched likelihood and gradient alone, for hardware counters:
     1024 points on the 16384 x 4096 shapes of the single-point benchmark
-    (the dense products read every entry, so a response histogrammed from
+    (the dense fold reads every entry, so a response histogrammed from
     fewer events does the same work), eight calls after the tuner has
-    picked its tiles: the weights, the forward product with its Poisson
-    epilogue, the adjoint product and the gradient contraction."""
+    picked the fold's row split."""
     import torch
     import synth
     import paper_2607_00488_amd as nr
@@ -634,8 +607,7 @@ def grad_counter_pass():
         nr.eval_nll_multi_dev([ctx], [tt], [nl], [gr])
     torch.cuda.synchronize()
     ctx.close()
-    log("[bench] gradient counter pass done: 8 calls of 1024 points at 16384 x 4096, "
-        "2 x 2 x 1024 x 16384 x 4096 flop in the two products")
+    log("[bench] gradient counter pass done: 8 calls of 1024 points at 16384 x 4096")
 
 
 def mlp_counter_pass():
@@ -777,11 +749,11 @@ def main():
                          "step kernel alone)")
     ap.add_argument("--surrogate-seconds", type=float, default=20.0)
     ap.add_argument("--gemm-counter-pass", action="store_true",
-                    help="short run for matrix-core counters: the batched "
-                         "likelihood GEMM of 1024 points on a 4096 x 4096 "
+                    help="short run for hardware counters: the batched "
+                         "likelihood of 1024 points on a 4096 x 4096 "
                          "dataset (a shape of the 64-dataset scan), 8 calls")
     ap.add_argument("--grad-counter-pass", action="store_true",
-                    help="short run for matrix-core counters of the batched "
+                    help="short run for hardware counters of the batched "
                          "gradient: 8 calls of 1024 points at 16384 x 4096")
     ap.add_argument("--mlp-counter-pass", action="store_true",
                     help="short run for matrix-core counters of the surrogate "
@@ -864,7 +836,7 @@ def main():
     dev_ms = ev0.elapsed_time(ev1)
     ms_step = dt * 1e3 / K
     evals_s = NE / dt
-    log(f"[bench] plain: {ms_step * 1e3:.2f} us/eval, {evals_s:.0f} evals/s")
+    log(f"[bench] plain: {ms_step * 1e3:.2f} us/step, {evals_s:.0f} evals/s")
 
     # host-visible synchronous latency (paper protocol: 10 calls, drop 1st)
     lat = []
@@ -911,11 +883,11 @@ def main():
                      "and the points' spectra and likelihoods from them")
     single = dict(bound="hbm", achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
                   unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
-                  traffic=measured_traffic(), launches=4,
+                  launches=3,
                   avg_us=round(step_ms * 1e3, 2),
                   algorithmic_bytes=alg_bytes,
-                  note="the whole evaluation of one point (fold, records, points, "
-                       "final), back to back; effective rate: the response's bytes "
+                  note="the whole evaluation of one point (fold, records and "
+                       "points, final), back to back; effective rate: the response's bytes "
                        "over its time, whether HBM or the Infinity Cache served "
                        "them; after a 512 MiB cache flush: "
                        "detail.step_after_cache_flush_us")

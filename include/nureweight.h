@@ -313,7 +313,7 @@ void *nr_stream(nr_ctx *ctx);
  * context). */
 int nr_time_stage(nr_ctx *ctx, int stage, int iters, double *avg_ms);
 
-/* Tuning knobs for sweeps.  rows_per_wg > 0: recoil rows per fold tile (a
+/* Tuning knobs for sweeps of the point-by-point route.  rows_per_wg > 0: recoil rows per fold tile (a
  * multiple of 8, at most 2048; 0 keeps the current value; NR_ESTATE before
  * nr_set_response).  use_graph: 1 replays cached HIP graphs of repeated
  * (pointer, n_pts) calls, 0 launches every kernel directly, -1 keeps the
@@ -428,8 +428,7 @@ int nr_eval_nll_templates_dev(nr_ctx *ctx, const double *d_theta, int n_pts,
 /* Diagnostic: the FP64 matrix-core rate the device sustains, from a stream
  * of independent v_mfma_f64_16x16x4_f64 on register operands (8 chains per
  * wave, `blocks` work-groups of 4 waves, `iters` trips of 16 rounds over
- * the chains; no memory traffic while timed).  *tflops receives the rate; the batched GEMM (Sec. III.B's
- * fold as a matrix product) is compared with it.  Returns NR_EINVAL for
+ * the chains; no memory traffic while timed).  *tflops receives the rate.  Returns NR_EINVAL for
  * bad arguments (blocks in 1..65536), NR_EHIP / NR_ENOMEM on device
  * errors; it does not set the nr_last_error message. */
 int nr_probe_mfma_f64(int device, int blocks, int iters, double *tflops);

@@ -80,8 +80,8 @@ void dfree(T** p) {
 // holds the context's stream and may order work against it: then they run on
 // the internal stream, ordered after everything already on the default stream,
 // and the default stream waits for their end.  That detour's four event calls
-// and two waits cost a batched call of 64 points 
-// 30 us of host time of 45 (121 against 109 us a call at 16384 x 4096).
+// and two waits cost a batched call of 64 points 30 us of host time of 45 (121
+// against 109 us a call at 16384 x 4096).
 struct Bridge {
     hipStream_t work = nullptr;
     hipEvent_t out = nullptr;

@@ -109,7 +109,7 @@ struct ShMultiFinal {
     int n_pts, n_slice, K, B, n_theta;
 };
 
-// Columns of one component folded (k_tmpl slabs, see launch_sh_mfold) and the
+// Columns of one component folded (slabs of rows, see launch_sh_mfold) and the
 // data of a multi-component record.
 struct ShMultiFold {
     const float* R;    // this component's rows

@@ -192,8 +192,7 @@ class Surrogate:
         return b
 
     def _exact(self, ctx: Context, theta: torch.Tensor, key: str):
-        """Exact -2lnL through the batched method, on buffers that stay put
-        so the library's cached graph is replayed."""
+        """Exact -2lnL through the batched method, on buffers kept by use."""
         n = theta.shape[0]
         th = self._buf(key + "_th", (n, 7), torch.float64)
         out = self._buf(key + "_nll", (n,), torch.float64)
