@@ -1548,14 +1548,10 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
     if (phys && !(phys->me > 0 && phys->gf > 0 && phys->alpha_em > 0 &&
                   phys->tau_frac >= 0 && phys->tau_frac <= 1))
         return fail(NR_EINVAL, "invalid physical constants");
-    int rc;
-    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
-    c->ph = make_phys(phys);
-    // copy, validate and sort the node tables (summation order is free)
-    c->src_off.assign(n_src + 1, 0);
-    c->src_n.assign(n_src, 0);
-    c->src_group.assign(n_src, 0);
-    c->hE.clear(); c->hW.clear(); c->hPe.clear();
+    // copy, validate and sort the node tables (summation order is free); the
+    // context keeps its own until everything is accepted
+    std::vector<int> src_off(n_src + 1, 0), src_n(n_src, 0), src_group(n_src, 0);
+    std::vector<double> hE, hW, hPe;
     double wmax = 0;
     for (int k = 0; k < n_src; ++k) {
         const nr_source& s = src[k];
@@ -1575,18 +1571,27 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
         }
         std::stable_sort(idx.begin(), idx.end(),
                          [&](int a, int b) { return s.E[a] < s.E[b]; });
-        c->src_off[k] = (int)c->hE.size();
-        c->src_n[k] = s.n;
-        c->src_group[k] = s.group;
+        src_off[k] = (int)hE.size();
+        src_n[k] = s.n;
+        src_group[k] = s.group;
         for (int j : idx) {
-            c->hE.push_back(s.E[j]);
-            c->hW.push_back(s.weight[j]);
-            c->hPe.push_back(s.p_ee[j]);
+            hE.push_back(s.E[j]);
+            hW.push_back(s.weight[j]);
+            hPe.push_back(s.p_ee[j]);
         }
     }
     if (!(wmax > 0)) return fail(NR_EINVAL, "all source weights are zero");
     // S is linear in the weights and only ratios enter w; scale to O(1).
-    for (double& w : c->hW) w /= wmax;
+    for (double& w : hW) w /= wmax;
+    int rc;
+    if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
+    c->ph = make_phys(phys);
+    c->src_off.swap(src_off);
+    c->src_n.swap(src_n);
+    c->src_group.swap(src_group);
+    c->hE.swap(hE);
+    c->hW.swap(hW);
+    c->hPe.swap(hPe);
     if (c->multi) {  // new sources drop the components built on the old ones
         c->multi = false;
         c->have_rsp = c->have_data = false;

@@ -1,0 +1,107 @@
+"""The library's host code against the CPU stand-in of the HIP runtime
+(tests/c/mock_hip.cpp) with hooks around its calls (tests/c/mock_routes.cpp):
+what the host side allocates, uploads and launches, checked without a GPU.
+Each scenario runs in a child process on a library built host-only."""
+import ctypes
+import glob
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.join(HERE, "..")
+CSRC = os.path.join(ROOT, "paper_2607_00488_amd", "csrc")
+HIPCC = "/opt/rocm/bin/hipcc"
+CLANGXX = "/opt/rocm/llvm/bin/clang++"
+FLAGS = ["--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include")]
+WRAPPED = ["hipMalloc", "hipMemcpy", "hipMemcpyAsync", "hipLaunchKernel", "__hipRegisterFunction"]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc is not installed")
+    d = tmp_path_factory.mktemp("routes")
+    srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip"))) + [
+        os.path.join(HERE, "c", f) for f in ("mock_hip.cpp", "mock_routes.cpp")]
+    objs = [str(d / (os.path.basename(s) + ".o")) for s in srcs]
+    procs = [subprocess.Popen([HIPCC] + FLAGS + ["-c", s, "-o", o], stdout=subprocess.PIPE,
+                              stderr=subprocess.STDOUT) for s, o in zip(srcs, objs)]
+    for p, s in zip(procs, srcs):
+        out = p.communicate()[0].decode()
+        assert p.returncode == 0, f"host-only build of {s} failed:\n{out}"
+    names = set()  # each object names its (absent) device image
+    for o in objs:
+        nm = subprocess.run(["nm", "-u", o], capture_output=True, text=True, check=True)
+        names |= {ln.split()[-1] for ln in nm.stdout.splitlines() if "__hip_fatbin_" in ln}
+    fat = d / "fatbins.c"
+    fat.write_text("".join(f"char {n}[64];\n" for n in sorted(names)))
+    subprocess.run([CLANGXX, "-x", "c", "-fPIC", "-c", str(fat), "-o", str(d / "fat.o")], check=True)
+    so = str(d / "libnureweight_routes.so")
+    subprocess.run([CLANGXX, "-shared", "-Wl,-Bsymbolic", "-o", so, str(d / "fat.o")] + objs +
+                   [f"-Wl,--wrap={w}" for w in WRAPPED], check=True)
+    return so
+
+
+def run(lib, scenario, **env):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), lib, scenario],
+                       capture_output=True, text=True, timeout=300, env=dict(os.environ, **env))
+    assert r.returncode == 0 and f"{scenario} done" in r.stdout, r.stdout[-3000:] + r.stderr[-3000:]
+
+
+def test_a_refused_set_sources_leaves_the_context_as_it_was(lib):
+    run(lib, "refused_sources")
+
+
+# ------------------------------------------------------------ child process
+def analysis(nr, n_t=40, n_reco=33, n_e=24):
+    import synth
+    src = synth.source_nodes(n_e)
+    ctx = nr.Context(0)
+    ctx.set_sources(src, n_t)
+    R = np.full((n_t, n_reco), 1.0 / n_reco, np.float32)
+    ctx.set_response(R, n_sig=1.0e4)
+    ctx.set_data(np.full(n_reco, 20.0), np.full(n_reco, 10.0))
+    return ctx, src, R
+
+
+def kept_factors(mock, n_t):
+    out = np.empty((n_t, 16))
+    assert mock.mock_kept(out.ctypes.data_as(ctypes.c_void_p)) == out.nbytes
+    return out
+
+
+def refused_sources(nr, mock):
+    """The row factors of a response set after a refused nr_set_sources are
+    those of the sources in force."""
+    mock.mock_fill(1, ctypes.c_double(1.0))  # S_SM = 1 in every row
+    n_t = 40
+    mock.mock_keep(n_t * 16 * 8)
+    ctx, src, R = analysis(nr, n_t)
+    before = kept_factors(mock, n_t)
+    assert np.any(before[:, 7] != 0)  # the group scaled by f_8B is there
+    bad = [dict(s) for s in src]
+    bad[0]["p_ee"] = np.full(len(bad[0]["p_ee"]), 2.0)
+    try:
+        ctx.set_sources(bad, n_t)
+        raise AssertionError("accepted")
+    except nr.NrError as e:
+        assert e.code == nr.NR_EINVAL
+    ctx.set_response(R, n_sig=1.0e4)
+    assert np.array_equal(kept_factors(mock, n_t), before)
+
+
+if __name__ == "__main__":
+    sys.path[:0] = [ROOT, HERE]
+    import paper_2607_00488_amd as nr_
+    nr_._LIB_PATH = sys.argv[1]
+    mock_ = ctypes.CDLL(sys.argv[1])
+    mock_.mock_kept.restype = ctypes.c_size_t
+    mock_.mock_mallocs.restype = mock_.mock_launches.restype = ctypes.c_long
+    mock_.mock_keep.argtypes = [ctypes.c_size_t]
+    mock_.mock_fail_at.argtypes = [ctypes.c_long]
+    globals()[sys.argv[2]](nr_, mock_)
+    print(sys.argv[2], "done", flush=True)
