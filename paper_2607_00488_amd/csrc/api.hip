@@ -364,7 +364,8 @@ void row_factors(const nr_ctx* c, const int* src, int n, bool groups, const doub
             double* g = f + (groups && c->src_group[src[q]] ? CB : 0);
             for (int b = 0; b < CB; ++b) g[b] += I[b];
         }
-        for (int b = 0; b < ng * CB; ++b) f[b] *= m[l] / ssm[l];
+        // in this order: m / S_SM overflows where S_SM is tiny, m I_b / S_SM does not
+        for (int b = 0; b < ng * CB; ++b) f[b] = m[l] * f[b] / ssm[l];
     }
 }
 

@@ -56,6 +56,10 @@ def test_a_refused_set_sources_leaves_the_context_as_it_was(lib):
     run(lib, "refused_sources")
 
 
+def test_row_factors_of_tiny_spectra_are_finite(lib):
+    run(lib, "tiny_spectra")
+
+
 # ------------------------------------------------------------ child process
 def analysis(nr, n_t=40, n_reco=33, n_e=24):
     import synth
@@ -92,6 +96,29 @@ def refused_sources(nr, mock):
         assert e.code == nr.NR_EINVAL
     ctx.set_response(R, n_sig=1.0e4)
     assert np.array_equal(kept_factors(mock, n_t), before)
+
+
+def tiny_spectra(nr, mock):
+    """Rows whose S_SM is so small that m / S_SM overflows though m I_b / S_SM
+    is an ordinary number: a line that reaches no row sets the scale of the
+    weights, the continuum's are 1e-305 of it."""
+    n_t = 40
+    mock.mock_fill(1, ctypes.c_double(1e-305))
+    mock.mock_keep(n_t * 16 * 8)
+    E = np.linspace(1.0, 15.0, 24)
+    src = [dict(kind=0, E=np.array([0.1]), weight=np.array([1.0]), p_ee=np.array([0.5]), group=0),
+           dict(kind=1, E=E, weight=np.full(24, 1e-305), p_ee=np.full(24, 0.4), group=0)]
+    ctx = nr.Context(0)
+    ctx.set_sources(src, n_t)
+    ctx.set_response(np.full((n_t, 8), 0.125, np.float32), m=np.full(n_t, 1.0e4))
+    F = kept_factors(mock, n_t)
+    assert np.all(np.isfinite(F))
+    T = (np.arange(n_t) + 0.5) * 16.0 / n_t
+    on = T[:, None] <= 2 * E * E / (0.51099895 + 2 * E)
+    ref = 1.0e4 * 0.4 * on.sum(1)  # I_0 = sum nu P_ee
+    # 24 sums, one product, one quotient
+    assert np.all(np.abs(F[:, 0] - ref) <= 32 * 2.0 ** -53 * ref)
+    assert np.all(F[:, 7:16] == 0)
 
 
 if __name__ == "__main__":
