@@ -36,9 +36,9 @@ class NllFunction(torch.autograd.Function):
     def forward(fctx, theta: torch.Tensor, context: Context, form="batched"):
         form = _form(form)
         # the library reads theta where it is; a copy only of other types,
-        # strides or broadcast rows
+        # strides, broadcast rows or values that are negated when read
         P, D = theta.shape[0], context.n_theta
-        th = theta.detach().to(torch.float64).expand(P, D).contiguous()
+        th = theta.detach().to(torch.float64).expand(P, D).contiguous().resolve_neg()
         nll = torch.empty(P, dtype=torch.float64, device=th.device)
         grad = torch.empty(P, D, dtype=torch.float64, device=th.device)
         stream = torch.cuda.current_stream(th.device)

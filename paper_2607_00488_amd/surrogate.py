@@ -126,6 +126,7 @@ class Surrogate:
         whole = (self.hidden == 256 and not log_every and steps_per_epoch > 0 and
                  theta.dtype == torch.float64 and theta.is_contiguous() and
                  targets.dtype == torch.float32 and targets.is_contiguous() and
+                 not theta.is_neg() and not targets.is_neg() and
                  theta.shape[1:] == (7,) and targets.shape == (P, self.n_out) and
                  theta.device == targets.device == self.dev)
         for ep in range(epochs):
