@@ -214,7 +214,8 @@ int nr_eval_mu_batched(nr_ctx *ctx, const double *theta, int n_pts,
 
 /* Several analyses (datasets with their own binning and response, all on
  * one device) in four launches per 16 of them: theta[d] ([n_pts[d]][7],
- * host), nll[d] ([n_pts[d]], host).  The stream of ctx[0] is used. */
+ * host), nll[d] ([n_pts[d]], host).  A context may occur more than once.  The
+ * stream of ctx[0] is used. */
 int nr_eval_nll_multi(nr_ctx *const *ctx, int n_ctx,
                       const double *const *theta, const int *n_pts,
                       double *const *nll);

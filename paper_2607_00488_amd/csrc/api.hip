@@ -247,7 +247,7 @@ struct nr_ctx {
     bool use_graph = true;
     std::map<GraphKey, hipGraphExec_t> graphs;
     // staging of the batched entry points
-    int b_cap = 0;
+    size_t b_cap = 0;
     double *d_bth = nullptr, *d_bnll = nullptr, *d_bgrad = nullptr, *d_bmu = nullptr;
     size_t b_cap_mu = 0;
     // template form: folded basis templates and the data, per reco bin
@@ -1189,13 +1189,13 @@ int check_single(nr_ctx* c) {
 namespace {
 
 // ------------------------------------------------------------ batched path
-int ensure_batch(nr_ctx* c, int n_pts, size_t mu_elems) {
+int ensure_batch(nr_ctx* c, size_t n_pts, size_t mu_elems) {
     int rc;
     if (n_pts > c->b_cap) {
-        const int cap = std::max(n_pts, 64);
-        if ((rc = dalloc(&c->d_bth, (size_t)cap * NR_NTHETA))) return rc;
-        if ((rc = dalloc(&c->d_bnll, (size_t)cap))) return rc;
-        if ((rc = dalloc(&c->d_bgrad, (size_t)cap * NR_NTHETA))) return rc;
+        const size_t cap = std::max(n_pts, (size_t)64);
+        if ((rc = dalloc(&c->d_bth, cap * NR_NTHETA))) return rc;
+        if ((rc = dalloc(&c->d_bnll, cap))) return rc;
+        if ((rc = dalloc(&c->d_bgrad, cap * NR_NTHETA))) return rc;
         c->b_cap = cap;
     }
     if (mu_elems > c->b_cap_mu) {
@@ -1206,9 +1206,7 @@ int ensure_batch(nr_ctx* c, int n_pts, size_t mu_elems) {
 }
 
 // The batched entry points' own workspace of one analysis.
-int ensure_shb(nr_ctx* c, int n_pts, bool grad, int cfg) {
-    ShWork w;
-    const size_t need = carve_sh(c, nullptr, n_pts, grad, cfg, &w);
+int ensure_shb(nr_ctx* c, size_t need) {
     if (need <= c->shb_bytes) return 0;
     int rc;
     c->shb_bytes = 0;
@@ -1227,12 +1225,28 @@ struct MultiCall {
     double* const* mu;           // device or null (array may be null)
 };
 
+// Where the workspace of entry d starts in its context's, in bytes: after those
+// of the earlier entries of the same context.
+size_t shb_offset(const MultiCall& mc, int d, bool grad, int cfg) {
+    ShWork w;
+    size_t off = 0;
+    for (int i = 0; i < d; ++i)
+        if (mc.ctx[i] == mc.ctx[d]) off += carve_sh(mc.ctx[i], nullptr, mc.n_pts[i], grad, cfg, &w);
+    return off;
+}
+
 // All analyses of a call in four launches per kShGroup of them.
 int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
     const bool grad = mc.grad != nullptr;
     int rc;
-    for (int d = 0; d < mc.n; ++d)
-        if ((rc = ensure_shb(mc.ctx[d], mc.n_pts[d], grad, cfg))) return rc;
+    std::vector<size_t> off(mc.n);
+    for (int d = 0; d < mc.n; ++d) {
+        ShWork w;
+        off[d] = shb_offset(mc, d, grad, cfg);
+        if ((rc = ensure_shb(mc.ctx[d], off[d] + carve_sh(mc.ctx[d], nullptr, mc.n_pts[d], grad,
+                                                          cfg, &w))))
+            return rc;
+    }
     for (int d0 = 0; d0 < mc.n; d0 += nr::kShGroup) {
         const int n = std::min(nr::kShGroup, mc.n - d0);
         nr::ShFold f[nr::kShGroup];
@@ -1245,7 +1259,7 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
             const int d = d0 + i;
             nr_ctx* c = mc.ctx[d];
             ShWork w;
-            carve_sh(c, c->d_shb, mc.n_pts[d], grad, cfg, &w);
+            carve_sh(c, c->d_shb + off[d] / sizeof(double), mc.n_pts[d], grad, cfg, &w);
             f[i] = sh_fold_args(c, cfg, w.part);
             r[i] = sh_rec_args(c, f[i], w.rec);
             e[i] = sh_eval_args(c, w.rec, mc.theta[d], mc.n_pts[d], w.dpart, w.hpart,
@@ -2306,24 +2320,28 @@ int nr_eval_nll_multi(nr_ctx* const* ctx, int n_ctx, const double* const* theta,
     if ((rc = set_device(ctx[0]))) return rc;
     std::vector<const double*> ths(n_ctx);
     std::vector<double*> nls(n_ctx);
+    std::vector<size_t> first(n_ctx, 0);  // points of earlier entries of the same context
     hipStream_t s = ctx[0]->stream;
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
-        if ((rc = ensure_batch(c, n_pts[d], 0))) return rc;
+        for (int i = 0; i < d; ++i)
+            if (ctx[i] == c) first[d] += n_pts[i];
+        if ((rc = ensure_batch(c, first[d] + n_pts[d], 0))) return rc;
         if (c->null_pending) ctx[0]->null_pending = true;  // all run on ctx[0]'s stream
     }
     if ((rc = own_stream(ctx[0]))) return rc;
     for (int d = 0; d < n_ctx; ++d) {
         nr_ctx* c = ctx[d];
-        HIPCHK(hipMemcpyAsync(c->d_bth, theta[d], sizeof(double) * n_pts[d] * NR_NTHETA,
+        double* th = c->d_bth + first[d] * NR_NTHETA;
+        HIPCHK(hipMemcpyAsync(th, theta[d], sizeof(double) * n_pts[d] * NR_NTHETA,
                               hipMemcpyHostToDevice, s));
-        ths[d] = c->d_bth;
-        nls[d] = c->d_bnll;
+        ths[d] = th;
+        nls[d] = c->d_bnll + first[d];
     }
     MultiCall mc{ctx, n_ctx, ths.data(), n_pts, nls.data(), nullptr, nullptr};
     if ((rc = run_multi(mc, s))) return rc;
     for (int d = 0; d < n_ctx; ++d)
-        HIPCHK(hipMemcpyAsync(nll[d], ctx[d]->d_bnll, sizeof(double) * n_pts[d],
+        HIPCHK(hipMemcpyAsync(nll[d], nls[d], sizeof(double) * n_pts[d],
                               hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
     return 0;

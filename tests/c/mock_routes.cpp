@@ -3,7 +3,7 @@
 // counted or refused, uploads kept, downloads filled with a value, and every
 // kernel launch seen by its name.  Test infrastructure, never linked into the
 // library.
-#include <hip/hip_runtime_api.h>
+#include "../../paper_2607_00488_amd/csrc/shared.h"
 #include <cstring>
 #include <map>
 #include <string>
@@ -16,6 +16,20 @@ std::vector<char> g_kept;
 bool g_fill_on = false;
 double g_fill = 0.0;
 long g_launches = 0;
+// what the entries of the last grouped launch of points read and write
+struct Range {
+    unsigned long long entry, kind, at, bytes;
+};
+std::vector<Range> g_ranges;
+void see_points(const nr::ShEval& e, int d) {
+    const unsigned long long p = e.n_pts;
+    g_ranges.push_back({(unsigned long long)d, 0, (unsigned long long)e.theta, p * 56});
+    g_ranges.push_back({(unsigned long long)d, 1, (unsigned long long)e.rec, 8});
+    g_ranges.push_back({(unsigned long long)d, 2, (unsigned long long)e.dpart, p * e.n_slice * 8});
+    if (e.hpart)
+        g_ranges.push_back({(unsigned long long)d, 3, (unsigned long long)e.hpart,
+                            p * e.n_slice * nr::kShAcc * 8});
+}
 std::map<const void*, std::string>& names() {
     static std::map<const void*, std::string> m;
     return m;
@@ -33,6 +47,13 @@ void mock_keep(size_t n) { g_keep = n; g_kept.clear(); }
 size_t mock_kept(void* out) {
     if (!g_kept.empty()) std::memcpy(out, g_kept.data(), g_kept.size());
     return g_kept.size();
+}
+// (entry, kind, address, bytes) of theta (0), records (1), deviance (2) and
+// gradient sums (3) of every entry of the last grouped launch
+long mock_ranges(unsigned long long* out, long cap) {
+    for (size_t i = 0; i < g_ranges.size() && (long)(4 * i + 4) <= cap; ++i)
+        std::memcpy(out + 4 * i, &g_ranges[i], 32);
+    return (long)g_ranges.size();
 }
 // asynchronous downloads deliver doubles of this value
 void mock_fill(int on, double v) { g_fill_on = on != 0; g_fill = v; }
@@ -70,6 +91,18 @@ hipError_t __real_hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipSt
 hipError_t __wrap_hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh,
                                   hipStream_t s) {
     ++g_launches;
+    const std::string& n = names()[f];
+    if (n.find("ELi16EE") != std::string::npos || n.find("ILi16EE") != std::string::npos) {
+        if (n.find("k_sh_eval") != std::string::npos) {
+            g_ranges.clear();
+            const auto& q = *(const nr::ShGroup<nr::ShEval, nr::kShGroup>*)args[0];
+            for (int d = 0; d < q.n; ++d) see_points(q.p[d], d);
+        } else if (n.find("k_sh_tail") != std::string::npos) {
+            g_ranges.clear();
+            const auto& q = *(const nr::ShGroup<nr::ShTail, nr::kShGroup>*)args[0];
+            for (int d = 0; d < q.n; ++d) see_points(q.p[d].e, d);
+        }
+    }
     return __real_hipLaunchKernel(f, g, b, args, sh, s);
 }
 }

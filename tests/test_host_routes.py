@@ -60,6 +60,11 @@ def test_row_factors_of_tiny_spectra_are_finite(lib):
     run(lib, "tiny_spectra")
 
 
+@pytest.mark.parametrize("points", ["5,40,17", "5,600,17"])  # records and points in one launch, in two
+def test_entries_of_one_context_have_their_own_buffers(lib, points):
+    run(lib, "repeated_context", POINTS=points, NR_GEMM_CONFIG="0")
+
+
 # ------------------------------------------------------------ child process
 def analysis(nr, n_t=40, n_reco=33, n_e=24):
     import synth
@@ -121,13 +126,43 @@ def tiny_spectra(nr, mock):
     assert np.all(F[:, 7:16] == 0)
 
 
+def repeated_context(nr, mock):
+    """A grouped call that lists a context several times: no entry's points,
+    sums or gradient sums lie in another's."""
+    import synth
+    a, b = analysis(nr)[0], analysis(nr, 50, 70)[0]
+    ctxs = [a, b, a]
+    ths = [synth.theta_prior(int(n), 5, f_range=(0.8, 1.2)) for n in os.environ["POINTS"].split(",")]
+
+    def check(kinds):
+        n = mock.mock_ranges(None, 0)
+        r = np.zeros((n, 4), np.uint64)
+        mock.mock_ranges(r.ctypes.data_as(ctypes.c_void_p), r.size)
+        for k in kinds:
+            q = r[r[:, 1] == k]
+            assert len(q) == 3
+            q = q[np.argsort(q[:, 2])]
+            assert np.all(q[:-1, 2] + q[:-1, 3] <= q[1:, 2]), (k, q)
+
+    nr.eval_nll_multi(ctxs, ths)
+    check((0, 2))
+    dev = [np.ascontiguousarray(t) for t in ths]
+    nll = [np.empty(len(t)) for t in ths]
+    grad = [np.empty((len(t), 7)) for t in ths]
+    p = lambda v: [x.ctypes.data for x in v]  # noqa: E731
+    nr.nr_eval_nll_multi_dev([c.h for c in ctxs], p(dev), [len(t) for t in ths], p(nll), p(grad))
+    check((0, 2, 3))
+
+
 if __name__ == "__main__":
     sys.path[:0] = [ROOT, HERE]
     import paper_2607_00488_amd as nr_
     nr_._LIB_PATH = sys.argv[1]
     mock_ = ctypes.CDLL(sys.argv[1])
     mock_.mock_kept.restype = ctypes.c_size_t
-    mock_.mock_mallocs.restype = mock_.mock_launches.restype = ctypes.c_long
+    for f_ in (mock_.mock_mallocs, mock_.mock_launches, mock_.mock_ranges):
+        f_.restype = ctypes.c_long
+    mock_.mock_ranges.argtypes = [ctypes.c_void_p, ctypes.c_long]
     mock_.mock_keep.argtypes = [ctypes.c_size_t]
     mock_.mock_fail_at.argtypes = [ctypes.c_long]
     globals()[sys.argv[2]](nr_, mock_)
