@@ -369,8 +369,9 @@ void row_factors(const nr_ctx* c, const int* src, int n, bool groups, const doub
     }
 }
 
+// The row factors of the response in place (or about to be).
 int upload_mrow(nr_ctx* c) {
-    if (!c->have_rsp || c->multi) return 0;
+    if (c->multi) return 0;
     HIPCHK(hipMemcpy(c->d_mrow, c->mrow.data(), sizeof(double) * c->n_t,
                      hipMemcpyHostToDevice));
     if (!c->have_src) return 0;  // nr_set_sources comes back here
@@ -527,6 +528,7 @@ int ensure_stage(nr_ctx* c, size_t pts, size_t mu_elems, size_t w_elems) {
     int rc;
     if (pts > c->cap_pts) {
         size_t n = std::max(pts, (size_t)64);
+        c->cap_pts = 0;  // none of them counts until all are there
         if ((rc = dalloc(&c->d_th, n * nr::kMaxTheta))) return rc;  // any form's theta
         if ((rc = dalloc(&c->d_out, n))) return rc;
         if ((rc = dalloc(&c->d_grad, n * nr::kMaxTheta))) return rc;  // any form's gradient
@@ -534,11 +536,13 @@ int ensure_stage(nr_ctx* c, size_t pts, size_t mu_elems, size_t w_elems) {
         clear_graphs(c);
     }
     if (mu_elems > c->cap_mu) {
+        c->cap_mu = 0;
         if ((rc = dalloc(&c->d_mu, mu_elems))) return rc;
         c->cap_mu = mu_elems;
         clear_graphs(c);
     }
     if (w_elems > c->cap_w) {
+        c->cap_w = 0;
         if ((rc = dalloc(&c->d_w, w_elems))) return rc;
         c->cap_w = w_elems;
     }
@@ -1193,12 +1197,14 @@ int ensure_batch(nr_ctx* c, size_t n_pts, size_t mu_elems) {
     int rc;
     if (n_pts > c->b_cap) {
         const size_t cap = std::max(n_pts, (size_t)64);
+        c->b_cap = 0;  // none of them counts until all are there
         if ((rc = dalloc(&c->d_bth, cap * NR_NTHETA))) return rc;
         if ((rc = dalloc(&c->d_bnll, cap))) return rc;
         if ((rc = dalloc(&c->d_bgrad, cap * NR_NTHETA))) return rc;
         c->b_cap = cap;
     }
     if (mu_elems > c->b_cap_mu) {
+        c->b_cap_mu = 0;
         if ((rc = dalloc(&c->d_bmu, mu_elems))) return rc;
         c->b_cap_mu = mu_elems;
     }
@@ -1600,6 +1606,7 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
     for (double& w : hW) w /= wmax;
     int rc;
     if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
+    c->have_src = false;  // until the last table is in place
     c->ph = make_phys(phys);
     c->src_off.swap(src_off);
     c->src_n.swap(src_n);
@@ -1710,7 +1717,10 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
     c->tmpl_ok = false;
     clear_graphs(c);
     recompute_mrow(c);
-    if ((rc = upload_mrow(c))) return rc;
+    if (c->have_rsp && (rc = upload_mrow(c))) {
+        c->have_src = false;
+        return rc;
+    }
     return 0;
 }
 
@@ -1733,11 +1743,9 @@ int nr_set_response(nr_ctx* c, const float* R, int n_t, int n_reco,
         if (!std::isfinite(R[i])) return fail(NR_EINVAL, "non-finite R at %zu", i);
     int rc;
     if ((rc = set_device(c))) return rc;
+    c->have_rsp = false;  // until every buffer of the new one is in place
     if (c->multi) {  // back to the single-component form
-        c->multi = false;
         c->have_data = false;
-        c->n_theta = NR_NTHETA;
-        c->n_comp = c->n_bkg = 1;
         if (c->have_src) {
             if ((rc = dalloc(&c->d_v[0], n_t)) || (rc = dalloc(&c->d_v[1], n_t))) return rc;
             c->comp_off = {0, c->n_src};
@@ -1748,6 +1756,9 @@ int nr_set_response(nr_ctx* c, const float* R, int n_t, int n_reco,
             HIPCHK(hipMemcpy(c->d_compsrc, c->comp_src.data(), sizeof(int) * c->n_src,
                              hipMemcpyHostToDevice));
         }
+        c->multi = false;
+        c->n_theta = NR_NTHETA;
+        c->n_comp = c->n_bkg = 1;
     }
     c->n_t = n_t;
     c->n_rows = n_t;
@@ -1764,11 +1775,11 @@ int nr_set_response(nr_ctx* c, const float* R, int n_t, int n_reco,
     c->m_user = m != nullptr;
     c->n_sig = n_sig;
     if (m) c->mrow.assign(m, m + n_t);
-    c->have_rsp = true;
     c->tmpl_ok = false;
     recompute_mrow(c);
     if ((rc = upload_mrow(c))) return rc;
     if ((rc = choose_tiling(c, 0))) return rc;
+    c->have_rsp = true;
     return 0;
 }
 
@@ -1789,6 +1800,7 @@ int nr_set_data(nr_ctx* c, const double* n, const double* b, int n_reco,
         return fail(NR_EINVAL, "non-finite pulls");
     int rc;
     if ((rc = set_device(c))) return rc;
+    c->have_data = false;  // until both arrays are in place
     if ((rc = dalloc(&c->d_n, n_reco)) || (rc = dalloc(&c->d_b, n_reco))) return rc;
     HIPCHK(hipMemcpy(c->d_n, n, sizeof(double) * n_reco, hipMemcpyHostToDevice));
     if (b) HIPCHK(hipMemcpy(c->d_b, b, sizeof(double) * n_reco, hipMemcpyHostToDevice));
@@ -1947,6 +1959,7 @@ int nr_set_mc_events(nr_ctx* c, const double* n_events, int n_t) {
             return fail(NR_EINVAL, "n_events[%d] must be finite and >= 0", l);
     int rc;
     if ((rc = set_device(c))) return rc;
+    c->have_nev = false;
     if ((rc = dalloc(&c->d_nev, n_t))) return rc;
     HIPCHK(hipMemcpy(c->d_nev, n_events, sizeof(double) * n_t, hipMemcpyHostToDevice));
     c->have_nev = true;
@@ -2082,6 +2095,18 @@ int nr_set_components(nr_ctx* c, const nr_components* k, int n_reco) {
     int rc;
     if ((rc = set_device(c)) || (rc = own_stream(c))) return rc;
     clear_graphs(c);
+    // no response, and the data and pulls follow the new parameter layout, until
+    // every buffer is in place
+    c->have_rsp = c->have_data = false;
+    c->multi = true;
+    c->tmpl_ok = false;
+    c->n_comp = K;
+    c->n_bkg = B;
+    c->n_theta = 5 + K + B;
+    c->n_rows = (int)n_rows;
+    c->n_reco = n_reco;
+    c->ldr = ldr;
+    c->m_user = true;
     if ((rc = dalloc(&c->d_R, n_rows * ldr)) || (rc = dalloc(&c->d_mrow, n_rows)) ||
         (rc = dalloc(&c->d_bkg, bkg.size())) || (rc = dalloc(&c->d_ssmc, n_rows)) ||
         (rc = dalloc(&c->d_v[0], n_rows)) || (rc = dalloc(&c->d_v[1], n_rows)) ||
@@ -2101,17 +2126,6 @@ int nr_set_components(nr_ctx* c, const nr_components* k, int n_reco) {
     HIPCHK(hipMemcpy(c->d_compsrc, src.data(), sizeof(int) * n_src, hipMemcpyHostToDevice));
     c->comp_off = off;
     c->comp_src = src;
-    c->multi = true;
-    c->tmpl_ok = false;
-    c->n_comp = K;
-    c->n_bkg = B;
-    c->n_theta = 5 + K + B;
-    c->n_rows = (int)n_rows;
-    c->n_reco = n_reco;
-    c->ldr = ldr;
-    c->m_user = true;
-    c->have_rsp = true;
-    c->have_data = false;  // data and pulls follow the new parameter layout
     // per-component SM spectra with the code the evaluations use (w = 1
     // exactly at the SM point)
     {
@@ -2130,6 +2144,7 @@ int nr_set_components(nr_ctx* c, const nr_components* k, int n_reco) {
     if ((rc = dalloc(&c->d_rf, F.size()))) return rc;
     HIPCHK(hipMemcpy(c->d_rf, F.data(), sizeof(double) * F.size(), hipMemcpyHostToDevice));
     if ((rc = choose_tiling(c, 0))) return rc;
+    c->have_rsp = true;
     return 0;
 }
 
@@ -2166,7 +2181,8 @@ int nr_set_fold_tiling(nr_ctx* c, int rows_per_wg, int use_graph) {
         int rc;
         if ((rc = set_device(c))) return rc;
         HIPCHK(hipStreamSynchronize(c->stream));
-        return choose_tiling(c, rows_per_wg);
+        if ((rc = choose_tiling(c, rows_per_wg))) c->have_rsp = false;
+        return rc;
     }
     return 0;
 }
@@ -2391,6 +2407,7 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
     int rc;
     if (B > q->cap) {
         const int cap = (B + 127) / 128 * 128;
+        q->cap = q->train_cap = 0;  // none of them counts until all are there
         if ((rc = dalloc(&q->x, (size_t)cap * 32))) return rc;
         for (int l = 0; l < 3; ++l) {
             if ((rc = dalloc(&q->h[l], (size_t)cap * (q->H + 8)))) return rc;
@@ -2402,10 +2419,10 @@ int mlp_alloc_batch(nr_mlp* q, int B, bool train) {
         if ((rc = dalloc(&q->part, (size_t)cap * nnt))) return rc;
         if ((rc = dalloc(&q->outside, (size_t)cap))) return rc;
         q->cap = cap;
-        q->train_cap = 0;
     }
     if (train && B > q->train_cap) {
         const int cap = q->cap;
+        q->train_cap = 0;
         const int tiles = (cap / 128) * ((q->n_out + 127) / 128);
         if ((rc = dalloc(&q->tile_loss, (size_t)tiles))) return rc;
         const int H = q->H, N = q->n_out;
@@ -2482,6 +2499,7 @@ int mlp_split_gemm(nr_mlp* q, nr::MlpGemm g, int mode, float* C32, long ldc, hip
     const size_t need = (size_t)n_split * slab;
     if (need > q->gpart_cap) {
         int rc;
+        q->gpart_cap = 0;
         if ((rc = dalloc(&q->gpart, need))) return rc;
         q->gpart_cap = need;
     }
@@ -3055,10 +3073,12 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
     const size_t ns = (size_t)slices;
     const size_t na = (size_t)(c->multi ? nr::sh_acc(c->n_comp, c->n_bkg) : nr::kShAcc);
     if (ns * n_pts > c->t_cap_d) {
+        c->t_cap_d = 0;
         if ((rc = dalloc(&c->d_tdp, ns * n_pts))) return rc;
         c->t_cap_d = ns * n_pts;
     }
     if (grad && ns * na * n_pts > c->t_cap_h) {
+        c->t_cap_h = 0;
         if ((rc = dalloc(&c->d_thp, ns * na * n_pts))) return rc;
         c->t_cap_h = ns * na * n_pts;
     }

@@ -65,6 +65,10 @@ def test_entries_of_one_context_have_their_own_buffers(lib, points):
     run(lib, "repeated_context", POINTS=points, NR_GEMM_CONFIG="0")
 
 
+def test_a_failed_allocation_leaves_nothing_to_launch_on(lib):
+    run(lib, "failed_allocations")
+
+
 # ------------------------------------------------------------ child process
 def analysis(nr, n_t=40, n_reco=33, n_e=24):
     import synth
@@ -152,6 +156,88 @@ def repeated_context(nr, mock):
     p = lambda v: [x.ctypes.data for x in v]  # noqa: E731
     nr.nr_eval_nll_multi_dev([c.h for c in ctxs], p(dev), [len(t) for t in ths], p(nll), p(grad))
     check((0, 2, 3))
+
+
+def refused(nr, f, *codes):
+    try:
+        f()
+    except nr.NrError as e:
+        assert e.code in codes, e
+        return True
+    return False
+
+
+def failed_allocations(nr, mock):
+    """Every device allocation of every set-up call refused in turn: what the
+    call was to replace is not evaluated on, and the call made again serves.
+    After a buffer that failed to grow, a smaller call allocates it again."""
+    import synth
+    th = synth.theta_prior(3, 5, f_range=(0.8, 1.2))
+    k = synth.component_inputs(40, 33, 20_000, 6)
+    args = [k.pop(n) for n in ("comp_of_source", "hist", "scale", "rate_sm")]
+    n20, b10 = np.full(33, 20.0), np.full(33, 10.0)
+
+    def components(c, src, R):
+        c.set_components(*args, **k)
+        c.set_data(n20, None)
+
+    def tiling(c, src, R):
+        c.set_fold_tiling(16)
+        c.set_response(R, n_sig=1.0e4)  # serves again after a failure
+
+    calls = dict(
+        sources=lambda c, src, R: c.set_sources(src, 40),
+        response=lambda c, src, R: c.set_response(R, n_sig=1.0e4),
+        data=lambda c, src, R: c.set_data(n20, b10),
+        components=components, tiling=tiling)
+    for name, call in calls.items():
+        failures = 0
+        while True:
+            ctx, src, R = analysis(nr)
+            ctx.eval_nll(th)
+            if name == "response":
+                components(ctx, src, R)  # back from the multi-component form
+            mock.mock_fail_at(mock.mock_mallocs() + failures + 1)
+            failed = refused(nr, lambda: call(ctx, src, R), nr.NR_ENOMEM)
+            mock.mock_fail_at(0)
+            if not failed:
+                break
+            failures += 1
+            w = mock.mock_launches()
+            t = np.ones((2, ctx.n_theta))
+            assert refused(nr, lambda: ctx.eval_nll(t), nr.NR_ESTATE), (name, failures)
+            assert mock.mock_launches() == w
+            if name == "tiling":
+                ctx.set_response(R, n_sig=1.0e4)
+            call(ctx, src, R)
+            if name == "response":
+                ctx.set_data(n20, b10)
+            ctx.eval_nll(np.ones((2, ctx.n_theta)))
+            ctx.close()
+        assert failures >= (2 if name == "data" else 5), (name, failures)
+
+    grow = dict(
+        batched=lambda c, n: c.eval_nll_grad_batched(synth.theta_prior(n, 7)),
+        mu=lambda c, n: c.eval_mu(synth.theta_prior(n, 7)),
+        mu_batched=lambda c, n: c.eval_mu_batched(synth.theta_prior(n, 7)),
+        weights=lambda c, n: c.eval_weights(synth.theta_prior(n, 7)),
+        templates=lambda c, n: c.eval_nll_templates(synth.theta_prior(n, 7), True))
+    for name, f in grow.items():
+        failures = 0
+        while True:
+            ctx = analysis(nr)[0]
+            f(ctx, 3)
+            mock.mock_fail_at(mock.mock_mallocs() + failures + 1)
+            failed = refused(nr, lambda: f(ctx, 500), nr.NR_ENOMEM)
+            mock.mock_fail_at(0)
+            if not failed:
+                break
+            failures += 1
+            m = mock.mock_mallocs()
+            f(ctx, 3)
+            assert mock.mock_mallocs() > m, (name, failures)
+            ctx.close()
+        assert failures >= 1, name
 
 
 if __name__ == "__main__":
