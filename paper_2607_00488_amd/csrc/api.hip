@@ -827,7 +827,8 @@ struct ShWork {
     double *part, *rec, *dpart, *hpart;
 };
 
-// Layout of the workspace for pts points at a time; the bytes it takes.
+// Layout of the workspace for pts points at a time; the bytes it takes, which grow
+// with the points.
 size_t carve_sh(const nr_ctx* c, double* base, int pts, bool grad, int cfg, ShWork* w) {
     size_t off = 0;
     auto take = [&](size_t n) {
@@ -835,13 +836,13 @@ size_t carve_sh(const nr_ctx* c, double* base, int pts, bool grad, int cfg, ShWo
         off += (n + 31) / 32 * 32;
         return p;
     };
-    int ns, rp, tiles, slices;
+    int ns, rp;
     sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &ns, &rp);
-    nr::sh_slices(pts, c->n_reco, false, &tiles, &slices);
+    const size_t sums = nr::sh_sums(pts, c->n_reco, false);
     w->part = take((size_t)ns * nr::kShCols * c->ldr);
     w->rec = take((size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins * nr::kShRec);
-    w->dpart = take((size_t)slices * pts);
-    w->hpart = grad ? take((size_t)slices * nr::kShAcc * pts) : nullptr;
+    w->dpart = take(sums);
+    w->hpart = grad ? take(sums * nr::kShAcc) : nullptr;
     return off * sizeof(double);
 }
 
@@ -1027,19 +1028,23 @@ size_t carve_blk(const nr_ctx* c, double* base, int pts, BlkWork* w) {
     return off * sizeof(double);
 }
 
-// Points per block in `limit` bytes of workspace: at most 4096, whole groups
-// of 64 (the fold's largest) where at least one fits, else whole blocks of
-// 16; 0 if not even one does.
+// Blocks of 16 points, of a list of n_pts, that `limit` bytes of workspace hold, in
+// points: at most 4096, 0 if not even one block fits.
 constexpr size_t kBlkBytes = (size_t)128 << 20;
 
-int blk_points(const nr_ctx* c, int n_pts, size_t limit) {
+int blk_fit(const nr_ctx* c, int n_pts, size_t limit) {
     BlkWork w;
-    const size_t b16 = carve_blk(c, nullptr, 16, &w);
-    if (b16 > limit) return 0;
-    int pts = 16;
+    int pts = 0;
     const int want = std::min((n_pts + 15) / 16 * 16, 4096);
     while (pts + 16 <= want && carve_blk(c, nullptr, pts + 16, &w) <= limit) pts += 16;
-    return pts < want && pts > 64 ? pts / 64 * 64 : pts;
+    return pts;
+}
+
+// Points at a time: the whole list if it fits, else whole groups of 64 (the fold's
+// largest) where at least one does.
+int blk_points(const nr_ctx* c, int n_pts, size_t limit) {
+    const int pts = blk_fit(c, n_pts, limit);
+    return pts < std::min((n_pts + 15) / 16 * 16, 4096) && pts > 64 ? pts / 64 * 64 : pts;
 }
 
 // Lists of three or more points share the stream over R (one or two run the
@@ -1055,10 +1060,10 @@ bool use_blocks(const nr_ctx* c, int n_pts) {
     return blk_points(c, 16, NR_NOALLOC_WORKSPACE_BYTES) > 0;
 }
 
-// The context's own workspace for a list of n_pts points.
+// The context's own workspace for a list of up to n_pts points.
 int ensure_blk(nr_ctx* c, int n_pts) {
     BlkWork w;
-    const int pts = std::max(16, blk_points(c, n_pts, kBlkBytes));
+    const int pts = std::max(16, blk_fit(c, n_pts, kBlkBytes));
     const size_t need = carve_blk(c, nullptr, pts, &w);
     if (need <= c->blk_bytes) return 0;
     int rc;
@@ -1248,10 +1253,12 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
     std::vector<size_t> off(mc.n);
     for (int d = 0; d < mc.n; ++d) {
         ShWork w;
+        size_t need = 0;  // of any configuration: another list's may be another one
+        for (int q = 0; q < kShConfigs; ++q)
+            need = std::max(need, shb_offset(mc, d, grad, q) +
+                                      carve_sh(mc.ctx[d], nullptr, mc.n_pts[d], grad, q, &w));
+        if ((rc = ensure_shb(mc.ctx[d], need))) return rc;
         off[d] = shb_offset(mc, d, grad, cfg);
-        if ((rc = ensure_shb(mc.ctx[d], off[d] + carve_sh(mc.ctx[d], nullptr, mc.n_pts[d], grad,
-                                                          cfg, &w))))
-            return rc;
     }
     for (int d0 = 0; d0 < mc.n; d0 += nr::kShGroup) {
         const int n = std::min(nr::kShGroup, mc.n - d0);
@@ -3068,19 +3075,17 @@ static int ensure_tmpl(nr_ctx* c, int n_pts, bool grad) {
     int rc;
     if ((rc = check_tmpl_form(c))) return rc;
     if ((!c->tmpl_ok || !c->tmpl_data_ok) && (rc = build_templates(c))) return rc;
-    int tiles, slices;
-    nr::sh_slices(n_pts, c->n_reco, c->multi, &tiles, &slices);
-    const size_t ns = (size_t)slices;
-    const size_t na = (size_t)(c->multi ? nr::sh_acc(c->n_comp, c->n_bkg) : nr::kShAcc);
-    if (ns * n_pts > c->t_cap_d) {
+    const size_t sums = nr::sh_sums(n_pts, c->n_reco, c->multi);
+    const size_t acc = sums * (c->multi ? nr::sh_acc(c->n_comp, c->n_bkg) : nr::kShAcc);
+    if (sums > c->t_cap_d) {
         c->t_cap_d = 0;
-        if ((rc = dalloc(&c->d_tdp, ns * n_pts))) return rc;
-        c->t_cap_d = ns * n_pts;
+        if ((rc = dalloc(&c->d_tdp, sums))) return rc;
+        c->t_cap_d = sums;
     }
-    if (grad && ns * na * n_pts > c->t_cap_h) {
+    if (grad && acc > c->t_cap_h) {
         c->t_cap_h = 0;
-        if ((rc = dalloc(&c->d_thp, ns * na * n_pts))) return rc;
-        c->t_cap_h = ns * na * n_pts;
+        if ((rc = dalloc(&c->d_thp, acc))) return rc;
+        c->t_cap_h = acc;
     }
     return 0;
 }

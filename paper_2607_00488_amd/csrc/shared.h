@@ -155,5 +155,8 @@ hipError_t launch_sh_data(const ShRec& p, hipStream_t s);
 
 // Column slices of an evaluation of n_pts points over n_reco bins.
 void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice);
+// Slices x points of any list of up to n_pts points (fewer points may take more
+// slices), at least.
+size_t sh_sums(int n_pts, int n_reco, bool multi);
 
 }  // namespace nr

@@ -862,16 +862,29 @@ hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s) {
 // three of the gradient's two (65536 x 4096: 3072 to 16384 waves within 5 %).
 // The multi-component form writes three to five times as many: one round of its
 // gradient's two waves of 16 points per SIMD.
+constexpr int kSliceTiles = 4;       // of short lists
+constexpr int kShortPts = 4096;
+constexpr int kWaves = 6144, kMultiWaves = 2048;
+
 void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice) {
     const int n_tile = (n_reco + kShBins - 1) / kShBins;
-    int t = 4;
-    const int grp = multi ? (n_pts + 15) / 16 : (n_pts + 63) / 64, waves = multi ? 2048 : 6144;
-    if (multi || n_pts > 4096) {
-        const int ns = std::max(1, waves / grp);
+    int t = kSliceTiles;
+    const int grp = multi ? (n_pts + 15) / 16 : (n_pts + 63) / 64;
+    if (multi || n_pts > kShortPts) {
+        const int ns = std::max(1, (multi ? kMultiWaves : kWaves) / grp);
         t = std::max(t, (n_tile + ns - 1) / ns);
     }
     *tiles = t;
     *n_slice = (n_tile + t - 1) / t;
+}
+
+// As few slices as fill the waves, but at least one, and never more than the
+// shortest ones: at most the waves' points, the list's, or those times the latter.
+size_t sh_sums(int n_pts, int n_reco, bool multi) {
+    const size_t n = n_pts, most = (n_reco + kSliceTiles * kShBins - 1) / (kSliceTiles * kShBins);
+    const size_t resident = multi ? (size_t)kMultiWaves * 16 : (size_t)kWaves * 64;
+    const size_t s = std::min(most * n, std::max(resident, n));
+    return multi ? s : std::max(s, most * std::min(n, (size_t)kShortPts));
 }
 
 }  // namespace nr

@@ -69,6 +69,12 @@ def test_a_failed_allocation_leaves_nothing_to_launch_on(lib):
     run(lib, "failed_allocations")
 
 
+def test_fewer_points_never_need_more_memory(lib):
+    """What a capture relies on: a call made before with at least as many points
+    has allocated all that a call needs."""
+    run(lib, "shorter_lists", NR_GEMM_CONFIG="0")
+
+
 # ------------------------------------------------------------ child process
 def analysis(nr, n_t=40, n_reco=33, n_e=24):
     import synth
@@ -238,6 +244,34 @@ def failed_allocations(nr, mock):
             assert mock.mock_mallocs() > m, (name, failures)
             ctx.close()
         assert failures >= 1, name
+
+
+def shorter_lists(nr, mock):
+    import synth
+
+    def components(n_t, n_reco):
+        k = synth.component_inputs(n_t, n_reco, 20_000, 6)
+        ctx = nr.Context(0)
+        ctx.set_sources(synth.source_nodes(24), n_t)
+        args = [k.pop(n) for n in ("comp_of_source", "hist", "scale", "rate_sm")]
+        ctx.set_components(*args, **k)
+        ctx.set_data(np.full(n_reco, 20.0), None)
+        return ctx
+
+    lists = (200_000, 65_536, 20_100, 5_000, 4_096, 1_000, 17)
+    templates = lambda c, t: c.eval_nll_templates(t, True)  # noqa: E731
+    cases = [(analysis(nr, 8, 1000)[0], lists, templates),
+             (analysis(nr, 8, 1000)[0], lists, lambda c, t: c.eval_nll_grad_batched(t)),
+             (components(64, 300), lists, templates),
+             # blocks: a list longer than the workspace, then ones around its size
+             (components(4000, 100), [2000] + list(range(100, 500, 16)), lambda c, t: c.eval_nll(t))]
+    for i, (ctx, sizes, f) in enumerate(cases):
+        t = np.full((max(sizes), ctx.n_theta), 0.5)
+        f(ctx, t)
+        m = mock.mock_mallocs()
+        for n in sizes:
+            f(ctx, t[:n])
+            assert mock.mock_mallocs() == m, (i, n)
 
 
 if __name__ == "__main__":
