@@ -1294,7 +1294,7 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
 }
 
 // ---- project autotuner for the grouped fold.  A shape class is the sorted
-// list of (points rounded up to 64, N_reco, N_T) of the call plus the mode;
+// list of (points rounded up to 64, N_reco, N_T) of the call plus the mode and form;
 // the first call of a class times every configuration on the real
 // problem (one warm-up and two timed runs each) and keeps the fastest, in
 // memory and in a small JSON file (NR_AUTOTUNE_CACHE, default
@@ -1364,6 +1364,11 @@ void tune_save() {
     (void)rename((g_tune.path + ".tmp").c_str(), g_tune.path.c_str());
 }
 
+// What an entry's number selects: another set of configurations, or another
+// meaning of theirs, is another form.  (Keys without one named tile shapes of
+// matrix products.)
+constexpr char kTuneForm[] = "|rowsplit1";
+
 std::string shape_class(const MultiCall& mc, bool grad) {
     std::vector<std::string> parts;
     for (int d = 0; d < mc.n; ++d) {
@@ -1373,13 +1378,15 @@ std::string shape_class(const MultiCall& mc, bool grad) {
         parts.push_back(b);
     }
     std::sort(parts.begin(), parts.end());
-    std::string key = grad ? "grad" : "nll";
+    std::string mode = grad ? "grad" : "nll";
+    mode += kTuneForm;
+    std::string key = mode;
     for (auto& p : parts) key += "|" + p;
     if (key.size() > 200) {  // long groups: a stable hash keeps the file small
         unsigned long h = 1469598103934665603ul;
         for (char ch : key) h = (h ^ (unsigned char)ch) * 1099511628211ul;
         char b[64];
-        snprintf(b, sizeof(b), "%s|n%d|h%016lx", grad ? "grad" : "nll", mc.n, h);
+        snprintf(b, sizeof(b), "%s|n%d|h%016lx", mode.c_str(), mc.n, h);
         key = b;
     }
     return key;

@@ -75,7 +75,24 @@ def test_fewer_points_never_need_more_memory(lib):
     run(lib, "shorter_lists", NR_GEMM_CONFIG="0")
 
 
+@pytest.mark.parametrize("n_ctx", [1, 30])  # a key of shapes, and a hashed one
+def test_tuning_of_the_former_products_is_not_obeyed(lib, tmp_path, n_ctx):
+    """The file's entries once named tile shapes of matrix products: such an entry
+    is not taken for a row split, and stays in the file for who wrote it."""
+    cache = tmp_path / "autotune.json"
+    cache.write_text('{\n  "grad|64x33x40": 1,\n  "nll|64x33x40": 2,\n'
+                     '  "nll|n30|h%016x": 2\n}\n' % fnv("nll" + "|64x33x40" * 30))
+    run(lib, "former_tuning", NR_AUTOTUNE_CACHE=str(cache), N_CTX=str(n_ctx))
+
+
 # ------------------------------------------------------------ child process
+def fnv(text):
+    h = 1469598103934665603
+    for ch in text.encode():
+        h = ((h ^ ch) * 1099511628211) % 2 ** 64
+    return h
+
+
 def analysis(nr, n_t=40, n_reco=33, n_e=24):
     import synth
     src = synth.source_nodes(n_e)
@@ -272,6 +289,21 @@ def shorter_lists(nr, mock):
         for n in sizes:
             f(ctx, t[:n])
             assert mock.mock_mallocs() == m, (i, n)
+
+
+def former_tuning(nr, mock):
+    import json
+    import synth
+    path, n = os.environ["NR_AUTOTUNE_CACHE"], int(os.environ["N_CTX"])
+    os.environ.pop("NR_GEMM_CONFIG", None)
+    old = json.load(open(path))
+    t = synth.theta_prior(5, 7)
+    ctxs = [analysis(nr)[0] for _ in range(n)]
+    for _ in range(2):
+        nr.eval_nll_multi(ctxs, [t] * n)
+    new = json.load(open(path))
+    assert len(new) == len(old) + 1, new
+    assert {k: new[k] for k in old} == old
 
 
 if __name__ == "__main__":
