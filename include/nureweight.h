@@ -48,7 +48,7 @@
  * stream and wait for it).  Distinct contexts may be used from different
  * threads: every entry point holds one process-wide lock while it does its
  * host-side work (for a synchronous entry point, until its results are
- * back), so calls from different threads run one at a time on the host
+ * back; nr_mlp_train_epoch_dev step by step), so calls from different threads run one at a time on the host
  * while their device work may overlap.  The lock exists because a call may
  * capture a HIP graph on its stream, and the HIP runtime fails an open
  * capture when another thread issues a default-stream operation; the

@@ -17,6 +17,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <tuple>
 #include <vector>
 #include <sys/stat.h>
@@ -135,9 +136,25 @@ std::recursive_mutex& api_mutex() {
 
 namespace {
 
+std::atomic<int> g_waiting{0};  // threads in front of the lock
+
 struct ApiLock {
-    std::lock_guard<std::recursive_mutex> g{nr::api_mutex()};
+    ApiLock() {
+        ++g_waiting;
+        nr::api_mutex().lock();
+        --g_waiting;
+    }
+    ~ApiLock() { nr::api_mutex().unlock(); }
+    ApiLock(const ApiLock&) = delete;
+    ApiLock& operator=(const ApiLock&) = delete;
 };
+
+// Between the parts of a long call, the lock released: who waits for it goes
+// first (the lock itself would be taken again before a waiting thread wakes up).
+// Bounded, so that a stream of short calls does not hold the long one up.
+void let_others_in() {
+    for (int i = 0; i < 1000 && g_waiting.load() > 0; ++i) std::this_thread::yield();
+}
 
 // Device address of the static workspace on each device, looked up once per
 // device by the first nr_create on it (under the API lock).
@@ -2855,18 +2872,20 @@ static int mlp_train_step(nr_mlp* q, const double* d_theta, const float* d_t, co
 int nr_mlp_train_epoch_dev(nr_mlp* q, const double* d_theta, const float* d_t,
                            const long long* d_idx, int n_steps, int B, const float* lr,
                            void* stream) {
-    const ApiLock api_lock;
     if (!q || !d_theta || !d_t || !d_idx || !lr || n_steps <= 0 || B <= 0 || B % 8)
         return fail(NR_EINVAL, "null argument, no steps, or a batch that is no positive multiple of 8");
     if (q->H != nr::kFusedHidden)
         return fail(NR_EINVAL, "needs hidden layers of %d", nr::kFusedHidden);
-    HIPCHK(hipSetDevice(q->device));
     int rc;
-    if ((rc = mlp_alloc_batch(q, B, true))) return rc;
-    for (int i = 0; i < n_steps; ++i)
-        if ((rc = mlp_train_step(q, d_theta, d_t, d_idx + (size_t)i * B, B, lr[i],
+    for (int i = 0; i < n_steps; ++i) {
+        if (i) let_others_in();  // a whole epoch may wait for a full queue
+        const ApiLock api_lock;
+        HIPCHK(hipSetDevice(q->device));
+        if ((rc = mlp_alloc_batch(q, B, true)) ||
+            (rc = mlp_train_step(q, d_theta, d_t, d_idx + (size_t)i * B, B, lr[i],
                                  (hipStream_t)stream)))
             return rc;
+    }
     return 0;
 }
 

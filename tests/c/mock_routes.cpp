@@ -4,9 +4,12 @@
 // kernel launch seen by its name.  Test infrastructure, never linked into the
 // library.
 #include "../../paper_2607_00488_amd/csrc/shared.h"
+#include <atomic>
+#include <chrono>
 #include <cstring>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 namespace {
@@ -15,7 +18,8 @@ size_t g_keep = 0;
 std::vector<char> g_kept;
 bool g_fill_on = false;
 double g_fill = 0.0;
-long g_launches = 0;
+std::atomic<long> g_launches{0};
+int g_launch_us = 0;
 // what the entries of the last grouped launch of points read and write
 struct Range {
     unsigned long long entry, kind, at, bytes;
@@ -42,6 +46,8 @@ extern "C" {
 long mock_mallocs() { return g_mallocs; }
 void mock_fail_at(long n) { g_fail_at = n; }
 long mock_launches() { return g_launches; }
+// a launch takes this long on the host (a full queue)
+void mock_launch_time(int us) { g_launch_us = us; }
 // keeps the last upload of exactly n bytes
 void mock_keep(size_t n) { g_keep = n; g_kept.clear(); }
 size_t mock_kept(void* out) {
@@ -91,6 +97,7 @@ hipError_t __real_hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipSt
 hipError_t __wrap_hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t sh,
                                   hipStream_t s) {
     ++g_launches;
+    if (g_launch_us) std::this_thread::sleep_for(std::chrono::microseconds(g_launch_us));
     const std::string& n = names()[f];
     if (n.find("ELi16EE") != std::string::npos || n.find("ILi16EE") != std::string::npos) {
         if (n.find("k_sh_eval") != std::string::npos) {

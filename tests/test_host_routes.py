@@ -85,6 +85,10 @@ def test_tuning_of_the_former_products_is_not_obeyed(lib, tmp_path, n_ctx):
     run(lib, "former_tuning", NR_AUTOTUNE_CACHE=str(cache), N_CTX=str(n_ctx))
 
 
+def test_other_threads_calls_go_between_the_steps_of_an_epoch(lib):
+    run(lib, "epoch_and_another_thread")
+
+
 # ------------------------------------------------------------ child process
 def fnv(text):
     h = 1469598103934665603
@@ -304,6 +308,36 @@ def former_tuning(nr, mock):
     new = json.load(open(path))
     assert len(new) == len(old) + 1, new
     assert {k: new[k] for k in old} == old
+
+
+def epoch_and_another_thread(nr, mock):
+    """While a thread enqueues an epoch, every launch waiting for the queue,
+    another thread's calls are answered after a few steps, not after the epoch."""
+    import threading
+    import time
+    ctx = analysis(nr)[0]
+    h = nr.nr_mlp_create(0, 256, 64)
+    buf = np.zeros(1 << 16)
+    epoch = lambda steps: nr.nr_mlp_train_epoch_dev(  # noqa: E731
+        h, buf.ctypes.data, buf.ctypes.data, buf.ctypes.data, steps, 8, [1e-3] * steps)
+    n = mock.mock_launches()
+    epoch(1)
+    n = mock.mock_launches()
+    epoch(1)
+    per_step = mock.mock_launches() - n
+    mock.mock_launch_time(2000)
+    start = mock.mock_launches()
+    t = threading.Thread(target=epoch, args=(100,))
+    t.start()
+    while mock.mock_launches() < start + 2 * per_step:
+        time.sleep(0.001)
+    for _ in range(3):
+        before = mock.mock_launches()
+        ctx.reference()
+        assert mock.mock_launches() - before <= 10 * per_step
+    assert t.is_alive()
+    t.join()
+    assert mock.mock_launches() == start + 100 * per_step
 
 
 if __name__ == "__main__":
