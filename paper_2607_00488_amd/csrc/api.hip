@@ -691,15 +691,16 @@ nr::FoldArgs fold_args(nr_ctx* c, const double* thp, const double* v,
     return fa;
 }
 
+// Weights of a list of points of a multi-component context.
 nr::PtsWeightArgs weight_args(nr_ctx* c, const double* d_theta, int n_pts, int n_pad, int ldw,
                               double* wt) {
     nr::PtsWeightArgs a{};
     a.rf = c->d_rf;
     a.n_t = c->n_t;
-    a.n_comp = c->multi ? c->n_comp : 1;
+    a.n_comp = c->n_comp;
     a.theta = d_theta;
     a.n_theta = c->n_theta;
-    a.rate_index = c->multi ? 5 : -1;
+    a.rate_index = 5;
     a.n_pts = n_pts;
     a.n_pad = n_pad;
     a.ldw = ldw;
@@ -961,9 +962,10 @@ nr::ShFinal sh_final_args(const nr_ctx* c, const nr::ShEval& e, double* nll, dou
 }
 
 // Work-groups per slice of the launch that makes records and points together, for
-// n_pts points on folded columns of n_split splits; 0: a launch for either.  One
-// block of 16 points per wave, or two, as long as adding the splits up again in
-// every work-group reads no more than 32 MB.  At 16384 x 4096: 1 point 74 -> 68 us,
+// n_pts points on folded columns of n_split splits; 0: a launch for either.  64
+// points each, or 128 (blocks of 16 for four or eight of its sixteen waves; all of
+// them add up the splits), as long as adding the splits up again in every
+// work-group reads no more than 32 MB.  At 16384 x 4096: 1 point 74 -> 68 us,
 // 100 points 60 -> 54; at 512 x 256, where the launches are short whatever they do,
 // 1057 points take 13.7 us with a launch for either and 13.9 together: up to 512.
 int sh_tail_wgs(const nr_ctx* c, int n_pts, int n_split) {
@@ -1125,11 +1127,11 @@ int enqueue_blocks(nr_ctx* c, const double* th, int n_pts, double* nll, double* 
         ga.n_ct = (c->n_reco + nr::kBlkFinCols - 1) / nr::kBlkFinCols;
         ga.theta = thp;
         ga.n_theta = c->n_theta;
-        ga.bkg_index = c->multi ? 5 + c->n_comp : 6;
-        ga.n_bkg = c->multi ? c->n_bkg : 1;
+        ga.bkg_index = 5 + c->n_comp;
+        ga.n_bkg = c->n_bkg;
         ga.n = c->d_n;
-        ga.b = c->multi ? c->d_bkg : c->d_b;
-        ga.mask = c->multi ? c->d_mask : nullptr;
+        ga.b = c->d_bkg;
+        ga.mask = c->d_mask;
         ga.dev = w.dev;
         ga.out_mu = mu ? mu + (size_t)p0 * c->n_reco : nullptr;
         ga.cdata = c->cdata;
@@ -1366,7 +1368,6 @@ void tune_load() {
 
 void tune_save() {
     std::string dir = g_tune.path.substr(0, g_tune.path.rfind('/'));
-    std::string cmd;
     for (size_t k = 1; k <= dir.size(); ++k)  // mkdir -p without a shell
         if (k == dir.size() || dir[k] == '/') (void)mkdir(dir.substr(0, k).c_str(), 0755);
     FILE* f = fopen((g_tune.path + ".tmp").c_str(), "w");

@@ -1,5 +1,5 @@
-// Internal declarations of the blocked fold: many parameter points share one
-// stream over the response.
+// Internal declarations of the blocked fold: many parameter points of a
+// multi-component context share one stream over the response.
 #pragma once
 #include "common.h"
 
@@ -31,12 +31,12 @@ struct BlkFoldArgs {
     int n_ct, n_split, rows_per;
     double* part;
     size_t split_stride;  // doubles between splits
-    // per column tile the rows [lo, hi) that hold its non-zero responses
-    // (multiples of 16), or null (every row)
+    // per column tile the rows [lo, hi) that hold its non-zero responses (lo a
+    // multiple of four), or null (every row)
     const int* band;
 };
 
-// mu_j, deviance and a_j of every point from the splits, then -2lnL.
+// mu_j and deviance of every point from the splits, then -2lnL.
 struct BlkFinishArgs {
     const double* part;
     size_t split_stride;
@@ -47,10 +47,7 @@ struct BlkFinishArgs {
     const double* b;      // [n_bkg][n_reco]
     const double* mask;   // [n_reco] or null
     double* dev;          // [n_pts][n_ct] deviance sums
-    double* gb;           // [n_pts][n_ct] sums of a_j b_j, or null
     double* out_mu;       // [n_pts][n_reco] or null
-    double* out_a;        // [ldr][lda] d(-2lnL)/d mu, or null
-    int lda;
     double cdata;
     double pull_mean[kMaxTheta];
     double pull_sigma[kMaxTheta];

@@ -223,12 +223,9 @@ void k_blk_fold(BlkFoldArgs a, int n_blk, int n_groups) {
 
 // ---------------------------------------------------------------- finish
 // 16 points x 128 columns per work-group, 16 lanes on a point: the split
-// sums in split order, then mu_j (backgrounds and mask of the
-// multi-component form included), the deviance mu - n + n ln(n / mu) and
-// a_j = d(-2lnL)/d mu_j as in the single-point reduction; a_j leaves through
-// LDS so that its rows of 16 points are written whole.
+// sums in split order, then mu_j with backgrounds and mask, and the deviance
+// mu - n + n ln(n / mu) as in the single-point reduction.
 __global__ __launch_bounds__(kThreads) void k_blk_finish(BlkFinishArgs a) {
-    __shared__ double at[kBlkFinCols][kBlkPts + 1];
     const int tid = threadIdx.x, pi = tid >> 4, c = tid & 15;
     const int j0 = blockIdx.x * kBlkFinCols, p0 = blockIdx.y * kBlkPts, p = p0 + pi;
     const bool okp = p < a.n_pts;
@@ -250,47 +247,28 @@ __global__ __launch_bounds__(kThreads) void k_blk_finish(BlkFinishArgs a) {
             }
         }
     }
-    double dsum = 0.0, gsum = 0.0;
+    double dsum = 0.0;
     const double* th = a.theta + (size_t)(okp ? p : 0) * a.n_theta;
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int jl = 32 * v + 2 * c + h, col = j0 + jl;
-            double aj = 0.0;
-            if (okp && col < a.n_reco) {
-                double mu = h ? s[v].y : s[v].x, bj = 0.0;
-                for (int q = 0; q < a.n_bkg; ++q) {
-                    const double t = a.b[(size_t)q * a.n_reco + col];
-                    mu += th[a.bkg_index + q] * t;
-                    bj = t;
-                }
-                if (a.mask) mu *= a.mask[col];
-                const double nj = a.n[col];
-                if (a.out_mu) a.out_mu[(size_t)p * a.n_reco + col] = mu;
-                if (nj > 0.0)
-                    dsum += mu > 0.0 ? (mu - nj + nj * log(nj / mu)) : INFINITY;
-                else
-                    dsum += mu;
-                // an empty bin's term is 2 mu_j: its derivative is 2
-                aj = nj > 0.0 ? 2.0 * (1.0 - nj / mu) : 2.0;
-                gsum += aj * bj;
-            }
-            if (a.out_a) at[jl][pi] = aj;
+            const int col = j0 + 32 * v + 2 * c + h;
+            if (!okp || col >= a.n_reco) continue;
+            double mu = h ? s[v].y : s[v].x;
+            for (int q = 0; q < a.n_bkg; ++q)
+                mu += th[a.bkg_index + q] * a.b[(size_t)q * a.n_reco + col];
+            if (a.mask) mu *= a.mask[col];
+            const double nj = a.n[col];
+            if (a.out_mu) a.out_mu[(size_t)p * a.n_reco + col] = mu;
+            if (nj > 0.0)
+                dsum += mu > 0.0 ? (mu - nj + nj * log(nj / mu)) : INFINITY;
+            else
+                dsum += mu;
         }
 #pragma unroll
-    for (int o = 8; o > 0; o >>= 1) {
-        dsum += __shfl_xor(dsum, o, 64);
-        gsum += __shfl_xor(gsum, o, 64);
-    }
-    if (c == 0 && okp) {
-        a.dev[(size_t)p * a.n_ct + blockIdx.x] = dsum;
-        if (a.gb) a.gb[(size_t)p * a.n_ct + blockIdx.x] = gsum;
-    }
-    if (!a.out_a) return;
-    __syncthreads();
-    for (int r = pi; r < kBlkFinCols; r += 16)
-        if (j0 + r < a.ldr) a.out_a[(size_t)(j0 + r) * a.lda + p0 + c] = at[r][c];
+    for (int o = 8; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o, 64);
+    if (c == 0 && okp) a.dev[(size_t)p * a.n_ct + blockIdx.x] = dsum;
 }
 
 // -2lnL = 2 (sum of the column tiles' deviances + C_data) + pulls.
