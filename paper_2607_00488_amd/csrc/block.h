@@ -7,7 +7,7 @@ namespace nr {
 
 constexpr int kBlkPts = 16;    // points of one matrix-instruction block
 constexpr int kBlkCols = 256;  // response columns per fold work-group
-constexpr int kBlkFinCols = 128;  // columns per likelihood work-group
+constexpr int kBlkFinCols = 32;  // columns per likelihood work-group
 
 // Weights of a list of points from the row factors (basis.h):
 // wt[r][p] = v_r(theta_p) for p < n_pts, 0 for n_pts <= p < n_pad.

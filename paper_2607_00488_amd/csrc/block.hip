@@ -222,63 +222,67 @@ void k_blk_fold(BlkFoldArgs a, int n_blk, int n_groups) {
 }
 
 // ---------------------------------------------------------------- finish
-// 16 points x 128 columns per work-group, 16 lanes on a point: the split
-// sums in split order, then mu_j with backgrounds and mask, and the deviance
-// mu - n + n ln(n / mu) as in the single-point reduction.
+// 16 points x 32 columns per work-group, 16 lanes on a point with two columns each:
+// the split sums in split order, sixteen of them in flight, then mu_j with
+// backgrounds and mask, and the deviance mu - n + n ln(n / mu) as in the
+// single-point reduction.  Bound by the latency of the splits' sums on short lists
+// and by reading them on long ones: three points of 2048 rows x 1024 bins x 5
+// components (64 splits) 7.6 us, 85 with one split's loads at a time; 100 points
+// 11 us.
 __global__ __launch_bounds__(kThreads) void k_blk_finish(BlkFinishArgs a) {
+    static_assert(kBlkFinCols == 32, "two columns per lane");
+    constexpr int U = 16;
     const int tid = threadIdx.x, pi = tid >> 4, c = tid & 15;
-    const int j0 = blockIdx.x * kBlkFinCols, p0 = blockIdx.y * kBlkPts, p = p0 + pi;
+    const int j = blockIdx.x * kBlkFinCols + 2 * c, p = blockIdx.y * kBlkPts + pi;
     const bool okp = p < a.n_pts;
-    constexpr int NV = kBlkFinCols / 32;  // column pairs per lane
-    double2 s[NV];
+    const int pc = min(p, a.n_pts - 1);
+    const double* src = a.part + (size_t)pc * a.ldr + min(j, a.ldr - 2);
+    double2 s = make_double2(0.0, 0.0);
+    for (int q = 0; q < a.n_split; q += U) {
+        double2 t[U];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = make_double2(0.0, 0.0);
-    const double* src = a.part + (size_t)p * a.ldr + j0 + 2 * c;
-    if (okp) {
-#pragma unroll 4
-        for (int q = 0; q < a.n_split; ++q) {
-            const double* x = src + (size_t)q * a.split_stride;
+        for (int u = 0; u < U; ++u)
+            t[u] = *reinterpret_cast<const double2*>(src + min(q + u, a.n_split - 1) * a.split_stride);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                if (j0 + 32 * v + 2 * c >= a.ldr) continue;
-                const double2 t = *reinterpret_cast<const double2*>(x + 32 * v);
-                s[v].x += t.x;
-                s[v].y += t.y;
+        for (int u = 0; u < U; ++u)
+            if (q + u < a.n_split) {
+                s.x += t[u].x;
+                s.y += t[u].y;
             }
-        }
     }
     double dsum = 0.0;
-    const double* th = a.theta + (size_t)(okp ? p : 0) * a.n_theta;
+    const double* th = a.theta + (size_t)pc * a.n_theta;
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int col = j0 + 32 * v + 2 * c + h;
-            if (!okp || col >= a.n_reco) continue;
-            double mu = h ? s[v].y : s[v].x;
-            for (int q = 0; q < a.n_bkg; ++q)
-                mu += th[a.bkg_index + q] * a.b[(size_t)q * a.n_reco + col];
-            if (a.mask) mu *= a.mask[col];
-            const double nj = a.n[col];
-            if (a.out_mu) a.out_mu[(size_t)p * a.n_reco + col] = mu;
-            if (nj > 0.0)
-                dsum += mu > 0.0 ? (mu - nj + nj * log(nj / mu)) : INFINITY;
-            else
-                dsum += mu;
-        }
+    for (int h = 0; h < 2; ++h) {
+        const int col = j + h;
+        if (!okp || col >= a.n_reco) continue;
+        double mu = h ? s.y : s.x;
+        for (int q = 0; q < a.n_bkg; ++q)
+            mu += th[a.bkg_index + q] * a.b[(size_t)q * a.n_reco + col];
+        if (a.mask) mu *= a.mask[col];
+        const double nj = a.n[col];
+        if (a.out_mu) a.out_mu[(size_t)p * a.n_reco + col] = mu;
+        if (nj > 0.0)
+            dsum += mu > 0.0 ? (mu - nj + nj * log(nj / mu)) : INFINITY;
+        else
+            dsum += mu;
+    }
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o, 64);
     if (c == 0 && okp) a.dev[(size_t)p * a.n_ct + blockIdx.x] = dsum;
 }
 
-// -2lnL = 2 (sum of the column tiles' deviances + C_data) + pulls.
+// -2lnL = 2 (sum of the column tiles' deviances + C_data) + pulls; 16 lanes on a
+// point, each every sixteenth tile.
 __global__ __launch_bounds__(64) void k_blk_final(BlkFinishArgs a) {
-    const int p = blockIdx.x * 64 + threadIdx.x;
-    if (p >= a.n_pts) return;
-    const double* x = a.dev + (size_t)p * a.n_ct;
+    const int c = threadIdx.x & 15, p = blockIdx.x * 4 + (threadIdx.x >> 4);
+    const double* x = a.dev + (size_t)min(p, a.n_pts - 1) * a.n_ct;
     double d = 0.0;
 #pragma unroll 8
-    for (int q = 0; q < a.n_ct; ++q) d += x[q];
+    for (int q = c; q < a.n_ct; q += 16) d += x[q];
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+    if (c != 0 || p >= a.n_pts) return;
     double pulls = 0.0;
     for (int i = 0; i < a.n_theta; ++i)
         if (a.pull_sigma[i] > 0.0) {
@@ -325,7 +329,7 @@ hipError_t launch_blk_finish(const BlkFinishArgs& a, hipStream_t s) {
                        dim3(kThreads), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_blk_final, dim3((a.n_pts + 63) / 64), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_blk_final, dim3((a.n_pts + 3) / 4), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 

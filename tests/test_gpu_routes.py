@@ -39,3 +39,46 @@ def test_grouped_call_with_a_context_several_times(points, monkeypatch):
         assert np.array_equal(v.cpu().numpy(), r) and np.array_equal(g.cpu().numpy(), s)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("n_t,n_reco,points", [
+    (130, 77, (3, 16, 17, 33, 49, 65, 113)), (1000, 33, (5, 129)), (31, 2, (3, 18)),
+    (700, 4100, (3, 500))])
+def test_blocks_of_a_multi_component_list(n_t, n_reco, points, monkeypatch):
+    """Lists of three or more points of a multi-component context (blocked fold)
+    against its points one at a time (the single-point launches): block and group
+    edges in the points, ragged rows and columns, more row splits than a round of
+    loads, and a list that takes the workspace several times.
+
+    Tolerance: the two routes add the same products in different orders and form
+    the weights from suffix sums or from the recoil basis, so a mu_j carries at
+    most (rows + nodes + 128) roundings of 2^-53 relative, and -2lnL moves by
+    2 sum_j |mu_j - n_j| times that plus its own summation."""
+    import paper_2607_00488_amd as nr
+    k = synth.component_inputs(n_t, n_reco, 200_000, 8521)
+    args = [k.pop(n) for n in ("comp_of_source", "hist", "scale", "rate_sm")]
+    ctx = nr.Context(0)
+    ctx.set_sources(synth.source_nodes(48), n_t)
+    ctx.set_components(*args, **k)
+    g = synth.rng(8522)
+    th = g.uniform(0.8, 1.2, (max(points), ctx.n_theta))
+    th[:, :5] = synth.theta_prior(len(th), 8523)[:, :5]
+    ctx.set_data(np.ones(n_reco), None)
+    n = g.poisson(ctx.eval_mu(th[:1])[0]).astype(np.float64)
+    ctx.set_data(n, None)
+    log(f"blocks, {n_t} x {n_reco}, {points} points")
+    one = sorted({0, 1, 2, *(i for p in points for i in (p // 2, p - 1))})
+    mu = {i: ctx.eval_mu(th[i:i + 1])[0] for i in one}
+    nll = {i: ctx.eval_nll(th[i:i + 1])[0] for i in one}
+    rel = (5 * n_t + 3 * 48 + 2 + 128) * EPS
+    full = ctx.eval_nll(th)
+    for p in points:
+        got, gmu = ctx.eval_nll(th[:p]), ctx.eval_mu(th[:p])
+        assert np.array_equal(got, full[:p]), p  # whatever list a point is in
+        for i in one:
+            if i >= p:
+                continue
+            assert np.all(np.abs(gmu[i] - mu[i]) <= rel * np.abs(mu[i])), (p, i)
+            tol = 2 * np.abs(mu[i] - n).sum() * rel + 2 * (mu[i] + n).sum() * 64 * EPS
+            assert abs(got[i] - nll[i]) <= tol, (p, i)
+    ctx.close()
