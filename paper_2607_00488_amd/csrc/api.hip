@@ -210,9 +210,10 @@ struct nr_ctx {
     std::vector<int> rowband;
     int *d_rowband = nullptr, *d_tileband = nullptr;
     bool skip_zero = false;
-    // per column tile of the blocked fold the rows [lo, hi) holding its
-    // non-zero responses
+    // per column tile of the blocked and basis folds the rows [lo, hi) holding its
+    // non-zero responses, and their share of all rows and tiles
     int* d_blkband = nullptr;
+    double band_share = 1.0;
     // workspace of the blocked fold (lists of points of the multi-component
     // form), and its size
     double* d_blk = nullptr;
@@ -455,6 +456,7 @@ int set_blk_bands(nr_ctx* c) {
     static_assert(nr::kBlkCols == nr::kShTile, "one table of bands");
     const int n_ct = (c->ldr + nr::kBlkCols - 1) / nr::kBlkCols;
     std::vector<int> bb((size_t)2 * n_ct, 0);
+    double rows = 0;
     for (int t = 0; t < n_ct; ++t) {
         const int c0 = t * nr::kBlkCols / 4, c1 = c0 + nr::kBlkCols / 4;
         int lo = c->n_rows, hi = 0;
@@ -468,8 +470,10 @@ int set_blk_bands(nr_ctx* c) {
         if (lo < hi) {
             bb[2 * t] = lo & ~3;
             bb[2 * t + 1] = hi;
+            rows += hi - bb[2 * t];
         }
     }
+    c->band_share = rows / ((double)n_ct * c->n_rows);
     int rc;
     if ((rc = dalloc(&c->d_blkband, bb.size()))) return rc;
     HIPCHK(hipMemcpy(c->d_blkband, bb.data(), sizeof(int) * bb.size(), hipMemcpyHostToDevice));
@@ -898,15 +902,18 @@ bool use_shared(const nr_ctx* c) {
            sh_points(c, NR_NOALLOC_WORKSPACE_BYTES) > 0;
 }
 
-nr::ShFold sh_fold_args(const nr_ctx* c, int cfg, double* part) {
+// Narrow tiles up to a share of 3/8 of the rows inside a tile's band (measured on
+// either side, see k_sh_fold).
+nr::ShFold sh_fold_args(const nr_ctx* c, int cfg, double* part, bool bands = true) {
     nr::ShFold f{};
     f.R = c->d_R;
     f.rf = c->d_rf;
     f.part = part;
-    f.band = c->skip_zero ? c->d_blkband : nullptr;
+    f.band = c->skip_zero && bands ? c->d_blkband : nullptr;
+    f.narrow = f.band && c->band_share <= 0.375;
     f.ldr = c->ldr;
     f.n_t = c->n_t;
-    f.n_ct = (c->ldr + nr::kShTile - 1) / nr::kShTile;
+    f.n_ct = nr::sh_tiles(c->ldr, f.narrow);
     sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &f.n_split, &f.rows_per);
     return f;
 }
@@ -3018,8 +3025,7 @@ int nr_eval_mu_batched_dev(nr_ctx* c, const double* d_theta, int n_pts,
 static int build_records(nr_ctx* c) {
     const size_t n_rec = (size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins;
     double* d_part = nullptr;
-    nr::ShFold f = sh_fold_args(c, 0, nullptr);
-    f.band = nullptr;
+    nr::ShFold f = sh_fold_args(c, 0, nullptr, false);
     int rc;
     if ((rc = dalloc(&d_part, (size_t)f.n_split * nr::kShCols * c->ldr)) ||
         (rc = dalloc(&c->d_trec, n_rec * nr::kShRec))) {

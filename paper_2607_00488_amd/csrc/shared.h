@@ -16,6 +16,7 @@ namespace nr {
 
 constexpr int kShCols = kNBasis + 1;  // folded columns: 14 spectra, constant rows
 constexpr int kShTile = 256;          // response columns per fold work-group
+constexpr int kShNarrow = 64;         // of the fold for narrow bands
 constexpr int kShStage = 32;          // rows per stage of the fold
 constexpr int kShRec = 18;            // record: 15 columns, b_j, n_j, 1 / n_j
 constexpr int kShBins = 16;           // bins per tile of the points kernel
@@ -34,6 +35,7 @@ struct ShFold {
     double* th_dst;
     int n_th;  // values
     int ldr, n_t, n_ct, n_split, rows_per;
+    bool narrow;  // tiles of kShNarrow columns
 };
 
 struct ShRec {
@@ -153,6 +155,11 @@ hipError_t launch_sh_mdata(const ShMultiData& p, hipStream_t s);
 // New data beside folded columns that stay.
 hipError_t launch_sh_data(const ShRec& p, hipStream_t s);
 
+// Column tiles of the fold.
+inline int sh_tiles(int ldr, bool narrow) {
+    const int cols = narrow ? kShNarrow : kShTile;
+    return (ldr + cols - 1) / cols;
+}
 // Column slices of an evaluation of n_pts points over n_reco bins.
 void sh_slices(int n_pts, int n_reco, bool multi, int* tiles, int* n_slice);
 // Slices x points of any list of up to n_pts points (fewer points may take more

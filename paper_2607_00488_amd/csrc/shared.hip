@@ -78,23 +78,33 @@ __device__ inline double sum_strided(const __attribute__((address_space(1))) dou
 //
 // Bound by the stream over R, with the matrix cores close behind (15 multiply-
 // adds per entry: 32 us of arithmetic at 16384 x 4096, measured with R in
-// cache).  16384 x 4096: 47 us, 5.7 TB/s, with one work-group per compute unit,
-// 53 us with 512 work-groups and 61 us with 1024 (more partial sums); stages of
-// 16 rows 56 us; masks on the prefetched factors, which made every stage wait
-// for the next one's loads, 64 us.
-template <int N>
+// cache).  16384 x 4096: 43 us, 6.2 TB/s, with one work-group per compute unit;
+// two or three stages ahead 44 and 47 us; masks on the prefetched factors, which
+// made every stage wait for the next one's loads, half as long again.
+//
+// That is W = 4.  Under band skipping only the tile x split pairs that meet the
+// band have rows to fold, each bound by its own compute unit's matrix cores (1024
+// rows x 256 columns: 32 us, however few of them there are).  For narrow bands W =
+// 1: one set of 16 columns per wave, a float per lane and 64 rows per stage, a
+// quarter of the work on four times the units; every column's sum is the same
+// chain.  A stage's loads are fenced off its products, which left to itself the
+// compiler moves them between (26 us where it is 16; W = 4 loses 1 us by it).
+// 16384 x 4096, share of the rows of a tile inside its band 1/8: 37 -> 16 us; 5/16:
+// 29; 9/16: 41 against 39, and 64 against 43 without bands.
+template <int N, int W>
 __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     int t;
     const ShFold& a = g.p[sh_find(g, &t)];
-    constexpr int ST = kShStage / 4;
+    constexpr int ST = kShStage / 4 * (W == 1 ? 2 : 1), ROWS = 4 * ST;
+    typedef float vec __attribute__((ext_vector_type(W)));
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int li = lane & 15, lk = lane >> 4;
     // splits first: with their usual multiple of eight, an XCD's work-groups share
     // rows, and its L2 reads the row factors of those rows only, not of all (8 data
     // sets 71.2 -> 66.1 us a call; 100 points at 16384 x 4096 52.9 -> 52.3)
     const int ct = t / a.n_split, sp = t % a.n_split;
-    const int ldr = a.ldr, ld4 = ldr >> 2;
-    const int c4 = ct * (kShTile / 4) + wave * 16 + li;
+    const int ldr = a.ldr;
+    const int col = (ct * 4 + wave) * 16 * W + W * li, cc = min(col, ldr - W);
     // the points of the call on their way to device memory: loaded here, stored
     // at the end
     const int gi = t * kThreads + tid, gn = a.n_ct * a.n_split * kThreads;
@@ -105,20 +115,21 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     }
     int kb = sp * a.rows_per, ke = min(a.n_t, kb + a.rows_per);
     if (a.band) {  // rows outside hold exact zeros in this tile's columns
-        kb = max(kb, gm(a.band)[2 * ct]);
-        ke = min(ke, gm(a.band)[2 * ct + 1]);
+        const int b = ct * W / 4;
+        kb = max(kb, gm(a.band)[2 * b]);
+        ke = min(ke, gm(a.band)[2 * b + 1]);
     }
     const auto* R = (const __attribute__((address_space(1))) char*)a.R;
     const auto* F = (const __attribute__((address_space(1))) char*)a.rf;
     // byte offsets of a lane within a stage (n_reco < 2^27 columns)
-    const unsigned roff = (unsigned)lk * ldr * 4u + 16u * min(c4, ld4 - 1);
+    const unsigned roff = (unsigned)lk * ldr * 4u + 4u * cc;
     const unsigned foff = (lk * 16 + li) * 8u;
     const size_t rq = (size_t)ldr * 16;  // bytes of four rows
-    v4d acc[4];
+    v4d acc[W];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = (v4d){0.0, 0.0, 0.0, 0.0};
+    for (int e = 0; e < W; ++e) acc[e] = (v4d){0.0, 0.0, 0.0, 0.0};
     struct Stage {
-        v4f x[ST];
+        vec x[ST];
         double f[ST];
     };
     auto load = [&](int k, Stage& s) {
@@ -127,48 +138,65 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
 #pragma unroll
         for (int q = 0; q < ST; ++q) {
             s.f[q] = *(const __attribute__((address_space(1))) double*)(fb + q * (kRF * 32) + foff);
-            s.x[q] = *(const __attribute__((address_space(1))) v4f*)(rb + q * rq + roff);
+            s.x[q] = *(const __attribute__((address_space(1))) vec*)(rb + q * rq + roff);
         }
-    };
-    auto quad = [&](double f, v4f x) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(f, (double)x[e], acc[e], 0, 0, 0);
     };
     auto compute = [&](const Stage& s) {
 #pragma unroll
-        for (int q = 0; q < ST; ++q) quad(s.f[q], s.x[q]);
+        for (int q = 0; q < ST; ++q)
+#pragma unroll
+            for (int e = 0; e < W; ++e)
+                acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(s.f[q], (double)s.x[q][e], acc[e], 0, 0, 0);
     };
-    const int nst = kb < ke ? (ke - kb) / kShStage : 0;  // whole stages
-    if (nst > 0) {
+    const int nst = kb < ke ? (ke - kb) / ROWS : 0;  // whole stages
+    if (nst > 0) {  // the loads past the end repeat the last
         Stage s0, s1;
-        load(kb, s0);
+        auto at = [&](int i) { return kb + min(i, nst - 1) * ROWS; };
+        load(at(0), s0);
         int i = 0;
         for (; i + 1 < nst; i += 2) {
-            load(kb + (i + 1) * kShStage, s1);
+            load(at(i + 1), s1);
+            if (W == 1) __builtin_amdgcn_sched_barrier(0);
             compute(s0);
-            load(kb + min(i + 2, nst - 1) * kShStage, s0);
+            load(at(i + 2), s0);
+            if (W == 1) __builtin_amdgcn_sched_barrier(0);
             compute(s1);
         }
         if (i < nst) compute(s0);
     }
-    // the last rows, four at a time; past the end a zero factor on the last row
-    for (int k = kb + nst * kShStage; k < ke; k += 4) {
-        const int row = k + lk, rc = min(row, a.n_t - 1);
-        const double f = *(const __attribute__((address_space(1))) double*)(F + ((size_t)rc * kRF + li) * 8);
-        const v4f x = *(const __attribute__((address_space(1))) v4f*)(R + (size_t)rc * ldr * 4 + 16u * min(c4, ld4 - 1));
-        quad(row < ke ? f : 0.0, x);
+    // the last rows, all loaded at once; past the end a zero factor on the last row
+    const int k0 = kb + nst * ROWS, left = ke - k0;
+    if (left > 0) {
+        Stage s;
+#pragma unroll
+        for (int q = 0; q < ST; ++q) {
+            const int row = k0 + 4 * q + lk, rc = min(row, a.n_t - 1);
+            s.f[q] = *(const __attribute__((address_space(1))) double*)(F + ((size_t)rc * kRF + li) * 8);
+            s.x[q] = *(const __attribute__((address_space(1))) vec*)(R + ((size_t)rc * ldr + cc) * 4);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < ST; ++q) {
+            const double f = k0 + 4 * q + lk < ke ? s.f[q] : 0.0;
+#pragma unroll
+            for (int e = 0; e < W; ++e)
+                acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(f, (double)s.x[q][e], acc[e], 0, 0, 0);
+        }
     }
     if (a.th_src && gi < a.n_th) gm(a.th_dst)[gi] = th;
-    if (c4 >= ld4) return;
-    auto* out = gm(a.part) + (size_t)sp * kShCols * ldr + 4 * (size_t)c4;
+    if (col >= ldr) return;
+    auto* out = gm(a.part) + (size_t)sp * kShCols * ldr + col;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int b = lk + 4 * r;  // output (i, j): lane j + 16 (i % 4), register i / 4
         if (b >= kShCols) continue;
-        auto* o = (__attribute__((address_space(1))) v2d*)(out + (size_t)b * ldr);
-        o[0] = (v2d){acc[0][r], acc[1][r]};
-        o[1] = (v2d){acc[2][r], acc[3][r]};
+        auto* o = out + (size_t)b * ldr;
+        if constexpr (W == 4) {
+            ((__attribute__((address_space(1))) v2d*)o)[0] = (v2d){acc[0][r], acc[1][r]};
+            ((__attribute__((address_space(1))) v2d*)o)[1] = (v2d){acc[2][r], acc[3][r]};
+        } else {
+            o[0] = acc[0][r];
+        }
     }
 }
 
@@ -709,6 +737,19 @@ ShGroup<P, N> make_group(const P* p, int n, Wgs wgs) {
         }                                                                               \
     } while (0)
 
+void launch_fold(const ShFold* p, int n, bool narrow, hipStream_t s) {
+    const auto wgs = [](const ShFold& f) { return f.n_ct * f.n_split; };
+    if (narrow) {
+#define SH_K(M) (k_sh_fold<M, 1>)
+        SH_LAUNCH(SH_K, ShFold, kThreads, wgs);
+#undef SH_K
+    } else {
+#define SH_K(M) (k_sh_fold<M, 4>)
+        SH_LAUNCH(SH_K, ShFold, kThreads, wgs);
+#undef SH_K
+    }
+}
+
 template <bool GRAD, bool MU, int NB, int KS = kShAcc / 4>
 void launch_eval(const ShEval* p, int n, hipStream_t s) {
     const auto wgs = [](const ShEval& e) {
@@ -747,12 +788,17 @@ hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s) {
     if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
     for (int d = 0; d < n; ++d)
         if (p[d].ldr % 4 || p[d].rows_per <= 0 || p[d].rows_per % kShStage || p[d].ldr >= (1 << 27) ||
-            p[d].n_ct != (p[d].ldr + kShTile - 1) / kShTile || p[d].n_split < 1 ||
+            p[d].n_ct != sh_tiles(p[d].ldr, p[d].narrow) || p[d].n_split < 1 ||
             (long)p[d].n_split * p[d].rows_per < p[d].n_t)
             return hipErrorInvalidValue;
-#define SH_K(M) (k_sh_fold<M>)
-    SH_LAUNCH(SH_K, ShFold, kThreads, [](const ShFold& f) { return f.n_ct * f.n_split; });
-#undef SH_K
+    // one launch for each kind of tile
+    for (const bool narrow : {false, true}) {
+        ShFold q[kShGroup];
+        int m = 0;
+        for (int d = 0; d < n; ++d)
+            if (p[d].narrow == narrow) q[m++] = p[d];
+        if (m) launch_fold(q, m, narrow, s);
+    }
     return hipGetLastError();
 }
 

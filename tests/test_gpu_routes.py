@@ -82,3 +82,52 @@ def test_blocks_of_a_multi_component_list(n_t, n_reco, points, monkeypatch):
             tol = 2 * np.abs(mu[i] - n).sum() * rel + 2 * (mu[i] + n).sum() * 64 * EPS
             assert abs(got[i] - nll[i]) <= tol, (p, i)
     ctx.close()
+
+
+def diagonal(n_t, n_reco, width, seed):
+    """An analysis whose response rows are non-zero over `width` bins only."""
+    import paper_2607_00488_amd as nr
+    g = synth.rng(seed)
+    c = np.arange(n_t) * n_reco // n_t
+    j = np.arange(n_reco)
+    R = np.where(np.abs(j - c[:, None]) <= width // 2,
+                 g.uniform(0.5, 1.5, (n_t, n_reco)), 0.0).astype(np.float32)
+    ctx = nr.Context(0)
+    ctx.set_sources(synth.source_nodes(24), n_t)
+    ctx.set_response(R, n_sig=1.0e4)
+    b = np.full(n_reco, 10.0)
+    ctx.set_data(b, b)
+    n = g.poisson(ctx.eval_mu(synth.theta_sm()[None])[0]).astype(np.float64)
+    ctx.set_data(n, b)
+    return ctx
+
+
+@pytest.mark.parametrize("n_t,n_reco,width", [
+    (4096, 2048, 100), (1003, 777, 60), (129, 1025, 30), (700, 321, 9), (2050, 1153, 450)])
+def test_bands_narrow_and_wide(n_t, n_reco, width, monkeypatch):
+    """Band skipping on responses whose bands are narrow (tiles of 64 columns) and
+    wide: every entry point bit for bit as without, also beside an analysis without
+    bands in one grouped call."""
+    import torch
+    import paper_2607_00488_amd as nr
+    monkeypatch.setenv("NR_GEMM_CONFIG", "0")
+    ctx, other = diagonal(n_t, n_reco, width, 8531), diagonal(100, 300, 300, 8532)
+    th = synth.theta_prior(19, 8533, f_range=(0.8, 1.2))
+    log(f"bands, {n_t} x {n_reco}, {width} bins wide")
+
+    def values():
+        dev = [torch.tensor(t, device="cuda:0") for t in (th, th[:7], th[3:])]
+        nll = [torch.empty(len(t), dtype=torch.float64, device="cuda:0") for t in dev]
+        nr.eval_nll_multi_dev([ctx, other, ctx], dev, nll)
+        torch.cuda.synchronize()
+        ctx.build_templates()
+        return [ctx.eval_nll(th), ctx.eval_nll(th[:1]), *ctx.eval_nll_grad(th), ctx.eval_mu(th),
+                ctx.eval_nll_batched(th), *ctx.eval_nll_grad_batched(th[:3]),
+                *ctx.eval_nll_templates(th, grad=True), *(v.cpu().numpy() for v in nll)]
+
+    dense = values()
+    ctx.set_band_skipping(True)
+    for i, (a, b) in enumerate(zip(dense, values())):
+        assert np.array_equal(a, b), i
+    ctx.close()
+    other.close()
