@@ -827,21 +827,47 @@ int enqueue_points(nr_ctx* c, const double* th, int n_pts, double* nll,
 // ---- the basis form (shared.hip): one pass over R per call, whatever the
 // number of points.
 
-// Row splits of the fold: column tiles x splits fill the chip's 256 compute
-// units `fill` times, a split of at least one stage.  They depend on the
-// response's shape only, so a point's result does not depend on its list.
-void sh_split(const nr_ctx* c, int fill_num, int fill_den, int* n_split, int* rows_per) {
-    const int n_ct = (c->ldr + nr::kShTile - 1) / nr::kShTile;
-    const int target = 256 * fill_num / fill_den;
-    const int s = std::max(1, std::min(target / n_ct, c->n_t / nr::kShStage));
-    *rows_per = ((c->n_t + s - 1) / s + nr::kShStage - 1) / nr::kShStage * nr::kShStage;
-    *n_split = (c->n_t + *rows_per - 1) / *rows_per;
+// Row splits of the fold.  They depend on the response's shape only, so a point's
+// result does not depend on its list.
+struct ShPlan {
+    nr::ShKind kind;
+    int n_split, rows_per;
+};
+
+ShPlan sh_plan(const nr_ctx* c, int fill_num, int fill_den) {
+    const int n_ct = nr::sh_tiles(c->ldr, nr::kShWide), n_t = c->n_t;
+    // Column tiles x splits fill the chip's 256 compute units `fill` times, a split
+    // of at least one stage.  With few columns that is many splits, which the next
+    // launch adds up sixteen at a time: at most as many as balance the two, about
+    // 1.9 us a round against 1.0 a stage.  One point at 16384 x 12: 256 splits 57
+    // us, 128 45, 64 41, 32 47; 100000 x 100: 256 71, 192 69, 96 74.
+    const int stages = (n_t + nr::kShStage - 1) / nr::kShStage;
+    const int most = std::max(16, (int)(std::sqrt(8.4 * stages) / 16 + 0.5) * 16);
+    int s = std::min({256 * fill_num / fill_den / n_ct, most * fill_num / fill_den,
+                      n_t / nr::kShStage});
+    s = std::max(1, s);
+    ShPlan p{nr::kShWide, s, nr::kShStage};
+    if (fill_num == fill_den && n_ct > 128 && n_t >= 512) {
+        // One split, and compute units left over: small tiles where their rounds on
+        // the chip (in units of all rows of 256 columns a unit) are shorter by a
+        // sixth; two splits of them up to 156 tiles, beyond which two would not fit
+        // the allocation-free workspace.  (Up to 128 tiles, or with 300 rows, the
+        // small ones were no faster.)
+        const int st = n_ct <= 156 ? 2 : 1, nt = nr::sh_tiles(c->ldr, nr::kShTall);
+        const int wide = (n_ct + 255) / 256;
+        const double tall = (nt * st + 255) / 256 / (4.0 * st);
+        if (tall < 0.85 * wide) p = {nr::kShTall, st, 4 * nr::kShStage};
+    }
+    const int step = p.rows_per;
+    p.rows_per = ((n_t + p.n_split - 1) / p.n_split + step - 1) / step * step;
+    p.n_split = (n_t + p.rows_per - 1) / p.rows_per;
+    return p;
 }
 
 // Configurations the autotuner picks from: work-groups per compute unit.
-// 0 (one) is what every call outside the batched entry points runs: at
-// 16384 x 4096 it reads R in 47 us, two in 53 us, four in 61 us (each doubling
-// writes and reads back twice the partial sums).
+// 0 (one) is what every call outside the batched entry points runs: at 16384 x 4096
+// it reads R in 43 us, two in 55 us (each doubling writes and reads back twice the
+// partial sums).
 constexpr int kShConfigs = 4;
 constexpr int kShFill[kShConfigs][2] = {{1, 1}, {2, 1}, {4, 1}, {1, 2}};
 
@@ -858,8 +884,7 @@ size_t carve_sh(const nr_ctx* c, double* base, int pts, bool grad, int cfg, ShWo
         off += (n + 31) / 32 * 32;
         return p;
     };
-    int ns, rp;
-    sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &ns, &rp);
+    const int ns = sh_plan(c, kShFill[cfg][0], kShFill[cfg][1]).n_split;
     const size_t sums = nr::sh_sums(pts, c->n_reco, false);
     w->part = take((size_t)ns * nr::kShCols * c->ldr);
     w->rec = take((size_t)(c->n_reco + nr::kShBins - 1) / nr::kShBins * nr::kShBins * nr::kShRec);
@@ -903,18 +928,21 @@ bool use_shared(const nr_ctx* c) {
 }
 
 // Narrow tiles up to a share of 3/8 of the rows inside a tile's band (measured on
-// either side, see k_sh_fold).
+// either side, see k_sh_fold), where the plan's are wide: a column's sum stays the
+// same chain.
 nr::ShFold sh_fold_args(const nr_ctx* c, int cfg, double* part, bool bands = true) {
     nr::ShFold f{};
     f.R = c->d_R;
     f.rf = c->d_rf;
     f.part = part;
+    const ShPlan p = sh_plan(c, kShFill[cfg][0], kShFill[cfg][1]);
     f.band = c->skip_zero && bands ? c->d_blkband : nullptr;
-    f.narrow = f.band && c->band_share <= 0.375;
+    f.kind = f.band && p.kind == nr::kShWide && c->band_share <= 0.375 ? nr::kShNarrow : p.kind;
     f.ldr = c->ldr;
     f.n_t = c->n_t;
-    f.n_ct = nr::sh_tiles(c->ldr, f.narrow);
-    sh_split(c, kShFill[cfg][0], kShFill[cfg][1], &f.n_split, &f.rows_per);
+    f.n_ct = nr::sh_tiles(c->ldr, f.kind);
+    f.n_split = p.n_split;
+    f.rows_per = p.rows_per;
     return f;
 }
 
@@ -1392,7 +1420,7 @@ void tune_save() {
 // What an entry's number selects: another set of configurations, or another
 // meaning of theirs, is another form.  (Keys without one named tile shapes of
 // matrix products.)
-constexpr char kTuneForm[] = "|rowsplit1";
+constexpr char kTuneForm[] = "|rowsplit2";
 
 std::string shape_class(const MultiCall& mc, bool grad) {
     std::vector<std::string> parts;

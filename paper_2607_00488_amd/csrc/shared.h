@@ -16,8 +16,12 @@ namespace nr {
 
 constexpr int kShCols = kNBasis + 1;  // folded columns: 14 spectra, constant rows
 constexpr int kShTile = 256;          // response columns per fold work-group
-constexpr int kShNarrow = 64;         // of the fold for narrow bands
+constexpr int kShSmallTile = 64;      // of the two other kinds
 constexpr int kShStage = 32;          // rows per stage of the fold
+// Work-groups of the fold: four waves side by side over 256 columns, the same with
+// narrow waves over 64, four waves over the same 64 columns and a quarter of the
+// split's rows each.
+enum ShKind { kShWide, kShNarrow, kShTall };
 constexpr int kShRec = 18;            // record: 15 columns, b_j, n_j, 1 / n_j
 constexpr int kShBins = 16;           // bins per tile of the points kernel
 constexpr int kShAcc = 16;            // contractions h per point (the last: b_j)
@@ -35,7 +39,7 @@ struct ShFold {
     double* th_dst;
     int n_th;  // values
     int ldr, n_t, n_ct, n_split, rows_per;
-    bool narrow;  // tiles of kShNarrow columns
+    ShKind kind;
 };
 
 struct ShRec {
@@ -156,8 +160,8 @@ hipError_t launch_sh_mdata(const ShMultiData& p, hipStream_t s);
 hipError_t launch_sh_data(const ShRec& p, hipStream_t s);
 
 // Column tiles of the fold.
-inline int sh_tiles(int ldr, bool narrow) {
-    const int cols = narrow ? kShNarrow : kShTile;
+inline int sh_tiles(int ldr, ShKind kind) {
+    const int cols = kind == kShWide ? kShTile : kShSmallTile;
     return (ldr + cols - 1) / cols;
 }
 // Column slices of an evaluation of n_pts points over n_reco bins.

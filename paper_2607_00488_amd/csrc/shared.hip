@@ -91,7 +91,13 @@ __device__ inline double sum_strided(const __attribute__((address_space(1))) dou
 // compiler moves them between (26 us where it is 16; W = 4 loses 1 us by it).
 // 16384 x 4096, share of the rows of a tile inside its band 1/8: 37 -> 16 us; 5/16:
 // 29; 9/16: 41 against 39, and 64 against 43 without bands.
-template <int N, int W>
+//
+// TALL: where too few tiles of 256 columns for a second split leave compute units
+// idle, or just too many fill them unevenly (the rule: sh_plan).  The waves' sums are
+// added in order through LDS, so that four times the work-groups write no more
+// partial sums.  8000 x 34000 (133 wide tiles) 284 -> 225 us, 65536 x 36864 (144)
+// 2264 -> 1847, 2048 x 40000 (157) 75 -> 67, 8000 x 49152 (192) 286 and 288.
+template <int N, int W, bool TALL>
 __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     int t;
     const ShFold& a = g.p[sh_find(g, &t)];
@@ -104,7 +110,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     // sets 71.2 -> 66.1 us a call; 100 points at 16384 x 4096 52.9 -> 52.3)
     const int ct = t / a.n_split, sp = t % a.n_split;
     const int ldr = a.ldr;
-    const int col = (ct * 4 + wave) * 16 * W + W * li, cc = min(col, ldr - W);
+    const int col = (TALL ? ct : ct * 4 + wave) * 16 * W + W * li, cc = min(col, ldr - W);
     // the points of the call on their way to device memory: loaded here, stored
     // at the end
     const int gi = t * kThreads + tid, gn = a.n_ct * a.n_split * kThreads;
@@ -113,9 +119,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
         if (gi < a.n_th) th = gm(a.th_src)[gi];
         for (int i = gi + gn; i < a.n_th; i += gn) gm(a.th_dst)[i] = gm(a.th_src)[i];
     }
-    int kb = sp * a.rows_per, ke = min(a.n_t, kb + a.rows_per);
+    const int rows = TALL ? a.rows_per / 4 : a.rows_per;
+    int kb = sp * a.rows_per + (TALL ? wave * rows : 0), ke = min(a.n_t, kb + rows);
     if (a.band) {  // rows outside hold exact zeros in this tile's columns
-        const int b = ct * W / 4;
+        const int b = W == 4 && !TALL ? ct : ct / 4;
         kb = max(kb, gm(a.band)[2 * b]);
         ke = min(ke, gm(a.band)[2 * b + 1]);
     }
@@ -184,6 +191,23 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
         }
     }
     if (a.th_src && gi < a.n_th) gm(a.th_dst)[gi] = th;
+    if constexpr (TALL) {
+        __shared__ __attribute__((aligned(16))) double red[4][16][kShSmallTile];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            auto* o = reinterpret_cast<v2d*>(&red[wave][lk + 4 * r][4 * li]);
+            o[0] = (v2d){acc[0][r], acc[1][r]};
+            o[1] = (v2d){acc[2][r], acc[3][r]};
+        }
+        __syncthreads();
+        for (int i = tid; i < kShCols * kShSmallTile; i += kThreads) {
+            const int b = i / kShSmallTile, j = i % kShSmallTile;
+            if (ct * kShSmallTile + j < ldr)
+                gm(a.part)[((size_t)sp * kShCols + b) * ldr + ct * kShSmallTile + j] =
+                    ((red[0][b][j] + red[1][b][j]) + red[2][b][j]) + red[3][b][j];
+        }
+        return;
+    }
     if (col >= ldr) return;
     auto* out = gm(a.part) + (size_t)sp * kShCols * ldr + col;
 #pragma unroll
@@ -737,17 +761,11 @@ ShGroup<P, N> make_group(const P* p, int n, Wgs wgs) {
         }                                                                               \
     } while (0)
 
-void launch_fold(const ShFold* p, int n, bool narrow, hipStream_t s) {
-    const auto wgs = [](const ShFold& f) { return f.n_ct * f.n_split; };
-    if (narrow) {
-#define SH_K(M) (k_sh_fold<M, 1>)
-        SH_LAUNCH(SH_K, ShFold, kThreads, wgs);
+template <int W, bool TALL>
+void launch_fold(const ShFold* p, int n, hipStream_t s) {
+#define SH_K(M) (k_sh_fold<M, W, TALL>)
+    SH_LAUNCH(SH_K, ShFold, kThreads, [](const ShFold& f) { return f.n_ct * f.n_split; });
 #undef SH_K
-    } else {
-#define SH_K(M) (k_sh_fold<M, 4>)
-        SH_LAUNCH(SH_K, ShFold, kThreads, wgs);
-#undef SH_K
-    }
 }
 
 template <bool GRAD, bool MU, int NB, int KS = kShAcc / 4>
@@ -788,16 +806,20 @@ hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s) {
     if (n < 1 || n > kShGroup) return hipErrorInvalidValue;
     for (int d = 0; d < n; ++d)
         if (p[d].ldr % 4 || p[d].rows_per <= 0 || p[d].rows_per % kShStage || p[d].ldr >= (1 << 27) ||
-            p[d].n_ct != sh_tiles(p[d].ldr, p[d].narrow) || p[d].n_split < 1 ||
+            p[d].n_ct != sh_tiles(p[d].ldr, p[d].kind) || p[d].n_split < 1 ||
+            (p[d].kind == kShTall && p[d].rows_per % (4 * kShStage)) ||
             (long)p[d].n_split * p[d].rows_per < p[d].n_t)
             return hipErrorInvalidValue;
     // one launch for each kind of tile
-    for (const bool narrow : {false, true}) {
+    for (const ShKind kind : {kShWide, kShNarrow, kShTall}) {
         ShFold q[kShGroup];
         int m = 0;
         for (int d = 0; d < n; ++d)
-            if (p[d].narrow == narrow) q[m++] = p[d];
-        if (m) launch_fold(q, m, narrow, s);
+            if (p[d].kind == kind) q[m++] = p[d];
+        if (!m) continue;
+        if (kind == kShWide) launch_fold<4, false>(q, m, s);
+        else if (kind == kShNarrow) launch_fold<1, false>(q, m, s);
+        else launch_fold<4, true>(q, m, s);
     }
     return hipGetLastError();
 }

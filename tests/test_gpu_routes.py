@@ -131,3 +131,52 @@ def test_bands_narrow_and_wide(n_t, n_reco, width, monkeypatch):
         assert np.array_equal(a, b), i
     ctx.close()
     other.close()
+
+
+@pytest.mark.parametrize("n_t,n_reco", [
+    (600, 34001), (512, 39936), (515, 41003), (301, 34001), (5001, 20), (16384, 65)])
+def test_row_splits_of_wide_and_of_tall_responses(n_t, n_reco):
+    """Responses whose rows the fold splits by another rule than their size: many
+    columns (four waves over the same 64, one split and two) and few (fewer splits
+    than compute units); band skipping and the allocation-free call bit for bit.
+
+    Tolerances of the basis form's other edges (tests/test_gpu_shared.py): rel =
+    (rows + nodes + 128) roundings of a mu_j, and what they and its own summation
+    move -2lnL and the gradient by.  -2lnL is compared as the difference of two
+    points with the exactly rounded sum over the oracle's spectra: the data constant,
+    and the oracle's own -2lnL, are sums of all bins in a row, whose rounding at
+    40000 bins is as large as the tolerance."""
+    import math
+    import torch
+    N_E = 24
+    p = inputs(n_t, n_reco, N_E, 400_000, 8541, 8542)
+    ctx = gpu_context(p)
+    th = synth.theta_prior(18, 8543, f_range=(0.8, 1.2))
+    log(f"row splits, {n_t} x {n_reco}")
+    nll, grad = ctx.eval_nll_grad(th)
+    o, n, mu = p["oracle"], p["n"], ctx.eval_mu(th)
+    rel = (n_t + 3 * N_E + 2 + 128) * EPS
+    ref, tol = {}, {}
+    for i in (0, 17):
+        m, g = o.mu(th[i]), o.nll_grad(th[i])[1]
+        assert np.all(np.abs(mu[i] - m) <= rel * np.abs(m)), i
+        ref[i] = 2 * math.fsum([*m, *(-k * math.log(x) for k, x in zip(n, m) if k > 0)])
+        tol[i] = 2 * np.abs(m - n).sum() * rel + 2 * (m + n).sum() * 64 * EPS
+        w = np.abs(2 * (1 - n / m)) + 2 * n / m
+        for k in range(7):
+            d = np.zeros_like(m)
+            for s in (-1.0, 1.0):
+                t = th[i].copy()
+                t[k] += s
+                d += np.abs(o.mu(t) - m)
+            assert abs(grad[i, k] - g[k]) <= 8 * rel * (w * d).sum(), (i, k)
+    assert abs(nll[17] - nll[0] - (ref[17] - ref[0])) <= tol[0] + tol[17]
+    assert np.array_equal(ctx.eval_nll(th[:1]), nll[:1])
+    tt = torch.tensor(th, device="cuda:0")
+    out = torch.empty(len(th), dtype=torch.float64, device="cuda:0")
+    ctx.eval_nll_dev_noalloc(tt, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), nll)
+    ctx.set_band_skipping(True)
+    assert np.array_equal(ctx.eval_nll(th), nll)
+    ctx.close()
