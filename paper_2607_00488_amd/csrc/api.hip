@@ -871,6 +871,10 @@ ShPlan sh_plan(const nr_ctx* c, int fill_num, int fill_den) {
 constexpr int kShConfigs = 4;
 constexpr int kShFill[kShConfigs][2] = {{1, 1}, {2, 1}, {4, 1}, {1, 2}};
 
+// Responses larger than the 256 MB Infinity Cache (with something over: one that
+// just fits is read faster from it) come from memory on every pass.
+bool streams(int n_t, int ldr) { return (double)n_t * ldr * sizeof(float) > 300.0e6; }
+
 struct ShWork {
     double *part, *rec, *dpart, *hpart;
 };
@@ -940,6 +944,7 @@ nr::ShFold sh_fold_args(const nr_ctx* c, int cfg, double* part, bool bands = tru
     f.kind = f.band && p.kind == nr::kShWide && c->band_share <= 0.375 ? nr::kShNarrow : p.kind;
     f.ldr = c->ldr;
     f.n_t = c->n_t;
+    f.stream = streams(c->n_t, c->ldr) && c->ldr % 32 == 0;
     f.n_ct = nr::sh_tiles(c->ldr, f.kind);
     f.n_split = p.n_split;
     f.rows_per = p.rows_per;
@@ -1831,6 +1836,10 @@ int nr_set_response(nr_ctx* c, const float* R, int n_t, int n_reco,
     c->n_rows = n_t;
     c->n_reco = n_reco;
     c->ldr = (n_reco + 3) / 4 * 4;
+    // rows of whole 128-byte lines where R comes from memory (16384 x 9000: fold 107
+    // -> 96 us); not near the 56000 bins where the basis form's workspace in the
+    // allocation-free call ends, which depends on it
+    if (streams(n_t, c->ldr) && n_reco < 50000) c->ldr = (n_reco + 31) / 32 * 32;
     if ((rc = dalloc(&c->d_R, (size_t)n_t * c->ldr))) return rc;
     if (c->ldr != n_reco)
         HIPCHK(hipMemset(c->d_R, 0, sizeof(float) * (size_t)n_t * c->ldr));

@@ -40,6 +40,7 @@ struct ShFold {
     int n_th;  // values
     int ldr, n_t, n_ct, n_split, rows_per;
     ShKind kind;
+    bool stream;  // read R past the caches (kinds of 64 columns per wave)
 };
 
 struct ShRec {

@@ -97,7 +97,13 @@ __device__ inline double sum_strided(const __attribute__((address_space(1))) dou
 // added in order through LDS, so that four times the work-groups write no more
 // partial sums.  8000 x 34000 (133 wide tiles) 284 -> 225 us, 65536 x 36864 (144)
 // 2264 -> 1847, 2048 x 40000 (157) 75 -> 67, 8000 x 49152 (192) 286 and 288.
-template <int N, int W, bool TALL>
+//
+// NT: responses larger than the Infinity Cache, in rows of whole cache lines, are
+// read without leaving them in any cache: 20000 x 4096 59 -> 54 us, 32768 x 8192 176
+// -> 162 (6.6 TB/s), 65536 x 36864 1847 -> 1731; 16384 x 4096, which just fits, 43
+// against 45.  Where rows share lines, the second use would read them again: 8000 x
+// 34000 225 against 241 us.
+template <int N, int W, bool TALL, bool NT>
 __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
     int t;
     const ShFold& a = g.p[sh_find(g, &t)];
@@ -139,13 +145,18 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
         vec x[ST];
         double f[ST];
     };
+    auto ldx = [](const __attribute__((address_space(1))) char* p) {
+        const auto* q = (const __attribute__((address_space(1))) vec*)p;
+        if constexpr (NT) return __builtin_nontemporal_load(q);
+        else return *q;
+    };
     auto load = [&](int k, Stage& s) {
         const auto* rb = R + (size_t)k * ldr * 4;
         const auto* fb = F + (size_t)k * (kRF * 8);
 #pragma unroll
         for (int q = 0; q < ST; ++q) {
             s.f[q] = *(const __attribute__((address_space(1))) double*)(fb + q * (kRF * 32) + foff);
-            s.x[q] = *(const __attribute__((address_space(1))) vec*)(rb + q * rq + roff);
+            s.x[q] = ldx(rb + q * rq + roff);
         }
     };
     auto compute = [&](const Stage& s) {
@@ -179,7 +190,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_sh_fold(ShGroup<ShFold, N> g) {
         for (int q = 0; q < ST; ++q) {
             const int row = k0 + 4 * q + lk, rc = min(row, a.n_t - 1);
             s.f[q] = *(const __attribute__((address_space(1))) double*)(F + ((size_t)rc * kRF + li) * 8);
-            s.x[q] = *(const __attribute__((address_space(1))) vec*)(R + ((size_t)rc * ldr + cc) * 4);
+            s.x[q] = ldx(R + ((size_t)rc * ldr + cc) * 4);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -761,9 +772,9 @@ ShGroup<P, N> make_group(const P* p, int n, Wgs wgs) {
         }                                                                               \
     } while (0)
 
-template <int W, bool TALL>
+template <int W, bool TALL, bool NT>
 void launch_fold(const ShFold* p, int n, hipStream_t s) {
-#define SH_K(M) (k_sh_fold<M, W, TALL>)
+#define SH_K(M) (k_sh_fold<M, W, TALL, NT>)
     SH_LAUNCH(SH_K, ShFold, kThreads, [](const ShFold& f) { return f.n_ct * f.n_split; });
 #undef SH_K
 }
@@ -810,17 +821,20 @@ hipError_t launch_sh_fold(const ShFold* p, int n, hipStream_t s) {
             (p[d].kind == kShTall && p[d].rows_per % (4 * kShStage)) ||
             (long)p[d].n_split * p[d].rows_per < p[d].n_t)
             return hipErrorInvalidValue;
-    // one launch for each kind of tile
-    for (const ShKind kind : {kShWide, kShNarrow, kShTall}) {
-        ShFold q[kShGroup];
-        int m = 0;
-        for (int d = 0; d < n; ++d)
-            if (p[d].kind == kind) q[m++] = p[d];
-        if (!m) continue;
-        if (kind == kShWide) launch_fold<4, false>(q, m, s);
-        else if (kind == kShNarrow) launch_fold<1, false>(q, m, s);
-        else launch_fold<4, true>(q, m, s);
-    }
+    // one launch for each kind of tile and load
+    for (const ShKind kind : {kShWide, kShNarrow, kShTall})
+        for (const bool nt : {false, true}) {
+            ShFold q[kShGroup];
+            int m = 0;
+            for (int d = 0; d < n; ++d)
+                if (p[d].kind == kind && (kind != kShNarrow && p[d].stream) == nt) q[m++] = p[d];
+            if (!m) continue;
+            if (kind == kShNarrow) launch_fold<1, false, false>(q, m, s);
+            else if (kind == kShWide && nt) launch_fold<4, false, true>(q, m, s);
+            else if (kind == kShWide) launch_fold<4, false, false>(q, m, s);
+            else if (nt) launch_fold<4, true, true>(q, m, s);
+            else launch_fold<4, true, false>(q, m, s);
+        }
     return hipGetLastError();
 }
 

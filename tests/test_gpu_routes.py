@@ -180,3 +180,44 @@ def test_row_splits_of_wide_and_of_tall_responses(n_t, n_reco):
     ctx.set_band_skipping(True)
     assert np.array_equal(ctx.eval_nll(th), nll)
     ctx.close()
+
+
+@pytest.mark.parametrize("n_t,n_reco", [(75_001, 1001), (2300, 34001)])
+def test_responses_beyond_the_cache(n_t, n_reco):
+    """Responses that are read past the caches, in rows padded to whole lines (300 MB
+    and more), of ragged sizes: spectra against the sums of the rows with the weights
+    of the single-point launches, likelihood and gradient against the spectra."""
+    import paper_2607_00488_amd as nr
+    g = synth.rng(8551)
+    R = g.random((n_t, n_reco), dtype=np.float32) / np.float32(n_reco)
+    n, b = g.poisson(20.0, n_reco).astype(np.float64), np.full(n_reco, 10.0)
+    m = g.uniform(0.5, 1.5, n_t) * 1.0e4 / n_t
+    src = synth.source_nodes(8)
+    th = synth.theta_prior(3, 8552, f_range=(0.8, 1.2))
+
+    log(f"beyond the cache, {n_t} x {n_reco}")
+    ctx = nr.Context(0)
+    ctx.set_sources(src, n_t)
+    ctx.set_response(R, m=m)
+    ctx.set_data(n, b)
+    mu = ctx.eval_mu(th)
+    nll, grad = ctx.eval_nll_grad(th)
+    w = ctx.eval_weights(th)
+    ref = th[:, 6:] * b + np.array([(m * x) @ R.astype(np.float64) for x in w])
+    rel = (n_t + 3 * 8 + 2 + 128) * EPS
+    assert np.all(np.abs(mu - ref) <= rel * ref)
+    one = 2 * (mu - n * np.log(mu)).sum(1)
+    tol = 2 * np.abs(mu - n).sum(1) * rel + 2 * (mu + n).sum(1) * 64 * EPS
+    assert abs((nll[1] - nll[0]) - (one[1] - one[0])) <= tol[0] + tol[1]
+    # mu is linear in f_bkg and f_8B: exact differences
+    a = 2 * (1 - n / mu)
+    for k in (5, 6):
+        up = th.copy()
+        up[:, k] += 1.0
+        d = ctx.eval_mu(up) - mu
+        bound = 8 * rel * ((np.abs(a) + 2 * n / mu) * (np.abs(d) + 2 * mu)).sum(1)
+        assert np.all(np.abs(grad[:, k] - (a * d).sum(1)) <= bound), k
+    assert np.array_equal(ctx.eval_nll(th[:1]), nll[:1])
+    ctx.set_band_skipping(True)
+    assert np.array_equal(ctx.eval_nll(th), nll)
+    ctx.close()
