@@ -847,14 +847,14 @@ ShPlan sh_plan(const nr_ctx* c, int fill_num, int fill_den) {
                       n_t / nr::kShStage});
     s = std::max(1, s);
     ShPlan p{nr::kShWide, s, nr::kShStage};
-    if (fill_num == fill_den && n_ct > 128 && n_t >= 512) {
-        // One split, and compute units left over: small tiles where their rounds on
-        // the chip (in units of all rows of 256 columns a unit) are shorter by a
-        // sixth; two splits of them up to 156 tiles, beyond which two would not fit
-        // the allocation-free workspace.  (Up to 128 tiles, or with 300 rows, the
-        // small ones were no faster.)
+    if (fill_num == fill_den && n_ct > 64 && n_t >= 1024) {
+        // Three splits or fewer, and compute units left over: small tiles where their
+        // rounds on the chip (in units of all rows of 256 columns a unit) are shorter
+        // by a sixth; two splits of them up to 156 tiles, beyond which two would not
+        // fit the allocation-free workspace.  8000 x 23000 144 -> 124 us, 8000 x 24576
+        // 144 -> 136; 600 x 23000 15 and 17, 300 x 34000 15 and 17.
         const int st = n_ct <= 156 ? 2 : 1, nt = nr::sh_tiles(c->ldr, nr::kShTall);
-        const int wide = (n_ct + 255) / 256;
+        const double wide = (n_ct * s + 255) / 256 / (double)s;
         const double tall = (nt * st + 255) / 256 / (4.0 * st);
         if (tall < 0.85 * wide) p = {nr::kShTall, st, 4 * nr::kShStage};
     }

@@ -134,7 +134,8 @@ def test_bands_narrow_and_wide(n_t, n_reco, width, monkeypatch):
 
 
 @pytest.mark.parametrize("n_t,n_reco", [
-    (600, 34001), (512, 39936), (515, 41003), (301, 34001), (5001, 20), (16384, 65)])
+    (1100, 34001), (1024, 39936), (1030, 41003), (1025, 23001), (301, 34001), (5001, 20),
+    (16384, 65)])
 def test_row_splits_of_wide_and_of_tall_responses(n_t, n_reco):
     """Responses whose rows the fold splits by another rule than their size: many
     columns (four waves over the same 64, one split and two) and few (fewer splits
