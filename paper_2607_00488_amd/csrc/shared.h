@@ -55,12 +55,13 @@ struct ShRec {
 // per component (seven spectra and the constant rows, coefficients r_k c_b and
 // r_k) and one per background (coefficient r_q), all times the common mask M_j:
 //   mu_j = M_j [sum_k r_k (G0^(k)_j + sum_b c_b G^(k)_bj) + sum_q r_q B_qj].
-// Its columns are padded with zeros to a multiple of four: two size classes, the
-// smaller for five components and four backgrounds (the solar species).
+// Its columns are padded with zeros to a multiple of four: three size classes, the
+// smallest for one component, the next for five and four backgrounds (the solar
+// species).
 constexpr int kShMaxComp = 8;
 constexpr int kShMaxBkg = 8;
 constexpr int kShCompCols = kCompBasis + 1;
-constexpr int kShSmall = 44, kShLarge = 72;  // columns of the classes
+constexpr int kShTiny = 12, kShSmall = 44, kShLarge = 72;  // columns of the classes
 
 struct ShEval {
     const double* rec;
@@ -76,7 +77,8 @@ struct ShEval {
 
 // Columns of a record and contractions of the gradient (whole blocks of 16).
 inline int sh_cols(int K, int B) {
-    return K == 0 ? kShAcc : kShCompCols * K + B <= kShSmall ? kShSmall : kShLarge;
+    const int n = kShCompCols * K + B;
+    return K == 0 ? kShAcc : n <= kShTiny ? kShTiny : n <= kShSmall ? kShSmall : kShLarge;
 }
 inline int sh_acc(int K, int B) { return (sh_cols(K, B) + 15) / 16 * 16; }
 

@@ -798,7 +798,12 @@ void launch_eval(const ShEval* p, int n, hipStream_t s) {
 template <bool GRAD, bool MU>
 void launch_eval_nb(const ShEval* p, int n, hipStream_t s) {
     if (p[0].K) {
-        if (sh_cols(p[0].K, p[0].B) == kShSmall) launch_eval<GRAD, MU, 1, kShSmall / 4>(p, n, s);
+        // every column is a step of both products: one component, 1500 bins, 20000 points
+        // with the gradient 171 us by the former kernel, which skipped absent columns,
+        // 238 with the 44 of the solar species, 125 with 12
+        const int cols = sh_cols(p[0].K, p[0].B);
+        if (cols == kShTiny) launch_eval<GRAD, MU, 1, kShTiny / 4>(p, n, s);
+        else if (cols == kShSmall) launch_eval<GRAD, MU, 1, kShSmall / 4>(p, n, s);
         else launch_eval<GRAD, MU, 1, kShLarge / 4>(p, n, s);
         return;
     }
@@ -930,6 +935,8 @@ hipError_t launch_sh_mfinal(const ShMultiFinal& p, hipStream_t s) {
         return hipErrorInvalidValue;
     if (!p.grad)
         hipLaunchKernelGGL(k_sh_mfinal, dim3((p.n_pts + 63) / 64), dim3(64), 0, s, p);
+    else if (sh_cols(p.K, p.B) == kShTiny)
+        hipLaunchKernelGGL(k_sh_mfinal_grad<kShTiny>, dim3((p.n_pts + 15) / 16), dim3(kThreads), 0, s, p);
     else if (sh_cols(p.K, p.B) == kShSmall)
         hipLaunchKernelGGL(k_sh_mfinal_grad<kShSmall>, dim3((p.n_pts + 15) / 16), dim3(kThreads), 0, s, p);
     else

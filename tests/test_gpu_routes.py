@@ -222,3 +222,13 @@ def test_responses_beyond_the_cache(n_t, n_reco):
     ctx.set_band_skipping(True)
     assert np.array_equal(ctx.eval_nll(th), nll)
     ctx.close()
+
+
+@pytest.mark.parametrize("B", [0, 1, 4, 5])
+def test_one_component_in_the_template_form(B):
+    """The smallest column class (one component and up to four backgrounds, the
+    first count beyond it) at sizes off the tiles, with the tolerances and the exact
+    differences of tests/test_gpu_shared.py."""
+    from test_gpu_shared import test_multi_component_columns
+    log(f"one component, {B} backgrounds")
+    test_multi_component_columns(1, B)
