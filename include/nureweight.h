@@ -305,8 +305,9 @@ void *nr_stream(nr_ctx *ctx);
  * between HIP events: stage 1: E-integral node table + weights (the weights
  * and diagnostic entry points), 2 and 5: the whole evaluation, 3: the same
  * with the gradient, 4: the R-streaming fold alone.  Contexts on the
- * point-by-point route (multi-component; responses of more than about 60000
- * bins): 2: fold + likelihood, 3: adjoint, 4: fold alone, 5: the steady-state
+ * point-by-point route (multi-component; single-component responses of more than
+ * about 56000 bins and few rows, whose basis workspace would not fit the static one
+ * of nr_eval_nll_dev_noalloc while the point-by-point one does): 2: fold + likelihood, 3: adjoint, 4: fold alone, 5: the steady-state
  * launch of the point pipeline.  The launches run on the context's own inputs
  * at the SM point (no stage's work depends on theta) and write only
  * library-internal buffers.  For roofline measurements.  NR_ESTATE before

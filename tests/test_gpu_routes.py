@@ -232,3 +232,68 @@ def test_one_component_in_the_template_form(B):
     from test_gpu_shared import test_multi_component_columns
     log(f"one component, {B} backgrounds")
     test_multi_component_columns(1, B)
+
+
+def test_point_by_point_route_and_its_adjoint():
+    """A single-component response of so many bins that the basis form does not fit
+    the allocation-free workspace: the single-point launches and the adjoint of the
+    fold.  Likelihood and gradient with pulls against the oracle, band skipping, the
+    allocation-free call and a replayed graph bit for bit, the batched (basis) form
+    as another route.  Tolerances as above; the pulls are a few exact operations."""
+    import math
+    import torch
+    n_t, n_reco, N_E = 40, 60001, 24
+    p = inputs(n_t, n_reco, N_E, 400_000, 8561, 8562)
+    mean = np.array([0.1, 0, 0, 0, 2.0, 1.0, 1.0])
+    sigma = np.array([0.5, 0, 0, 0, 3.0, 0.1, 0.1])
+    ctx = gpu_context(p, pulls=(mean, sigma))
+    th = synth.theta_prior(5, 8563, f_range=(0.8, 1.2))
+    log(f"point by point, {n_t} x {n_reco}")
+    on = sigma > 0
+    pull = (((th - mean)[:, on] / sigma[on]) ** 2).sum(1)
+    dpull = np.where(on, 2 * (th - mean) / np.where(on, sigma, 1.0) ** 2, 0.0)
+    nll, grad = ctx.eval_nll_grad(th)
+    mu = ctx.eval_mu(th)
+    o, n = p["oracle"], p["n"]
+    rel = (n_t + 3 * N_E + 2 + 128) * EPS
+    ref, tol, w = np.zeros(5), np.zeros(5), np.zeros((5, n_reco))
+    for i in range(5):
+        m, g = o.mu(th[i]), o.nll_grad(th[i])[1]
+        assert np.all(np.abs(mu[i] - m) <= rel * np.abs(m)), i
+        ref[i] = 2 * math.fsum([*m, *(-k * math.log(x) for k, x in zip(n, m) if k > 0)]) + pull[i]
+        tol[i] = 2 * np.abs(m - n).sum() * rel + 2 * (m + n).sum() * 64 * EPS
+        w[i] = np.abs(2 * (1 - n / m)) + 2 * n / m
+        for k in range(7):
+            d = np.zeros_like(m)
+            for s in (-1.0, 1.0):
+                t = th[i].copy()
+                t[k] += s
+                d += np.abs(o.mu(t) - m)
+            assert abs(grad[i, k] - g[k] - dpull[i, k]) <= \
+                8 * rel * (w[i] * d).sum() + 8 * EPS * abs(dpull[i, k]), (i, k)
+    assert np.all(np.abs(nll - nll[0] - (ref - ref[0])) <= tol + tol[0])
+    # another route: the grouped calls take the basis form
+    bn, bg = ctx.eval_nll_grad_batched(th)
+    assert np.all(np.abs(bn - nll) <= 2 * tol)
+    tt = torch.tensor(th, device="cuda:0")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    for call in (ctx.eval_nll_dev, ctx.eval_nll_dev, ctx.eval_nll_dev_noalloc):
+        out = torch.full((5,), float("nan"), dtype=torch.float64, device="cuda:0")
+        g = torch.full((5, 7), float("nan"), dtype=torch.float64, device="cuda:0")
+        torch.cuda.synchronize()
+        for _ in range(3):  # the second and third replay the first's graph
+            call(tt, out, g, stream=s)
+            s.synchronize()
+            assert np.array_equal(out.cpu().numpy(), nll)
+            assert np.array_equal(g.cpu().numpy(), grad)
+        call(tt, out, stream=s)
+        s.synchronize()
+        assert np.array_equal(out.cpu().numpy(), ctx.eval_nll(th))
+    plain = ctx.eval_nll(th)
+    assert np.all(np.abs(plain - nll) <= 2 * tol)
+    ctx.set_band_skipping(True)
+    v, g = ctx.eval_nll_grad(th)
+    assert np.array_equal(v, nll) and np.array_equal(g, grad)
+    assert np.array_equal(ctx.eval_nll(th), plain)
+    ctx.close()
