@@ -1692,6 +1692,7 @@ int nr_set_sources(nr_ctx* c, const nr_source* src, int n_src, int n_t,
         c->n_theta = NR_NTHETA;
         c->n_comp = c->n_bkg = 1;
     }
+    if (n_t != c->n_t) c->have_nev = false;
     c->n_src = n_src;
     c->n_nodes = (int)c->hE.size();
     c->src_off[n_src] = c->n_nodes;
@@ -1832,6 +1833,7 @@ int nr_set_response(nr_ctx* c, const float* R, int n_t, int n_reco,
         c->n_theta = NR_NTHETA;
         c->n_comp = c->n_bkg = 1;
     }
+    if (n_t != c->n_t) c->have_nev = false;  // event counts of other rows
     c->n_t = n_t;
     c->n_rows = n_t;
     c->n_reco = n_reco;

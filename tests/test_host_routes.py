@@ -89,6 +89,10 @@ def test_other_threads_calls_go_between_the_steps_of_an_epoch(lib):
     run(lib, "epoch_and_another_thread")
 
 
+def test_mc_events_belong_to_their_rows(lib):
+    run(lib, "mc_events")
+
+
 # ------------------------------------------------------------ child process
 def fnv(text):
     h = 1469598103934665603
@@ -338,6 +342,23 @@ def epoch_and_another_thread(nr, mock):
     assert t.is_alive()
     t.join()
     assert mock.mock_launches() == start + 100 * per_step
+
+
+def mc_events(nr, mock):
+    """Event counts of a response of other rows are not read with a later one."""
+    import synth
+    ctx = nr.Context(0)
+    for n_t in (40, 80, 80):
+        ctx.set_response(np.full((n_t, 33), 1 / 33, np.float32), m=np.ones(n_t))
+        if n_t == 40:
+            ctx.set_mc_events(np.ones(40))
+    ctx.set_sources(synth.source_nodes(24), 80)
+    ctx.set_data(np.full(33, 20.0), np.full(33, 10.0))
+    t = synth.theta_prior(2, 5)
+    assert refused(nr, lambda: ctx.eval_ess(t), nr.NR_ESTATE)
+    ctx.set_mc_events(np.ones(80))
+    ctx.set_response(np.full((80, 33), 1 / 33, np.float32), m=np.ones(80))
+    ctx.eval_ess(t)  # the same rows: the counts still hold
 
 
 if __name__ == "__main__":
