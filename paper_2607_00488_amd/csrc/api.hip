@@ -382,8 +382,10 @@ void row_factors(const nr_ctx* c, const int* src, int n, bool groups, const doub
             double* g = f + (groups && c->src_group[src[q]] ? CB : 0);
             for (int b = 0; b < CB; ++b) g[b] += I[b];
         }
-        // in this order: m / S_SM overflows where S_SM is tiny, m I_b / S_SM does not
-        for (int b = 0; b < ng * CB; ++b) f[b] = m[l] * f[b] / ssm[l];
+        // m / S_SM overflows where S_SM is tiny, m I_b / S_SM does not
+        const double s = m[l] / ssm[l];
+        for (int b = 0; b < ng * CB; ++b)
+            f[b] = std::isnormal(s) ? f[b] * s : m[l] * f[b] / ssm[l];
     }
 }
 
