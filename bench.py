@@ -896,7 +896,8 @@ def main():
                points_per_step=PPS,
                higher_is_better=True, scaling="weak", vs_baseline=None,
                dtype="f64", data="synthetic",
-               config=dict(workload="plain single-point eval: N_T=16384 "
+               config=dict(workload=f"plain evals in calls of {PPS} points that "
+                           "share one read of the response: N_T=16384 "
                            "recoil bins, N_reco=4096, N_E=2048 per continuum "
                            "(5 solar sources), dense FP32 response 256 MiB "
                            "from 1e8 seeded MC events",

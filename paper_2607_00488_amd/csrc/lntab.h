@@ -1,5 +1,7 @@
 // Natural logarithm of a positive normal double by table, for the per-bin
-// Poisson terms of the basis form.
+// Poisson terms of the basis form: the table-driven method of P. T. P. Tang (ACM
+// Trans. Math. Softw. 16, 1990, 378), with the interval from the leading bits of a
+// shifted argument and a reciprocal in place of its breakpoint.
 //
 // x = 2^k z with z in [0.6875, 1.375); the top eight bits of z's offset pick
 // one of 256 intervals with a reciprocal c of its centre, r = z c - 1 is formed
@@ -8,7 +10,7 @@
 // The two intervals beside z = 1 have c = 1 exactly, so that near x = 1 the
 // result is accurate relative to its own small size (near a fit's minimum the
 // terms n ln(n / mu) are such numbers); elsewhere its absolute error stays
-// within a few 1e-16 times max(1, |ln x|).
+// within a few 1e-16 times max(1, |ln x|), where the library function's is relative.
 //
 // 15 instructions and one 16-byte LDS read, against 28 of the series in
 // lnpos.h with its reciprocal of (m + 1).  The table is formed by the compiler

@@ -291,8 +291,9 @@ __global__ __launch_bounds__(kThreads) void k_sh_data(ShRec a) {
 //
 // Bound by those vector instructions (about 25 per point and bin, 40 with the
 // gradient) and the matrix instructions, which share the FP64 rate with them
-// (64 cycles of about 150 per 64 elements).  65536 points x 4096 bins: 291 us,
-// against 510 with one point per lane and the series logarithm.
+// (64 cycles of about 150 per 64 elements).  65536 points x 4096 bins: 292 us in
+// calls with pauses, 335-350 one after the other (the clock falls), against 510 with
+// one point per lane and the series logarithm.
 __device__ __constant__ const LnTable g_ln = make_ln_table();
 
 // The terms that the fast path leaves out: an empty or underflowed spectrum, an
