@@ -1313,13 +1313,16 @@ int enqueue_multi(const MultiCall& mc, int cfg, hipStream_t s) {
     int rc;
     std::vector<size_t> off(mc.n);
     for (int d = 0; d < mc.n; ++d) {
-        ShWork w;
+        const auto end = [&](int q) {
+            ShWork w;
+            off[d] = shb_offset(mc, d, grad, q);
+            return off[d] + carve_sh(mc.ctx[d], nullptr, mc.n_pts[d], grad, q, &w);
+        };
+        if (end(cfg) <= mc.ctx[d]->shb_bytes) continue;
         size_t need = 0;  // of any configuration: another list's may be another one
-        for (int q = 0; q < kShConfigs; ++q)
-            need = std::max(need, shb_offset(mc, d, grad, q) +
-                                      carve_sh(mc.ctx[d], nullptr, mc.n_pts[d], grad, q, &w));
+        for (int q = 0; q < kShConfigs; ++q) need = std::max(need, end(q));
         if ((rc = ensure_shb(mc.ctx[d], need))) return rc;
-        off[d] = shb_offset(mc, d, grad, cfg);
+        end(cfg);
     }
     for (int d0 = 0; d0 < mc.n; d0 += nr::kShGroup) {
         const int n = std::min(nr::kShGroup, mc.n - d0);
