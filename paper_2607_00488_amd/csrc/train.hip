@@ -10,6 +10,7 @@
 #include "train.h"
 
 #include <cmath>
+#include <utility>
 
 namespace nr {
 
@@ -452,36 +453,40 @@ __global__ __launch_bounds__(kThreads, 1) void k_train_hidden(TrainHidden a) {
 // with the moments loaded after the sum: 30.8 -> 26.8 us at N = 4096, 2048 points.
 // The thread that ends up with an element of G updates its parameter, its
 // moments and its BF16 copies (those in fragment order through LDS).
+// Tiles of 64 x 32, eight pairs of waves, where few tiles of a long reduction leave
+// the chip idle (the rule: launch_train_w).
 typedef SplitTile<1, 3, 6, 2> WTile;
+typedef SplitTile<1, 1, 8, 2> WTileSmall;
 
-__global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
+template <class Tile, int NW>
+__global__ __launch_bounds__(Tile::T) void k_train_w(TrainW a) {
     __shared__ __attribute__((aligned(16))) union {
-        float part[6][WTile::TM][WTile::TN];
+        float part[NW][Tile::TM][Tile::TN];
         struct {
-            bf16 f[WTile::TM][WTile::TN + 8], t[WTile::TN][WTile::TM + 8];
+            bf16 f[Tile::TM][Tile::TN + 8], t[Tile::TN][Tile::TM + 8];
         } w;
     } sh;
     int li = 3;
     while (li > 0 && (int)blockIdx.x < a.l[li].first) --li;
     const TrainLayer& L = a.l[li];
-    const int nt = (L.N + WTile::TN - 1) / WTile::TN, t = (int)blockIdx.x - L.first, u = t >> 3;
-    const int m0 = (u / nt * 8 + (t & 7)) * WTile::TM, n0 = u % nt * WTile::TN;
+    const int nt = (L.N + Tile::TN - 1) / Tile::TN, t = (int)blockIdx.x - L.first, u = t >> 3;
+    const int m0 = (u / nt * 8 + (t & 7)) * Tile::TM, n0 = u % nt * Tile::TN;
     if (m0 >= L.M) return;
-    float v[WTile::EPT], ow[WTile::EPT], om[WTile::EPT], ov[WTile::EPT];
-    WTile::run(L.A, L.Bm, L.M, L.N, a.B, a.steps, L.sp, m0, n0, sh.part, v, [&] {
+    float v[Tile::EPT], ow[Tile::EPT], om[Tile::EPT], ov[Tile::EPT];
+    Tile::run(L.A, L.Bm, L.M, L.N, a.B, a.steps, L.sp, m0, n0, sh.part, v, [&] {
 #pragma unroll
-        for (int i = 0; i < WTile::EPT; ++i) {
-            const int e = threadIdx.x + i * WTile::T;
-            const size_t o = (size_t)min(m0 + e / WTile::TN, L.M - 1) * L.N +
-                             min(n0 + e % WTile::TN, L.N - 1);
+        for (int i = 0; i < Tile::EPT; ++i) {
+            const int e = threadIdx.x + i * Tile::T;
+            const size_t o = (size_t)min(m0 + e / Tile::TN, L.M - 1) * L.N +
+                             min(n0 + e % Tile::TN, L.N - 1);
             ow[i] = L.w[o];
             om[i] = L.m[o];
             ov[i] = L.v[o];
         }
     });
 #pragma unroll
-    for (int i = 0; i < WTile::EPT; ++i) {
-        const int e = threadIdx.x + i * WTile::T, ml = e / WTile::TN, nl = e % WTile::TN;
+    for (int i = 0; i < Tile::EPT; ++i) {
+        const int e = threadIdx.x + i * Tile::T, ml = e / Tile::TN, nl = e % Tile::TN;
         if (m0 + ml >= L.M || n0 + nl >= L.N) continue;
         const size_t o = (size_t)(m0 + ml) * L.N + n0 + nl;
         const float g = v[i];
@@ -499,14 +504,14 @@ __global__ __launch_bounds__(WTile::T) void k_train_w(TrainW a) {
     __syncthreads();
     const int sm = frag_steps(L.M), sn = frag_steps(L.N);
     // M and N are multiples of eight: whole 16-byte pieces
-    for (int c = threadIdx.x; c < WTile::TN * (WTile::TM / 8); c += WTile::T) {
-        const int nl = c % WTile::TN, ml = c / WTile::TN * 8;
+    for (int c = threadIdx.x; c < Tile::TN * (Tile::TM / 8); c += Tile::T) {
+        const int nl = c % Tile::TN, ml = c / Tile::TN * 8;
         if (n0 + nl < L.N && m0 + ml < L.M)
             *reinterpret_cast<uint4*>(L.wt + frag_at(n0 + nl, m0 + ml, sm)) =
                 *reinterpret_cast<const uint4*>(&sh.w.t[nl][ml]);
     }
-    for (int c = threadIdx.x; c < WTile::TM * (WTile::TN / 8); c += WTile::T) {
-        const int ml = c % WTile::TM, nl = c / WTile::TM * 8;
+    for (int c = threadIdx.x; c < Tile::TM * (Tile::TN / 8); c += Tile::T) {
+        const int ml = c % Tile::TM, nl = c / Tile::TM * 8;
         if (n0 + nl < L.N && m0 + ml < L.M)
             *reinterpret_cast<uint4*>(L.wf + frag_at(m0 + ml, n0 + nl, sn)) =
                 *reinterpret_cast<const uint4*>(&sh.w.f[ml][nl]);
@@ -565,13 +570,30 @@ hipError_t launch_train_hidden(const TrainHidden& a, hipStream_t s) {
 }
 
 hipError_t launch_train_w(TrainW a, hipStream_t s) {
-    int n = 0;
-    for (int l = 0; l < 4; ++l) {
+    const auto tiles = [&](int tm, int tn) {  // of all layers; their first work-groups
+        int n = 0, all = 0;
+        for (int l = 0; l < 4; ++l) {
+            const int nt = (a.l[l].N + tn - 1) / tn;
+            a.l[l].first = n;
+            n += (a.l[l].M + 8 * tm - 1) / (8 * tm) * 8 * nt;
+            all += (a.l[l].M + tm - 1) / tm * nt;
+        }
+        return std::pair<int, int>(n, all);
+    };
+    for (int l = 0; l < 4; ++l)
         if (a.l[l].M % 8 || a.l[l].N % 8 || !split_ok(a.l[l].sp, a.B)) return hipErrorInvalidValue;
-        a.l[l].first = n;
-        n += ((a.l[l].M + 8 * WTile::TM - 1) / (8 * WTile::TM)) * 8 * ((a.l[l].N + WTile::TN - 1) / WTile::TN);
+    auto n = tiles(WTile::TM, WTile::TN);
+    // Four layers of up to 1024 outputs are 76 tiles or fewer: a large batch went
+    // through them one work-group a compute unit, and most of the units idle.  Four
+    // steps, large tiles -> small: 262144 x 64 13.0 -> 9.5 ms (layer by layer 11.2),
+    // 131072 x 256 7.0 -> 5.5 (6.8), 65536 x 1024 4.90 -> 4.81, 2048 x 256 273 -> 229
+    // us; 124 tiles, 65536 x 2048: 6.96 and 7.02 ms.
+    if (n.second < 100) {
+        n = tiles(WTileSmall::TM, WTileSmall::TN);
+        hipLaunchKernelGGL((k_train_w<WTileSmall, 8>), dim3(n.first), dim3(WTileSmall::T), 0, s, a);
+    } else {
+        hipLaunchKernelGGL((k_train_w<WTile, 6>), dim3(n.first), dim3(WTile::T), 0, s, a);
     }
-    hipLaunchKernelGGL(k_train_w, dim3(n), dim3(WTile::T), 0, s, a);
     return hipGetLastError();
 }
 

@@ -298,3 +298,12 @@ def test_point_by_point_route_and_its_adjoint():
     assert np.array_equal(v, nll) and np.array_equal(g, grad)
     assert np.array_equal(ctx.eval_nll(th), plain)
     ctx.close()
+
+
+@pytest.mark.parametrize("B,N", [(136, 1096), (72, 1608), (264, 4008)])
+def test_training_steps_of_either_gradient_tile(B, N):
+    """The last counts of outputs with 64 x 32 tiles of the weight gradient and ones
+    with 64 x 96, ragged, through the checks of the smaller networks."""
+    from test_gpu_train import test_ragged_steps
+    log(f"training step, {B} points x {N} outputs")
+    test_ragged_steps(B, N)
