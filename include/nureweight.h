@@ -213,8 +213,9 @@ int nr_eval_mu_batched(nr_ctx *ctx, const double *theta, int n_pts,
                        double *mu);
 
 /* Several analyses (datasets with their own binning and response, all on
- * one device) in four launches per 16 of them: theta[d] ([n_pts[d]][7],
- * host), nll[d] ([n_pts[d]], host).  A context may occur more than once.  The
+ * one device) in four launches per 16 of them, a fold more for each further kind
+ * of tile among their responses: theta[d] ([n_pts[d]][7], host), nll[d]
+ * ([n_pts[d]], host).  A context may occur more than once.  The
  * stream of ctx[0] is used. */
 int nr_eval_nll_multi(nr_ctx *const *ctx, int n_ctx,
                       const double *const *theta, const int *n_pts,

@@ -929,8 +929,9 @@ int ensure_shared(nr_ctx* c) {
 bool use_shared(const nr_ctx* c) {
     if (c->multi) return false;
     Work w;
-    return carve_work(c, nullptr, &w) > (size_t)NR_NOALLOC_WORKSPACE_BYTES ||
-           sh_points(c, NR_NOALLOC_WORKSPACE_BYTES) > 0;
+    ShWork sw;
+    return carve_sh(c, nullptr, 16, true, 0, &sw) <= (size_t)NR_NOALLOC_WORKSPACE_BYTES ||
+           carve_work(c, nullptr, &w) > (size_t)NR_NOALLOC_WORKSPACE_BYTES;
 }
 
 // Narrow tiles up to a share of 3/8 of the rows inside a tile's band (measured on
